@@ -1,0 +1,360 @@
+// Kernels that run several axes of the transform in one memory pass, and
+// their launchers (part of the kernels.hip translation unit).
+#pragma once
+
+#include "cx.h"
+#include "engine.h"
+#include "kernels.h"
+#include "pass_common.h"
+
+namespace gfft {
+
+// FFT stages of R transforms side by side per thread (a[y], y < R), sharing
+// their twiddles and barriers; exchanges through LDS as real, then imaginary
+// parts.  Column c of TC; transform y occupies its own padded N x TC block.
+template <typename T, int N, int E, int R, int S, int L, int RM, int TC, int PS>
+__device__ __forceinline__ void fft_multi(cx<T> (&a)[R][E], int t, int c, const cx<T>* __restrict__ tw,
+                                          int tws, T* lds) {
+    constexpr int RX = stage_radix<N, E, L, RM>::value;
+    constexpr int NB = E / RX, TPT = N / E;
+    constexpr int NP = padded_len<N, PS>::value;
+#pragma unroll
+    for (int q = 0; q < NB; ++q) {
+        const int j = t + q * TPT;
+        const int k = j & (L - 1);
+        cx<T> w[RX];
+        if constexpr (L > 1) {
+#pragma unroll
+            for (int r = 1; r < RX; ++r) w[r] = tw[r * k * (N / (L * RX)) * tws];
+        }
+#pragma unroll
+        for (int y = 0; y < R; ++y) {
+            cx<T> b[RX];
+#pragma unroll
+            for (int r = 0; r < RX; ++r) b[r] = a[y][q + r * NB];
+            if constexpr (L > 1) {
+#pragma unroll
+                for (int r = 1; r < RX; ++r) b[r] = twiddle<S>(b[r], w[r]);
+            }
+            dft<RX, S>(b);
+#pragma unroll
+            for (int r = 0; r < RX; ++r) a[y][q + r * NB] = b[r];
+        }
+    }
+    if constexpr (L * RX < N) {
+        using G = xgeom<N, E, L, RX>;
+        using IX = idx_cols<TC, PS>;
+        const IX ix{c};
+#pragma unroll
+        for (int part = 0; part < 2; ++part) {
+#pragma unroll
+            for (int y = 0; y < R; ++y)
+#pragma unroll
+                for (int s = 0; s < E; ++s)
+                    lds[y * NP * TC + ix.at(G::template out_pad<PS>(t, s))] = part ? a[y][s].y : a[y][s].x;
+            __syncthreads();
+#pragma unroll
+            for (int y = 0; y < R; ++y)
+#pragma unroll
+                for (int m = 0; m < E; ++m) {
+                    const T v = lds[y * NP * TC + ix.at(G::template in_pad<PS>(t, m))];
+                    if (part) a[y][m].y = v;
+                    else a[y][m].x = v;
+                }
+            __syncthreads();
+        }
+        fft_multi<T, N, E, R, S, L * RX, RM, TC, PS>(a, t, c, tw, tws, lds);
+    }
+}
+
+// ---------------------------------------------------------------- plane 2D R2C / C2R
+// z R2C and y C2C of one x-plane (section 3, step 1; R = 1), or of every R-th
+// row of it, in one kernel with the rows held in registers.  With R > 1 the
+// y transform is split as N = NY R (y = y0 + R j, ky = k1 + NY k0): a tile
+// takes the NY rows of one y0, transforms them along z and j, and writes
+// bin k1 to row y0 NY + k1; the strided pass that follows (k_strided_r)
+// reads the R rows {y0 NY + k1} of one k1, applies the twiddles W_N^(y0 k1)
+// and the R-point DFT over y0, and writes the rows {k1 + NY k0} -- the same
+// rows, so that pass stays in place.  The inverse runs the same steps
+// backwards.
+//   z phase: thread (r, t), r < NY rows, t < TZ = M/E, holds z[t + TZ m] of
+//            row r (z[n] = x[2n] + i x[2n+1]); M-point FFT;
+//   y phase: thread (s, p), p < M/2, holds columns p and M - p at rows
+//            s + TY m, m < E/2; two NY-point FFTs.
+// Between the phases the tile moves through LDS, real parts then imaginary
+// parts.  The column pair makes the real split (bin k from Z[k] and Z[M-k];
+// the inverse's pre-process likewise) a register operation with one twiddle
+// per thread.  Columns 0 and M/2, their own partners, share thread p = 0.
+// The z half spectrum has M + 1 columns; kz = 0 and kz = M are real
+// for a real row, so they travel together as one complex column
+// P = X[.][0] + i X[.][M] (two real transforms for one complex one) and are
+// separated after the y FFT: X0 = (P + conj P(-k1)) / 2, XM = (P - conj
+// P(-k1)) / 2i.  The inverse packs the Hermitian parts of the kz = 0 and
+// kz = M columns the same way (the C2R keeps only the real part of those
+// columns after the y inverse, which is the inverse of their Hermitian
+// parts; both hold for the rows of one y0 by themselves, which are real
+// sequences in j).  Every load of a tile precedes the first barrier and
+// every store follows the last, so with R = 1 a plane may be transformed in
+// place.
+template <typename T, int N, int R, int E>
+struct plane_shape {
+    static constexpr int M = N / 2, K = M + 1, NY = N / R, H = M / 2;
+    static constexpr int EY = E / 2;
+    static constexpr int TZ = M / E, TY = NY / EY;
+    static constexpr int NT = NY * TZ;  // = H * TY
+    static constexpr int RM = radix_cap<T>();
+    static constexpr int PS = TZ > 1 ? first_radix_shift<E, RM>::value : 0;
+    static constexpr int MP = padded_len<M, PS>::value;
+    // column exchange: padded where a row of H values covers fewer than all
+    // 64 banks, so that the rows a wave touches fall on different ones
+    static constexpr int PY = H * int(sizeof(T)) / 4 >= 64 ? 0 : first_radix_shift<EY, RM>::value;
+    static constexpr int NP = padded_len<NY, PY>::value;
+    // row stride of the transpose buffer: a wave's lanes are TZ values of
+    // 64/TZ rows, so rows are staggered by TZ banks
+    static constexpr int LD = M + TZ;
+    static constexpr int A = TZ > 1 ? NY * MP : 0, B = TY > 1 ? NP * M : 0, C = NY * LD,
+                         D = 6 * NY;
+    static constexpr int AB = A > B ? A : B, CD = C > D ? C : D;
+    static constexpr int LDS = AB > CD ? AB : CD;  // values of type T
+    static_assert(M % E == 0 && NY % EY == 0 && NY * TZ == H * TY, "plane shape");
+};
+
+template <typename T, int N, int R, int E, int W>
+__global__ __launch_bounds__((plane_shape<T, N, R, E>::NT), W) void k_plane_r2c(
+    const T* in, cx<T>* out, const cx<T>* __restrict__ tw, row_map map, T mul_edge, T mul_int) {
+    using P = plane_shape<T, N, R, E>;
+    constexpr int M = P::M, K = P::K, H = P::H, NY = P::NY, TZ = P::TZ, TY = P::TY, EY = P::EY,
+                  RM = P::RM;
+    __shared__ T lds[P::LDS];
+    const int64_t tile = R > 1 ? xcd_tile(blockIdx.x, gridDim.x) : int64_t(blockIdx.x);
+    const int64_t plane = tile / R;
+    const int y0 = int(tile % R);
+    const int tid = threadIdx.x;
+    const int r = tid / TZ, t = tid % TZ;          // z phase
+    const int p = tid % H, s = tid / H;            // y phase
+    const int c1 = p == 0 ? H : M - p;             // columns p and c1
+
+    // z phase: row y0 + R r of the plane, read as M complex values
+    cx<T> a[E];
+    const cx<T>* src = reinterpret_cast<const cx<T>*>(in + (plane * N + y0 + R * r) * map.rs);
+#pragma unroll
+    for (int m = 0; m < E; ++m) a[m] = src[t + TZ * m];
+    using IR = idx_rows<P::PS>;
+    fft_regs<T, M, E, -1, RM>(a, t, tw, 2, xch_split<T, IR>{lds, IR{r * P::MP}});
+
+    // rows -> columns
+    const cx<T> w = tw[p];
+    cx<T> b[2][EY];
+#pragma unroll
+    for (int m = 0; m < E; ++m) lds[r * P::LD + t + TZ * m] = a[m].x;
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < EY; ++m) {
+        b[0][m].x = lds[(s + TY * m) * P::LD + p];
+        b[1][m].x = lds[(s + TY * m) * P::LD + c1];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < E; ++m) lds[r * P::LD + t + TZ * m] = a[m].y;
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < EY; ++m) {
+        b[0][m].y = lds[(s + TY * m) * P::LD + p];
+        b[1][m].y = lds[(s + TY * m) * P::LD + c1];
+    }
+    __syncthreads();
+    // real split, bin multipliers applied: with A = (Z[p] + conj Z[M-p])/2,
+    // B = (Z[p] - conj Z[M-p])/2 and w = W_N^p,
+    //   X[p] = A - i w B,  X[M-p] = conj(A + i w B);
+    // p = 0: column 0 becomes (X[0], X[M]) = (Re Z[0] + Im Z[0], Re - Im),
+    // column M/2 its conjugate.
+    const bool edge = p == 0;
+#pragma unroll
+    for (int m = 0; m < EY; ++m) {
+        const cx<T> z = b[0][m], v = b[1][m];
+        const cx<T> A = scal(z + conjg(v), T(0.5)), B = cmul(w, scal(z - conjg(v), T(0.5)));
+        b[0][m].x = edge ? (z.x + z.y) * mul_edge : (A.x + B.y) * mul_int;
+        b[0][m].y = edge ? (z.x - z.y) * mul_edge : (A.y - B.x) * mul_int;
+        b[1][m].x = edge ? v.x * mul_int : (A.x - B.y) * mul_int;
+        b[1][m].y = edge ? -v.y * mul_int : (-A.y - B.x) * mul_int;
+    }
+
+    // y phase: NY-point FFTs of columns p and c1
+    fft_multi<T, NY, EY, 2, -1, 1, RM, H, P::PY>(b, s, p, tw, R, lds);
+
+    // the packed column goes through LDS; one thread per row separates it
+    cx<T>* col0 = reinterpret_cast<cx<T>*>(lds);
+    if (p == 0) {
+#pragma unroll
+        for (int m = 0; m < EY; ++m) col0[s + TY * m] = b[0][m];
+    }
+    __syncthreads();
+    // store rows of the half spectrum: wave lanes are consecutive columns
+    auto row_of = [&](int k1) {
+        const int64_t row = plane * N + y0 * NY + k1;
+        return out + (R > 1 ? row : map_row(row, map)) * K;
+    };
+#pragma unroll
+    for (int m = 0; m < EY; ++m) {
+        cx<T>* dst = row_of(s + TY * m);
+        if (p != 0) dst[p] = b[0][m];
+        dst[c1] = b[1][m];
+    }
+    if (tid < NY) {
+        const cx<T> v = col0[tid], pc = conjg(col0[(NY - tid) & (NY - 1)]);
+        const cx<T> sum = v + pc, dif = v - pc;
+        cx<T>* dst = row_of(tid);
+        dst[0] = cx<T>{T(0.5) * sum.x, T(0.5) * sum.y};   // X[k1][0]
+        dst[M] = cx<T>{T(0.5) * dif.y, T(-0.5) * dif.x};  // X[k1][M] = dif / 2i
+    }
+}
+
+template <typename T, int N, int R, int E, int W>
+__global__ __launch_bounds__((plane_shape<T, N, R, E>::NT), W) void k_plane_c2r(
+    const cx<T>* in, T* out, const cx<T>* __restrict__ tw, row_map map, T mul_edge, T mul_int) {
+    using P = plane_shape<T, N, R, E>;
+    constexpr int M = P::M, K = P::K, H = P::H, NY = P::NY, TZ = P::TZ, TY = P::TY, EY = P::EY,
+                  RM = P::RM;
+    __shared__ T lds[P::LDS];
+    const int64_t tile = R > 1 ? xcd_tile(blockIdx.x, gridDim.x) : int64_t(blockIdx.x);
+    const int64_t plane = tile / R;
+    const int y0 = int(tile % R);
+    const int tid = threadIdx.x;
+    const int r = tid / TZ, t = tid % TZ;
+    const int p = tid % H, s = tid / H;
+    const int c1 = p == 0 ? H : M - p;
+
+    // y phase input: columns p and c1 of the half spectrum; column 0 is
+    // replaced by the Hermitian parts of kz = 0 (real) and kz = M
+    // (imaginary), formed through LDS by one thread per row
+    auto row_of = [&](int k1) {
+        const int64_t row = plane * N + y0 * NY + k1;
+        return in + (R > 1 ? row : map_row(row, map)) * K;
+    };
+    cx<T> b[2][EY];
+    cx<T>* col0 = reinterpret_cast<cx<T>*>(lds);
+#pragma unroll
+    for (int m = 0; m < EY; ++m) {
+        const cx<T>* g = row_of(s + TY * m);
+        b[0][m] = g[p];
+        b[1][m] = g[c1];
+    }
+    if (tid < NY) {
+        const cx<T>* g = row_of(tid);
+        col0[tid] = g[0];
+        col0[NY + tid] = g[M];
+    }
+    __syncthreads();
+    if (tid < NY) {
+        const int kn = (NY - tid) & (NY - 1);
+        const cx<T> h0 = scal(col0[tid] + conjg(col0[kn]), T(0.5));
+        const cx<T> hm = scal(col0[NY + tid] + conjg(col0[NY + kn]), T(0.5));
+        col0[2 * NY + tid] = cx<T>{h0.x - hm.y, h0.y + hm.x};  // h0 + i hm
+    }
+    __syncthreads();
+    if (p == 0) {
+#pragma unroll
+        for (int m = 0; m < EY; ++m) b[0][m] = col0[2 * NY + s + TY * m];
+    }
+    __syncthreads();
+    fft_multi<T, NY, EY, 2, +1, 1, RM, H, P::PY>(b, s, p, tw, R, lds);
+
+    // pre-process of the row C2R, bin multipliers applied: with
+    // S = G[p] + conj G[M-p], D = G[p] - conj G[M-p], w = W_N^p,
+    //   Z'[p] = S + i conj(w) D,  Z'[M-p] = conj(S - i conj(w) D);
+    // p = 0: column 0 holds the real bins (G[0], G[M]) and becomes
+    // Z'[0] = (G[0] + G[M], G[0] - G[M]); Z'[M/2] = 2 conj G[M/2].
+    const cx<T> w = tw[p];
+    const bool edge = p == 0;
+#pragma unroll
+    for (int m = 0; m < EY; ++m) {
+        const cx<T> z = b[0][m], u = conjg(b[1][m]);
+        const cx<T> S = scal(z + u, mul_int), D = cmulc(scal(z - u, mul_int), w);
+        b[0][m].x = edge ? (z.x + z.y) * mul_edge : S.x - D.y;
+        b[0][m].y = edge ? (z.x - z.y) * mul_edge : S.y + D.x;
+        b[1][m].x = edge ? u.x * (T(2) * mul_int) : S.x + D.y;
+        b[1][m].y = edge ? u.y * (T(2) * mul_int) : D.x - S.y;
+    }
+
+    // columns -> rows
+    cx<T> g[E];
+#pragma unroll
+    for (int m = 0; m < EY; ++m) {
+        lds[(s + TY * m) * P::LD + p] = b[0][m].x;
+        lds[(s + TY * m) * P::LD + c1] = b[1][m].x;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < E; ++m) g[m].x = lds[r * P::LD + t + TZ * m];
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < EY; ++m) {
+        lds[(s + TY * m) * P::LD + p] = b[0][m].y;
+        lds[(s + TY * m) * P::LD + c1] = b[1][m].y;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < E; ++m) g[m].y = lds[r * P::LD + t + TZ * m];
+    __syncthreads();
+    using IR = idx_rows<P::PS>;
+    fft_regs<T, M, E, +1, RM>(g, t, tw, 2, xch_split<T, IR>{lds, IR{r * P::MP}});
+    cx<T>* dst = reinterpret_cast<cx<T>*>(out + (plane * N + y0 + R * r) * map.rs);
+#pragma unroll
+    for (int m = 0; m < E; ++m) dst[t + TZ * m] = g[m];
+}
+
+// Shape of the one-plane kernels: elements per thread and the minimum of
+// waves per SIMD the register allocation keeps.  Measured over 537 MB of
+// reals (forward / inverse step 1, us; in brackets the separate z and y
+// passes, or for FP32 forward the earlier plane kernel): FP64 N = 64 8 per
+// thread 199 / 200 (417 / 490), 16 per thread 201 / 231; N = 128 16 per
+// thread at 2 waves 215 / 209 (405 / 433), at 4 waves 238 / 212, 8 per thread
+// 227 / 308; FP32 N = 64 8 per thread 219 / 222 (252 / 455), 16 per thread
+// 252 / 255; N = 128 16 per thread 228 / 220 (272 / 491), 8 per thread
+// 247 / 261; N = 256 32 per thread 327 / 333 (379 / 451): there one plane
+// fills half a CU's registers and its phases do not overlap another's.  The
+// streaming copy of the same bytes takes 173.
+template <typename T, int N>
+struct plane_cfg {
+    static constexpr bool F64 = sizeof(T) == 8;
+    static constexpr int E = N == 64 ? 8 : N == 128 ? 16 : 32;
+    static constexpr int W = F64 && N == 128 ? 2 : 4;
+};
+
+template <typename T, int N>
+static hipError_t plane_n(bool forward, const void* in, void* out, const void* tw, int64_t planes,
+                          row_map map, double me, double mi, hipStream_t s) {
+    using C = plane_cfg<T, N>;
+    constexpr int NT = plane_shape<T, N, 1, C::E>::NT;
+    if (planes == 0) return hipSuccess;
+    if (!grid_fits(planes, NT)) return hipErrorInvalidValue;
+    if (forward)
+        hipLaunchKernelGGL((k_plane_r2c<T, N, 1, C::E, C::W>), dim3(planes), dim3(NT), 0, s,
+                           static_cast<const T*>(in), static_cast<cx<T>*>(out),
+                           static_cast<const cx<T>*>(tw), map, T(me), T(mi));
+    else
+        hipLaunchKernelGGL((k_plane_c2r<T, N, 1, C::E, C::W>), dim3(planes), dim3(NT), 0, s,
+                           static_cast<const cx<T>*>(in), static_cast<T*>(out),
+                           static_cast<const cx<T>*>(tw), map, T(me), T(mi));
+    return hipGetLastError();
+}
+
+// Where a plane fits on a CU with room for a second one (FP64 up to
+// N = 128: 131 KB) or at least once (FP32 N = 256: 262 KB); an FP64 256 x 256
+// plane (524 KB) would take the whole register file.
+bool plane_supported(bool f64, int n) { return n == 64 || n == 128 || (!f64 && n == 256); }
+
+hipError_t launch_plane(bool f64, bool forward, int n, const void* in, void* out, const void* tw,
+                        int64_t planes, row_map map, double me, double mi, hipStream_t s) {
+    if (!plane_supported(f64, n)) return hipErrorInvalidValue;
+    if (f64)
+        return n == 64 ? plane_n<double, 64>(forward, in, out, tw, planes, map, me, mi, s)
+                       : plane_n<double, 128>(forward, in, out, tw, planes, map, me, mi, s);
+    switch (n) {
+        case 64: return plane_n<float, 64>(forward, in, out, tw, planes, map, me, mi, s);
+        case 128: return plane_n<float, 128>(forward, in, out, tw, planes, map, me, mi, s);
+        default: return plane_n<float, 256>(forward, in, out, tw, planes, map, me, mi, s);
+    }
+}
+
+}  // namespace gfft

@@ -251,11 +251,10 @@ gfft_status check_r2c_args(const gfft_plan* p, const void* real, const void* cpl
 }
 
 // Step 1 or its inverse as one pass per plane where a plane fits on a CU
-// and that is measured faster (FP32, N = 64..256; not for pencil plans,
-// whose z output is cut into kz chunks, nor with the matrix-core stage,
-// which belongs to the y pass).
-bool plane_pass(const gfft_plan* p, bool fwd) {
-    return !p->pencil && mfma_terms(p) == 0 && gfft::plane_supported(f64(p), int(p->n), fwd);
+// (not for pencil plans, whose z output is cut into kz chunks, nor with the
+// matrix-core stage, which belongs to the y pass).
+bool plane_pass(const gfft_plan* p) {
+    return !p->pencil && mfma_terms(p) == 0 && gfft::plane_supported(f64(p), int(p->n));
 }
 
 gfft_status run_plane(const gfft_plan* p, bool fwd, const void* in, void* out, double scale,
@@ -273,7 +272,7 @@ gfft_status forward(const gfft_plan* p, const void* in, void* out, double scale,
     if (!std::isfinite(scale)) return GFFT_E_INVALID_ARG;
     if ((st = check_device(p)) != GFFT_OK) return st;
     hipStream_t s = as_stream(stream);
-    if (plane_pass(p, true)) {
+    if (plane_pass(p)) {
         if ((st = run_plane(p, true, in, out, scale, weighted, s)) != GFFT_OK) return st;
     } else {
         if ((st = run_z_r2c(p, in, out, scale, weighted, s)) != GFFT_OK) return st;
@@ -292,7 +291,7 @@ gfft_status inverse(const gfft_plan* p, void* in, void* out, double scale, bool 
     if ((st = check_device(p)) != GFFT_OK) return st;
     hipStream_t s = as_stream(stream);
     if (p->p == 1 && (st = run_x(p, in, +1, s)) != GFFT_OK) return st;
-    if (plane_pass(p, false)) return run_plane(p, false, in, out, scale, weighted, s);
+    if (plane_pass(p)) return run_plane(p, false, in, out, scale, weighted, s);
     if ((st = run_y(p, in, +1, s)) != GFFT_OK) return st;
     return run_z_c2r(p, in, out, scale, weighted, s);
 }

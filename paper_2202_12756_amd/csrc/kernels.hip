@@ -15,22 +15,17 @@
 // z pass scatters each row's bins to the first exchange's chunks, and the
 // y/x passes address the received pencils through their line maps.
 // Memory bound: each pass reads and writes its array once.
+// fused.h holds the kernels that take several axes in one pass.
 #include "cx.h"
 #include "engine.h"
+#include "fused.h"
 #include "kernels.h"
 #include "mfma_dft16.h"
+#include "pass_common.h"
 
 namespace gfft {
 
 constexpr int kThreads = 256;
-
-constexpr int ilog2_c(int v) { return v <= 1 ? 0 : 1 + ilog2_c(v / 2); }
-
-// Largest radix per FFT stage.  The FP32 vector kernels take radix-32
-// stages, one LDS exchange fewer for 512- and 1024-point transforms (FP32 is
-// bound by instruction issue); FP64 and the matrix-core stage keep radix 16.
-template <typename T, int MF = 0>
-constexpr int radix_cap() { return sizeof(T) == 4 && MF == 0 ? 32 : 16; }
 
 // A workgroup-uniform value in scalar registers that the optimiser cannot
 // see through: expressions of it are formed where they are used.
@@ -46,17 +41,6 @@ __device__ __forceinline__ int64_t opaque_uniform(int64_t v) {
     return int64_t((uint64_t(hi) << 32) | lo);
 }
 
-__device__ __forceinline__ int64_t map_row(int64_t r, row_map m) {
-    const int64_t bx = r >> m.lg_n;
-    const int64_t y = r & ((int64_t(1) << m.lg_n) - 1);
-    const int64_t b = bx >> m.lg_x;
-    const int64_t xl = bx & ((int64_t(1) << m.lg_x) - 1);
-    if (m.paper) return (b << (m.lg_x + m.lg_n)) + (y << m.lg_x) + xl;
-    const int64_t j = y >> m.lg_y;
-    const int64_t yl = y & ((int64_t(1) << m.lg_y) - 1);
-    return (b << (m.lg_x + m.lg_n)) + ((((j << m.lg_x) + xl)) << m.lg_y) + yl;
-}
-
 // Offset (in complex values) of bin k of row r in a pencil plan's
 // first-exchange order (row_map::pencil).
 __device__ __forceinline__ int64_t pencil_bin(int64_t r, int k, int K, const row_map& m) {
@@ -65,16 +49,6 @@ __device__ __forceinline__ int64_t pencil_bin(int64_t r, int k, int K, const row
     const int c = (k >> m.lg_w) < m.pc_last ? (k >> m.lg_w) : m.pc_last;
     const int64_t wc = (int64_t(1) << m.lg_w) + (c == m.pc_last ? 1 : 0);
     return ((item * K + (int64_t(c) << m.lg_w)) << m.lg_rows) + rl * wc + (k - (c << m.lg_w));
-}
-
-// Consecutive workgroup ids are dealt round-robin to the 8 XCDs, each with
-// its own L2.  Remap so that XCD x works through one contiguous range of
-// tiles: neighbouring tiles share cache lines at their edges.
-__device__ __forceinline__ int64_t xcd_tile(int64_t g, int64_t G) {
-    constexpr int kXcd = 8;
-    const int64_t per = G / kXcd;
-    if (g >= per * kXcd) return g;
-    return (g % kXcd) * per + g / kXcd;
 }
 
 template <int M, int EMAX = 16, int THREADS = kThreads>
@@ -301,231 +275,6 @@ __global__ __launch_bounds__((zshape<N / 2, EMAX, THREADS>::NT)) void k_z_c2r_pe
     const cx<T>* __restrict__ in, T* __restrict__ out, const cx<T>* __restrict__ tw,
     int64_t rows, row_map map, T mul_edge, T mul_int) {
     z_c2r_body<T, N, EMAX, THREADS, REMAP, NTS, true>(in, out, tw, rows, map, mul_edge, mul_int);
-}
-
-// ---------------------------------------------------------------- plane 2D R2C / C2R
-// Step 1 of the method (the 2D R2C over (y, z) of one x-plane) in one kernel
-// when a plane fits on a CU: FP32, N = 64, 128, 256 (a 256 x 256 plane is
-// 256 KiB of reals and 264 KiB of half spectrum; the register file holds it),
-// and the inverse for N = 64 and 128 (plane_supported says where each runs).
-// One workgroup per plane, NT = N M / 32 threads, 32 complex values per
-// thread in both phases:
-//   z phase: thread (r, t), r < N rows, t < TZ = M/32, holds z[t + TZ m] of
-//            row r (z[n] = x[2n] + i x[2n+1]); M-point FFT;
-//   y phase: thread (s, c), c < M columns, s < TY = N/32, holds column c at
-//            rows s + TY m; N-point FFT.
-// Between the phases the plane moves through LDS, real parts then imaginary
-// parts.  The forward's real split (bin k from Z[k] and Z[M-k]) is formed
-// by the column threads as they read the transposed plane, column c taking
-// columns c and M - c from LDS; the inverse forms its pre-process the same
-// way after the transpose back, through a mirror exchange of half the rows
-// at a time.  The z half spectrum has M + 1 columns; kz = 0 and kz = M are real
-// for a real row, so they travel together as one complex column
-// P = X[.][0] + i X[.][M] (two real transforms for one complex one) and are
-// separated after the y FFT: X0 = (P + conj P(-ky)) / 2, XM = (P - conj
-// P(-ky)) / 2i.  The inverse packs the Hermitian parts of the kz = 0 and
-// kz = M columns the same way (the C2R keeps only the real part of those
-// columns after the y inverse, which is the inverse of their Hermitian
-// parts).  Every load of a plane precedes the first barrier and every store
-// follows the last, so the plane may be transformed in place.
-template <int N>
-struct plane_shape {
-    static constexpr int M = N / 2, K = M + 1;
-    static constexpr int E = 32;
-    static constexpr int TZ = M / E, TY = N / E;
-    static constexpr int NT = N * TZ;  // = M * TY
-    static constexpr int PS = 5;       // first radix 32: one pad per 32 positions
-    static constexpr int MP = M + (M >> PS);
-    static constexpr int NP = N + (N >> PS);
-    static constexpr int LD = M + 1;   // odd row stride of the transpose buffer
-    static constexpr int A = N * MP, B = NP * M, C = N * LD, D = (N / 2) * MP * 2;
-    static constexpr int AB = A > B ? A : B, CD = C > D ? C : D;
-    static constexpr int LDS = AB > CD ? AB : CD;  // floats
-    static_assert(TZ >= 1 && TY >= 1 && N * TZ == M * TY, "plane shape");
-};
-
-// The z phase's mirror exchange: every thread replaces v[m] (bin
-// k = t + TZ m of row r) by f(m, v[m], v_r[(M - k) mod M]), the mirror value
-// read back through LDS as a whole complex value; half of the rows at a time.
-template <int N, class F>
-__device__ __forceinline__ void plane_mirror(float* lds, int r, int t, cx<float> (&v)[32],
-                                             F&& f) {
-    using P = plane_shape<N>;
-    cx<float>* buf = reinterpret_cast<cx<float>*>(lds);
-    const int rl = r & (N / 2 - 1);
-#pragma unroll
-    for (int half = 0; half < 2; ++half) {
-        const bool mine = (r >= N / 2) == (half != 0);
-        if (mine) {
-#pragma unroll
-            for (int m = 0; m < 32; ++m) buf[rl * P::MP + t + P::TZ * m] = v[m];
-        }
-        __syncthreads();
-        if (mine) {
-#pragma unroll
-            for (int m = 0; m < 32; ++m)
-                v[m] = f(m, v[m], buf[rl * P::MP + ((P::M - (t + P::TZ * m)) & (P::M - 1))]);
-        }
-        __syncthreads();
-    }
-}
-
-template <int N>
-__global__ __launch_bounds__(plane_shape<N>::NT) void k_plane_r2c(
-    const float* in, cx<float>* out, const cx<float>* __restrict__ tw, int64_t planes,
-    row_map map, float mul_edge, float mul_int) {
-    using P = plane_shape<N>;
-    constexpr int M = P::M, K = P::K, TZ = P::TZ, TY = P::TY;
-    __shared__ float lds[P::LDS];
-    const int64_t plane = blockIdx.x;
-    const int tid = threadIdx.x;
-    const int r = tid / TZ, t = tid % TZ;  // z phase
-    const int c = tid % M, s = tid / M;    // y phase
-
-    // z phase: row r of the plane, read as M complex values
-    cx<float> a[32];
-    const cx<float>* src = reinterpret_cast<const cx<float>*>(in + (plane * N + r) * map.rs);
-#pragma unroll
-    for (int m = 0; m < 32; ++m) a[m] = src[t + TZ * m];
-    fft_regs<float, M, 32, -1, 32>(a, t, tw, 2,
-                                   xch_split<float, idx_rows<P::PS>>{lds, idx_rows<P::PS>{r * P::MP}});
-
-    // rows -> columns, real then imaginary parts, with the real split folded
-    // in: column thread c reads Z[y][c] and Z[y][M-c] and forms
-    //   X[c] = (Z[c] + conj Z[M-c])/2 - (i/2) W_N^c (Z[c] - conj Z[M-c])
-    // as a part from the real parts and a part from the imaginary parts
-    // (bin multipliers applied); kz = 0 and kz = M (both real, X[M] =
-    // Re Z[0] - Im Z[0]) travel as one complex column c = 0.
-    const int cm = (M - c) & (M - 1);
-    const cx<float> w = tw[c];
-    const float f = c == 0 ? mul_edge : mul_int;
-    cx<float> b[32];
-#pragma unroll
-    for (int m = 0; m < 32; ++m) lds[r * P::LD + t + TZ * m] = a[m].x;
-    __syncthreads();
-#pragma unroll
-    for (int m = 0; m < 32; ++m) {
-        const float zr = lds[(s + TY * m) * P::LD + c], mr = lds[(s + TY * m) * P::LD + cm];
-        const float hd = 0.5f * (zr - mr);
-        b[m] = cx<float>{0.5f * (zr + mr) + w.y * hd, -w.x * hd};
-    }
-    __syncthreads();
-#pragma unroll
-    for (int m = 0; m < 32; ++m) lds[r * P::LD + t + TZ * m] = a[m].y;
-    __syncthreads();
-#pragma unroll
-    for (int m = 0; m < 32; ++m) {
-        const float zi = lds[(s + TY * m) * P::LD + c], mi = lds[(s + TY * m) * P::LD + cm];
-        const float hs = 0.5f * (zi + mi);
-        const float vx = b[m].x + w.x * hs;
-        // c = 0: b[m].x holds Re Z[0], the imaginary part carries X[M]
-        const float vy = c == 0 ? b[m].x - zi : b[m].y + 0.5f * (zi - mi) + w.y * hs;
-        b[m] = cx<float>{vx * f, vy * f};
-    }
-    __syncthreads();
-
-    // y phase: column c, N-point FFT
-    fft_regs<float, N, 32, -1, 32>(b, s, tw, 1,
-                                   xch_split<float, idx_cols<M, P::PS>>{lds, idx_cols<M, P::PS>{c}});
-
-    // separate the packed column: thread (s, 0) needs P(-ky) from (s', 0)
-    cx<float>* col0 = reinterpret_cast<cx<float>*>(lds);
-    if (c == 0) {
-#pragma unroll
-        for (int m = 0; m < 32; ++m) col0[s + TY * m] = b[m];
-    }
-    __syncthreads();
-    // store rows of the half spectrum: wave lanes are consecutive columns
-#pragma unroll
-    for (int m = 0; m < 32; ++m) {
-        const int ky = s + TY * m;
-        cx<float>* dst = out + map_row(plane * N + ky, map) * K;
-        if (c == 0) {
-            const cx<float> pc = conjg(col0[(N - ky) & (N - 1)]);
-            const cx<float> sum = b[m] + pc, dif = b[m] - pc;
-            dst[0] = cx<float>{0.5f * sum.x, 0.5f * sum.y};   // X[ky][0]
-            dst[M] = cx<float>{0.5f * dif.y, -0.5f * dif.x};  // X[ky][M] = dif / 2i
-        } else {
-            dst[c] = b[m];
-        }
-    }
-}
-
-template <int N>
-__global__ __launch_bounds__(plane_shape<N>::NT) void k_plane_c2r(
-    const cx<float>* in, float* out, const cx<float>* __restrict__ tw, int64_t planes,
-    row_map map, float mul_edge, float mul_int) {
-    using P = plane_shape<N>;
-    constexpr int M = P::M, K = P::K, TZ = P::TZ, TY = P::TY;
-    __shared__ float lds[P::LDS];
-    const int64_t plane = blockIdx.x;
-    const int tid = threadIdx.x;
-    const int r = tid / TZ, t = tid % TZ;
-    const int c = tid % M, s = tid / M;
-
-    // y phase input: column c of the half spectrum, bin multipliers applied;
-    // column 0 carries the Hermitian parts of kz = 0 (real) and kz = M
-    // (imaginary), formed through LDS
-    cx<float> b[32];
-    cx<float>* col0 = reinterpret_cast<cx<float>*>(lds);
-#pragma unroll
-    for (int m = 0; m < 32; ++m) {
-        const int ky = s + TY * m;
-        const cx<float>* row = in + map_row(plane * N + ky, map) * K;
-        if (c == 0) {
-            col0[ky] = scal(row[0], mul_edge);
-            col0[N + ky] = scal(row[M], mul_edge);
-        } else {
-            b[m] = scal(row[c], mul_int);
-        }
-    }
-    __syncthreads();
-    if (c == 0) {
-#pragma unroll
-        for (int m = 0; m < 32; ++m) {
-            const int ky = s + TY * m, kn = (N - ky) & (N - 1);
-            const cx<float> h0 = scal(col0[ky] + conjg(col0[kn]), 0.5f);
-            const cx<float> hm = scal(col0[N + ky] + conjg(col0[N + kn]), 0.5f);
-            b[m] = cx<float>{h0.x - hm.y, h0.y + hm.x};  // h0 + i hm
-        }
-    }
-    __syncthreads();
-    fft_regs<float, N, 32, +1, 32>(b, s, tw, 1,
-                                   xch_split<float, idx_cols<M, P::PS>>{lds, idx_cols<M, P::PS>{c}});
-
-    // columns -> rows, real then imaginary parts; column 0's real part is
-    // G[y][0] and its imaginary part G[y][M], both real bins of the z C2R
-    cx<float> g[32];
-#pragma unroll
-    for (int m = 0; m < 32; ++m) lds[(s + TY * m) * P::LD + c] = b[m].x;
-    __syncthreads();
-#pragma unroll
-    for (int m = 0; m < 32; ++m) g[m].x = lds[r * P::LD + t + TZ * m];
-    __syncthreads();
-#pragma unroll
-    for (int m = 0; m < 32; ++m) lds[(s + TY * m) * P::LD + c] = b[m].y;
-    __syncthreads();
-#pragma unroll
-    for (int m = 0; m < 32; ++m) g[m].y = lds[r * P::LD + t + TZ * m];
-    __syncthreads();
-    // thread t = 0 of row r: g[0] = (G[0], G[M]) as read; split them
-    const float g_m = g[0].y;
-    if (t == 0) g[0].y = 0.f;
-
-    // z C2R: Z'[k] = (G[k] + conj G[M-k]) + i conj(W_N^k) (G[k] - conj G[M-k]),
-    // with G[M] = g_m for k = 0
-    plane_mirror<N>(lds, r, t, g, [&](int m, cx<float> gk, cx<float> gmir) {
-        const int k = t + TZ * m;
-        const cx<float> gc = conjg(k == 0 ? cx<float>{g_m, 0.f} : gmir);
-        const cx<float> sm = gk + gc;
-        const cx<float> d = cmulc(gk - gc, tw[k]);
-        return cx<float>{sm.x - d.y, sm.y + d.x};
-    });
-    fft_regs<float, M, 32, +1, 32>(g, t, tw, 2,
-                                   xch_split<float, idx_rows<P::PS>>{lds, idx_rows<P::PS>{r * P::MP}});
-    cx<float>* dst = reinterpret_cast<cx<float>*>(out + (plane * N + r) * map.rs);
-#pragma unroll
-    for (int m = 0; m < 32; ++m) dst[t + TZ * m] = g[m];
 }
 
 // ---------------------------------------------------------------- y / x C2C
@@ -778,12 +527,6 @@ __global__ __launch_bounds__(kThreads) void k_copy16(const uint4* __restrict__ s
 }
 
 // ---------------------------------------------------------------- launchers
-// Grids are one-dimensional, and a dispatch carries its size in work-items
-// as a 32-bit count: refuse grids beyond either limit.
-static bool grid_fits(int64_t blocks, int64_t threads) {
-    return blocks <= 0x7fffffff && blocks * threads <= int64_t(0xffffffff);
-}
-
 template <typename T, int N>
 static hipError_t z_r2c_n(const void* in, void* out, const void* tw, int64_t rows,
                           row_map map, double me, double mi, hipStream_t s) {
@@ -972,49 +715,6 @@ hipError_t launch_pack_rows(bool f64, const void* src, void* dst, int64_t rows, 
                            static_cast<const cx<float>*>(src), static_cast<cx<float>*>(dst),
                            rows, k, map, to_send);
     return hipGetLastError();
-}
-
-template <int N>
-static hipError_t plane_n(bool forward, const void* in, void* out, const void* tw, int64_t planes,
-                          row_map map, double me, double mi, hipStream_t s) {
-    if (planes == 0) return hipSuccess;
-    if (!grid_fits(planes, plane_shape<N>::NT)) return hipErrorInvalidValue;
-    if (forward) {
-        hipLaunchKernelGGL(k_plane_r2c<N>, dim3(planes), dim3(plane_shape<N>::NT), 0, s,
-                           static_cast<const float*>(in), static_cast<cx<float>*>(out),
-                           static_cast<const cx<float>*>(tw), planes, map, float(me), float(mi));
-    } else {
-        if constexpr (N <= 128) {
-            hipLaunchKernelGGL(k_plane_c2r<N>, dim3(planes), dim3(plane_shape<N>::NT), 0, s,
-                               static_cast<const cx<float>*>(in), static_cast<float*>(out),
-                               static_cast<const cx<float>*>(tw), planes, map, float(me),
-                               float(mi));
-        } else {
-            return hipErrorInvalidValue;
-        }
-    }
-    return hipGetLastError();
-}
-
-// Measured against the separate passes over 537 MB of FP32 reals (a pair is
-// forward + inverse): N = 64 1.10 vs 2.14 ms per pair, N = 128 1.22 vs
-// 1.57 ms; at N = 256 the plane fills half the register file, one workgroup
-// runs per CU, and only the forward gains (0.65 vs 0.73 ms with the x pass;
-// the inverse takes 0.81 vs 0.72 ms), so the inverse keeps the separate
-// passes there.
-bool plane_supported(bool f64, int n, bool forward) {
-    return !f64 && (n == 64 || n == 128 || (forward && n == 256));
-}
-
-hipError_t launch_plane(bool f64, bool forward, int n, const void* in, void* out, const void* tw,
-                        int64_t planes, row_map map, double me, double mi, hipStream_t s) {
-    if (!plane_supported(f64, n, forward)) return hipErrorInvalidValue;
-    switch (n) {
-        case 64: return plane_n<64>(forward, in, out, tw, planes, map, me, mi, s);
-        case 128: return plane_n<128>(forward, in, out, tw, planes, map, me, mi, s);
-        case 256: return plane_n<256>(forward, in, out, tw, planes, map, me, mi, s);
-        default: return hipErrorInvalidValue;
-    }
 }
 
 hipError_t launch_copy16(const void* src, void* dst, int64_t n16, hipStream_t s) {

@@ -1,0 +1,44 @@
+// Addressing and launch helpers shared by the pass kernels.
+#pragma once
+
+#include "cx.h"
+#include "kernels.h"
+
+namespace gfft {
+
+constexpr int ilog2_c(int v) { return v <= 1 ? 0 : 1 + ilog2_c(v / 2); }
+
+// Largest radix per FFT stage.  The FP32 vector kernels take radix-32
+// stages, one LDS exchange fewer for 512- and 1024-point transforms (FP32 is
+// bound by instruction issue); FP64 and the matrix-core stage keep radix 16.
+template <typename T, int MF = 0>
+constexpr int radix_cap() { return sizeof(T) == 4 && MF == 0 ? 32 : 16; }
+
+__device__ __forceinline__ int64_t map_row(int64_t r, row_map m) {
+    const int64_t bx = r >> m.lg_n;
+    const int64_t y = r & ((int64_t(1) << m.lg_n) - 1);
+    const int64_t b = bx >> m.lg_x;
+    const int64_t xl = bx & ((int64_t(1) << m.lg_x) - 1);
+    if (m.paper) return (b << (m.lg_x + m.lg_n)) + (y << m.lg_x) + xl;
+    const int64_t j = y >> m.lg_y;
+    const int64_t yl = y & ((int64_t(1) << m.lg_y) - 1);
+    return (b << (m.lg_x + m.lg_n)) + ((((j << m.lg_x) + xl)) << m.lg_y) + yl;
+}
+
+// Consecutive workgroup ids are dealt round-robin to the 8 XCDs, each with
+// its own L2.  Remap so that XCD x works through one contiguous range of
+// tiles: neighbouring tiles share cache lines at their edges.
+__device__ __forceinline__ int64_t xcd_tile(int64_t g, int64_t G) {
+    constexpr int kXcd = 8;
+    const int64_t per = G / kXcd;
+    if (g >= per * kXcd) return g;
+    return (g % kXcd) * per + g / kXcd;
+}
+
+// Grids are one-dimensional, and a dispatch carries its size in work-items
+// as a 32-bit count: refuse grids beyond either limit.
+inline bool grid_fits(int64_t blocks, int64_t threads) {
+    return blocks <= 0x7fffffff && blocks * threads <= int64_t(0xffffffff);
+}
+
+}  // namespace gfft
