@@ -9,6 +9,17 @@
 
 namespace gfft {
 
+// p advanced by a 32-bit byte offset: a uniform pointer and one vector
+// register address the element.
+template <typename C>
+__device__ __forceinline__ const C* at_bytes(const C* p, uint32_t off) {
+    return reinterpret_cast<const C*>(reinterpret_cast<const char*>(p) + off);
+}
+template <typename C>
+__device__ __forceinline__ C* at_bytes(C* p, uint32_t off) {
+    return reinterpret_cast<C*>(reinterpret_cast<char*>(p) + off);
+}
+
 // FFT stages of R transforms side by side per thread (a[y], y < R), sharing
 // their twiddles and barriers; exchanges through LDS as real, then imaginary
 // parts.  Column c of TC; transform y occupies its own padded N x TC block.
@@ -303,6 +314,98 @@ __global__ __launch_bounds__((plane_shape<T, N, R, E>::NT), W) void k_plane_c2r(
     for (int m = 0; m < E; ++m) dst[t + TZ * m] = g[m];
 }
 
+// ---------------------------------------------------------------- x C2C with the y radix-R step
+// Second half of a split y transform (k_plane_* with R > 1) and the x
+// transform, in one strided pass over [b][x][y][kz] (y and kz flattened to
+// one contiguous column index per x).  A workgroup owns TC adjacent columns
+// of the first NY rows' range and the R - 1 column runs NY K further on each:
+// thread (c, t) holds x = t + TPT i of all R rows, so the R-point DFT over y0
+// needs no exchange.  src and dst may be the same buffer.
+//   NT: non-temporal loads and stores (no reuse), where every 128-byte line
+//       belongs to one tile;
+//   RMP: XCD-contiguous tile order.
+template <typename T, int N, int R, int TC, int EX>
+struct xr_shape {
+    static constexpr int K = N / 2 + 1, NY = N / R, TPT = N / EX, NT = TC * TPT;
+    static constexpr int RM = radix_cap<T>();
+    static constexpr int PS = first_radix_shift<EX, RM>::value;
+    static constexpr int NP = padded_len<N, PS>::value;
+    static constexpr int LDS = R * NP * TC;  // values of type T
+    static constexpr int COLS = NY * K;
+    static constexpr int TILES = (COLS + TC - 1) / TC;  // per grid
+};
+
+template <typename T, int N, int R, int TC, int EX, int S, bool NT, int W, bool RMP>
+__global__ __launch_bounds__((xr_shape<T, N, R, TC, EX>::NT), W) void k_strided_r(
+    const cx<T>* src, cx<T>* dst, const cx<T>* __restrict__ tw) {
+    using P = xr_shape<T, N, R, TC, EX>;
+    constexpr int K = P::K, NY = P::NY, TPT = P::TPT;
+    __shared__ T lds[P::LDS];
+    const int c = threadIdx.x % TC, t = threadIdx.x / TC;
+    const int64_t tile = RMP ? xcd_tile(blockIdx.x, gridDim.x) : int64_t(blockIdx.x);
+    const int64_t b = tile / P::TILES;
+    const int m = int(tile - b * P::TILES) * TC + c;
+    const bool valid = m < P::COLS;
+    const int ml = valid ? m : P::COLS - 1;
+    const int k1 = ml / K;
+    // Element (x, y0) of this lane: a workgroup-uniform base plus the lane's
+    // byte offset, which fits 32 bits (checked below), so that one vector
+    // register addresses all of them.
+    constexpr int64_t XS = int64_t(N) * K, YS = int64_t(NY) * K;
+    static_assert((TPT * XS + NY * K) * int64_t(sizeof(cx<T>)) < (int64_t(1) << 32), "lane offset");
+    const uint32_t lane = uint32_t((t * XS + ml) * int64_t(sizeof(cx<T>)));
+    src += b * N * XS;
+    dst += b * N * XS;
+
+    cx<T> a[R][EX];
+#pragma unroll
+    for (int i = 0; i < EX; ++i)
+#pragma unroll
+        for (int y = 0; y < R; ++y) {
+            const cx<T>* p = at_bytes(src + (i * TPT) * XS + y * YS, lane);
+            if constexpr (NT) {
+                a[y][i].x = __builtin_nontemporal_load(&p->x);
+                a[y][i].y = __builtin_nontemporal_load(&p->y);
+            } else {
+                a[y][i] = *p;
+            }
+        }
+    cx<T> w[R];
+#pragma unroll
+    for (int y = 1; y < R; ++y) w[y] = tw[y * k1];
+#pragma unroll
+    for (int i = 0; i < EX; ++i) {
+        cx<T> v[R];
+#pragma unroll
+        for (int y = 0; y < R; ++y) v[y] = a[y][i];
+        if constexpr (S < 0) {
+#pragma unroll
+            for (int y = 1; y < R; ++y) v[y] = twiddle<S>(v[y], w[y]);
+        }
+        dft<R, S>(v);
+        if constexpr (S > 0) {
+#pragma unroll
+            for (int y = 1; y < R; ++y) v[y] = twiddle<S>(v[y], w[y]);
+        }
+#pragma unroll
+        for (int y = 0; y < R; ++y) a[y][i] = v[y];
+    }
+    fft_multi<T, N, EX, R, S, 1, P::RM, TC, P::PS>(a, t, c, tw, 1, lds);
+    if (!valid) return;
+#pragma unroll
+    for (int i = 0; i < EX; ++i)
+#pragma unroll
+        for (int y = 0; y < R; ++y) {
+            cx<T>* p = at_bytes(dst + (i * TPT) * XS + y * YS, lane);
+            if constexpr (NT) {
+                __builtin_nontemporal_store(a[y][i].x, &p->x);
+                __builtin_nontemporal_store(a[y][i].y, &p->y);
+            } else {
+                *p = a[y][i];
+            }
+        }
+}
+
 // Shape of the one-plane kernels: elements per thread and the minimum of
 // waves per SIMD the register allocation keeps.  Measured over 537 MB of
 // reals (forward / inverse step 1, us; in brackets the separate z and y
@@ -355,6 +458,117 @@ hipError_t launch_plane(bool f64, bool forward, int n, const void* in, void* out
         case 128: return plane_n<float, 128>(forward, in, out, tw, planes, map, me, mi, s);
         default: return plane_n<float, 256>(forward, in, out, tw, planes, map, me, mi, s);
     }
+}
+
+// Split y transform: R (row tiles of 64 rows), the row tile's elements per thread, and the x pass's
+// columns per tile, elements per row and thread, hints and tile order.  64
+// rows leave room for two or more row tiles on a CU and keep the x tile's
+// runs at 64 bytes or more.  Measured over 537 MB of
+// reals, row tiles forward / inverse and x pass, us (in brackets the step 1
+// and x passes they replace):
+//   FP64 N = 128, R = 2: 205 / 204 + 194 (215 / 209 + 217)
+//        N = 256, R = 4: 207 / 209 + 244 (397 / 414 + 242)
+//   FP32 N = 128, R = 2: 215 / 222 + 182 (228 / 220 + 218)
+//        N = 256, R = 4: 212 / 218 + 231 (327 / 333 + 233)
+//        N = 512, R = 8: 226 / 237 + 331 (448 / 445 + 272)
+// FP64 N = 512 would need R = 8 with 4-column x tiles that fill a CU:
+// 446 / 492 + 691 against 815 / 803 + 458, not taken.  N = 64 planes have
+// room as they are.  The x tiles at N = 128 cover whole 128-byte lines and
+// run fastest without the XCD order and non-temporally (FP32 182 against
+// 198 with the order, 212 without the hint); at N = 256 FP64 the order and
+// plain accesses (244 against 254 and 250), FP32 plain accesses without the
+// order (231 against 242); at FP32 N = 512 the tiles' 64-byte runs share
+// lines, so both the order and plain accesses (331 against 376, 460).
+template <typename T, int N>
+struct split_cfg {
+    static constexpr bool F64 = sizeof(T) == 8;
+    static constexpr int R = N / 64;
+    static constexpr int E = !F64 && N == 128 ? 8 : 16, W = F64 && N == 128 ? 2 : 4;
+    static constexpr int TC = N == 128 ? 32 : F64 ? 8 : N == 256 ? 16 : 8, EX = 8;
+    static constexpr int WX = R * EX * int(sizeof(cx<T>)) > 256 ? 2 : 4;
+    static constexpr bool NT = N == 128, RMP = N == 512 || (F64 && N == 256);
+};
+
+template <typename T, int N>
+static hipError_t split_rows_n(bool forward, const void* in, void* out, const void* tw,
+                               int64_t planes, row_map map, double me, double mi, hipStream_t s) {
+    using C = split_cfg<T, N>;
+    constexpr int NT = plane_shape<T, N, C::R, C::E>::NT;
+    const int64_t blocks = planes * C::R;
+    if (blocks == 0) return hipSuccess;
+    if (!grid_fits(blocks, NT)) return hipErrorInvalidValue;
+    if (forward)
+        hipLaunchKernelGGL((k_plane_r2c<T, N, C::R, C::E, C::W>), dim3(blocks), dim3(NT), 0, s,
+                           static_cast<const T*>(in), static_cast<cx<T>*>(out),
+                           static_cast<const cx<T>*>(tw), map, T(me), T(mi));
+    else
+        hipLaunchKernelGGL((k_plane_c2r<T, N, C::R, C::E, C::W>), dim3(blocks), dim3(NT), 0, s,
+                           static_cast<const cx<T>*>(in), static_cast<T*>(out),
+                           static_cast<const cx<T>*>(tw), map, T(me), T(mi));
+    return hipGetLastError();
+}
+
+template <typename T, int N, int S, bool NT, bool RMP>
+static hipError_t split_x_run(const void* src, void* dst, const void* tw, int64_t batch,
+                              hipStream_t s) {
+    using C = split_cfg<T, N>;
+    using P = xr_shape<T, N, C::R, C::TC, C::EX>;
+    const int64_t blocks = batch * P::TILES;
+    if (blocks == 0) return hipSuccess;
+    if (!grid_fits(blocks, P::NT)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_strided_r<T, N, C::R, C::TC, C::EX, S, NT, C::WX, RMP>), dim3(blocks),
+                       dim3(P::NT), 0, s, static_cast<const cx<T>*>(src),
+                       static_cast<cx<T>*>(dst), static_cast<const cx<T>*>(tw));
+    return hipGetLastError();
+}
+
+template <typename T, int N, int S>
+static hipError_t split_x_n(const void* src, void* dst, const void* tw, int64_t batch,
+                            hipStream_t s) {
+    using C = split_cfg<T, N>;
+    // the non-temporal hint is for tiles that own their lines: a buffer off
+    // the 128-byte grid takes plain accesses in XCD order
+    if constexpr (C::NT) {
+        const uintptr_t both = reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst);
+        if (both % 128 != 0) return split_x_run<T, N, S, false, true>(src, dst, tw, batch, s);
+    }
+    return split_x_run<T, N, S, C::NT, C::RMP>(src, dst, tw, batch, s);
+}
+
+bool split_supported(bool f64, int n) { return n == 128 || n == 256 || (!f64 && n == 512); }
+
+hipError_t launch_split_rows(bool f64, bool forward, int n, const void* in, void* out,
+                             const void* tw, int64_t planes, row_map map, double me, double mi,
+                             hipStream_t s) {
+    if (!split_supported(f64, n)) return hipErrorInvalidValue;
+    if (f64)
+        return n == 128 ? split_rows_n<double, 128>(forward, in, out, tw, planes, map, me, mi, s)
+                        : split_rows_n<double, 256>(forward, in, out, tw, planes, map, me, mi, s);
+    switch (n) {
+        case 128: return split_rows_n<float, 128>(forward, in, out, tw, planes, map, me, mi, s);
+        case 256: return split_rows_n<float, 256>(forward, in, out, tw, planes, map, me, mi, s);
+        default: return split_rows_n<float, 512>(forward, in, out, tw, planes, map, me, mi, s);
+    }
+}
+
+template <int S>
+static hipError_t split_x_sign(bool f64, int n, const void* src, void* dst, const void* tw,
+                               int64_t batch, hipStream_t s) {
+    if (f64)
+        return n == 128 ? split_x_n<double, 128, S>(src, dst, tw, batch, s)
+                        : split_x_n<double, 256, S>(src, dst, tw, batch, s);
+    switch (n) {
+        case 128: return split_x_n<float, 128, S>(src, dst, tw, batch, s);
+        case 256: return split_x_n<float, 256, S>(src, dst, tw, batch, s);
+        default: return split_x_n<float, 512, S>(src, dst, tw, batch, s);
+    }
+}
+
+hipError_t launch_split_x(bool f64, int n, int sign, const void* src, void* dst, const void* tw,
+                          int64_t batch, hipStream_t s) {
+    if (!split_supported(f64, n)) return hipErrorInvalidValue;
+    return sign < 0 ? split_x_sign<-1>(f64, n, src, dst, tw, batch, s)
+                    : split_x_sign<+1>(f64, n, src, dst, tw, batch, s);
 }
 
 }  // namespace gfft

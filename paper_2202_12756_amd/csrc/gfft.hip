@@ -264,6 +264,24 @@ gfft_status run_plane(const gfft_plan* p, bool fwd, const void* in, void* out, d
                                          p->batch * p->x, zmap(p), me, mi, s));
 }
 
+// Two passes for the whole transform of a full grid.  Not in place: the row
+// tiles of a plane write rows that other tiles have still to read.
+bool split_pass(const gfft_plan* p) {
+    return !p->pencil && p->p == 1 && !(p->flags & GFFT_INPLACE) && mfma_terms(p) == 0 &&
+           gfft::split_supported(f64(p), int(p->n));
+}
+
+gfft_status run_split_rows(const gfft_plan* p, bool fwd, const void* in, void* out, double scale,
+                           bool weighted, hipStream_t s) {
+    const double me = scale, mi = weighted ? (fwd ? 2.0 : 0.5) * scale : scale;
+    return hip_status(gfft::launch_split_rows(f64(p), fwd, int(p->n), in, out, p->tw,
+                                              p->batch * p->x, zmap(p), me, mi, s));
+}
+
+gfft_status run_split_x(const gfft_plan* p, int sign, void* data, hipStream_t s) {
+    return hip_status(gfft::launch_split_x(f64(p), int(p->n), sign, data, data, p->tw, p->batch, s));
+}
+
 gfft_status forward(const gfft_plan* p, const void* in, void* out, double scale,
                     bool weighted, void* stream) {
     gfft_status st = check_r2c_args(p, in, out);
@@ -272,6 +290,10 @@ gfft_status forward(const gfft_plan* p, const void* in, void* out, double scale,
     if (!std::isfinite(scale)) return GFFT_E_INVALID_ARG;
     if ((st = check_device(p)) != GFFT_OK) return st;
     hipStream_t s = as_stream(stream);
+    if (split_pass(p)) {
+        if ((st = run_split_rows(p, true, in, out, scale, weighted, s)) != GFFT_OK) return st;
+        return run_split_x(p, -1, out, s);
+    }
     if (plane_pass(p)) {
         if ((st = run_plane(p, true, in, out, scale, weighted, s)) != GFFT_OK) return st;
     } else {
@@ -290,6 +312,10 @@ gfft_status inverse(const gfft_plan* p, void* in, void* out, double scale, bool 
     if (!std::isfinite(scale)) return GFFT_E_INVALID_ARG;
     if ((st = check_device(p)) != GFFT_OK) return st;
     hipStream_t s = as_stream(stream);
+    if (split_pass(p)) {
+        if ((st = run_split_x(p, +1, in, s)) != GFFT_OK) return st;
+        return run_split_rows(p, false, in, out, scale, weighted, s);
+    }
     if (p->p == 1 && (st = run_x(p, in, +1, s)) != GFFT_OK) return st;
     if (plane_pass(p)) return run_plane(p, false, in, out, scale, weighted, s);
     if ((st = run_y(p, in, +1, s)) != GFFT_OK) return st;

@@ -42,3 +42,51 @@ def test_plane_step1(n, x, batch, order, dtype):
     torch.cuda.synchronize()
     assert rel_l2(S, want) <= TOL[dtype]
     assert rel_l2(host(out), back) <= TOL[dtype]
+
+
+def _offset(shape, dtype, nbytes=16):
+    """An empty buffer that starts 16 bytes past a line boundary."""
+    skip = nbytes // torch.empty((), dtype=dtype).element_size()
+    size = 1
+    for v in shape:
+        size *= v
+    return torch.empty(size + skip, dtype=dtype, device="cuda")[skip:].view(shape)
+
+
+@pytest.mark.parametrize("aligned", [True, False], ids=["line", "off_line"])
+@pytest.mark.parametrize("n,batch,dtype", [(128, 3, F64), (128, 2, F32), (256, 1, F64),
+                                           (256, 2, F32), (512, 1, F32)])
+def test_split_y_full_grid(n, batch, dtype, aligned):
+    """Full grids through the two-pass kernels against the separate z, y and
+    x passes, with the adjoints' weights, on buffers on and off the 128-byte
+    line grid; up to 256^3 also against the oracle."""
+    p = Plan(n, dtype, batch=batch)
+    xin, xref = real_input(p.real_shape, 22000 + n, dtype)
+    out = p.empty_spectrum() if aligned else _offset(p.spectrum_shape, p.cdtype)
+    F = p.r2c(xin, out)
+    W = p.c2r_adjoint(xin, scale=3.0)
+    sep, sepw = p.z_r2c(xin), p.z_r2c(xin, scale=3.0, weighted=True)
+    for s in (sep, sepw):
+        p.y_c2c(s, -1)
+        p.x_c2c(s, -1)
+    tol = TOL[dtype]
+
+    def off(a, b):
+        return (torch.linalg.vector_norm(a - b) / torch.linalg.vector_norm(b)).item()
+
+    assert off(F, sep) <= tol and off(W, sepw) <= tol
+    if n <= 256 and aligned:
+        assert rel_l2(host(F), oracle.r2c3d(xref)) <= tol
+    del sep, sepw, W, F, out, xref
+    # inverse on a non-Hermitian half spectrum
+    g, gref = cplx_input(p.spectrum_shape, 22500 + n, dtype)
+    gs = g.clone()
+    p.x_c2c(gs, +1)
+    p.y_c2c(gs, +1)
+    want, wantw = p.z_c2r(gs, scale=0.5), p.z_c2r(gs, scale=0.25, weighted=True)
+    work = torch.empty_like(g) if aligned else _offset(p.spectrum_shape, p.cdtype)
+    got = p.c2r(work.copy_(g), scale=0.5)
+    gotw = p.r2c_adjoint(work.copy_(g), scale=0.25)
+    assert off(got, want) <= tol and off(gotw, wantw) <= tol
+    if n == 128 and aligned:
+        assert rel_l2(host(got), 0.5 * oracle.c2r3d(gref, n)) <= tol
