@@ -307,7 +307,9 @@ struct sshape {
     static constexpr int MAXT = F64 ? (WIDE ? 512 : 256) : (BIG32 || MFMA ? 1024 : 512);
     static constexpr int LDS = (F64 ? WIDE && !Y512 : BIG32) ? 131072 : 65536;
     static constexpr int TC_T = MAXT / TPT;
-    static constexpr int CAP = C32 ? 32 : (256 / TPT) > 16 ? (256 / TPT) : 16;
+    // FP64 x lines of N = 64: 32 columns, 5.85 against 5.33 TB/s with 64
+    static constexpr int CAP = C32 || (F64 && !MFMA && AX == 1 && N == 64) ? 32
+                               : (256 / TPT) > 16 ? (256 / TPT) : 16;
     static constexpr int FULL = LDS / (N * int(sizeof(cx<T>)));
     static constexpr int A0 = TC_T < CAP ? TC_T : CAP;
     static constexpr int A1 = A0 < 2 * FULL ? A0 : 2 * FULL;
@@ -322,7 +324,9 @@ struct sshape {
 // MF: 0 vector stages; 2 or 3 the first radix-16 stage on the matrix cores;
 // -1 no transform (each element replaced by its conjugate): the same loads
 // and stores as the pass, a yardstick for its memory-access ceiling.
-template <typename T, int N, int TC, int XP, int S, int E = 16, int MF = 0, bool NT = false>
+// RMP: tiles in XCD-contiguous order (false: in launch order).
+template <typename T, int N, int TC, int XP, int S, int E = 16, int MF = 0, bool NT = false,
+          bool RMP = true>
 __global__ __launch_bounds__(TC * N / E) void k_strided(
     cx<T>* __restrict__ data, const cx<T>* __restrict__ tw, int64_t m_cols,
     int64_t tiles_m, line_map lm) {
@@ -337,7 +341,7 @@ __global__ __launch_bounds__(TC * N / E) void k_strided(
 
     const int c = threadIdx.x % TC;
     const int t = threadIdx.x / TC;
-    const int64_t tile = xcd_tile(blockIdx.x, gridDim.x);
+    const int64_t tile = RMP ? xcd_tile(blockIdx.x, gridDim.x) : int64_t(blockIdx.x);
     const int64_t b = tile / tiles_m;
     const int64_t m0 = (tile - b * tiles_m) * TC;
     const int64_t m = m0 + c;
@@ -584,9 +588,9 @@ static bool whole_lines(const void* data, int64_t m_cols, const line_map& lm, in
            lm.b_hi % la == 0 && lm.b_lo % la == 0 && lm.s_hi % la == 0 && lm.s_lo % la == 0;
 }
 
-template <typename T, int N, int AX, int MF>
-static hipError_t strided_ax(int sign, void* data, const void* tw, int64_t m_cols,
-                             int64_t n_b, line_map lm, hipStream_t s) {
+template <typename T, int N, int AX, int MF, bool NT, bool RMP>
+static hipError_t strided_run(int sign, void* data, const void* tw, int64_t m_cols,
+                              int64_t n_b, line_map lm, hipStream_t s) {
     using SH = sshape<T, N, AX, (MF > 0)>;
     constexpr int TC = SH::TC;
     const int64_t tiles_m = (m_cols + TC - 1) / TC;
@@ -594,35 +598,59 @@ static hipError_t strided_ax(int sign, void* data, const void* tw, int64_t m_col
     if (blocks == 0) return hipSuccess;
     if (!grid_fits(blocks, TC * SH::TPT)) return hipErrorInvalidValue;
     const dim3 threads(TC * SH::TPT);
-    // x lines stream through non-temporally when every tile owns whole
-    // 128-byte lines: at 1024^3 2% faster in FP64 and 4% in FP32, at 2048^3
-    // 8% faster in FP32 but 5% slower in FP64 (one 512-thread workgroup per
-    // CU), so FP64 uses it for N = 512 and 1024 only, FP32 from N = 256.
-    // Where neighbouring tiles share lines, as in the y passes, the hint
-    // makes them travel twice (15-50% slower).
-    if constexpr (AX == 1 && MF <= 0 && (N >= 512 || (sizeof(T) == 4 && N == 256)) &&
-                  (sizeof(T) == 4 || N <= 1024) && (TC * sizeof(cx<T>)) % 128 == 0) {
-        if (whole_lines(data, m_cols, lm, 128 / int64_t(sizeof(cx<T>)))) {
-            if (MF < 0 || sign < 0)
-                hipLaunchKernelGGL((k_strided<T, N, TC, SH::XP, -1, SH::E, MF, true>), dim3(blocks),
-                                   threads, 0, s, static_cast<cx<T>*>(data),
-                                   static_cast<const cx<T>*>(tw), m_cols, tiles_m, lm);
-            else if constexpr (MF == 0)
-                hipLaunchKernelGGL((k_strided<T, N, TC, SH::XP, +1, SH::E, 0, true>), dim3(blocks),
-                                   threads, 0, s, static_cast<cx<T>*>(data),
-                                   static_cast<const cx<T>*>(tw), m_cols, tiles_m, lm);
-            return hipGetLastError();
+    if (MF < 0 || sign < 0)
+        hipLaunchKernelGGL((k_strided<T, N, TC, SH::XP, -1, SH::E, MF, NT, RMP>), dim3(blocks),
+                           threads, 0, s, static_cast<cx<T>*>(data),
+                           static_cast<const cx<T>*>(tw), m_cols, tiles_m, lm);
+    else if constexpr (MF >= 0)
+        hipLaunchKernelGGL((k_strided<T, N, TC, SH::XP, +1, SH::E, MF, NT, RMP>), dim3(blocks),
+                           threads, 0, s, static_cast<cx<T>*>(data),
+                           static_cast<const cx<T>*>(tw), m_cols, tiles_m, lm);
+    return hipGetLastError();
+}
+
+// Tile order and hints of the x passes.  Where every tile owns whole
+// 128-byte lines the lines stream through non-temporally; neighbouring tiles
+// then share nothing, and launch order (the 8 XCDs side by side on one run of
+// columns) beats the XCD-contiguous order except where a line's elements lie
+// megabytes apart.  TB/s on 0.5-1.1 GB of received pencils, launch order /
+// XCD order (both with the hint, the N <= 128 and FP64 256 ones in XCD order
+// without it):
+//   FP64 N = 64 5.85 / 5.42, 128 5.71 / 5.02, 512 4.94 / 4.73 (full grids),
+//        4.80 / 3.90 (p = 8); 1024 4.74 / 4.31 (p = 32), 4.73 / 4.68 (p = 8),
+//        4.69 / 4.94 (p = 4), 4.57 / 5.11 (full grid); 256 4.67 / 4.44 (p = 2)
+//        but 3.73 / 4.31 (full grid, elements 516 KB apart)
+//   FP32 N = 64 6.11 / 5.53, 128 5.54 / 4.94, 256 4.65 / 4.25, 512 5.04 / 4.11,
+//        1024 4.56 / 4.23 (p = 8), 4.59 / 4.45 (p = 4), 4.69 / 4.84 (p = 2);
+//        2048 3.87 / 3.67 (p = 32), 3.84 / 3.88 (p = 4)
+// Hence launch order up to 2 MiB between elements (any distance up to
+// N = 512; FP64 256 up to 512 KB), and not below 4 KB, where few columns
+// remain (FP32 128 at 2 KB 3.39 / 5.19).  The XCD order keeps the hint from
+// N = 512 (FP32 256) up, but FP64 2048 (one 512-thread workgroup per CU) is 5%
+// slower with it.  Where neighbouring tiles share lines, as in the y passes,
+// the hint makes them travel twice (15-50% slower).
+template <typename T, int N, int AX, int MF>
+static hipError_t strided_ax(int sign, void* data, const void* tw, int64_t m_cols,
+                             int64_t n_b, line_map lm, hipStream_t s) {
+    constexpr bool F64 = sizeof(T) == 8;
+    constexpr int ES = int(sizeof(cx<T>));
+    using SH = sshape<T, N, AX, (MF > 0)>;
+    if constexpr (AX == 1 && MF <= 0 && N >= 64 && (!F64 || N <= 1024) && (SH::TC * ES) % 128 == 0) {
+        if (whole_lines(data, m_cols, lm, 128 / ES)) {
+            // mean distance between neighbouring elements of a line
+            constexpr int64_t HALF = N / 2;
+            const int64_t step = ((HALF >> lm.lg_y) * lm.s_hi +
+                                  (HALF & ((int64_t(1) << lm.lg_y) - 1)) * lm.s_lo) / HALF * ES;
+            constexpr int64_t FAR = F64 && N == 256 ? int64_t(512) << 10
+                                    : N <= 512      ? int64_t(1) << 62
+                                                    : int64_t(2) << 20;
+            if (step >= 4096 && step < FAR)
+                return strided_run<T, N, AX, MF, true, false>(sign, data, tw, m_cols, n_b, lm, s);
+            if constexpr (N >= 512 || (!F64 && N == 256))
+                return strided_run<T, N, AX, MF, true, true>(sign, data, tw, m_cols, n_b, lm, s);
         }
     }
-    if (MF < 0 || sign < 0)
-        hipLaunchKernelGGL((k_strided<T, N, TC, SH::XP, -1, SH::E, MF>), dim3(blocks), threads,
-                           0, s, static_cast<cx<T>*>(data), static_cast<const cx<T>*>(tw),
-                           m_cols, tiles_m, lm);
-    else if constexpr (MF >= 0)
-        hipLaunchKernelGGL((k_strided<T, N, TC, SH::XP, +1, SH::E, MF>), dim3(blocks), threads,
-                           0, s, static_cast<cx<T>*>(data), static_cast<const cx<T>*>(tw),
-                           m_cols, tiles_m, lm);
-    return hipGetLastError();
+    return strided_run<T, N, AX, MF, false, true>(sign, data, tw, m_cols, n_b, lm, s);
 }
 
 template <typename T, int N>

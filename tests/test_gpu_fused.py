@@ -90,3 +90,20 @@ def test_split_y_full_grid(n, batch, dtype, aligned):
     assert off(got, want) <= tol and off(gotw, wantw) <= tol
     if n == 128 and aligned:
         assert rel_l2(host(got), 0.5 * oracle.c2r3d(gref, n)) <= tol
+
+
+@DTYPES
+@pytest.mark.parametrize("n,ranks,batch", [(64, 1, 3), (64, 8, 2), (64, 64, 2), (128, 16, 2),
+                                           (256, 1, 1), (256, 8, 1), (1024, 64, 1)])
+def test_x_pass_orders(n, ranks, batch, dtype):
+    """x passes on both sides of the tile order's bounds (elements under
+    4 KB apart, up to and beyond 512 KB), on buffers on and off the 128-byte
+    line grid, both signs."""
+    p = Plan(n, dtype, slab_x=n // ranks, batch=batch)
+    pen, ref = cplx_input(p.pencil_shape, 23000 + n + ranks, dtype)
+    for sign in (-1, +1):
+        want = oracle.c2c_axis(ref, 1, sign)
+        for buf in (torch.empty_like(pen), _offset(p.pencil_shape, p.cdtype)):
+            got = p.x_c2c(buf.copy_(pen), sign)
+            torch.cuda.synchronize()
+            assert rel_l2(host(got), want) <= TOL[dtype]
