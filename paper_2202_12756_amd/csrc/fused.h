@@ -314,6 +314,192 @@ __global__ __launch_bounds__((plane_shape<T, N, R, E>::NT), W) void k_plane_c2r(
     for (int m = 0; m < E; ++m) dst[t + TZ * m] = g[m];
 }
 
+// ---------------------------------------------------------------- whole grids of N = 16 and 32
+// The whole 3D transform of one small grid per workgroup: one read, one
+// write, one launch.  A grid is N N M complex values z (M = N/2, z[n] =
+// x[2n] + i x[2n+1] along z), one line of N values (or two of M along z) per
+// thread, so every axis is a register transform and the grid only moves
+// through LDS between them:
+//   thread tid = (y, z) = y M + z    holds the x line of (y, z),
+//          tid = (x, z) = x M + z    the y line,
+//          l = x N + y, l = tid and tid + NT, the two z lines.
+// The real split acts on the 3D transform Z of the packed grid: with
+// C = conj Z(-kx, -ky, -kz), X = (Z + C)/2 - (i/2) W_N^kz (Z - C), and
+// X(kz = M) = (Z + C)/2 + (i/2)(Z - C) at kz = 0; the inverse forms
+// Z' = (G + P) + i conj(W_N^kz) (G - P), P = conj G(-kx, -ky, M - kz), with
+// the Hermitian parts of kz = 0 and kz = M at kz = 0 (their anti-Hermitian
+// parts do not reach the real field).  Exchanges go real parts first, then
+// imaginary parts.  Row stride M + 1 and plane stride N (M + 1) + M keep the
+// lanes of all three line orders on different LDS banks (and leave room for
+// the M + 1 columns of a half spectrum).  All loads precede the first
+// barrier and all stores follow the last: grids may be transformed in place.
+template <typename T, int N>
+struct box_shape {
+    static constexpr int M = N / 2, K = M + 1, NT = N * M;
+    static constexpr int SY = M + 1, SX = N * SY + M;
+    static constexpr int LDS = N * SX;                     // values of type T
+    static constexpr int W = sizeof(T) == 8 && N == 32 ? 2 : 4;  // waves per SIMD
+    static_assert(LDS >= 6 * N * N, "room for the packed columns");
+};
+
+// LDS exchange of the grid between two line orders: value m of the thread
+// goes to from(m) and value m of the new line is read at to(m).
+template <int N, typename T, class F, class G>
+__device__ __forceinline__ void box_exchange(T* lds, cx<T> (&a)[N], F&& from, G&& to) {
+#pragma unroll
+    for (int part = 0; part < 2; ++part) {
+#pragma unroll
+        for (int m = 0; m < N; ++m) lds[from(m)] = part ? a[m].y : a[m].x;
+        __syncthreads();
+#pragma unroll
+        for (int m = 0; m < N; ++m) {
+            const T v = lds[to(m)];
+            if (part) a[m].y = v;
+            else a[m].x = v;
+        }
+        __syncthreads();
+    }
+}
+
+template <typename T, int N>
+__global__ __launch_bounds__((box_shape<T, N>::NT), (box_shape<T, N>::W)) void k_box_r2c(
+    const T* in, cx<T>* out, const cx<T>* __restrict__ tw, int64_t rs, T mul_edge, T mul_int) {
+    using P = box_shape<T, N>;
+    constexpr int M = P::M, K = P::K, NT = P::NT, SY = P::SY, SX = P::SX;
+    __shared__ T lds[P::LDS];
+    const int tid = threadIdx.x, hi = tid / M, z = tid % M;
+    const int half = int(rs / 2);  // complex values between real rows
+    const cx<T>* src = reinterpret_cast<const cx<T>*>(in) + int64_t(blockIdx.x) * N * N * half;
+    auto xline = [&](int m) { return m * SX + hi * SY + z; };  // hi = y
+    auto yline = [&](int m) { return hi * SX + m * SY + z; };  // hi = x
+    auto zline = [&](int m) {
+        const int l = tid + (m / M) * NT;
+        return (l / N) * SX + (l % N) * SY + m % M;
+    };
+    cx<T> a[N];
+#pragma unroll
+    for (int m = 0; m < N; ++m) a[m] = src[(hi * N + m) * half + z];
+    dft<N, -1>(a);
+    box_exchange<N>(lds, a, yline, zline);
+    dft<M, -1>(a);
+    dft<M, -1>(a + M);
+    box_exchange<N>(lds, a, zline, xline);
+    dft<N, -1>(a);
+
+    // real split: thread (ky, kz) reads the mirrored values of its x line
+    const int ym = (N - hi) & (N - 1), zm = (M - z) & (M - 1);
+    const cx<T> w = tw[z];
+    T s[N];  // sums of the real parts; a[m].x becomes their difference
+#pragma unroll
+    for (int m = 0; m < N; ++m) lds[xline(m)] = a[m].x;
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < N; ++m) {
+        const T c = lds[((N - m) & (N - 1)) * SX + ym * SY + zm];
+        s[m] = T(0.5) * (a[m].x + c);
+        a[m].x = T(0.5) * (a[m].x - c);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < N; ++m) lds[xline(m)] = a[m].y;
+    __syncthreads();
+    cx<T>* dst = out + int64_t(blockIdx.x) * N * N * K + hi * K + z;
+    const T f = z == 0 ? mul_edge : mul_int;
+#pragma unroll
+    for (int m = 0; m < N; ++m) {
+        const T c = lds[((N - m) & (N - 1)) * SX + ym * SY + zm];
+        const cx<T> A{s[m], T(0.5) * (a[m].y - c)}, D{a[m].x, T(0.5) * (a[m].y + c)};
+        const cx<T> B = cmul(w, D);
+        dst[m * N * K] = cx<T>{(A.x + B.y) * f, (A.y - B.x) * f};
+        if (z == 0) dst[m * N * K + M] = cx<T>{(A.x - B.y) * f, (A.y + B.x) * f};
+    }
+}
+
+template <typename T, int N>
+__global__ __launch_bounds__((box_shape<T, N>::NT), (box_shape<T, N>::W)) void k_box_c2r(
+    const cx<T>* in, T* out, const cx<T>* __restrict__ tw, int64_t rs, T mul_edge, T mul_int) {
+    using P = box_shape<T, N>;
+    constexpr int M = P::M, K = P::K, NT = P::NT, SY = P::SY, SX = P::SX;
+    __shared__ T lds[P::LDS];
+    const int tid = threadIdx.x, hi = tid / M, z = tid % M;
+    const cx<T>* src = in + int64_t(blockIdx.x) * N * N * K;
+    auto xline = [&](int m) { return m * SX + hi * SY + z; };  // hi = ky
+    auto yline = [&](int m) { return hi * SX + m * SY + z; };  // hi = x
+    auto zline = [&](int m) {
+        const int l = tid + (m / M) * NT;
+        return (l / N) * SX + (l % N) * SY + m % M;
+    };
+    cx<T> a[N];
+#pragma unroll
+    for (int m = 0; m < N; ++m) a[m] = src[(m * N + hi) * K + z];
+
+    // kz = 0 and kz = M: with H0, HM their Hermitian parts,
+    // Z'(kz = 0) = (H0 + HM) + i (H0 - HM); two (kx, ky) per thread
+    cx<T>* col = reinterpret_cast<cx<T>*>(lds);
+    cx<T> g0[2], gm[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        g0[i] = src[(tid + i * NT) * K];
+        gm[i] = src[(tid + i * NT) * K + M];
+        col[tid + i * NT] = g0[i];
+        col[N * N + tid + i * NT] = gm[i];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int l = tid + i * NT;
+        const int lm = ((N - l / N) & (N - 1)) * N + ((N - l % N) & (N - 1));
+        const cx<T> h0 = scal(g0[i] + conjg(col[lm]), T(0.5) * mul_edge);
+        const cx<T> hm = scal(gm[i] + conjg(col[N * N + lm]), T(0.5) * mul_edge);
+        const cx<T> s = h0 + hm, d = h0 - hm;
+        col[2 * N * N + l] = cx<T>{s.x - d.y, s.y + d.x};
+    }
+    __syncthreads();
+    if (z == 0) {
+#pragma unroll
+        for (int m = 0; m < N; ++m) a[m] = col[2 * N * N + m * N + hi];
+    }
+    __syncthreads();
+
+    // 0 < kz < M: the mirrored values through LDS
+    const int ym = (N - hi) & (N - 1), zm = M - z;
+    const cx<T> w = tw[z];
+    T d[N];  // differences of the real parts; a[m].x becomes their sum
+#pragma unroll
+    for (int m = 0; m < N; ++m) lds[xline(m)] = a[m].x;
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < N; ++m) {
+        const T c = lds[((N - m) & (N - 1)) * SX + ym * SY + zm];
+        d[m] = a[m].x - c;
+        a[m].x = z == 0 ? a[m].x : a[m].x + c;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < N; ++m) lds[xline(m)] = a[m].y;
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < N; ++m) {
+        const T c = lds[((N - m) & (N - 1)) * SX + ym * SY + zm];
+        const cx<T> D = cmulc(cx<T>{d[m], a[m].y + c}, w);
+        const cx<T> v{(a[m].x - D.y) * mul_int, (a[m].y - c + D.x) * mul_int};
+        a[m].x = z == 0 ? a[m].x : v.x;
+        a[m].y = z == 0 ? a[m].y : v.y;
+    }
+    __syncthreads();
+
+    dft<N, +1>(a);
+    box_exchange<N>(lds, a, xline, zline);
+    dft<M, +1>(a);
+    dft<M, +1>(a + M);
+    box_exchange<N>(lds, a, zline, yline);
+    dft<N, +1>(a);
+    const int half = int(rs / 2);
+    cx<T>* dst = reinterpret_cast<cx<T>*>(out) + int64_t(blockIdx.x) * N * N * half;
+#pragma unroll
+    for (int m = 0; m < N; ++m) dst[(hi * N + m) * half + z] = a[m];
+}
+
 // ---------------------------------------------------------------- x C2C with the y radix-R step
 // Second half of a split y transform (k_plane_* with R > 1) and the x
 // transform, in one strided pass over [b][x][y][kz] (y and kz flattened to
@@ -416,11 +602,13 @@ __global__ __launch_bounds__((xr_shape<T, N, R, TC, EX>::NT), W) void k_strided_
 // 252 / 255; N = 128 16 per thread 228 / 220 (272 / 491), 8 per thread
 // 247 / 261; N = 256 32 per thread 327 / 333 (379 / 451): there one plane
 // fills half a CU's registers and its phases do not overlap another's.  The
-// streaming copy of the same bytes takes 173.
+// streaming copy of the same bytes takes 173.  N = 32 (8 per thread, one wave a
+// plane; 4 per thread the same within 5%): a whole transform of 333 grids with
+// its x pass 59 (126) in FP64, 37 (81) in FP32.
 template <typename T, int N>
 struct plane_cfg {
     static constexpr bool F64 = sizeof(T) == 8;
-    static constexpr int E = N == 64 ? 8 : N == 128 ? 16 : 32;
+    static constexpr int E = N <= 64 ? 8 : N == 128 ? 16 : 32;
     static constexpr int W = F64 && N == 128 ? 2 : 4;
 };
 
@@ -442,18 +630,25 @@ static hipError_t plane_n(bool forward, const void* in, void* out, const void* t
     return hipGetLastError();
 }
 
-// Where a plane fits on a CU with room for a second one (FP64 up to
-// N = 128: 131 KB) or at least once (FP32 N = 256: 262 KB); an FP64 256 x 256
+// Where a plane fills at least a wave and fits on a CU with room for a second
+// one (FP64 up to N = 128: 131 KB) or at least once (FP32 N = 256: 262 KB); an FP64 256 x 256
 // plane (524 KB) would take the whole register file.
-bool plane_supported(bool f64, int n) { return n == 64 || n == 128 || (!f64 && n == 256); }
+bool plane_supported(bool f64, int n) {
+    return n == 32 || n == 64 || n == 128 || (!f64 && n == 256);
+}
 
 hipError_t launch_plane(bool f64, bool forward, int n, const void* in, void* out, const void* tw,
                         int64_t planes, row_map map, double me, double mi, hipStream_t s) {
     if (!plane_supported(f64, n)) return hipErrorInvalidValue;
-    if (f64)
-        return n == 64 ? plane_n<double, 64>(forward, in, out, tw, planes, map, me, mi, s)
-                       : plane_n<double, 128>(forward, in, out, tw, planes, map, me, mi, s);
+    if (f64) {
+        switch (n) {
+            case 32: return plane_n<double, 32>(forward, in, out, tw, planes, map, me, mi, s);
+            case 64: return plane_n<double, 64>(forward, in, out, tw, planes, map, me, mi, s);
+            default: return plane_n<double, 128>(forward, in, out, tw, planes, map, me, mi, s);
+        }
+    }
     switch (n) {
+        case 32: return plane_n<float, 32>(forward, in, out, tw, planes, map, me, mi, s);
         case 64: return plane_n<float, 64>(forward, in, out, tw, planes, map, me, mi, s);
         case 128: return plane_n<float, 128>(forward, in, out, tw, planes, map, me, mi, s);
         default: return plane_n<float, 256>(forward, in, out, tw, planes, map, me, mi, s);
@@ -569,6 +764,41 @@ hipError_t launch_split_x(bool f64, int n, int sign, const void* src, void* dst,
     if (!split_supported(f64, n)) return hipErrorInvalidValue;
     return sign < 0 ? split_x_sign<-1>(f64, n, src, dst, tw, batch, s)
                     : split_x_sign<+1>(f64, n, src, dst, tw, batch, s);
+}
+
+template <typename T, int N>
+static hipError_t box_n(bool forward, const void* in, void* out, const void* tw, int64_t grids,
+                        int64_t rs, double me, double mi, hipStream_t s) {
+    constexpr int NT = box_shape<T, N>::NT;
+    if (grids == 0) return hipSuccess;
+    if (!grid_fits(grids, NT)) return hipErrorInvalidValue;
+    if (forward)
+        hipLaunchKernelGGL((k_box_r2c<T, N>), dim3(grids), dim3(NT), 0, s,
+                           static_cast<const T*>(in), static_cast<cx<T>*>(out),
+                           static_cast<const cx<T>*>(tw), rs, T(me), T(mi));
+    else
+        hipLaunchKernelGGL((k_box_c2r<T, N>), dim3(grids), dim3(NT), 0, s,
+                           static_cast<const cx<T>*>(in), static_cast<T*>(out),
+                           static_cast<const cx<T>*>(tw), rs, T(me), T(mi));
+    return hipGetLastError();
+}
+
+// One workgroup per grid pays where a grid is tiny or where there are enough
+// of them for the chip.  GPU time of a forward, box kernel against plane and
+// x passes (three passes at N = 16), us: FP64 N = 16 5.4 / 9.4 for one grid,
+// 15.8 / 53 for 1000; N = 32 17 / 8 for one, 18.2 / 14.2 for 32, 19.3 / 23.2
+// for 64, 137 / 195 for 1000; FP32 N = 16 4.7 / 7.9 and 10.0 / 44, N = 32
+// 12.6 / 7.3, 13.4 / 10.3, 14.1 / 15.4 and 62 / 97.
+bool box_supported(int n, int64_t grids) { return n == 16 || (n == 32 && grids >= 64); }
+
+hipError_t launch_box(bool f64, bool forward, int n, const void* in, void* out, const void* tw,
+                      int64_t grids, int64_t rs, double me, double mi, hipStream_t s) {
+    if (n != 16 && n != 32) return hipErrorInvalidValue;
+    if (f64)
+        return n == 16 ? box_n<double, 16>(forward, in, out, tw, grids, rs, me, mi, s)
+                       : box_n<double, 32>(forward, in, out, tw, grids, rs, me, mi, s);
+    return n == 16 ? box_n<float, 16>(forward, in, out, tw, grids, rs, me, mi, s)
+                   : box_n<float, 32>(forward, in, out, tw, grids, rs, me, mi, s);
 }
 
 }  // namespace gfft

@@ -282,6 +282,19 @@ gfft_status run_split_x(const gfft_plan* p, int sign, void* data, hipStream_t s)
     return hip_status(gfft::launch_split_x(f64(p), int(p->n), sign, data, data, p->tw, p->batch, s));
 }
 
+// One pass for the whole transform of small full grids.
+bool box_pass(const gfft_plan* p) {
+    return !p->pencil && p->p == 1 && mfma_terms(p) == 0 &&
+           gfft::box_supported(int(p->n), p->batch);
+}
+
+gfft_status run_box(const gfft_plan* p, bool fwd, const void* in, void* out, double scale,
+                    bool weighted, hipStream_t s) {
+    const double me = scale, mi = weighted ? (fwd ? 2.0 : 0.5) * scale : scale;
+    return hip_status(gfft::launch_box(f64(p), fwd, int(p->n), in, out, p->tw, p->batch, p->rs, me,
+                                       mi, s));
+}
+
 gfft_status forward(const gfft_plan* p, const void* in, void* out, double scale,
                     bool weighted, void* stream) {
     gfft_status st = check_r2c_args(p, in, out);
@@ -290,6 +303,7 @@ gfft_status forward(const gfft_plan* p, const void* in, void* out, double scale,
     if (!std::isfinite(scale)) return GFFT_E_INVALID_ARG;
     if ((st = check_device(p)) != GFFT_OK) return st;
     hipStream_t s = as_stream(stream);
+    if (box_pass(p)) return run_box(p, true, in, out, scale, weighted, s);
     if (split_pass(p)) {
         if ((st = run_split_rows(p, true, in, out, scale, weighted, s)) != GFFT_OK) return st;
         return run_split_x(p, -1, out, s);
@@ -312,6 +326,7 @@ gfft_status inverse(const gfft_plan* p, void* in, void* out, double scale, bool 
     if (!std::isfinite(scale)) return GFFT_E_INVALID_ARG;
     if ((st = check_device(p)) != GFFT_OK) return st;
     hipStream_t s = as_stream(stream);
+    if (box_pass(p)) return run_box(p, false, in, out, scale, weighted, s);
     if (split_pass(p)) {
         if ((st = run_split_x(p, +1, in, s)) != GFFT_OK) return st;
         return run_split_rows(p, false, in, out, scale, weighted, s);

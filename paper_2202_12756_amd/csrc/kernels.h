@@ -68,7 +68,7 @@ hipError_t launch_pack_rows(bool f64, const void* src, void* dst, int64_t rows, 
 
 // Step 1 (z R2C and y C2C of every x-plane) in one pass, or its inverse
 // (y C2C, then z C2R), one plane per workgroup, where a plane fits on a CU
-// (plane_supported: N = 64 and 128, FP32 also N = 256).  Rows of the half
+// (plane_supported: N = 32 to 128, FP32 also N = 256).  Rows of the half
 // spectrum follow `map` as in the z passes; the bin multipliers are those of
 // the z passes.  `in` and `out` may be the same buffer (in-place plans): each
 // plane is read whole before any of it is written.
@@ -90,6 +90,14 @@ hipError_t launch_split_rows(bool f64, bool forward, int n, const void* in, void
                              double mul_int, hipStream_t s);
 hipError_t launch_split_x(bool f64, int n, int sign, const void* src, void* dst, const void* tw,
                           int64_t batch, hipStream_t s);
+
+// The whole 3D transform of natural-order grids of N = 16 or 32, one grid per
+// workgroup in one pass (box_supported: also says whether `grids` of them are
+// better off so).  rs: reals between real rows (N, or N + 2 in place); `in`
+// and `out` may be the same buffer.
+bool box_supported(int n, int64_t grids);
+hipError_t launch_box(bool f64, bool forward, int n, const void* in, void* out, const void* tw,
+                      int64_t grids, int64_t rs, double mul_edge, double mul_int, hipStream_t s);
 
 // Copy n16 16-byte elements from src to dst (one per work-item).
 hipError_t launch_copy16(const void* src, void* dst, int64_t n16, hipStream_t s);

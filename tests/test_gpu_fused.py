@@ -17,7 +17,7 @@ DTYPES = pytest.mark.parametrize("dtype", [F64, F32], ids=["f64", "f32"])
 
 @DTYPES
 @pytest.mark.parametrize("order", ["natural", "send", "paper", "inplace"])
-@pytest.mark.parametrize("n,x,batch", [(64, 1, 3), (64, 16, 1), (128, 2, 3), (128, 8, 1),
+@pytest.mark.parametrize("n,x,batch", [(32, 1, 3), (32, 8, 2), (64, 1, 3), (64, 16, 1), (128, 2, 3), (128, 8, 1),
                                        (256, 1, 1), (256, 4, 3)])
 def test_plane_step1(n, x, batch, order, dtype):
     """Step 1 and its inverse plane by plane, in every row layout, on
@@ -107,3 +107,32 @@ def test_x_pass_orders(n, ranks, batch, dtype):
             got = p.x_c2c(buf.copy_(pen), sign)
             torch.cuda.synchronize()
             assert rel_l2(host(got), want) <= TOL[dtype]
+
+
+@DTYPES
+@pytest.mark.parametrize("inplace", [False, True], ids=["out_of_place", "inplace"])
+@pytest.mark.parametrize("n,batch", [(16, 1), (16, 7), (32, 1), (32, 63), (32, 65)])
+def test_small_grids(n, batch, inplace, dtype):
+    """Whole grids of N = 16 and 32, with the adjoints, the inverse on
+    non-Hermitian input."""
+    p = Plan(n, dtype, batch=batch, inplace=inplace)
+    tol = TOL[dtype]
+    xin, xref = real_input(p.real_shape, 24000 + n + batch, dtype)
+    g, gref = cplx_input((batch, n, n, n // 2 + 1), 24500 + n + batch, dtype)
+
+    def fwd(call, call_, scale):
+        if not inplace:
+            return call(xin, **scale)
+        buf = p.empty_inplace()
+        p.real_view(buf).copy_(xin)
+        return call_(buf, **scale)
+
+    F = fwd(p.r2c, p.r2c_, {})
+    A = fwd(p.c2r_adjoint, p.c2r_adjoint_, {"scale": 3.0})
+    f = (p.c2r_ if inplace else p.c2r)(g.clone(), scale=0.5)
+    a = (p.r2c_adjoint_ if inplace else p.r2c_adjoint)(g.clone(), scale=0.25)
+    torch.cuda.synchronize()
+    assert rel_l2(host(F), oracle.r2c3d(xref)) <= tol
+    assert rel_l2(host(A), 3.0 * oracle.c2r3d_adjoint(xref)) <= tol
+    assert rel_l2(host(f), 0.5 * oracle.c2r3d(gref, n)) <= tol
+    assert rel_l2(host(a), 0.25 * oracle.r2c3d_adjoint(gref, n)) <= tol
