@@ -250,6 +250,24 @@ gfft_status gfft_exec_c2r_adjoint(const gfft_plan *plan, const void *in_real,
                                   void *out_cplx, double scale, void *stream);
 
 /*
+ * The inverse, or with `adjoint` nonzero the adjoint of the forward
+ * transform, leaving its input as it was: gfft_exec_c2r and
+ * gfft_exec_r2c_adjoint on a copy of in_cplx, without the copy (the first
+ * pass reads in_cplx and writes work).
+ *   work : caller-owned scratch of gfft_inverse_work_bytes(plan) bytes,
+ *          overlapping neither array (contents on return are undefined; not
+ *          looked at where that is 0).
+ * GFFT_E_INVALID_ARG for GFFT_INPLACE plans, GFFT_E_UNSUPPORTED for pencils.
+ */
+gfft_status gfft_exec_inverse_keep(const gfft_plan *plan, const void *in_cplx,
+                                   void *work, void *out_real, double scale,
+                                   int adjoint, void *stream);
+
+/* Scratch bytes of gfft_exec_inverse_keep: the plan's complex_bytes, or 0
+ * where it needs none (also for plans it refuses, and NULL). */
+int64_t gfft_inverse_work_bytes(const gfft_plan *plan);
+
+/*
  * Section 3 steps 2-3 as one permutation (standalone form of what
  * GFFT_FUSE_PACK folds into the z pass): from a slab's natural half
  * spectrum S[X][N][K], write p contiguous chunks

@@ -38,6 +38,7 @@ EXPORTS = (
     "gfft_exec_c2r_adjoint", "gfft_pack_slab_for_alltoall",
     "gfft_unpack_slab_from_alltoall", "gfft_exec_x_c2c",
     "gfft_exec_z_r2c", "gfft_exec_y_c2c", "gfft_exec_z_c2r",
+    "gfft_exec_inverse_keep", "gfft_inverse_work_bytes",
     "gfft_device_copy", "gfft_exec_pass_copy", "gfft_status_string", "gfft_version",
 )
 
@@ -83,6 +84,8 @@ def load(path: str = LIB_PATH):
         "gfft_exec_z_r2c": [vp, vp, vp, dbl, i32, vp],
         "gfft_exec_y_c2c": [vp, vp, i32, vp],
         "gfft_exec_z_c2r": [vp, vp, vp, dbl, i32, vp],
+        "gfft_exec_inverse_keep": [vp, vp, vp, vp, dbl, i32, vp],
+        "gfft_inverse_work_bytes": [vp],
         "gfft_device_copy": [vp, vp, i64, vp],
         "gfft_exec_pass_copy": [vp, i32, vp, vp],
         "gfft_status_string": [i32],
@@ -93,6 +96,7 @@ def load(path: str = LIB_PATH):
         fn.argtypes = args
         fn.restype = i32
     lib.gfft_status_string.restype = ctypes.c_char_p
+    lib.gfft_inverse_work_bytes.restype = i64
     _lib = lib
     return lib
 
@@ -169,6 +173,14 @@ def gfft_exec_y_c2c(plan, data, sign, stream):
 
 def gfft_exec_z_c2r(plan, in_cplx, out_real, scale, weighted, stream):
     return load().gfft_exec_z_c2r(plan, in_cplx, out_real, scale, weighted, stream)
+
+
+def gfft_exec_inverse_keep(plan, in_cplx, work, out_real, scale, adjoint, stream):
+    return load().gfft_exec_inverse_keep(plan, in_cplx, work, out_real, scale, adjoint, stream)
+
+
+def gfft_inverse_work_bytes(plan):
+    return load().gfft_inverse_work_bytes(plan)
 
 
 def gfft_device_copy(dst, src, nbytes, stream):

@@ -25,9 +25,7 @@ class RFFT3(torch.autograd.Function):
 
     @staticmethod
     def backward(ctx, g: torch.Tensor):
-        plan = ctx.plan
-        g = g.contiguous().clone()        # the adjoint clobbers its input
-        return plan.r2c_adjoint(g, scale=1.0), None
+        return ctx.plan.inverse_keep(g, scale=1.0, adjoint=True), None
 
 
 class IRFFT3(torch.autograd.Function):
@@ -35,7 +33,7 @@ class IRFFT3(torch.autograd.Function):
     def forward(ctx, G: torch.Tensor, plan: Plan, scale: float):
         ctx.plan = plan
         ctx.scale = scale
-        return plan.c2r(G.contiguous().clone(), scale=scale)
+        return plan.inverse_keep(G, scale=scale)
 
     @staticmethod
     def backward(ctx, h: torch.Tensor):

@@ -221,13 +221,15 @@ int mfma_terms(const gfft_plan* p) {
 }
 
 // copy: the pass's loads and stores without its transform (gfft_exec_pass_copy)
-gfft_status run_y(const gfft_plan* p, void* data, int sign, hipStream_t s, bool copy = false) {
+gfft_status run_y(const gfft_plan* p, const void* src, void* data, int sign, hipStream_t s,
+                  bool copy = false) {
     const int64_t cols = p->pencil ? p->w : p->k;
     return hip_status(gfft::launch_strided(f64(p), int(p->n), 0, copy ? -1 : mfma_terms(p), sign,
-                                           data, p->tw, cols, p->batch * p->x, ymap(p), s));
+                                           src, data, p->tw, cols, p->batch * p->x, ymap(p), s));
 }
 
-gfft_status run_x(const gfft_plan* p, void* data, int sign, hipStream_t s, bool copy = false) {
+gfft_status run_x(const gfft_plan* p, const void* src, void* data, int sign, hipStream_t s,
+                  bool copy = false) {
     int64_t cols = paper(p) ? p->k : p->y * p->k;
     int64_t sets = paper(p) ? p->batch * p->y : p->batch;
     if (p->pencil) {
@@ -235,7 +237,7 @@ gfft_status run_x(const gfft_plan* p, void* data, int sign, hipStream_t s, bool 
         sets = p->h > 1 ? p->batch : p->batch * p->g;
     }
     return hip_status(gfft::launch_strided(f64(p), int(p->n), 1, copy ? -1 : mfma_terms(p), sign,
-                                           data, p->tw, cols, sets, xmap(p), s));
+                                           src, data, p->tw, cols, sets, xmap(p), s));
 }
 
 // `real` and `cplx` are the two buffers of a z pass: distinct and disjoint,
@@ -278,8 +280,8 @@ gfft_status run_split_rows(const gfft_plan* p, bool fwd, const void* in, void* o
                                               p->batch * p->x, zmap(p), me, mi, s));
 }
 
-gfft_status run_split_x(const gfft_plan* p, int sign, void* data, hipStream_t s) {
-    return hip_status(gfft::launch_split_x(f64(p), int(p->n), sign, data, data, p->tw, p->batch, s));
+gfft_status run_split_x(const gfft_plan* p, int sign, const void* src, void* data, hipStream_t s) {
+    return hip_status(gfft::launch_split_x(f64(p), int(p->n), sign, src, data, p->tw, p->batch, s));
 }
 
 // One pass for the whole transform of small full grids.
@@ -306,16 +308,36 @@ gfft_status forward(const gfft_plan* p, const void* in, void* out, double scale,
     if (box_pass(p)) return run_box(p, true, in, out, scale, weighted, s);
     if (split_pass(p)) {
         if ((st = run_split_rows(p, true, in, out, scale, weighted, s)) != GFFT_OK) return st;
-        return run_split_x(p, -1, out, s);
+        return run_split_x(p, -1, out, out, s);
     }
     if (plane_pass(p)) {
         if ((st = run_plane(p, true, in, out, scale, weighted, s)) != GFFT_OK) return st;
     } else {
         if ((st = run_z_r2c(p, in, out, scale, weighted, s)) != GFFT_OK) return st;
-        if ((st = run_y(p, out, -1, s)) != GFFT_OK) return st;
+        if ((st = run_y(p, out, out, -1, s)) != GFFT_OK) return st;
     }
-    if (p->p == 1) st = run_x(p, out, -1, s);
+    if (p->p == 1) st = run_x(p, out, out, -1, s);
     return st;
+}
+
+// The inverse's kernels.  The first strided pass reads `in` and writes
+// `work`, the later ones run in place there: work == in transforms `in`
+// itself, a distinct work buffer leaves it as it was.
+gfft_status run_inverse(const gfft_plan* p, const void* in, void* work, void* out, double scale,
+                        bool weighted, hipStream_t s) {
+    gfft_status st;
+    if (box_pass(p)) return run_box(p, false, in, out, scale, weighted, s);
+    if (split_pass(p)) {
+        if ((st = run_split_x(p, +1, in, work, s)) != GFFT_OK) return st;
+        return run_split_rows(p, false, work, out, scale, weighted, s);
+    }
+    if (p->p == 1) {
+        if ((st = run_x(p, in, work, +1, s)) != GFFT_OK) return st;
+        in = work;
+    }
+    if (plane_pass(p)) return run_plane(p, false, in, out, scale, weighted, s);
+    if ((st = run_y(p, in, work, +1, s)) != GFFT_OK) return st;
+    return run_z_c2r(p, work, out, scale, weighted, s);
 }
 
 gfft_status inverse(const gfft_plan* p, void* in, void* out, double scale, bool weighted,
@@ -325,16 +347,14 @@ gfft_status inverse(const gfft_plan* p, void* in, void* out, double scale, bool 
     if (p->pencil) return GFFT_E_UNSUPPORTED;
     if (!std::isfinite(scale)) return GFFT_E_INVALID_ARG;
     if ((st = check_device(p)) != GFFT_OK) return st;
-    hipStream_t s = as_stream(stream);
-    if (box_pass(p)) return run_box(p, false, in, out, scale, weighted, s);
-    if (split_pass(p)) {
-        if ((st = run_split_x(p, +1, in, s)) != GFFT_OK) return st;
-        return run_split_rows(p, false, in, out, scale, weighted, s);
-    }
-    if (p->p == 1 && (st = run_x(p, in, +1, s)) != GFFT_OK) return st;
-    if (plane_pass(p)) return run_plane(p, false, in, out, scale, weighted, s);
-    if ((st = run_y(p, in, +1, s)) != GFFT_OK) return st;
-    return run_z_c2r(p, in, out, scale, weighted, s);
+    return run_inverse(p, in, in, out, scale, weighted, as_stream(stream));
+}
+
+// Bytes of the work buffer that an inverse which leaves its input needs:
+// the spectrum, or nothing where one kernel reads the input and writes the
+// field (small grids; slabs with step 1 in one pass).
+int64_t keep_work_bytes(const gfft_plan* p) {
+    return box_pass(p) || (p->p > 1 && plane_pass(p)) ? 0 : cplx_bytes(p);
 }
 
 // Second-exchange pack of a pencil plan with pr > pc: every y-pencil block
@@ -589,6 +609,27 @@ gfft_status gfft_exec_r2c_adjoint(const gfft_plan* p, void* in, void* out, doubl
     return inverse(p, in, out, scale, true, stream);
 }
 
+int64_t gfft_inverse_work_bytes(const gfft_plan* p) {
+    return p && !p->pencil && !(p->flags & GFFT_INPLACE) ? keep_work_bytes(p) : 0;
+}
+
+gfft_status gfft_exec_inverse_keep(const gfft_plan* p, const void* in, void* work, void* out,
+                                   double scale, int adjoint, void* stream) {
+    gfft_status st = check_r2c_args(p, out, in);
+    if (st != GFFT_OK) return st;
+    if (p->pencil) return GFFT_E_UNSUPPORTED;
+    if (p->flags & GFFT_INPLACE) return GFFT_E_INVALID_ARG;
+    if (!std::isfinite(scale)) return GFFT_E_INVALID_ARG;
+    if (keep_work_bytes(p) > 0) {
+        if ((st = check_ptr(work)) != GFFT_OK) return st;
+        if (overlap(work, cplx_bytes(p), in, cplx_bytes(p)) ||
+            overlap(work, cplx_bytes(p), out, real_bytes(p)))
+            return GFFT_E_INVALID_ARG;
+    }
+    if ((st = check_device(p)) != GFFT_OK) return st;
+    return run_inverse(p, in, work, out, scale, adjoint != 0, as_stream(stream));
+}
+
 gfft_status gfft_pack_slab_for_alltoall(const gfft_plan* p, const void* src, void* dst,
                                         void* stream) {
     if (!p) return GFFT_E_INVALID_ARG;
@@ -624,7 +665,7 @@ gfft_status gfft_exec_x_c2c(const gfft_plan* p, void* pencil, int sign, void* st
     if (sign != -1 && sign != 1) return GFFT_E_INVALID_ARG;
     gfft_status st = check_ptr(pencil);
     if (st != GFFT_OK || (st = check_device(p)) != GFFT_OK) return st;
-    return run_x(p, pencil, sign, as_stream(stream));
+    return run_x(p, pencil, pencil, sign, as_stream(stream));
 }
 
 gfft_status gfft_exec_z_r2c(const gfft_plan* p, const void* in, void* out, double scale,
@@ -641,7 +682,7 @@ gfft_status gfft_exec_y_c2c(const gfft_plan* p, void* data, int sign, void* stre
     if (sign != -1 && sign != 1) return GFFT_E_INVALID_ARG;
     gfft_status st = check_ptr(data);
     if (st != GFFT_OK || (st = check_device(p)) != GFFT_OK) return st;
-    return run_y(p, data, sign, as_stream(stream));
+    return run_y(p, data, data, sign, as_stream(stream));
 }
 
 gfft_status gfft_exec_z_c2r(const gfft_plan* p, const void* in, void* out, double scale,
@@ -658,8 +699,8 @@ gfft_status gfft_exec_pass_copy(const gfft_plan* p, int axis, void* data, void* 
     if (axis != 0 && axis != 1) return GFFT_E_INVALID_ARG;
     gfft_status st = check_ptr(data);
     if (st != GFFT_OK || (st = check_device(p)) != GFFT_OK) return st;
-    return axis == 0 ? run_y(p, data, -1, as_stream(stream), true)
-                     : run_x(p, data, -1, as_stream(stream), true);
+    return axis == 0 ? run_y(p, data, data, -1, as_stream(stream), true)
+                     : run_x(p, data, data, -1, as_stream(stream), true);
 }
 
 gfft_status gfft_device_copy(void* dst, const void* src, int64_t bytes, void* stream) {

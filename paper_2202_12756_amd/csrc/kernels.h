@@ -50,9 +50,10 @@ hipError_t launch_z_c2r(bool f64, int n, const void* in, void* out, const void* 
 // only) runs the first radix-16 stage on the matrix cores with that many
 // BF16 terms per operand; 0 keeps every stage on the vector ALUs; -1 runs
 // no transform but the vector pass's loads and stores, storing each element's
-// conjugate (sign ignored).
-hipError_t launch_strided(bool f64, int n, int axis, int mfma_terms, int sign, void* data,
-                          const void* tw, int64_t m_cols, int64_t n_b, line_map lm,
+// conjugate (sign ignored).  src == data transforms in place; a distinct src
+// of the same layout is read and left as it is.
+hipError_t launch_strided(bool f64, int n, int axis, int mfma_terms, int sign, const void* src,
+                          void* data, const void* tw, int64_t m_cols, int64_t n_b, line_map lm,
                           hipStream_t s);
 // Copy `chunks` runs of `len` complex values: run c = (bb, j, xl) goes from
 // natural offset bb*X*N*K + (xl*N + j*Y)*K to send offset

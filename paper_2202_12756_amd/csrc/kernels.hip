@@ -325,10 +325,12 @@ struct sshape {
 // -1 no transform (each element replaced by its conjugate): the same loads
 // and stores as the pass, a yardstick for its memory-access ceiling.
 // RMP: tiles in XCD-contiguous order (false: in launch order).
+// src may be data itself (in place) or a distinct buffer of the same layout:
+// every load of a tile precedes its stores, and tiles own their elements.
 template <typename T, int N, int TC, int XP, int S, int E = 16, int MF = 0, bool NT = false,
           bool RMP = true>
 __global__ __launch_bounds__(TC * N / E) void k_strided(
-    cx<T>* __restrict__ data, const cx<T>* __restrict__ tw, int64_t m_cols,
+    const cx<T>* src, cx<T>* data, const cx<T>* __restrict__ tw, int64_t m_cols,
     int64_t tiles_m, line_map lm) {
     constexpr int TPT = N / E;
     constexpr bool SPLIT = XP == 2;
@@ -347,7 +349,9 @@ __global__ __launch_bounds__(TC * N / E) void k_strided(
     const int64_t m = m0 + c;
     const bool valid = m < m_cols;
     const int64_t ymask = (int64_t(1) << lm.lg_y) - 1;
-    cx<T>* plane = data + (b >> lm.lg_bx) * lm.b_hi + (b & ((int64_t(1) << lm.lg_bx) - 1)) * lm.b_lo;
+    const int64_t set = (b >> lm.lg_bx) * lm.b_hi + (b & ((int64_t(1) << lm.lg_bx) - 1)) * lm.b_lo;
+    const cx<T>* from = src + set;
+    cx<T>* plane = data + set;
     auto off = [&](int64_t n) { return (n >> lm.lg_y) * lm.s_hi + (n & ymask) * lm.s_lo; };
     // Element n = t + i*TPT of a line: t < TPT and i*TPT have disjoint bits
     // (TPT a power of two), and off() adds over disjoint bit fields, so
@@ -368,7 +372,7 @@ __global__ __launch_bounds__(TC * N / E) void k_strided(
         return int64_t(i >> d) * H + int64_t(i & ((1 << d) - 1)) * Lo;
     };
     int64_t lane_off = (valid ? m : m_cols - 1) + off(t);
-    const cx<T>* lane = plane + lane_off;
+    const cx<T>* lane = from + lane_off;
 
     cx<T> a[E];
     if constexpr (MF < 0) {
@@ -421,7 +425,7 @@ __global__ __launch_bounds__(TC * N / E) void k_strided(
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 const int64_t n = bt[g] + (8 * h + j) * TPT;
-                in[j] = vb ? plane[m0 + bc[g] + off(n)] : cx<float>{0.f, 0.f};
+                in[j] = vb ? from[m0 + bc[g] + off(n)] : cx<float>{0.f, 0.f};
             }
             dft.run(in, y[g]);
         }
@@ -589,7 +593,7 @@ static bool whole_lines(const void* data, int64_t m_cols, const line_map& lm, in
 }
 
 template <typename T, int N, int AX, int MF, bool NT, bool RMP>
-static hipError_t strided_run(int sign, void* data, const void* tw, int64_t m_cols,
+static hipError_t strided_run(int sign, const void* src, void* data, const void* tw, int64_t m_cols,
                               int64_t n_b, line_map lm, hipStream_t s) {
     using SH = sshape<T, N, AX, (MF > 0)>;
     constexpr int TC = SH::TC;
@@ -600,12 +604,12 @@ static hipError_t strided_run(int sign, void* data, const void* tw, int64_t m_co
     const dim3 threads(TC * SH::TPT);
     if (MF < 0 || sign < 0)
         hipLaunchKernelGGL((k_strided<T, N, TC, SH::XP, -1, SH::E, MF, NT, RMP>), dim3(blocks),
-                           threads, 0, s, static_cast<cx<T>*>(data),
-                           static_cast<const cx<T>*>(tw), m_cols, tiles_m, lm);
+                           threads, 0, s, static_cast<const cx<T>*>(src),
+                           static_cast<cx<T>*>(data), static_cast<const cx<T>*>(tw), m_cols, tiles_m, lm);
     else if constexpr (MF >= 0)
         hipLaunchKernelGGL((k_strided<T, N, TC, SH::XP, +1, SH::E, MF, NT, RMP>), dim3(blocks),
-                           threads, 0, s, static_cast<cx<T>*>(data),
-                           static_cast<const cx<T>*>(tw), m_cols, tiles_m, lm);
+                           threads, 0, s, static_cast<const cx<T>*>(src),
+                           static_cast<cx<T>*>(data), static_cast<const cx<T>*>(tw), m_cols, tiles_m, lm);
     return hipGetLastError();
 }
 
@@ -630,13 +634,13 @@ static hipError_t strided_run(int sign, void* data, const void* tw, int64_t m_co
 // slower with it.  Where neighbouring tiles share lines, as in the y passes,
 // the hint makes them travel twice (15-50% slower).
 template <typename T, int N, int AX, int MF>
-static hipError_t strided_ax(int sign, void* data, const void* tw, int64_t m_cols,
+static hipError_t strided_ax(int sign, const void* src, void* data, const void* tw, int64_t m_cols,
                              int64_t n_b, line_map lm, hipStream_t s) {
     constexpr bool F64 = sizeof(T) == 8;
     constexpr int ES = int(sizeof(cx<T>));
     using SH = sshape<T, N, AX, (MF > 0)>;
     if constexpr (AX == 1 && MF <= 0 && N >= 64 && (!F64 || N <= 1024) && (SH::TC * ES) % 128 == 0) {
-        if (whole_lines(data, m_cols, lm, 128 / ES)) {
+        if (whole_lines(src, m_cols, lm, 128 / ES) && whole_lines(data, m_cols, lm, 128 / ES)) {
             // mean distance between neighbouring elements of a line
             constexpr int64_t HALF = N / 2;
             const int64_t step = ((HALF >> lm.lg_y) * lm.s_hi +
@@ -645,31 +649,31 @@ static hipError_t strided_ax(int sign, void* data, const void* tw, int64_t m_col
                                     : N <= 512      ? int64_t(1) << 62
                                                     : int64_t(2) << 20;
             if (step >= 4096 && step < FAR)
-                return strided_run<T, N, AX, MF, true, false>(sign, data, tw, m_cols, n_b, lm, s);
+                return strided_run<T, N, AX, MF, true, false>(sign, src, data, tw, m_cols, n_b, lm, s);
             if constexpr (N >= 512 || (!F64 && N == 256))
-                return strided_run<T, N, AX, MF, true, true>(sign, data, tw, m_cols, n_b, lm, s);
+                return strided_run<T, N, AX, MF, true, true>(sign, src, data, tw, m_cols, n_b, lm, s);
         }
     }
-    return strided_run<T, N, AX, MF, false, true>(sign, data, tw, m_cols, n_b, lm, s);
+    return strided_run<T, N, AX, MF, false, true>(sign, src, data, tw, m_cols, n_b, lm, s);
 }
 
 template <typename T, int N>
-static hipError_t strided_n(int axis, int mfma_terms, int sign, void* data, const void* tw,
-                            int64_t m_cols, int64_t n_b, line_map lm, hipStream_t s) {
+static hipError_t strided_n(int axis, int mfma_terms, int sign, const void* src, void* data,
+                            const void* tw, int64_t m_cols, int64_t n_b, line_map lm, hipStream_t s) {
     if (mfma_terms == -1)
-        return axis == 0 ? strided_ax<T, N, 0, -1>(sign, data, tw, m_cols, n_b, lm, s)
-                         : strided_ax<T, N, 1, -1>(sign, data, tw, m_cols, n_b, lm, s);
+        return axis == 0 ? strided_ax<T, N, 0, -1>(sign, src, data, tw, m_cols, n_b, lm, s)
+                         : strided_ax<T, N, 1, -1>(sign, src, data, tw, m_cols, n_b, lm, s);
     if constexpr (sizeof(T) == 4 && N >= 32) {
         if (mfma_terms == 2)
-            return axis == 0 ? strided_ax<T, N, 0, 2>(sign, data, tw, m_cols, n_b, lm, s)
-                             : strided_ax<T, N, 1, 2>(sign, data, tw, m_cols, n_b, lm, s);
+            return axis == 0 ? strided_ax<T, N, 0, 2>(sign, src, data, tw, m_cols, n_b, lm, s)
+                             : strided_ax<T, N, 1, 2>(sign, src, data, tw, m_cols, n_b, lm, s);
         if (mfma_terms == 3)
-            return axis == 0 ? strided_ax<T, N, 0, 3>(sign, data, tw, m_cols, n_b, lm, s)
-                             : strided_ax<T, N, 1, 3>(sign, data, tw, m_cols, n_b, lm, s);
+            return axis == 0 ? strided_ax<T, N, 0, 3>(sign, src, data, tw, m_cols, n_b, lm, s)
+                             : strided_ax<T, N, 1, 3>(sign, src, data, tw, m_cols, n_b, lm, s);
     }
     if (mfma_terms != 0) return hipErrorInvalidValue;
-    if (axis == 0) return strided_ax<T, N, 0, 0>(sign, data, tw, m_cols, n_b, lm, s);
-    return strided_ax<T, N, 1, 0>(sign, data, tw, m_cols, n_b, lm, s);
+    if (axis == 0) return strided_ax<T, N, 0, 0>(sign, src, data, tw, m_cols, n_b, lm, s);
+    return strided_ax<T, N, 1, 0>(sign, src, data, tw, m_cols, n_b, lm, s);
 }
 
 #define GFFT_DISPATCH_N(FN, T, ...)                 \
@@ -698,11 +702,11 @@ hipError_t launch_z_c2r(bool f64, int n, const void* in, void* out, const void* 
     GFFT_DISPATCH_N(z_c2r_n, float, in, out, tw, rows, map, me, mi, s)
 }
 
-hipError_t launch_strided(bool f64, int n, int axis, int mfma_terms, int sign, void* data,
-                          const void* tw, int64_t m_cols, int64_t n_b, line_map lm,
+hipError_t launch_strided(bool f64, int n, int axis, int mfma_terms, int sign, const void* src,
+                          void* data, const void* tw, int64_t m_cols, int64_t n_b, line_map lm,
                           hipStream_t s) {
-    if (f64) { GFFT_DISPATCH_N(strided_n, double, axis, mfma_terms, sign, data, tw, m_cols, n_b, lm, s) }
-    GFFT_DISPATCH_N(strided_n, float, axis, mfma_terms, sign, data, tw, m_cols, n_b, lm, s)
+    if (f64) { GFFT_DISPATCH_N(strided_n, double, axis, mfma_terms, sign, src, data, tw, m_cols, n_b, lm, s) }
+    GFFT_DISPATCH_N(strided_n, float, axis, mfma_terms, sign, src, data, tw, m_cols, n_b, lm, s)
 }
 
 hipError_t launch_pack(bool f64, const void* src, void* dst, int64_t chunks, int lg_x,

@@ -186,6 +186,23 @@ class Plan(_Exec):
         self._exec(_lib.gfft_exec_r2c_adjoint, a, b, float(scale))
         return out
 
+    def inverse_keep(self, g: torch.Tensor, scale: float = 1.0, adjoint: bool = False):
+        """``c2r`` (or with ``adjoint`` ``r2c_adjoint``) that leaves ``g`` as
+        it is.  Takes any strides, lazy conjugates and alignments: what the
+        kernels cannot read in place is copied first."""
+        if isinstance(g, torch.Tensor):
+            g = g.contiguous().resolve_conj().resolve_neg()
+            if g.data_ptr() % 16:
+                g = g.clone()
+        out = self.empty_real()
+        a = self._check(g, self.cdtype, self._ncplx(), "input")
+        b = self._check(out, self.dtype, self._nreal(), "output")
+        work = (torch.empty(self._ncplx(), dtype=self.cdtype, device=self.device)
+                if _lib.gfft_inverse_work_bytes(self._h) else None)
+        self._exec(_lib.gfft_exec_inverse_keep, a, None if work is None else work.data_ptr(), b,
+                   float(scale), int(adjoint))
+        return out
+
     def c2r_adjoint(self, h: torch.Tensor, out=None, scale: float = 1.0):
         """scale * C2R^T(h) = scale * w * R2C(h)."""
         out = self.empty_spectrum() if out is None else out
