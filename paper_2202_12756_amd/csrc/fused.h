@@ -314,6 +314,243 @@ __global__ __launch_bounds__((plane_shape<T, N, R, E>::NT), W) void k_plane_c2r(
     for (int m = 0; m < E; ++m) dst[t + TZ * m] = g[m];
 }
 
+// ---------------------------------------------------------------- long rows: z with a short y step
+// z R2C of rows too long for a plane to fit on a CU, NY rows at a time:
+// with N = NY R, y = y0 + R j, ky = k1 + NY k0, a tile takes the NY rows of
+// one y0 through z and the NY-point DFT over j, applies W_N^(y0 k1) and
+// writes bin k1 to row y0 NY + k1; what is left of the y transform is an
+// R-point strided pass over n = y0 (rows n NY + k1, in place), an ordinary
+// k_strided of shorter lines.  NY = 1 is a plain z pass.  As in k_plane_*,
+// thread (r, t) transforms row r, thread p then holds the columns p and M - p
+// (p = lt + NT1 q, q < Q) of all NY rows, so the real split and the y step
+// need no further exchange, and kz = 0 and kz = M travel as one column.
+// Exchanges are split into real and imaginary parts: whole values would
+// leave 4 waves on a CU at N = 4096.  Out of place for NY > 1.
+template <typename T, int N, int NY, int E, int G>
+struct rows_shape {
+    static constexpr int M = N / 2, K = M + 1, H = M / 2, R = N / NY;
+    static constexpr int TZ = M / E, NT1 = NY * TZ, NT = G * NT1, Q = H / NT1;
+    static constexpr int RM = radix_cap<T>();
+    static constexpr int PS = first_radix_shift<E, RM>::value;
+    static constexpr int MP = padded_len<M, PS>::value;
+    static constexpr int LD = TZ < 64 ? M + TZ : M;
+    static constexpr int SZ = NY * (MP > LD ? MP : LD);  // values of type T per tile
+    static_assert(Q >= 1 && Q * NT1 == H, "rows shape");
+};
+
+template <typename T, int N, int NY, int E, int G, int W, bool RMP, bool PENCIL>
+__global__ __launch_bounds__((rows_shape<T, N, NY, E, G>::NT), W) void k_rows_r2c(
+    const T* in, cx<T>* out, const cx<T>* __restrict__ tw, int64_t tiles, row_map map, T mul_edge,
+    T mul_int) {
+    using P = rows_shape<T, N, NY, E, G>;
+    constexpr int M = P::M, K = P::K, H = P::H, R = P::R, TZ = P::TZ, NT1 = P::NT1, Q = P::Q,
+                  RM = P::RM, LD = P::LD;
+    __shared__ T lds_all[G * P::SZ];
+    const int grp = threadIdx.x / NT1, lt = threadIdx.x % NT1;
+    T* lds = lds_all + grp * P::SZ;
+    const int r = lt / TZ, t = lt % TZ;
+    const int64_t blk = RMP ? xcd_tile(blockIdx.x, gridDim.x) : int64_t(blockIdx.x);
+    const int64_t tile = blk * G + grp;
+    const bool valid = tile < tiles;
+    // tiles past the end (last workgroup) load the last tile and drop it
+    const int64_t tl = valid ? tile : tiles - 1;
+    const int64_t plane = NY > 1 ? tl / R : 0;
+    const int y0 = NY > 1 ? int(tl % R) : 0;
+    const int64_t row0 = NY > 1 ? plane * N + y0 : tl;
+
+    cx<T> a[E];
+    const cx<T>* src = reinterpret_cast<const cx<T>*>(in + (row0 + R * r) * map.rs);
+#pragma unroll
+    for (int m = 0; m < E; ++m) a[m] = src[t + TZ * m];
+    using IR = idx_rows<P::PS>;
+    fft_regs<T, M, E, -1, RM>(a, t, tw, 2, xch_split<T, IR>{lds, IR{r * P::MP}});
+
+    cx<T> b[Q][2][NY];
+#pragma unroll
+    for (int part = 0; part < 2; ++part) {
+#pragma unroll
+        for (int m = 0; m < E; ++m) lds[r * LD + t + TZ * m] = part ? a[m].y : a[m].x;
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int p = lt + NT1 * q, c1 = p == 0 ? H : M - p;
+#pragma unroll
+            for (int j = 0; j < NY; ++j) {
+                const T u = lds[j * LD + p], v = lds[j * LD + c1];
+                if (part) {
+                    b[q][0][j].y = u;
+                    b[q][1][j].y = v;
+                } else {
+                    b[q][0][j].x = u;
+                    b[q][1][j].x = v;
+                }
+            }
+        }
+        if (part == 0) __syncthreads();
+    }
+    if (!valid) return;
+
+    cx<T> wy[NY];
+#pragma unroll
+    for (int k1 = 1; k1 < NY; ++k1) wy[k1] = tw[y0 * k1];
+    auto row_of = [&](int k1) {
+        return out + map_row(NY > 1 ? plane * N + y0 * NY + k1 : tl, map) * K;
+    };
+    auto put = [&](int k1, int k, cx<T> v) {
+        if constexpr (PENCIL) out[pencil_bin(tl, k, K, map)] = v;
+        else row_of(k1)[k] = v;
+    };
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const int p = lt + NT1 * q, c1 = p == 0 ? H : M - p;
+        const cx<T> w = tw[p];
+        const bool edge = p == 0;
+        cx<T> u[NY], v[NY];
+#pragma unroll
+        for (int j = 0; j < NY; ++j) {
+            const cx<T> z = b[q][0][j], y = b[q][1][j];
+            const cx<T> A = scal(z + conjg(y), T(0.5)), B = cmul(w, scal(z - conjg(y), T(0.5)));
+            u[j].x = edge ? (z.x + z.y) * mul_edge : (A.x + B.y) * mul_int;
+            u[j].y = edge ? (z.x - z.y) * mul_edge : (A.y - B.x) * mul_int;
+            v[j].x = edge ? y.x * mul_int : (A.x - B.y) * mul_int;
+            v[j].y = edge ? -y.y * mul_int : (-A.y - B.x) * mul_int;
+        }
+        dft<NY, -1>(u);
+        dft<NY, -1>(v);
+        if (edge) {
+            // X0 = (P + conj P(-k1)) / 2, XM = (P - conj P(-k1)) / 2i
+#pragma unroll
+            for (int k1 = 0; k1 < NY; ++k1) {
+                const cx<T> pc = conjg(u[(NY - k1) % NY]), s = u[k1] + pc, d = u[k1] - pc;
+                cx<T> x0{T(0.5) * s.x, T(0.5) * s.y}, xm{T(0.5) * d.y, T(-0.5) * d.x};
+                if (k1 > 0) {
+                    x0 = cmul(x0, wy[k1]);
+                    xm = cmul(xm, wy[k1]);
+                }
+                put(k1, 0, x0);
+                put(k1, M, xm);
+            }
+        }
+#pragma unroll
+        for (int k1 = 0; k1 < NY; ++k1) {
+            if (!edge) put(k1, p, k1 > 0 ? cmul(u[k1], wy[k1]) : u[k1]);
+            put(k1, c1, k1 > 0 ? cmul(v[k1], wy[k1]) : v[k1]);
+        }
+    }
+}
+
+template <typename T, int N, int NY, int E, int G, int W, bool RMP, bool NTS, bool PENCIL>
+__global__ __launch_bounds__((rows_shape<T, N, NY, E, G>::NT), W) void k_rows_c2r(
+    const cx<T>* in, T* out, const cx<T>* __restrict__ tw, int64_t tiles, row_map map, T mul_edge,
+    T mul_int) {
+    using P = rows_shape<T, N, NY, E, G>;
+    constexpr int M = P::M, K = P::K, H = P::H, R = P::R, TZ = P::TZ, NT1 = P::NT1, Q = P::Q,
+                  RM = P::RM, LD = P::LD;
+    __shared__ T lds_all[G * P::SZ];
+    const int grp = threadIdx.x / NT1, lt = threadIdx.x % NT1;
+    T* lds = lds_all + grp * P::SZ;
+    const int r = lt / TZ, t = lt % TZ;
+    const int64_t blk = RMP ? xcd_tile(blockIdx.x, gridDim.x) : int64_t(blockIdx.x);
+    const int64_t tile = blk * G + grp;
+    const bool valid = tile < tiles;
+    const int64_t tl = valid ? tile : tiles - 1;
+    const int64_t plane = NY > 1 ? tl / R : 0;
+    const int y0 = NY > 1 ? int(tl % R) : 0;
+
+    auto get = [&](int k1, int k) {
+        if constexpr (PENCIL) return in[pencil_bin(tl, k, K, map)];
+        else return in[map_row(NY > 1 ? plane * N + y0 * NY + k1 : tl, map) * K + k];
+    };
+    cx<T> b[Q][2][NY];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const int p = lt + NT1 * q, c1 = p == 0 ? H : M - p;
+#pragma unroll
+        for (int k1 = 0; k1 < NY; ++k1) {
+            b[q][0][k1] = get(k1, p);
+            b[q][1][k1] = get(k1, c1);
+        }
+    }
+    cx<T> wy[NY];
+#pragma unroll
+    for (int k1 = 1; k1 < NY; ++k1) wy[k1] = tw[y0 * k1];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const int p = lt + NT1 * q;
+        const cx<T> w = tw[p];
+        const bool edge = p == 0;
+#pragma unroll
+        for (int k1 = 1; k1 < NY; ++k1) {
+            b[q][0][k1] = cmulc(b[q][0][k1], wy[k1]);
+            b[q][1][k1] = cmulc(b[q][1][k1], wy[k1]);
+        }
+        if (q == 0 && edge) {
+            // column 0: Hermitian parts (over the NY values of k1) of kz = 0
+            // (real) and kz = M (imaginary)
+            cx<T> g[NY], h[NY];
+#pragma unroll
+            for (int k1 = 0; k1 < NY; ++k1) {
+                h[k1] = get(k1, M);
+                if (k1 > 0) h[k1] = cmulc(h[k1], wy[k1]);
+            }
+#pragma unroll
+            for (int k1 = 0; k1 < NY; ++k1) {
+                const cx<T> h0 = scal(b[0][0][k1] + conjg(b[0][0][(NY - k1) % NY]), T(0.5));
+                const cx<T> hm = scal(h[k1] + conjg(h[(NY - k1) % NY]), T(0.5));
+                g[k1] = cx<T>{h0.x - hm.y, h0.y + hm.x};
+            }
+#pragma unroll
+            for (int k1 = 0; k1 < NY; ++k1) b[0][0][k1] = g[k1];
+        }
+        dft<NY, +1>(b[q][0]);
+        dft<NY, +1>(b[q][1]);
+#pragma unroll
+        for (int j = 0; j < NY; ++j) {
+            const cx<T> z = b[q][0][j], u = conjg(b[q][1][j]);
+            const cx<T> S = scal(z + u, mul_int), D = cmulc(scal(z - u, mul_int), w);
+            b[q][0][j].x = edge ? (z.x + z.y) * mul_edge : S.x - D.y;
+            b[q][0][j].y = edge ? (z.x - z.y) * mul_edge : S.y + D.x;
+            b[q][1][j].x = edge ? u.x * (T(2) * mul_int) : S.x + D.y;
+            b[q][1][j].y = edge ? u.y * (T(2) * mul_int) : D.x - S.y;
+        }
+    }
+    cx<T> a[E];
+#pragma unroll
+    for (int part = 0; part < 2; ++part) {
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int p = lt + NT1 * q, c1 = p == 0 ? H : M - p;
+#pragma unroll
+            for (int j = 0; j < NY; ++j) {
+                lds[j * LD + p] = part ? b[q][0][j].y : b[q][0][j].x;
+                lds[j * LD + c1] = part ? b[q][1][j].y : b[q][1][j].x;
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int m = 0; m < E; ++m) {
+            const T v = lds[r * LD + t + TZ * m];
+            if (part) a[m].y = v;
+            else a[m].x = v;
+        }
+        __syncthreads();
+    }
+    using IR = idx_rows<P::PS>;
+    fft_regs<T, M, E, +1, RM>(a, t, tw, 2, xch_split<T, IR>{lds, IR{r * P::MP}});
+    if (!valid) return;
+    const int64_t row0 = NY > 1 ? plane * N + y0 : tl;
+    cx<T>* dst = reinterpret_cast<cx<T>*>(out + (row0 + R * r) * map.rs);
+#pragma unroll
+    for (int m = 0; m < E; ++m) {
+        if constexpr (NTS) {
+            __builtin_nontemporal_store(a[m].x, &dst[t + TZ * m].x);
+            __builtin_nontemporal_store(a[m].y, &dst[t + TZ * m].y);
+        } else {
+            dst[t + TZ * m] = a[m];
+        }
+    }
+}
+
 // ---------------------------------------------------------------- whole grids of N = 16 and 32
 // The whole 3D transform of one small grid per workgroup: one read, one
 // write, one launch.  A grid is N N M complex values z (M = N/2, z[n] =

@@ -41,16 +41,6 @@ __device__ __forceinline__ int64_t opaque_uniform(int64_t v) {
     return int64_t((uint64_t(hi) << 32) | lo);
 }
 
-// Offset (in complex values) of bin k of row r in a pencil plan's
-// first-exchange order (row_map::pencil).
-__device__ __forceinline__ int64_t pencil_bin(int64_t r, int k, int K, const row_map& m) {
-    const int64_t item = r >> m.lg_rows;
-    const int64_t rl = r & ((int64_t(1) << m.lg_rows) - 1);
-    const int c = (k >> m.lg_w) < m.pc_last ? (k >> m.lg_w) : m.pc_last;
-    const int64_t wc = (int64_t(1) << m.lg_w) + (c == m.pc_last ? 1 : 0);
-    return ((item * K + (int64_t(c) << m.lg_w)) << m.lg_rows) + rl * wc + (k - (c << m.lg_w));
-}
-
 template <int M, int EMAX = 16, int THREADS = kThreads>
 struct zshape {
     static constexpr int E = M < EMAX ? M : EMAX;  // elements per thread

@@ -25,6 +25,16 @@ __device__ __forceinline__ int64_t map_row(int64_t r, row_map m) {
     return (b << (m.lg_x + m.lg_n)) + ((((j << m.lg_x) + xl)) << m.lg_y) + yl;
 }
 
+// Offset (in complex values) of bin k of row r in a pencil plan's
+// first-exchange order (row_map::pencil).
+__device__ __forceinline__ int64_t pencil_bin(int64_t r, int k, int K, const row_map& m) {
+    const int64_t item = r >> m.lg_rows;
+    const int64_t rl = r & ((int64_t(1) << m.lg_rows) - 1);
+    const int c = (k >> m.lg_w) < m.pc_last ? (k >> m.lg_w) : m.pc_last;
+    const int64_t wc = (int64_t(1) << m.lg_w) + (c == m.pc_last ? 1 : 0);
+    return ((item * K + (int64_t(c) << m.lg_w)) << m.lg_rows) + rl * wc + (k - (c << m.lg_w));
+}
+
 // Consecutive workgroup ids are dealt round-robin to the 8 XCDs, each with
 // its own L2.  Remap so that XCD x works through one contiguous range of
 // tiles: neighbouring tiles share cache lines at their edges.
