@@ -346,7 +346,10 @@ __global__ __launch_bounds__((rows_shape<T, N, NY, E, G>::NT), W) void k_rows_r2
     constexpr int M = P::M, K = P::K, H = P::H, R = P::R, TZ = P::TZ, NT1 = P::NT1, Q = P::Q,
                   RM = P::RM, LD = P::LD;
     __shared__ T lds_all[G * P::SZ];
-    const int grp = threadIdx.x / NT1, lt = threadIdx.x % NT1;
+    // whole waves belong to one tile: its row addresses stay in scalar registers
+    const int grp = NT1 % 64 == 0 ? __builtin_amdgcn_readfirstlane(int(threadIdx.x) / NT1)
+                                  : int(threadIdx.x) / NT1;
+    const int lt = threadIdx.x % NT1;
     T* lds = lds_all + grp * P::SZ;
     const int r = lt / TZ, t = lt % TZ;
     const int64_t blk = RMP ? xcd_tile(blockIdx.x, gridDim.x) : int64_t(blockIdx.x);
@@ -447,7 +450,10 @@ __global__ __launch_bounds__((rows_shape<T, N, NY, E, G>::NT), W) void k_rows_c2
     constexpr int M = P::M, K = P::K, H = P::H, R = P::R, TZ = P::TZ, NT1 = P::NT1, Q = P::Q,
                   RM = P::RM, LD = P::LD;
     __shared__ T lds_all[G * P::SZ];
-    const int grp = threadIdx.x / NT1, lt = threadIdx.x % NT1;
+    // whole waves belong to one tile: its row addresses stay in scalar registers
+    const int grp = NT1 % 64 == 0 ? __builtin_amdgcn_readfirstlane(int(threadIdx.x) / NT1)
+                                  : int(threadIdx.x) / NT1;
+    const int lt = threadIdx.x % NT1;
     T* lds = lds_all + grp * P::SZ;
     const int r = lt / TZ, t = lt % TZ;
     const int64_t blk = RMP ? xcd_tile(blockIdx.x, gridDim.x) : int64_t(blockIdx.x);
@@ -1001,6 +1007,84 @@ hipError_t launch_split_x(bool f64, int n, int sign, const void* src, void* dst,
     if (!split_supported(f64, n)) return hipErrorInvalidValue;
     return sign < 0 ? split_x_sign<-1>(f64, n, src, dst, tw, batch, s)
                     : split_x_sign<+1>(f64, n, src, dst, tw, batch, s);
+}
+
+// Long rows: elements per thread and tiles per workgroup, forward (F) and
+// inverse (I).  Measured over 2.1 / 4.3 GB of FP64 and half as much FP32
+// reals (N = 2048 / 4096, 64 / 32 planes), us, in brackets k_z_* (whole-value
+// exchanges), forward / inverse:
+//   NY = 1 (z pass)  FP64 2048 818 / 803 (924 / 871), 4096 1682 / 1550
+//                    (1777 / 1724); FP32 2048 459 / 441 (460 / 470), 4096
+//                    949 / 914 (1011 / 1039)
+//   NY = N / 1024    FP64 2048 888 / 839, 4096 1786 / 1640; FP32 2048 451 /
+//                    472, 4096 1056 / 968; the y lines left are 1024 long
+// One tile a workgroup at N = 4096, NY = 1 takes 2029: rows share a line at
+// their ends, so four tiles of neighbouring rows go together.
+template <typename T, int N, int NY>
+struct rows_cfg {
+    static constexpr bool F64 = sizeof(T) == 8;
+    static constexpr int EF = F64 && (N == 2048 || NY == 4) ? 16 : 32;
+    static constexpr int EI = F64 && N == 2048 ? 16 : 32;
+    static constexpr int GF = NY == 4 ? (F64 ? 1 : 2) : NY == 2 ? 4 : F64 ? (N == 4096 ? 2 : 4)
+                                                                  : (N == 4096 ? 4 : 8);
+    static constexpr int GI = NY == 4 ? 1 : NY == 2 ? (F64 ? 2 : 4) : F64 ? 4 : (N == 4096 ? 4 : 8);
+    static constexpr int WF = EF == 16 ? 4 : 2, WI = EI == 16 ? 4 : 2;
+};
+
+template <typename T, int N, int NY>
+static hipError_t rows_n(bool forward, const void* in, void* out, const void* tw, int64_t rows,
+                         row_map map, double me, double mi, hipStream_t s) {
+    using C = rows_cfg<T, N, NY>;
+    const int64_t tiles = rows / NY;
+    if (tiles == 0) return hipSuccess;
+    auto go = [&](auto kernel, int64_t g, int nt, auto pin, auto pout) {
+        const int64_t blocks = (tiles + g - 1) / g;
+        if (!grid_fits(blocks, nt)) return hipErrorInvalidValue;
+        hipLaunchKernelGGL(kernel, dim3(blocks), dim3(nt), 0, s, pin, pout,
+                           static_cast<const cx<T>*>(tw), tiles, map, T(me), T(mi));
+        return hipGetLastError();
+    };
+    if (forward) {
+        constexpr int NT = rows_shape<T, N, NY, C::EF, C::GF>::NT;
+        const T* pi = static_cast<const T*>(in);
+        cx<T>* po = static_cast<cx<T>*>(out);
+        if constexpr (NY == 1) {
+            if (map.pencil)
+                return go(k_rows_r2c<T, N, 1, C::EF, C::GF, C::WF, true, true>, C::GF, NT, pi, po);
+        }
+        return go(k_rows_r2c<T, N, NY, C::EF, C::GF, C::WF, true, false>, C::GF, NT, pi, po);
+    }
+    constexpr int NT = rows_shape<T, N, NY, C::EI, C::GI>::NT;
+    const cx<T>* pi = static_cast<const cx<T>*>(in);
+    T* po = static_cast<T*>(out);
+    if constexpr (NY == 1) {
+        if (map.pencil)
+            return go(k_rows_c2r<T, N, 1, C::EI, C::GI, C::WI, true, true, true>, C::GI, NT, pi, po);
+    }
+    return go(k_rows_c2r<T, N, NY, C::EI, C::GI, C::WI, true, true, false>, C::GI, NT, pi, po);
+}
+
+int rows_step(int n) { return n >= 2048 ? n / 1024 : 1; }
+
+template <typename T>
+static hipError_t rows_t(bool forward, int n, int ny, const void* in, void* out, const void* tw,
+                         int64_t rows, row_map map, double me, double mi, hipStream_t s) {
+    if (n == 2048 && ny == 1)
+        return rows_n<T, 2048, 1>(forward, in, out, tw, rows, map, me, mi, s);
+    if (n == 2048 && ny == 2)
+        return rows_n<T, 2048, 2>(forward, in, out, tw, rows, map, me, mi, s);
+    if (n == 4096 && ny == 1)
+        return rows_n<T, 4096, 1>(forward, in, out, tw, rows, map, me, mi, s);
+    if (n == 4096 && ny == 4)
+        return rows_n<T, 4096, 4>(forward, in, out, tw, rows, map, me, mi, s);
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_rows(bool f64, bool forward, int n, int ny, const void* in, void* out,
+                       const void* tw, int64_t rows, row_map map, double me, double mi,
+                       hipStream_t s) {
+    return f64 ? rows_t<double>(forward, n, ny, in, out, tw, rows, map, me, mi, s)
+               : rows_t<float>(forward, n, ny, in, out, tw, rows, map, me, mi, s);
 }
 
 template <typename T, int N>

@@ -55,6 +55,22 @@ hipError_t launch_z_c2r(bool f64, int n, const void* in, void* out, const void* 
 hipError_t launch_strided(bool f64, int n, int axis, int mfma_terms, int sign, const void* src,
                           void* data, const void* tw, int64_t m_cols, int64_t n_b, line_map lm,
                           hipStream_t s);
+// Rows of N = 2048 or 4096 in `rows` z rows (a multiple of N for ny > 1).
+// ny = 1: the z pass, also in place and for pencils (launch_z_* use it).
+// ny = rows_step(n) = N / 1024: z R2C of the rows y0 + (N/ny) j of a plane,
+// the ny-point y step over j and its twiddles, bin k1 to row y0 ny + k1
+// (forward; out of place), or the reverse; launch_strided_1024 is the rest of
+// the y transform: 1024-point lines over y0 (rows y0 ny + k1), in place or
+// from src.  Rows of the half spectrum follow `map`, ny consecutive ones
+// contiguous.
+int rows_step(int n);
+hipError_t launch_rows(bool f64, bool forward, int n, int ny, const void* in, void* out,
+                       const void* tw, int64_t rows, row_map map, double mul_edge, double mul_int,
+                       hipStream_t s);
+hipError_t launch_strided_1024(bool f64, int n, int sign, const void* src, void* data,
+                               const void* tw, int64_t m_cols, int64_t n_b, line_map lm,
+                               hipStream_t s);
+
 // Copy `chunks` runs of `len` complex values: run c = (bb, j, xl) goes from
 // natural offset bb*X*N*K + (xl*N + j*Y)*K to send offset
 // bb*X*N*K + (j*X + xl)*Y*K (to_send = true) or back (to_send = false).

@@ -49,16 +49,16 @@ struct zshape {
     static constexpr int RPB = NT / TPT;           // rows per workgroup
 };
 
-// Workgroup shape of the z passes, chosen by measurement (2^18 and 2^20
-// rows): FP64 R2C 8 elements per thread in 256-thread workgroups up to
-// N = 512, 16 per thread in 128-thread ones for N = 1024 and 2048 (7-8%
-// faster there), 32 per thread for N = 4096; FP64 C2R 16 per thread in
-// 64-thread workgroups; FP32 32 per thread, in 256-thread workgroups for the
-// R2C from N = 1024 up (4-10% faster with the radix-32 stages) and 64-thread
-// ones otherwise, except at N = 256 and 512: 16 per thread in 256-thread
-// workgroups (the C2R of N = 512 in 128-thread ones), 5-13% faster there.
+// Workgroup shape of the z passes up to N = 1024 (longer rows: k_rows_*),
+// chosen by measurement (2^18 and 2^20 rows): FP64 R2C 8 elements per thread
+// in 256-thread workgroups up to N = 512, 16 per thread in 128-thread ones for
+// N = 1024 (7-8% faster there); FP64 C2R 16 per thread in 64-thread
+// workgroups; FP32 32 per thread, in 256-thread workgroups for the R2C of
+// N = 1024 (4-10% faster with the radix-32 stages) and 64-thread ones
+// otherwise, except at N = 256 and 512: 16 per thread in 256-thread workgroups
+// (the C2R of N = 512 in 128-thread ones), 5-13% faster there.
 // Workgroups are dealt to XCDs in contiguous ranges by the C2R at every N
-// (3-5%) and by the R2C from N = 1024 up (2-3%) and at the FP32 N = 256 and
+// (3-5%) and by the R2C at N = 1024 (2-3%) and at the FP32 N = 256 and
 // 512 shapes.  The C2R also stores its line-aligned real rows
 // non-temporally (they are not read again soon); the R2C's complex rows are
 // not line-aligned and gain nothing from it.
@@ -67,7 +67,7 @@ struct zcfg {
     static constexpr bool F64 = sizeof(T) == 8;
     static constexpr bool MID32 = !F64 && (N == 256 || N == 512);
     static constexpr int EMAX =
-        F64 ? (FWD ? (N >= 4096 ? 32 : N >= 1024 ? 16 : 8) : 16) : (MID32 ? 16 : 32);
+        F64 ? (FWD ? (N >= 1024 ? 16 : 8) : 16) : (MID32 ? 16 : 32);
     static constexpr int THREADS =
         F64 ? (FWD ? (N >= 1024 ? 128 : 256) : 64)
             : MID32 ? (FWD || N == 256 ? 256 : 128) : (FWD && N >= 1024 ? 256 : 64);
@@ -315,10 +315,11 @@ struct sshape {
 // -1 no transform (each element replaced by its conjugate): the same loads
 // and stores as the pass, a yardstick for its memory-access ceiling.
 // RMP: tiles in XCD-contiguous order (false: in launch order).
+// TWS: tw is the table of a transform TWS times as long.
 // src may be data itself (in place) or a distinct buffer of the same layout:
 // every load of a tile precedes its stores, and tiles own their elements.
 template <typename T, int N, int TC, int XP, int S, int E = 16, int MF = 0, bool NT = false,
-          bool RMP = true>
+          bool RMP = true, int TWS = 1>
 __global__ __launch_bounds__(TC * N / E) void k_strided(
     const cx<T>* src, cx<T>* data, const cx<T>* __restrict__ tw, int64_t m_cols,
     int64_t tiles_m, line_map lm) {
@@ -390,10 +391,10 @@ __global__ __launch_bounds__(TC * N / E) void k_strided(
             }
         }
         if constexpr (SPLIT)
-            fft_regs<T, N, E, S, RM>(a, t, tw, 1,
+            fft_regs<T, N, E, S, RM>(a, t, tw, TWS,
                                      xch_split<T, IX>{reinterpret_cast<T*>(lds), IX{c}});
         else
-            fft_regs<T, N, E, S, RM>(a, t, tw, 1, xch_full<T, IX>{lds, IX{c}});
+            fft_regs<T, N, E, S, RM>(a, t, tw, TWS, xch_full<T, IX>{lds, IX{c}});
     } else {
         // First radix-16 stage on the matrix cores.  The wave's 64 butterflies
         // (those of its own threads, j = t for thread (c, t)) go in two groups
@@ -582,7 +583,7 @@ static bool whole_lines(const void* data, int64_t m_cols, const line_map& lm, in
            lm.b_hi % la == 0 && lm.b_lo % la == 0 && lm.s_hi % la == 0 && lm.s_lo % la == 0;
 }
 
-template <typename T, int N, int AX, int MF, bool NT, bool RMP>
+template <typename T, int N, int AX, int MF, bool NT, bool RMP, int TWS = 1>
 static hipError_t strided_run(int sign, const void* src, void* data, const void* tw, int64_t m_cols,
                               int64_t n_b, line_map lm, hipStream_t s) {
     using SH = sshape<T, N, AX, (MF > 0)>;
@@ -593,11 +594,11 @@ static hipError_t strided_run(int sign, const void* src, void* data, const void*
     if (!grid_fits(blocks, TC * SH::TPT)) return hipErrorInvalidValue;
     const dim3 threads(TC * SH::TPT);
     if (MF < 0 || sign < 0)
-        hipLaunchKernelGGL((k_strided<T, N, TC, SH::XP, -1, SH::E, MF, NT, RMP>), dim3(blocks),
+        hipLaunchKernelGGL((k_strided<T, N, TC, SH::XP, -1, SH::E, MF, NT, RMP, TWS>), dim3(blocks),
                            threads, 0, s, static_cast<const cx<T>*>(src),
                            static_cast<cx<T>*>(data), static_cast<const cx<T>*>(tw), m_cols, tiles_m, lm);
     else if constexpr (MF >= 0)
-        hipLaunchKernelGGL((k_strided<T, N, TC, SH::XP, +1, SH::E, MF, NT, RMP>), dim3(blocks),
+        hipLaunchKernelGGL((k_strided<T, N, TC, SH::XP, +1, SH::E, MF, NT, RMP, TWS>), dim3(blocks),
                            threads, 0, s, static_cast<const cx<T>*>(src),
                            static_cast<cx<T>*>(data), static_cast<const cx<T>*>(tw), m_cols, tiles_m, lm);
     return hipGetLastError();
@@ -666,15 +667,22 @@ static hipError_t strided_n(int axis, int mfma_terms, int sign, const void* src,
     return strided_ax<T, N, 1, 0>(sign, src, data, tw, m_cols, n_b, lm, s);
 }
 
+#define GFFT_CASES_TO_1024(FN, T, ...)              \
+    case 16: return FN<T, 16>(__VA_ARGS__);         \
+    case 32: return FN<T, 32>(__VA_ARGS__);         \
+    case 64: return FN<T, 64>(__VA_ARGS__);         \
+    case 128: return FN<T, 128>(__VA_ARGS__);       \
+    case 256: return FN<T, 256>(__VA_ARGS__);       \
+    case 512: return FN<T, 512>(__VA_ARGS__);       \
+    case 1024: return FN<T, 1024>(__VA_ARGS__);
+#define GFFT_DISPATCH_TO_1024(FN, T, ...)           \
+    switch (n) {                                    \
+        GFFT_CASES_TO_1024(FN, T, __VA_ARGS__)      \
+        default: return hipErrorInvalidValue;       \
+    }
 #define GFFT_DISPATCH_N(FN, T, ...)                 \
     switch (n) {                                    \
-        case 16: return FN<T, 16>(__VA_ARGS__);     \
-        case 32: return FN<T, 32>(__VA_ARGS__);     \
-        case 64: return FN<T, 64>(__VA_ARGS__);     \
-        case 128: return FN<T, 128>(__VA_ARGS__);   \
-        case 256: return FN<T, 256>(__VA_ARGS__);   \
-        case 512: return FN<T, 512>(__VA_ARGS__);   \
-        case 1024: return FN<T, 1024>(__VA_ARGS__); \
+        GFFT_CASES_TO_1024(FN, T, __VA_ARGS__)      \
         case 2048: return FN<T, 2048>(__VA_ARGS__); \
         case 4096: return FN<T, 4096>(__VA_ARGS__); \
         default: return hipErrorInvalidValue;       \
@@ -682,14 +690,16 @@ static hipError_t strided_n(int axis, int mfma_terms, int sign, const void* src,
 
 hipError_t launch_z_r2c(bool f64, int n, const void* in, void* out, const void* tw,
                         int64_t rows, row_map map, double me, double mi, hipStream_t s) {
-    if (f64) { GFFT_DISPATCH_N(z_r2c_n, double, in, out, tw, rows, map, me, mi, s) }
-    GFFT_DISPATCH_N(z_r2c_n, float, in, out, tw, rows, map, me, mi, s)
+    if (n >= 2048) return launch_rows(f64, true, n, 1, in, out, tw, rows, map, me, mi, s);
+    if (f64) { GFFT_DISPATCH_TO_1024(z_r2c_n, double, in, out, tw, rows, map, me, mi, s) }
+    GFFT_DISPATCH_TO_1024(z_r2c_n, float, in, out, tw, rows, map, me, mi, s)
 }
 
 hipError_t launch_z_c2r(bool f64, int n, const void* in, void* out, const void* tw,
                         int64_t rows, row_map map, double me, double mi, hipStream_t s) {
-    if (f64) { GFFT_DISPATCH_N(z_c2r_n, double, in, out, tw, rows, map, me, mi, s) }
-    GFFT_DISPATCH_N(z_c2r_n, float, in, out, tw, rows, map, me, mi, s)
+    if (n >= 2048) return launch_rows(f64, false, n, 1, in, out, tw, rows, map, me, mi, s);
+    if (f64) { GFFT_DISPATCH_TO_1024(z_c2r_n, double, in, out, tw, rows, map, me, mi, s) }
+    GFFT_DISPATCH_TO_1024(z_c2r_n, float, in, out, tw, rows, map, me, mi, s)
 }
 
 hipError_t launch_strided(bool f64, int n, int axis, int mfma_terms, int sign, const void* src,
@@ -697,6 +707,23 @@ hipError_t launch_strided(bool f64, int n, int axis, int mfma_terms, int sign, c
                           hipStream_t s) {
     if (f64) { GFFT_DISPATCH_N(strided_n, double, axis, mfma_terms, sign, src, data, tw, m_cols, n_b, lm, s) }
     GFFT_DISPATCH_N(strided_n, float, axis, mfma_terms, sign, src, data, tw, m_cols, n_b, lm, s)
+}
+
+template <typename T>
+static hipError_t strided_1024(int n, int sign, const void* src, void* data, const void* tw,
+                               int64_t m_cols, int64_t n_b, line_map lm, hipStream_t s) {
+    if (n == 2048)
+        return strided_run<T, 1024, 0, 0, false, true, 2>(sign, src, data, tw, m_cols, n_b, lm, s);
+    if (n == 4096)
+        return strided_run<T, 1024, 0, 0, false, true, 4>(sign, src, data, tw, m_cols, n_b, lm, s);
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_strided_1024(bool f64, int n, int sign, const void* src, void* data,
+                               const void* tw, int64_t m_cols, int64_t n_b, line_map lm,
+                               hipStream_t s) {
+    return f64 ? strided_1024<double>(n, sign, src, data, tw, m_cols, n_b, lm, s)
+               : strided_1024<float>(n, sign, src, data, tw, m_cols, n_b, lm, s);
 }
 
 hipError_t launch_pack(bool f64, const void* src, void* dst, int64_t chunks, int lg_x,

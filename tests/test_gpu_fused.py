@@ -136,3 +136,44 @@ def test_small_grids(n, batch, inplace, dtype):
     assert rel_l2(host(A), 3.0 * oracle.c2r3d_adjoint(xref)) <= tol
     assert rel_l2(host(f), 0.5 * oracle.c2r3d(gref, n)) <= tol
     assert rel_l2(host(a), 0.25 * oracle.r2c3d_adjoint(gref, n)) <= tol
+
+
+@DTYPES
+@pytest.mark.parametrize("n,x,batch,order", [
+    (2048, 1, 2, "natural"), (2048, 2, 1, "send"), (2048, 1, 1, "send"), (2048, 2, 1, "paper"),
+    (2048, 1, 1, "inplace"), (4096, 1, 1, "natural"), (4096, 4, 1, "send"), (4096, 2, 1, "send")])
+def test_long_rows_step1(n, x, batch, order, dtype):
+    """Step 1 at N = 2048 and 4096 with y split between the z and y passes,
+    and the layouts that keep the whole y pass, against the separate passes
+    (and one plane of them against the oracle), weighted and not."""
+    p = Plan(n, dtype, slab_x=x, batch=batch, fuse_pack=order in ("send", "paper"),
+             paper_order=order == "paper", inplace=order == "inplace")
+    s = Plan(n, dtype, slab_x=x, batch=batch)
+    tol = TOL[dtype]
+
+    def off(a, b):
+        return (torch.linalg.vector_norm(a - b) / torch.linalg.vector_norm(b)).item()
+
+    xin, xref = real_input(s.real_shape, 26000 + n, dtype)
+    sep, sepw = s.z_r2c(xin), s.z_r2c(xin, scale=3.0, weighted=True)
+    for a in (sep, sepw):
+        s.y_c2c(a, -1)
+    assert rel_l2(host(sep[:1, :1]), oracle.r2c2d_planes(xref[:1, :1])) <= tol
+    g, _ = cplx_input(s.spectrum_shape, 26500 + n, dtype)
+    gy = s.y_c2c(g.clone(), +1)
+    want, wantw = s.z_c2r(gy, scale=0.5), s.z_c2r(gy, scale=0.25, weighted=True)
+    if order == "inplace":
+        def padded():
+            buf = p.empty_inplace()
+            p.real_view(buf).copy_(xin)
+            return buf
+        F, W = p.r2c_(padded()), p.c2r_adjoint_(padded(), scale=3.0)
+        f, w = p.c2r_(g.clone(), scale=0.5), p.r2c_adjoint_(g.clone(), scale=0.25)
+    else:
+        if order != "natural":
+            sep, sepw, g = p.pack(sep), p.pack(sepw), p.pack(g)
+        F, W = p.r2c(xin), p.c2r_adjoint(xin, scale=3.0)
+        f, w = p.c2r(g.clone(), scale=0.5), p.r2c_adjoint(g.clone(), scale=0.25)
+        assert torch.equal(p.inverse_keep(g, scale=0.5), f)
+    assert off(F, sep) <= tol and off(W, sepw) <= tol
+    assert off(f, want) <= tol and off(w, wantw) <= tol
