@@ -137,7 +137,7 @@ __global__ __launch_bounds__((plane_shape<T, N, R, E>::NT), W) void k_plane_r2c(
     constexpr int M = P::M, K = P::K, H = P::H, NY = P::NY, TZ = P::TZ, TY = P::TY, EY = P::EY,
                   RM = P::RM;
     __shared__ T lds[P::LDS];
-    const int64_t tile = R > 1 ? xcd_tile(blockIdx.x, gridDim.x) : int64_t(blockIdx.x);
+    const int64_t tile = xcd_tile<kGrouped>(blockIdx.x, gridDim.x);
     const int64_t plane = tile / R;
     const int y0 = int(tile % R);
     const int tid = threadIdx.x;
@@ -227,7 +227,7 @@ __global__ __launch_bounds__((plane_shape<T, N, R, E>::NT), W) void k_plane_c2r(
     constexpr int M = P::M, K = P::K, H = P::H, NY = P::NY, TZ = P::TZ, TY = P::TY, EY = P::EY,
                   RM = P::RM;
     __shared__ T lds[P::LDS];
-    const int64_t tile = R > 1 ? xcd_tile(blockIdx.x, gridDim.x) : int64_t(blockIdx.x);
+    const int64_t tile = xcd_tile<kGrouped>(blockIdx.x, gridDim.x);
     const int64_t plane = tile / R;
     const int y0 = int(tile % R);
     const int tid = threadIdx.x;
@@ -338,7 +338,7 @@ struct rows_shape {
     static_assert(Q >= 1 && Q * NT1 == H, "rows shape");
 };
 
-template <typename T, int N, int NY, int E, int G, int W, bool RMP, bool PENCIL>
+template <typename T, int N, int NY, int E, int G, int W, bool PENCIL>
 __global__ __launch_bounds__((rows_shape<T, N, NY, E, G>::NT), W) void k_rows_r2c(
     const T* in, cx<T>* out, const cx<T>* __restrict__ tw, int64_t tiles, row_map map, T mul_edge,
     T mul_int) {
@@ -352,7 +352,7 @@ __global__ __launch_bounds__((rows_shape<T, N, NY, E, G>::NT), W) void k_rows_r2
     const int lt = threadIdx.x % NT1;
     T* lds = lds_all + grp * P::SZ;
     const int r = lt / TZ, t = lt % TZ;
-    const int64_t blk = RMP ? xcd_tile(blockIdx.x, gridDim.x) : int64_t(blockIdx.x);
+    const int64_t blk = xcd_tile<kGrouped>(blockIdx.x, gridDim.x);
     const int64_t tile = blk * G + grp;
     const bool valid = tile < tiles;
     // tiles past the end (last workgroup) load the last tile and drop it
@@ -442,7 +442,7 @@ __global__ __launch_bounds__((rows_shape<T, N, NY, E, G>::NT), W) void k_rows_r2
     }
 }
 
-template <typename T, int N, int NY, int E, int G, int W, bool RMP, bool NTS, bool PENCIL>
+template <typename T, int N, int NY, int E, int G, int W, bool PENCIL>
 __global__ __launch_bounds__((rows_shape<T, N, NY, E, G>::NT), W) void k_rows_c2r(
     const cx<T>* in, T* out, const cx<T>* __restrict__ tw, int64_t tiles, row_map map, T mul_edge,
     T mul_int) {
@@ -456,7 +456,7 @@ __global__ __launch_bounds__((rows_shape<T, N, NY, E, G>::NT), W) void k_rows_c2
     const int lt = threadIdx.x % NT1;
     T* lds = lds_all + grp * P::SZ;
     const int r = lt / TZ, t = lt % TZ;
-    const int64_t blk = RMP ? xcd_tile(blockIdx.x, gridDim.x) : int64_t(blockIdx.x);
+    const int64_t blk = xcd_tile<kGrouped>(blockIdx.x, gridDim.x);
     const int64_t tile = blk * G + grp;
     const bool valid = tile < tiles;
     const int64_t tl = valid ? tile : tiles - 1;
@@ -548,12 +548,8 @@ __global__ __launch_bounds__((rows_shape<T, N, NY, E, G>::NT), W) void k_rows_c2
     cx<T>* dst = reinterpret_cast<cx<T>*>(out + (row0 + R * r) * map.rs);
 #pragma unroll
     for (int m = 0; m < E; ++m) {
-        if constexpr (NTS) {
-            __builtin_nontemporal_store(a[m].x, &dst[t + TZ * m].x);
-            __builtin_nontemporal_store(a[m].y, &dst[t + TZ * m].y);
-        } else {
-            dst[t + TZ * m] = a[m];
-        }
+        __builtin_nontemporal_store(a[m].x, &dst[t + TZ * m].x);
+        __builtin_nontemporal_store(a[m].y, &dst[t + TZ * m].y);
     }
 }
 
@@ -752,7 +748,7 @@ __global__ __launch_bounds__((box_shape<T, N>::NT), (box_shape<T, N>::W)) void k
 // needs no exchange.  src and dst may be the same buffer.
 //   NT: non-temporal loads and stores (no reuse), where every 128-byte line
 //       belongs to one tile;
-//   RMP: XCD-contiguous tile order.
+//   ORD: tile order (xcd_tile).
 template <typename T, int N, int R, int TC, int EX>
 struct xr_shape {
     static constexpr int K = N / 2 + 1, NY = N / R, TPT = N / EX, NT = TC * TPT;
@@ -764,14 +760,14 @@ struct xr_shape {
     static constexpr int TILES = (COLS + TC - 1) / TC;  // per grid
 };
 
-template <typename T, int N, int R, int TC, int EX, int S, bool NT, int W, bool RMP>
+template <typename T, int N, int R, int TC, int EX, int S, bool NT, int W, int ORD>
 __global__ __launch_bounds__((xr_shape<T, N, R, TC, EX>::NT), W) void k_strided_r(
     const cx<T>* src, cx<T>* dst, const cx<T>* __restrict__ tw) {
     using P = xr_shape<T, N, R, TC, EX>;
     constexpr int K = P::K, NY = P::NY, TPT = P::TPT;
     __shared__ T lds[P::LDS];
     const int c = threadIdx.x % TC, t = threadIdx.x / TC;
-    const int64_t tile = RMP ? xcd_tile(blockIdx.x, gridDim.x) : int64_t(blockIdx.x);
+    const int64_t tile = xcd_tile<ORD>(blockIdx.x, gridDim.x);
     const int64_t b = tile / P::TILES;
     const int m = int(tile - b * P::TILES) * TC + c;
     const bool valid = m < P::COLS;
@@ -898,33 +894,34 @@ hipError_t launch_plane(bool f64, bool forward, int n, const void* in, void* out
     }
 }
 
-// Split y transform: R (row tiles of 64 rows), the row tile's elements per thread, and the x pass's
-// columns per tile, elements per row and thread, hints and tile order.  64
-// rows leave room for two or more row tiles on a CU and keep the x tile's
-// runs at 64 bytes or more.  Measured over 537 MB of
+// Split y transform: R (row tiles of 64 rows), the row tile's elements per
+// thread, and the x pass's columns per tile, elements per row and thread,
+// hints and tile order.  64 rows leave room for two or more row tiles on a CU
+// and keep the x tile's runs at 64 bytes or more.  Measured over 537 MB of
 // reals, row tiles forward / inverse and x pass, us (in brackets the step 1
 // and x passes they replace):
-//   FP64 N = 128, R = 2: 205 / 204 + 194 (215 / 209 + 217)
-//        N = 256, R = 4: 207 / 209 + 244 (397 / 414 + 242)
-//   FP32 N = 128, R = 2: 215 / 222 + 182 (228 / 220 + 218)
-//        N = 256, R = 4: 212 / 218 + 231 (327 / 333 + 233)
-//        N = 512, R = 8: 226 / 237 + 331 (448 / 445 + 272)
-// FP64 N = 512 would need R = 8 with 4-column x tiles that fill a CU:
-// 446 / 492 + 691 against 815 / 803 + 458, not taken.  N = 64 planes have
-// room as they are.  The x tiles at N = 128 cover whole 128-byte lines and
-// run fastest without the XCD order and non-temporally (FP32 182 against
-// 198 with the order, 212 without the hint); at N = 256 FP64 the order and
-// plain accesses (244 against 254 and 250), FP32 plain accesses without the
-// order (231 against 242); at FP32 N = 512 the tiles' 64-byte runs share
-// lines, so both the order and plain accesses (331 against 376, 460).
+//   FP64 N = 128, R = 2: 198 / 198 + 194 (215 / 209 + 217)
+//        N = 256, R = 4: 207 / 209 + 229 (397 / 414 + 242)
+//   FP32 N = 128, R = 2: 208 / 215 + 182 (228 / 220 + 218)
+//        N = 256, R = 4: 212 / 206 + 217 (327 / 333 + 233)
+//        N = 512, R = 8: 226 / 237 + 311 (448 / 445 + 214)
+// and over 1.07 GB FP64 N = 512, R = 8: 446 / 492 + 598 (815 / 803 + 415).
+// N = 64 planes have room as they are.  Tiles in groups (ORD) of 64 run the x
+// pass at 4.73 TB/s for FP64 256 (contiguous 4.41), 4.93 for FP32 256 (4.43),
+// and 3.46 / 3.60 for FP32 / FP64 512 (3.27 / 3.08), whose 64-byte runs share
+// lines; N = 128 in launch order, non-temporally (FP32 5.96, contiguous 5.53,
+// without the hint 5.1).  At N = 256 the hint gains nothing.
 template <typename T, int N>
 struct split_cfg {
     static constexpr bool F64 = sizeof(T) == 8;
     static constexpr int R = N / 64;
-    static constexpr int E = !F64 && N == 128 ? 8 : 16, W = F64 && N == 128 ? 2 : 4;
-    static constexpr int TC = N == 128 ? 32 : F64 ? 8 : N == 256 ? 16 : 8, EX = 8;
+    static constexpr int E = !F64 && N == 128 ? 8 : 16;
+    static constexpr int W = F64 && (N == 128 || N == 512) ? 2 : 4;
+    static constexpr int TC = N == 128 ? 32 : N == 256 ? (F64 ? 8 : 16) : (F64 ? 4 : 8);
+    static constexpr int EX = F64 && N == 512 ? 4 : 8;
     static constexpr int WX = R * EX * int(sizeof(cx<T>)) > 256 ? 2 : 4;
-    static constexpr bool NT = N == 128, RMP = N == 512 || (F64 && N == 256);
+    static constexpr bool NT = N == 128;
+    static constexpr int ORD = N == 128 ? 0 : 6;
 };
 
 template <typename T, int N>
@@ -946,15 +943,16 @@ static hipError_t split_rows_n(bool forward, const void* in, void* out, const vo
     return hipGetLastError();
 }
 
-template <typename T, int N, int S, bool NT, bool RMP>
+template <typename T, int N, int S, bool NT>
 static hipError_t split_x_run(const void* src, void* dst, const void* tw, int64_t batch,
                               hipStream_t s) {
     using C = split_cfg<T, N>;
     using P = xr_shape<T, N, C::R, C::TC, C::EX>;
+    constexpr int ORD = NT == C::NT ? C::ORD : kGrouped;
     const int64_t blocks = batch * P::TILES;
     if (blocks == 0) return hipSuccess;
     if (!grid_fits(blocks, P::NT)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_strided_r<T, N, C::R, C::TC, C::EX, S, NT, C::WX, RMP>), dim3(blocks),
+    hipLaunchKernelGGL((k_strided_r<T, N, C::R, C::TC, C::EX, S, NT, C::WX, ORD>), dim3(blocks),
                        dim3(P::NT), 0, s, static_cast<const cx<T>*>(src),
                        static_cast<cx<T>*>(dst), static_cast<const cx<T>*>(tw));
     return hipGetLastError();
@@ -963,25 +961,28 @@ static hipError_t split_x_run(const void* src, void* dst, const void* tw, int64_
 template <typename T, int N, int S>
 static hipError_t split_x_n(const void* src, void* dst, const void* tw, int64_t batch,
                             hipStream_t s) {
-    using C = split_cfg<T, N>;
     // the non-temporal hint is for tiles that own their lines: a buffer off
-    // the 128-byte grid takes plain accesses in XCD order
-    if constexpr (C::NT) {
+    // the 128-byte grid takes plain accesses
+    if constexpr (split_cfg<T, N>::NT) {
         const uintptr_t both = reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst);
-        if (both % 128 != 0) return split_x_run<T, N, S, false, true>(src, dst, tw, batch, s);
+        if (both % 128 == 0) return split_x_run<T, N, S, true>(src, dst, tw, batch, s);
     }
-    return split_x_run<T, N, S, C::NT, C::RMP>(src, dst, tw, batch, s);
+    return split_x_run<T, N, S, false>(src, dst, tw, batch, s);
 }
 
-bool split_supported(bool f64, int n) { return n == 128 || n == 256 || (!f64 && n == 512); }
+bool split_supported(int n) { return n == 128 || n == 256 || n == 512; }
 
 hipError_t launch_split_rows(bool f64, bool forward, int n, const void* in, void* out,
                              const void* tw, int64_t planes, row_map map, double me, double mi,
                              hipStream_t s) {
-    if (!split_supported(f64, n)) return hipErrorInvalidValue;
-    if (f64)
-        return n == 128 ? split_rows_n<double, 128>(forward, in, out, tw, planes, map, me, mi, s)
-                        : split_rows_n<double, 256>(forward, in, out, tw, planes, map, me, mi, s);
+    if (!split_supported(n)) return hipErrorInvalidValue;
+    if (f64) {
+        switch (n) {
+            case 128: return split_rows_n<double, 128>(forward, in, out, tw, planes, map, me, mi, s);
+            case 256: return split_rows_n<double, 256>(forward, in, out, tw, planes, map, me, mi, s);
+            default: return split_rows_n<double, 512>(forward, in, out, tw, planes, map, me, mi, s);
+        }
+    }
     switch (n) {
         case 128: return split_rows_n<float, 128>(forward, in, out, tw, planes, map, me, mi, s);
         case 256: return split_rows_n<float, 256>(forward, in, out, tw, planes, map, me, mi, s);
@@ -992,9 +993,13 @@ hipError_t launch_split_rows(bool f64, bool forward, int n, const void* in, void
 template <int S>
 static hipError_t split_x_sign(bool f64, int n, const void* src, void* dst, const void* tw,
                                int64_t batch, hipStream_t s) {
-    if (f64)
-        return n == 128 ? split_x_n<double, 128, S>(src, dst, tw, batch, s)
-                        : split_x_n<double, 256, S>(src, dst, tw, batch, s);
+    if (f64) {
+        switch (n) {
+            case 128: return split_x_n<double, 128, S>(src, dst, tw, batch, s);
+            case 256: return split_x_n<double, 256, S>(src, dst, tw, batch, s);
+            default: return split_x_n<double, 512, S>(src, dst, tw, batch, s);
+        }
+    }
     switch (n) {
         case 128: return split_x_n<float, 128, S>(src, dst, tw, batch, s);
         case 256: return split_x_n<float, 256, S>(src, dst, tw, batch, s);
@@ -1004,30 +1009,30 @@ static hipError_t split_x_sign(bool f64, int n, const void* src, void* dst, cons
 
 hipError_t launch_split_x(bool f64, int n, int sign, const void* src, void* dst, const void* tw,
                           int64_t batch, hipStream_t s) {
-    if (!split_supported(f64, n)) return hipErrorInvalidValue;
+    if (!split_supported(n)) return hipErrorInvalidValue;
     return sign < 0 ? split_x_sign<-1>(f64, n, src, dst, tw, batch, s)
                     : split_x_sign<+1>(f64, n, src, dst, tw, batch, s);
 }
 
 // Long rows: elements per thread and tiles per workgroup, forward (F) and
 // inverse (I).  Measured over 2.1 / 4.3 GB of FP64 and half as much FP32
-// reals (N = 2048 / 4096, 64 / 32 planes), us, in brackets k_z_* (whole-value
-// exchanges), forward / inverse:
-//   NY = 1 (z pass)  FP64 2048 818 / 803 (924 / 871), 4096 1682 / 1550
-//                    (1777 / 1724); FP32 2048 459 / 441 (460 / 470), 4096
-//                    949 / 914 (1011 / 1039)
-//   NY = N / 1024    FP64 2048 888 / 839, 4096 1786 / 1640; FP32 2048 451 /
-//                    472, 4096 1056 / 968; the y lines left are 1024 long
-// One tile a workgroup at N = 4096, NY = 1 takes 2029: rows share a line at
-// their ends, so four tiles of neighbouring rows go together.
+// reals (N = 2048 / 4096, 64 / 32 planes), TB/s, forward / inverse, in brackets
+// passes with whole-value exchanges in contiguous order:
+//   NY = 1 (z pass)  FP64 2048 5.66 / 5.95 (4.65 / 4.93), 4096 5.27 / 5.76
+//                    (4.84 / 4.98); FP32 2048 4.96 / 5.41 (4.67 / 4.57), 4096
+//                    4.80 / 5.13 (4.25 / 4.13)
+//   NY = N / 1024    FP64 2048 5.23 / 5.67, 4096 4.81 / 5.47; FP32 2048 5.07 /
+//                    4.95, 4096 4.51 / 5.03; the y lines left are 1024 long
+// One tile a workgroup at N = 4096, NY = 1 runs at 4.2: rows share a line at
+// their ends, so tiles of neighbouring rows go together.
 template <typename T, int N, int NY>
 struct rows_cfg {
     static constexpr bool F64 = sizeof(T) == 8;
     static constexpr int EF = F64 && (N == 2048 || NY == 4) ? 16 : 32;
     static constexpr int EI = F64 && N == 2048 ? 16 : 32;
-    static constexpr int GF = NY == 4 ? (F64 ? 1 : 2) : NY == 2 ? 4 : F64 ? (N == 4096 ? 2 : 4)
-                                                                  : (N == 4096 ? 4 : 8);
-    static constexpr int GI = NY == 4 ? 1 : NY == 2 ? (F64 ? 2 : 4) : F64 ? 4 : (N == 4096 ? 4 : 8);
+    static constexpr int GF = NY == 4 ? 1 : NY == 2 ? (F64 ? 2 : 4) : N == 4096 ? (F64 ? 2 : 4)
+                                                                    : (F64 ? 4 : 8);
+    static constexpr int GI = NY == 4 ? 1 : NY == 2 ? (F64 ? 2 : 4) : N == 4096 || F64 ? 4 : 8;
     static constexpr int WF = EF == 16 ? 4 : 2, WI = EI == 16 ? 4 : 2;
 };
 
@@ -1050,18 +1055,18 @@ static hipError_t rows_n(bool forward, const void* in, void* out, const void* tw
         cx<T>* po = static_cast<cx<T>*>(out);
         if constexpr (NY == 1) {
             if (map.pencil)
-                return go(k_rows_r2c<T, N, 1, C::EF, C::GF, C::WF, true, true>, C::GF, NT, pi, po);
+                return go(k_rows_r2c<T, N, 1, C::EF, C::GF, C::WF, true>, C::GF, NT, pi, po);
         }
-        return go(k_rows_r2c<T, N, NY, C::EF, C::GF, C::WF, true, false>, C::GF, NT, pi, po);
+        return go(k_rows_r2c<T, N, NY, C::EF, C::GF, C::WF, false>, C::GF, NT, pi, po);
     }
     constexpr int NT = rows_shape<T, N, NY, C::EI, C::GI>::NT;
     const cx<T>* pi = static_cast<const cx<T>*>(in);
     T* po = static_cast<T*>(out);
     if constexpr (NY == 1) {
         if (map.pencil)
-            return go(k_rows_c2r<T, N, 1, C::EI, C::GI, C::WI, true, true, true>, C::GI, NT, pi, po);
+            return go(k_rows_c2r<T, N, 1, C::EI, C::GI, C::WI, true>, C::GI, NT, pi, po);
     }
-    return go(k_rows_c2r<T, N, NY, C::EI, C::GI, C::WI, true, true, false>, C::GI, NT, pi, po);
+    return go(k_rows_c2r<T, N, NY, C::EI, C::GI, C::WI, false>, C::GI, NT, pi, po);
 }
 
 int rows_step(int n) { return n >= 2048 ? n / 1024 : 1; }

@@ -270,7 +270,7 @@ gfft_status run_plane(const gfft_plan* p, bool fwd, const void* in, void* out, d
 // tiles of a plane write rows that other tiles have still to read.
 bool split_pass(const gfft_plan* p) {
     return !p->pencil && p->p == 1 && !(p->flags & GFFT_INPLACE) && mfma_terms(p) == 0 &&
-           gfft::split_supported(f64(p), int(p->n));
+           gfft::split_supported(int(p->n));
 }
 
 gfft_status run_split_rows(const gfft_plan* p, bool fwd, const void* in, void* out, double scale,

@@ -95,13 +95,13 @@ hipError_t launch_plane(bool f64, bool forward, int n, const void* in, void* out
                         hipStream_t s);
 
 // The whole 3D transform of natural-order grids in two passes, with the y
-// transform split between them (split_supported: N = 128 and 256, FP32 also
-// 512).  Forward: launch_split_rows (z R2C and the first y step of every
-// x-plane, out of place: `in` and `out` must differ), then launch_split_x with
-// sign -1 on its output (second y step and x; src and dst may be the same
-// buffer).  Inverse: launch_split_x with sign +1, then launch_split_rows.
+// transform split between them (split_supported: N = 128, 256 and 512).
+// Forward: launch_split_rows (z R2C and the first y step of every x-plane, out
+// of place: `in` and `out` must differ), then launch_split_x with sign -1 on
+// its output (second y step and x; src and dst may be the same buffer).
+// Inverse: launch_split_x with sign +1, then launch_split_rows.
 // Between the two the half spectrum holds no meaningful order.
-bool split_supported(bool f64, int n);
+bool split_supported(int n);
 hipError_t launch_split_rows(bool f64, bool forward, int n, const void* in, void* out,
                              const void* tw, int64_t planes, row_map map, double mul_edge,
                              double mul_int, hipStream_t s);

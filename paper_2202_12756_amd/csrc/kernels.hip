@@ -57,9 +57,10 @@ struct zshape {
 // N = 1024 (4-10% faster with the radix-32 stages) and 64-thread ones
 // otherwise, except at N = 256 and 512: 16 per thread in 256-thread workgroups
 // (the C2R of N = 512 in 128-thread ones), 5-13% faster there.
-// Workgroups are dealt to XCDs in contiguous ranges by the C2R at every N
-// (3-5%) and by the R2C at N = 1024 (2-3%) and at the FP32 N = 256 and
-// 512 shapes.  The C2R also stores its line-aligned real rows
+// Workgroups are dealt to the XCDs in groups of 16: TB/s against contiguous
+// eighths, R2C / C2R, FP64 N = 1024 5.89 / 5.95 (5.56 / 5.63), 512 5.76 / 6.09
+// (5.39 / 5.75), FP32 1024 5.32 / 5.35 (4.96 / 5.07), 512 5.19 / 5.25 (4.93 /
+// 5.08).  The C2R also stores its line-aligned real rows
 // non-temporally (they are not read again soon); the R2C's complex rows are
 // not line-aligned and gain nothing from it.
 template <typename T, bool FWD, int N>
@@ -71,7 +72,6 @@ struct zcfg {
     static constexpr int THREADS =
         F64 ? (FWD ? (N >= 1024 ? 128 : 256) : 64)
             : MID32 ? (FWD || N == 256 ? 256 : 128) : (FWD && N >= 1024 ? 256 : 64);
-    static constexpr bool REMAP = !FWD || N >= 1024 || MID32;
     static constexpr bool NTS = !FWD;
 };
 
@@ -79,7 +79,7 @@ struct zcfg {
 // ALIAS: `in` and `out` are the same buffer (in-place plans).  Each row is
 // read completely before the first barrier and written after the last one,
 // so a row is never overwritten before all of it has been loaded.
-template <typename T, int N, int EMAX, int THREADS, bool REMAP, bool NTS, bool ALIAS,
+template <typename T, int N, int EMAX, int THREADS, bool NTS, bool ALIAS,
           bool PENCIL = false>
 __device__ __forceinline__ void z_r2c_body(
     const T* in, cx<T>* out, const cx<T>* __restrict__ tw,
@@ -93,7 +93,7 @@ __device__ __forceinline__ void z_r2c_body(
 
     const int rl = threadIdx.x / TPT;
     const int t = threadIdx.x % TPT;
-    const int64_t blk = REMAP ? xcd_tile(blockIdx.x, gridDim.x) : int64_t(blockIdx.x);
+    const int64_t blk = xcd_tile<kGrouped>(blockIdx.x, gridDim.x);
     const int64_t row = blk * RPB + rl;
     const bool valid = row < rows;
 
@@ -148,31 +148,31 @@ __device__ __forceinline__ void z_r2c_body(
     if (t == 0) put(M, x_m);
 }
 
-template <typename T, int N, int EMAX, int THREADS, bool REMAP, bool NTS>
+template <typename T, int N, int EMAX, int THREADS, bool NTS>
 __global__ __launch_bounds__((zshape<N / 2, EMAX, THREADS>::NT)) void k_z_r2c(
     const T* __restrict__ in, cx<T>* __restrict__ out, const cx<T>* __restrict__ tw,
     int64_t rows, row_map map, T mul_edge, T mul_int) {
-    z_r2c_body<T, N, EMAX, THREADS, REMAP, NTS, false>(in, out, tw, rows, map, mul_edge, mul_int);
+    z_r2c_body<T, N, EMAX, THREADS, NTS, false>(in, out, tw, rows, map, mul_edge, mul_int);
 }
 
-template <typename T, int N, int EMAX, int THREADS, bool REMAP, bool NTS>
+template <typename T, int N, int EMAX, int THREADS, bool NTS>
 __global__ __launch_bounds__((zshape<N / 2, EMAX, THREADS>::NT)) void k_z_r2c_inplace(
     const T* in, cx<T>* out, const cx<T>* __restrict__ tw,
     int64_t rows, row_map map, T mul_edge, T mul_int) {
-    z_r2c_body<T, N, EMAX, THREADS, REMAP, NTS, true>(in, out, tw, rows, map, mul_edge, mul_int);
+    z_r2c_body<T, N, EMAX, THREADS, NTS, true>(in, out, tw, rows, map, mul_edge, mul_int);
 }
 
 // Pencil plans: bins scattered to the first exchange's chunks.
-template <typename T, int N, int EMAX, int THREADS, bool REMAP>
+template <typename T, int N, int EMAX, int THREADS>
 __global__ __launch_bounds__((zshape<N / 2, EMAX, THREADS>::NT)) void k_z_r2c_pencil(
     const T* __restrict__ in, cx<T>* __restrict__ out, const cx<T>* __restrict__ tw,
     int64_t rows, row_map map, T mul_edge, T mul_int) {
-    z_r2c_body<T, N, EMAX, THREADS, REMAP, false, false, true>(in, out, tw, rows, map, mul_edge,
+    z_r2c_body<T, N, EMAX, THREADS, false, false, true>(in, out, tw, rows, map, mul_edge,
                                                                mul_int);
 }
 
 // ---------------------------------------------------------------- z C2R
-template <typename T, int N, int EMAX, int THREADS, bool REMAP, bool NTS, bool PENCIL = false>
+template <typename T, int N, int EMAX, int THREADS, bool NTS, bool PENCIL = false>
 __device__ __forceinline__ void z_c2r_body(
     const cx<T>* in, T* out, const cx<T>* __restrict__ tw,
     int64_t rows, row_map map, T mul_edge, T mul_int) {
@@ -185,7 +185,7 @@ __device__ __forceinline__ void z_c2r_body(
 
     const int rl = threadIdx.x / TPT;
     const int t = threadIdx.x % TPT;
-    const int64_t blk = REMAP ? xcd_tile(blockIdx.x, gridDim.x) : int64_t(blockIdx.x);
+    const int64_t blk = xcd_tile<kGrouped>(blockIdx.x, gridDim.x);
     const int64_t row = blk * RPB + rl;
     const bool valid = row < rows;
     const idx_rows<PS> ix{rl * MP};
@@ -243,28 +243,28 @@ __device__ __forceinline__ void z_c2r_body(
     }
 }
 
-template <typename T, int N, int EMAX, int THREADS, bool REMAP, bool NTS>
+template <typename T, int N, int EMAX, int THREADS, bool NTS>
 __global__ __launch_bounds__((zshape<N / 2, EMAX, THREADS>::NT)) void k_z_c2r(
     const cx<T>* __restrict__ in, T* __restrict__ out, const cx<T>* __restrict__ tw,
     int64_t rows, row_map map, T mul_edge, T mul_int) {
-    z_c2r_body<T, N, EMAX, THREADS, REMAP, NTS>(in, out, tw, rows, map, mul_edge, mul_int);
+    z_c2r_body<T, N, EMAX, THREADS, NTS>(in, out, tw, rows, map, mul_edge, mul_int);
 }
 
 // In place: every load of a row precedes the barrier after the LDS fill, and
 // every store follows the last barrier of the FFT.
-template <typename T, int N, int EMAX, int THREADS, bool REMAP, bool NTS>
+template <typename T, int N, int EMAX, int THREADS, bool NTS>
 __global__ __launch_bounds__((zshape<N / 2, EMAX, THREADS>::NT)) void k_z_c2r_inplace(
     const cx<T>* in, T* out, const cx<T>* __restrict__ tw,
     int64_t rows, row_map map, T mul_edge, T mul_int) {
-    z_c2r_body<T, N, EMAX, THREADS, REMAP, NTS>(in, out, tw, rows, map, mul_edge, mul_int);
+    z_c2r_body<T, N, EMAX, THREADS, NTS>(in, out, tw, rows, map, mul_edge, mul_int);
 }
 
 // Pencil plans: bins gathered from the first exchange's chunks.
-template <typename T, int N, int EMAX, int THREADS, bool REMAP, bool NTS>
+template <typename T, int N, int EMAX, int THREADS, bool NTS>
 __global__ __launch_bounds__((zshape<N / 2, EMAX, THREADS>::NT)) void k_z_c2r_pencil(
     const cx<T>* __restrict__ in, T* __restrict__ out, const cx<T>* __restrict__ tw,
     int64_t rows, row_map map, T mul_edge, T mul_int) {
-    z_c2r_body<T, N, EMAX, THREADS, REMAP, NTS, true>(in, out, tw, rows, map, mul_edge, mul_int);
+    z_c2r_body<T, N, EMAX, THREADS, NTS, true>(in, out, tw, rows, map, mul_edge, mul_int);
 }
 
 // ---------------------------------------------------------------- y / x C2C
@@ -314,12 +314,12 @@ struct sshape {
 // MF: 0 vector stages; 2 or 3 the first radix-16 stage on the matrix cores;
 // -1 no transform (each element replaced by its conjugate): the same loads
 // and stores as the pass, a yardstick for its memory-access ceiling.
-// RMP: tiles in XCD-contiguous order (false: in launch order).
+// ORD: tile order (xcd_tile).
 // TWS: tw is the table of a transform TWS times as long.
 // src may be data itself (in place) or a distinct buffer of the same layout:
 // every load of a tile precedes its stores, and tiles own their elements.
 template <typename T, int N, int TC, int XP, int S, int E = 16, int MF = 0, bool NT = false,
-          bool RMP = true, int TWS = 1>
+          int ORD = kContig, int TWS = 1>
 __global__ __launch_bounds__(TC * N / E) void k_strided(
     const cx<T>* src, cx<T>* data, const cx<T>* __restrict__ tw, int64_t m_cols,
     int64_t tiles_m, line_map lm) {
@@ -334,7 +334,7 @@ __global__ __launch_bounds__(TC * N / E) void k_strided(
 
     const int c = threadIdx.x % TC;
     const int t = threadIdx.x / TC;
-    const int64_t tile = RMP ? xcd_tile(blockIdx.x, gridDim.x) : int64_t(blockIdx.x);
+    const int64_t tile = xcd_tile<ORD>(blockIdx.x, gridDim.x);
     const int64_t b = tile / tiles_m;
     const int64_t m0 = (tile - b * tiles_m) * TC;
     const int64_t m = m0 + c;
@@ -535,16 +535,16 @@ static hipError_t z_r2c_n(const void* in, void* out, const void* tw, int64_t row
     if (blocks == 0) return hipSuccess;
     if (!grid_fits(blocks, Z::NT)) return hipErrorInvalidValue;
     if (map.pencil)
-        hipLaunchKernelGGL((k_z_r2c_pencil<T, N, C::EMAX, C::THREADS, C::REMAP>), dim3(blocks),
+        hipLaunchKernelGGL((k_z_r2c_pencil<T, N, C::EMAX, C::THREADS>), dim3(blocks),
                            dim3(Z::NT), 0, s, static_cast<const T*>(in), static_cast<cx<T>*>(out),
                            static_cast<const cx<T>*>(tw), rows, map, T(me), T(mi));
     else if (in == out)
-        hipLaunchKernelGGL((k_z_r2c_inplace<T, N, C::EMAX, C::THREADS, C::REMAP, C::NTS>),
+        hipLaunchKernelGGL((k_z_r2c_inplace<T, N, C::EMAX, C::THREADS, C::NTS>),
                            dim3(blocks), dim3(Z::NT), 0, s, static_cast<const T*>(in),
                            static_cast<cx<T>*>(out), static_cast<const cx<T>*>(tw), rows, map,
                            T(me), T(mi));
     else
-        hipLaunchKernelGGL((k_z_r2c<T, N, C::EMAX, C::THREADS, C::REMAP, C::NTS>), dim3(blocks),
+        hipLaunchKernelGGL((k_z_r2c<T, N, C::EMAX, C::THREADS, C::NTS>), dim3(blocks),
                            dim3(Z::NT), 0, s, static_cast<const T*>(in), static_cast<cx<T>*>(out),
                            static_cast<const cx<T>*>(tw), rows, map, T(me), T(mi));
     return hipGetLastError();
@@ -559,17 +559,17 @@ static hipError_t z_c2r_n(const void* in, void* out, const void* tw, int64_t row
     if (blocks == 0) return hipSuccess;
     if (!grid_fits(blocks, Z::NT)) return hipErrorInvalidValue;
     if (map.pencil)
-        hipLaunchKernelGGL((k_z_c2r_pencil<T, N, C::EMAX, C::THREADS, C::REMAP, C::NTS>),
+        hipLaunchKernelGGL((k_z_c2r_pencil<T, N, C::EMAX, C::THREADS, C::NTS>),
                            dim3(blocks), dim3(Z::NT), 0, s, static_cast<const cx<T>*>(in),
                            static_cast<T*>(out), static_cast<const cx<T>*>(tw), rows, map,
                            T(me), T(mi));
     else if (in == out)
-        hipLaunchKernelGGL((k_z_c2r_inplace<T, N, C::EMAX, C::THREADS, C::REMAP, C::NTS>),
+        hipLaunchKernelGGL((k_z_c2r_inplace<T, N, C::EMAX, C::THREADS, C::NTS>),
                            dim3(blocks), dim3(Z::NT), 0, s, static_cast<const cx<T>*>(in),
                            static_cast<T*>(out), static_cast<const cx<T>*>(tw), rows, map,
                            T(me), T(mi));
     else
-        hipLaunchKernelGGL((k_z_c2r<T, N, C::EMAX, C::THREADS, C::REMAP, C::NTS>), dim3(blocks),
+        hipLaunchKernelGGL((k_z_c2r<T, N, C::EMAX, C::THREADS, C::NTS>), dim3(blocks),
                            dim3(Z::NT), 0, s, static_cast<const cx<T>*>(in), static_cast<T*>(out),
                            static_cast<const cx<T>*>(tw), rows, map, T(me), T(mi));
     return hipGetLastError();
@@ -583,7 +583,7 @@ static bool whole_lines(const void* data, int64_t m_cols, const line_map& lm, in
            lm.b_hi % la == 0 && lm.b_lo % la == 0 && lm.s_hi % la == 0 && lm.s_lo % la == 0;
 }
 
-template <typename T, int N, int AX, int MF, bool NT, bool RMP, int TWS = 1>
+template <typename T, int N, int AX, int MF, bool NT, int ORD, int TWS = 1>
 static hipError_t strided_run(int sign, const void* src, void* data, const void* tw, int64_t m_cols,
                               int64_t n_b, line_map lm, hipStream_t s) {
     using SH = sshape<T, N, AX, (MF > 0)>;
@@ -594,58 +594,63 @@ static hipError_t strided_run(int sign, const void* src, void* data, const void*
     if (!grid_fits(blocks, TC * SH::TPT)) return hipErrorInvalidValue;
     const dim3 threads(TC * SH::TPT);
     if (MF < 0 || sign < 0)
-        hipLaunchKernelGGL((k_strided<T, N, TC, SH::XP, -1, SH::E, MF, NT, RMP, TWS>), dim3(blocks),
+        hipLaunchKernelGGL((k_strided<T, N, TC, SH::XP, -1, SH::E, MF, NT, ORD, TWS>), dim3(blocks),
                            threads, 0, s, static_cast<const cx<T>*>(src),
                            static_cast<cx<T>*>(data), static_cast<const cx<T>*>(tw), m_cols, tiles_m, lm);
     else if constexpr (MF >= 0)
-        hipLaunchKernelGGL((k_strided<T, N, TC, SH::XP, +1, SH::E, MF, NT, RMP, TWS>), dim3(blocks),
+        hipLaunchKernelGGL((k_strided<T, N, TC, SH::XP, +1, SH::E, MF, NT, ORD, TWS>), dim3(blocks),
                            threads, 0, s, static_cast<const cx<T>*>(src),
                            static_cast<cx<T>*>(data), static_cast<const cx<T>*>(tw), m_cols, tiles_m, lm);
     return hipGetLastError();
 }
 
-// Tile order and hints of the x passes.  Where every tile owns whole
-// 128-byte lines the lines stream through non-temporally; neighbouring tiles
-// then share nothing, and launch order (the 8 XCDs side by side on one run of
-// columns) beats the XCD-contiguous order except where a line's elements lie
-// megabytes apart.  TB/s on 0.5-1.1 GB of received pencils, launch order /
-// XCD order (both with the hint, the N <= 128 and FP64 256 ones in XCD order
-// without it):
-//   FP64 N = 64 5.85 / 5.42, 128 5.71 / 5.02, 512 4.94 / 4.73 (full grids),
-//        4.80 / 3.90 (p = 8); 1024 4.74 / 4.31 (p = 32), 4.73 / 4.68 (p = 8),
-//        4.69 / 4.94 (p = 4), 4.57 / 5.11 (full grid); 256 4.67 / 4.44 (p = 2)
-//        but 3.73 / 4.31 (full grid, elements 516 KB apart)
-//   FP32 N = 64 6.11 / 5.53, 128 5.54 / 4.94, 256 4.65 / 4.25, 512 5.04 / 4.11,
-//        1024 4.56 / 4.23 (p = 8), 4.59 / 4.45 (p = 4), 4.69 / 4.84 (p = 2);
-//        2048 3.87 / 3.67 (p = 32), 3.84 / 3.88 (p = 4)
-// Hence launch order up to 2 MiB between elements (any distance up to
-// N = 512; FP64 256 up to 512 KB), and not below 4 KB, where few columns
-// remain (FP32 128 at 2 KB 3.39 / 5.19).  The XCD order keeps the hint from
-// N = 512 (FP32 256) up, but FP64 2048 (one 512-thread workgroup per CU) is 5%
-// slower with it.  Where neighbouring tiles share lines, as in the y passes,
-// the hint makes them travel twice (15-50% slower).
+// Tile order and hints of the strided passes.  x passes whose tiles own whole
+// 128-byte lines stream through non-temporally: neighbouring tiles share
+// nothing, and the eight XCDs are kept on one run of columns by dealing small
+// groups of tiles (line_order gives log2 of the group).  TB/s over 0.5-1.1 GB
+// of received pencils, groups / launch order / contiguous eighths:
+//   FP64 N = 64 5.93 / 5.80 / 5.84, 128 5.86 / 5.65 / 5.28, 512 full grid 5.17 /
+//        4.92 / 4.67 and p = 8 4.89 / 4.82 / 4.34, 1024 full grid 5.14 / 4.56 /
+//        5.10, p = 4 5.15 / 4.68 / 4.93, p = 16 5.06 / 4.73 / 4.50
+//   FP32 N = 64 6.00 / 6.00 / 5.61, 128 5.62 / 5.45 / 5.19, 256 4.92 / 4.52 /
+//        4.66 (p = 1) and 5.6 / 5.7 / 5.2 (p = 8), 512 5.02 / 5.01 / 3.92, 1024
+//        full grid 4.87 / 4.57 / 4.81, p = 8 4.96 / 4.59 / 4.22, 2048 p = 32
+//        3.93 / 3.91 / 3.68
+// FP64 256 gains from it up to 512 KB between a line's elements (p = 2 4.67 /
+// 4.44 against a full grid's 3.73 / 4.31, launch order / contiguous without
+// the hint).  Below 4 KB few columns remain (FP32 128 at 2 KB 4.3 / 5.2), and
+// FP64 2048 (one 512-thread workgroup per CU) is 5% slower with the hint:
+// these, lines shared between tiles and the y passes take plain accesses, in
+// contiguous order (FP64 y 1024 4.88 against 4.76 in groups of 16, 512 5.23
+// against 4.65) except FP32 4096, whose 64-byte runs need their neighbours in
+// time (y 3.34 against 2.84, pencil x 3.00 against 2.60 in groups of 16).
+// Where tiles share lines the hint makes them travel twice (15-50% slower).
+template <typename T, int N>
+struct line_order {
+    static constexpr bool F64 = sizeof(T) == 8;
+    static constexpr int NT = N <= 128 ? 2 : N == 512 ? 1 : (!F64 && N == 1024) || (F64 && N == 256) ? 4 : 6;
+    static constexpr int PLAIN = !F64 && N == 4096 ? kGrouped : kContig;
+};
+
 template <typename T, int N, int AX, int MF>
 static hipError_t strided_ax(int sign, const void* src, void* data, const void* tw, int64_t m_cols,
                              int64_t n_b, line_map lm, hipStream_t s) {
     constexpr bool F64 = sizeof(T) == 8;
     constexpr int ES = int(sizeof(cx<T>));
     using SH = sshape<T, N, AX, (MF > 0)>;
+    using O = line_order<T, N>;
     if constexpr (AX == 1 && MF <= 0 && N >= 64 && (!F64 || N <= 1024) && (SH::TC * ES) % 128 == 0) {
         if (whole_lines(src, m_cols, lm, 128 / ES) && whole_lines(data, m_cols, lm, 128 / ES)) {
             // mean distance between neighbouring elements of a line
             constexpr int64_t HALF = N / 2;
             const int64_t step = ((HALF >> lm.lg_y) * lm.s_hi +
                                   (HALF & ((int64_t(1) << lm.lg_y) - 1)) * lm.s_lo) / HALF * ES;
-            constexpr int64_t FAR = F64 && N == 256 ? int64_t(512) << 10
-                                    : N <= 512      ? int64_t(1) << 62
-                                                    : int64_t(2) << 20;
+            constexpr int64_t FAR = F64 && N == 256 ? int64_t(512) << 10 : int64_t(1) << 62;
             if (step >= 4096 && step < FAR)
-                return strided_run<T, N, AX, MF, true, false>(sign, src, data, tw, m_cols, n_b, lm, s);
-            if constexpr (N >= 512 || (!F64 && N == 256))
-                return strided_run<T, N, AX, MF, true, true>(sign, src, data, tw, m_cols, n_b, lm, s);
+                return strided_run<T, N, AX, MF, true, O::NT>(sign, src, data, tw, m_cols, n_b, lm, s);
         }
     }
-    return strided_run<T, N, AX, MF, false, true>(sign, src, data, tw, m_cols, n_b, lm, s);
+    return strided_run<T, N, AX, MF, false, O::PLAIN>(sign, src, data, tw, m_cols, n_b, lm, s);
 }
 
 template <typename T, int N>
@@ -713,9 +718,11 @@ template <typename T>
 static hipError_t strided_1024(int n, int sign, const void* src, void* data, const void* tw,
                                int64_t m_cols, int64_t n_b, line_map lm, hipStream_t s) {
     if (n == 2048)
-        return strided_run<T, 1024, 0, 0, false, true, 2>(sign, src, data, tw, m_cols, n_b, lm, s);
+        return strided_run<T, 1024, 0, 0, false, kContig, 2>(sign, src, data, tw, m_cols, n_b, lm, s);
+    // FP32 4.71 TB/s in groups of 16, 4.39 contiguous; FP64 4.58, 4.68
+    constexpr int ORD = sizeof(T) == 4 ? kGrouped : kContig;
     if (n == 4096)
-        return strided_run<T, 1024, 0, 0, false, true, 4>(sign, src, data, tw, m_cols, n_b, lm, s);
+        return strided_run<T, 1024, 0, 0, false, ORD, 4>(sign, src, data, tw, m_cols, n_b, lm, s);
     return hipErrorInvalidValue;
 }
 

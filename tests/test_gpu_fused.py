@@ -55,7 +55,7 @@ def _offset(shape, dtype, nbytes=16):
 
 @pytest.mark.parametrize("aligned", [True, False], ids=["line", "off_line"])
 @pytest.mark.parametrize("n,batch,dtype", [(128, 3, F64), (128, 2, F32), (256, 1, F64),
-                                           (256, 2, F32), (512, 1, F32)])
+                                           (256, 2, F32), (512, 1, F64), (512, 1, F32)])
 def test_split_y_full_grid(n, batch, dtype, aligned):
     """Full grids through the two-pass kernels against the separate z, y and
     x passes, with the adjoints' weights, on buffers on and off the 128-byte
