@@ -130,14 +130,14 @@ struct plane_shape {
     static_assert(M % E == 0 && NY % EY == 0 && NY * TZ == H * TY, "plane shape");
 };
 
-template <typename T, int N, int R, int E, int W>
+template <typename T, int N, int R, int E, int W, int ORD = kGrouped>
 __global__ __launch_bounds__((plane_shape<T, N, R, E>::NT), W) void k_plane_r2c(
     const T* in, cx<T>* out, const cx<T>* __restrict__ tw, row_map map, T mul_edge, T mul_int) {
     using P = plane_shape<T, N, R, E>;
     constexpr int M = P::M, K = P::K, H = P::H, NY = P::NY, TZ = P::TZ, TY = P::TY, EY = P::EY,
                   RM = P::RM;
     __shared__ T lds[P::LDS];
-    const int64_t tile = xcd_tile<kGrouped>(blockIdx.x, gridDim.x);
+    const int64_t tile = xcd_tile<ORD>(blockIdx.x, gridDim.x);
     const int64_t plane = tile / R;
     const int y0 = int(tile % R);
     const int tid = threadIdx.x;
@@ -220,14 +220,14 @@ __global__ __launch_bounds__((plane_shape<T, N, R, E>::NT), W) void k_plane_r2c(
     }
 }
 
-template <typename T, int N, int R, int E, int W>
+template <typename T, int N, int R, int E, int W, int ORD = kGrouped>
 __global__ __launch_bounds__((plane_shape<T, N, R, E>::NT), W) void k_plane_c2r(
     const cx<T>* in, T* out, const cx<T>* __restrict__ tw, row_map map, T mul_edge, T mul_int) {
     using P = plane_shape<T, N, R, E>;
     constexpr int M = P::M, K = P::K, H = P::H, NY = P::NY, TZ = P::TZ, TY = P::TY, EY = P::EY,
                   RM = P::RM;
     __shared__ T lds[P::LDS];
-    const int64_t tile = xcd_tile<kGrouped>(blockIdx.x, gridDim.x);
+    const int64_t tile = xcd_tile<ORD>(blockIdx.x, gridDim.x);
     const int64_t plane = tile / R;
     const int y0 = int(tile % R);
     const int tid = threadIdx.x;
@@ -922,6 +922,9 @@ struct split_cfg {
     static constexpr int WX = R * EX * int(sizeof(cx<T>)) > 256 ? 2 : 4;
     static constexpr bool NT = N == 128;
     static constexpr int ORD = N == 128 ? 0 : 6;
+    // row tiles: groups of 16 (FP64 512 pair 2097 us, contiguous 2138), but
+    // FP64 256 contiguous (three pairs 644 us, groups 665)
+    static constexpr int ROWS_ORD = F64 && N == 256 ? kContig : kGrouped;
 };
 
 template <typename T, int N>
@@ -933,11 +936,11 @@ static hipError_t split_rows_n(bool forward, const void* in, void* out, const vo
     if (blocks == 0) return hipSuccess;
     if (!grid_fits(blocks, NT)) return hipErrorInvalidValue;
     if (forward)
-        hipLaunchKernelGGL((k_plane_r2c<T, N, C::R, C::E, C::W>), dim3(blocks), dim3(NT), 0, s,
+        hipLaunchKernelGGL((k_plane_r2c<T, N, C::R, C::E, C::W, C::ROWS_ORD>), dim3(blocks), dim3(NT), 0, s,
                            static_cast<const T*>(in), static_cast<cx<T>*>(out),
                            static_cast<const cx<T>*>(tw), map, T(me), T(mi));
     else
-        hipLaunchKernelGGL((k_plane_c2r<T, N, C::R, C::E, C::W>), dim3(blocks), dim3(NT), 0, s,
+        hipLaunchKernelGGL((k_plane_c2r<T, N, C::R, C::E, C::W, C::ROWS_ORD>), dim3(blocks), dim3(NT), 0, s,
                            static_cast<const cx<T>*>(in), static_cast<T*>(out),
                            static_cast<const cx<T>*>(tw), map, T(me), T(mi));
     return hipGetLastError();

@@ -177,3 +177,18 @@ def test_long_rows_step1(n, x, batch, order, dtype):
         assert torch.equal(p.inverse_keep(g, scale=0.5), f)
     assert off(F, sep) <= tol and off(W, sepw) <= tol
     assert off(f, want) <= tol and off(w, wantw) <= tol
+
+
+@pytest.mark.parametrize("n,x,batch,dtype", [
+    (16, 1, 3, F32), (16, 2, 3, F32), (64, 4, 5, F32), (64, 4, 5, F64), (512, 1, 1, F32),
+    (512, 1, 1, F64), (256, 4, 1, F64), (1024, 2, 1, F32)])
+def test_pack_run_lengths(n, x, batch, dtype):
+    """The slab pack is the oracle's permutation, bit for bit, for runs of
+    one to many rounds of a workgroup, whole, paired and odd."""
+    p = Plan(n, dtype, slab_x=x, batch=batch)
+    s, ref = cplx_input((batch, x, n, n // 2 + 1), 27000 + n + x, dtype)
+    send = p.pack(s)
+    back = p.unpack(send)
+    torch.cuda.synchronize()
+    assert (host(send) == oracle.pack_slab(ref, n // x)).all()
+    assert torch.equal(back, s)
