@@ -107,6 +107,9 @@ __device__ __forceinline__ void fft_multi(cx<T> (&a)[R][E], int t, int c, const 
 // sequences in j).  Every load of a tile precedes the first barrier and
 // every store follows the last, so with R = 1 a plane may be transformed in
 // place.
+// TWD: the tile applies the twiddles W_N^(y0 k1) itself, which leaves an
+// ordinary R-point y pass (rows follow `map`, NY of them contiguous), as in
+// k_rows_*.
 template <typename T, int N, int R, int E>
 struct plane_shape {
     static constexpr int M = N / 2, K = M + 1, NY = N / R, H = M / 2;
@@ -130,7 +133,7 @@ struct plane_shape {
     static_assert(M % E == 0 && NY % EY == 0 && NY * TZ == H * TY, "plane shape");
 };
 
-template <typename T, int N, int R, int E, int W, int ORD = kGrouped>
+template <typename T, int N, int R, int E, int W, int ORD = kGrouped, bool TWD = false>
 __global__ __launch_bounds__((plane_shape<T, N, R, E>::NT), W) void k_plane_r2c(
     const T* in, cx<T>* out, const cx<T>* __restrict__ tw, row_map map, T mul_edge, T mul_int) {
     using P = plane_shape<T, N, R, E>;
@@ -142,7 +145,7 @@ __global__ __launch_bounds__((plane_shape<T, N, R, E>::NT), W) void k_plane_r2c(
     const int y0 = int(tile % R);
     const int tid = threadIdx.x;
     const int r = tid / TZ, t = tid % TZ;          // z phase
-    const int p = tid % H, s = tid / H;            // y phase
+    const int p = tid % H, s = TY == 1 ? 0 : tid / H;  // y phase
     const int c1 = p == 0 ? H : M - p;             // columns p and c1
 
     // z phase: row y0 + R r of the plane, read as M complex values
@@ -203,8 +206,19 @@ __global__ __launch_bounds__((plane_shape<T, N, R, E>::NT), W) void k_plane_r2c(
     // store rows of the half spectrum: wave lanes are consecutive columns
     auto row_of = [&](int k1) {
         const int64_t row = plane * N + y0 * NY + k1;
-        return out + (R > 1 ? row : map_row(row, map)) * K;
+        return out + (R > 1 && !TWD ? row : map_row(row, map)) * K;
     };
+    // twiddles first: a load behind the stores would wait for them
+    cx<T> wt{T(1), T(0)};
+    if constexpr (TWD) {
+        if (tid < NY) wt = tw[y0 * tid];
+#pragma unroll
+        for (int m = 0; m < EY; ++m) {
+            const cx<T> wm = tw[y0 * (s + TY * m)];
+            b[0][m] = cmul(b[0][m], wm);
+            b[1][m] = cmul(b[1][m], wm);
+        }
+    }
 #pragma unroll
     for (int m = 0; m < EY; ++m) {
         cx<T>* dst = row_of(s + TY * m);
@@ -214,13 +228,18 @@ __global__ __launch_bounds__((plane_shape<T, N, R, E>::NT), W) void k_plane_r2c(
     if (tid < NY) {
         const cx<T> v = col0[tid], pc = conjg(col0[(NY - tid) & (NY - 1)]);
         const cx<T> sum = v + pc, dif = v - pc;
+        cx<T> x0{T(0.5) * sum.x, T(0.5) * sum.y}, xm{T(0.5) * dif.y, T(-0.5) * dif.x};
+        if constexpr (TWD) {
+            x0 = cmul(x0, wt);
+            xm = cmul(xm, wt);
+        }
         cx<T>* dst = row_of(tid);
-        dst[0] = cx<T>{T(0.5) * sum.x, T(0.5) * sum.y};   // X[k1][0]
-        dst[M] = cx<T>{T(0.5) * dif.y, T(-0.5) * dif.x};  // X[k1][M] = dif / 2i
+        dst[0] = x0;  // X[k1][0]
+        dst[M] = xm;  // X[k1][M] = dif / 2i
     }
 }
 
-template <typename T, int N, int R, int E, int W, int ORD = kGrouped>
+template <typename T, int N, int R, int E, int W, int ORD = kGrouped, bool TWD = false>
 __global__ __launch_bounds__((plane_shape<T, N, R, E>::NT), W) void k_plane_c2r(
     const cx<T>* in, T* out, const cx<T>* __restrict__ tw, row_map map, T mul_edge, T mul_int) {
     using P = plane_shape<T, N, R, E>;
@@ -232,7 +251,7 @@ __global__ __launch_bounds__((plane_shape<T, N, R, E>::NT), W) void k_plane_c2r(
     const int y0 = int(tile % R);
     const int tid = threadIdx.x;
     const int r = tid / TZ, t = tid % TZ;
-    const int p = tid % H, s = tid / H;
+    const int p = tid % H, s = TY == 1 ? 0 : tid / H;
     const int c1 = p == 0 ? H : M - p;
 
     // y phase input: columns p and c1 of the half spectrum; column 0 is
@@ -240,8 +259,9 @@ __global__ __launch_bounds__((plane_shape<T, N, R, E>::NT), W) void k_plane_c2r(
     // (imaginary), formed through LDS by one thread per row
     auto row_of = [&](int k1) {
         const int64_t row = plane * N + y0 * NY + k1;
-        return in + (R > 1 ? row : map_row(row, map)) * K;
+        return in + (R > 1 && !TWD ? row : map_row(row, map)) * K;
     };
+    auto turn = [&](cx<T> v, int k1) { return TWD ? cmulc(v, tw[y0 * k1]) : v; };
     cx<T> b[2][EY];
     cx<T>* col0 = reinterpret_cast<cx<T>*>(lds);
 #pragma unroll
@@ -250,10 +270,17 @@ __global__ __launch_bounds__((plane_shape<T, N, R, E>::NT), W) void k_plane_c2r(
         b[0][m] = g[p];
         b[1][m] = g[c1];
     }
+    if constexpr (TWD) {
+#pragma unroll
+        for (int m = 0; m < EY; ++m) {
+            b[0][m] = turn(b[0][m], s + TY * m);
+            b[1][m] = turn(b[1][m], s + TY * m);
+        }
+    }
     if (tid < NY) {
         const cx<T>* g = row_of(tid);
-        col0[tid] = g[0];
-        col0[NY + tid] = g[M];
+        col0[tid] = turn(g[0], tid);
+        col0[NY + tid] = turn(g[M], tid);
     }
     __syncthreads();
     if (tid < NY) {
@@ -315,7 +342,7 @@ __global__ __launch_bounds__((plane_shape<T, N, R, E>::NT), W) void k_plane_c2r(
 }
 
 // ---------------------------------------------------------------- long rows: z with a short y step
-// z R2C of rows too long for a plane to fit on a CU, NY rows at a time:
+// z R2C of long rows, NY rows at a time:
 // with N = NY R, y = y0 + R j, ky = k1 + NY k0, a tile takes the NY rows of
 // one y0 through z and the NY-point DFT over j, applies W_N^(y0 k1) and
 // writes bin k1 to row y0 NY + k1; what is left of the y transform is an
@@ -393,9 +420,15 @@ __global__ __launch_bounds__((rows_shape<T, N, NY, E, G>::NT), W) void k_rows_r2
     }
     if (!valid) return;
 
-    cx<T> wy[NY];
+    // all twiddles before the first store: a load behind it would wait for it
+    // (FP64 with a y step has few columns and no registers to spare: 3.60 ms
+    // without, 3.73 with at N = 4096)
+    constexpr bool WQ = sizeof(T) == 4 || NY == 1;
+    cx<T> wy[NY], wq[Q];
 #pragma unroll
     for (int k1 = 1; k1 < NY; ++k1) wy[k1] = tw[y0 * k1];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) wq[q] = WQ ? tw[lt + NT1 * q] : cx<T>{};
     auto row_of = [&](int k1) {
         return out + map_row(NY > 1 ? plane * N + y0 * NY + k1 : tl, map) * K;
     };
@@ -406,7 +439,7 @@ __global__ __launch_bounds__((rows_shape<T, N, NY, E, G>::NT), W) void k_rows_r2
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
         const int p = lt + NT1 * q, c1 = p == 0 ? H : M - p;
-        const cx<T> w = tw[p];
+        const cx<T> w = WQ ? wq[q] : tw[p];
         const bool edge = p == 0;
         cx<T> u[NY], v[NY];
 #pragma unroll
@@ -1017,15 +1050,38 @@ hipError_t launch_split_x(bool f64, int n, int sign, const void* src, void* dst,
                     : split_x_sign<+1>(f64, n, src, dst, tw, batch, s);
 }
 
-// Long rows: elements per thread and tiles per workgroup, forward (F) and
-// inverse (I).  Measured over 2.1 / 4.3 GB of FP64 and half as much FP32
-// reals (N = 2048 / 4096, 64 / 32 planes), TB/s, forward / inverse, in brackets
-// passes with whole-value exchanges in contiguous order:
-//   NY = 1 (z pass)  FP64 2048 5.66 / 5.95 (4.65 / 4.93), 4096 5.27 / 5.76
-//                    (4.84 / 4.98); FP32 2048 4.96 / 5.41 (4.67 / 4.57), 4096
-//                    4.80 / 5.13 (4.25 / 4.13)
-//   NY = N / 1024    FP64 2048 5.23 / 5.67, 4096 4.81 / 5.47; FP32 2048 5.07 /
-//                    4.95, 4096 4.51 / 5.03; the y lines left are 1024 long
+// First y step of the z pass (rows_step): NY rows a tile, leaving y lines of
+// L = N / NY for launch_strided_lines.  TB/s of the z passes with the step,
+// forward / inverse, and of the lines; in brackets the plain z and y passes:
+//   FP64 N = 1024, NY = 8   5.53 / 5.58 and 5.49 (5.70 / 5.80 and 4.86)
+//        2048, 4            5.19 / 5.53 and 5.1  (5.66 / 5.95 and 4.24)
+//        4096, 4            4.81 / 5.47 and 4.69 (5.27 / 5.76 and 3.52)
+//   FP32 N = 512, NY = 16   5.61 / 5.37 and 5.78 (4.93 / 5.08 and 4.77)
+//        1024, 16           5.55 / 5.60 and 5.55 (4.65 / 5.0 and 4.55)
+//        2048, 8            4.78 / 5.04 and 5.27 (4.96 / 5.41 and 3.76)
+//        4096, 4            4.51 / 5.03 and 4.71 (4.80 / 5.13 and 2.84)
+// Shorter lines run faster, longer first steps slower (FP32 1024 with 32 rows
+// 4.9, 4096 with 8 3.1 / 4.5; FP64 1024 with 16 5.2): NY is where the two
+// together are fastest.  FP64 512 gains nothing (16 rows 5.42 / 5.48 and 5.70
+// against 5.76 / 6.09 and 5.23).  k_plane_* takes the step up to N = 1024
+// (k_rows_r2c 4.7 there: its packed column needs every row in one thread),
+// k_rows_* longer rows.
+int rows_step(bool f64, int n) {
+    switch (n) {
+        case 512: return f64 ? 1 : 16;
+        case 1024: return f64 ? 8 : 16;
+        case 2048: return f64 ? 4 : 8;
+        case 4096: return 4;
+        default: return 1;
+    }
+}
+
+// Elements per thread and tiles per workgroup of k_rows_*, forward (F) and
+// inverse (I).  TB/s over 2.1 / 4.3 GB of FP64 and half as much FP32 reals
+// (N = 2048 / 4096, 64 / 32 planes) at NY = 1, the plain z passes, forward /
+// inverse, in brackets passes with whole-value exchanges in contiguous order:
+//   FP64 2048 5.66 / 5.95 (4.65 / 4.93), 4096 5.27 / 5.76 (4.84 / 4.98)
+//   FP32 2048 4.96 / 5.41 (4.67 / 4.57), 4096 4.80 / 5.13 (4.25 / 4.13)
 // One tile a workgroup at N = 4096, NY = 1 runs at 4.2: rows share a line at
 // their ends, so tiles of neighbouring rows go together.
 template <typename T, int N, int NY>
@@ -1033,66 +1089,82 @@ struct rows_cfg {
     static constexpr bool F64 = sizeof(T) == 8;
     static constexpr int EF = F64 && (N == 2048 || NY == 4) ? 16 : 32;
     static constexpr int EI = F64 && N == 2048 ? 16 : 32;
-    static constexpr int GF = NY == 4 ? 1 : NY == 2 ? (F64 ? 2 : 4) : N == 4096 ? (F64 ? 2 : 4)
-                                                                    : (F64 ? 4 : 8);
-    static constexpr int GI = NY == 4 ? 1 : NY == 2 ? (F64 ? 2 : 4) : N == 4096 || F64 ? 4 : 8;
+    static constexpr int GF = NY > 1 ? 1 : N == 4096 ? (F64 ? 2 : 4) : (F64 ? 4 : 8);
+    static constexpr int GI = NY > 1 ? 1 : N == 4096 || F64 ? 4 : 8;
     static constexpr int WF = EF == 16 ? 4 : 2, WI = EI == 16 ? 4 : 2;
 };
 
 template <typename T, int N, int NY>
 static hipError_t rows_n(bool forward, const void* in, void* out, const void* tw, int64_t rows,
                          row_map map, double me, double mi, hipStream_t s) {
-    using C = rows_cfg<T, N, NY>;
     const int64_t tiles = rows / NY;
     if (tiles == 0) return hipSuccess;
-    auto go = [&](auto kernel, int64_t g, int nt, auto pin, auto pout) {
-        const int64_t blocks = (tiles + g - 1) / g;
-        if (!grid_fits(blocks, nt)) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(kernel, dim3(blocks), dim3(nt), 0, s, pin, pout,
-                           static_cast<const cx<T>*>(tw), tiles, map, T(me), T(mi));
+    const cx<T>* t = static_cast<const cx<T>*>(tw);
+    if constexpr (N <= 1024) {
+        // k_plane_*: 2 NY elements per thread, two NY-point columns of it
+        constexpr int E = 2 * NY, R = N / NY, W = 2;
+        constexpr int NT = plane_shape<T, N, R, E>::NT;
+        if (!grid_fits(tiles, NT)) return hipErrorInvalidValue;
+        if (forward)
+            hipLaunchKernelGGL((k_plane_r2c<T, N, R, E, W, kGrouped, true>), dim3(tiles), dim3(NT),
+                               0, s, static_cast<const T*>(in), static_cast<cx<T>*>(out), t, map,
+                               T(me), T(mi));
+        else
+            hipLaunchKernelGGL((k_plane_c2r<T, N, R, E, W, kGrouped, true>), dim3(tiles), dim3(NT),
+                               0, s, static_cast<const cx<T>*>(in), static_cast<T*>(out), t, map,
+                               T(me), T(mi));
         return hipGetLastError();
-    };
-    if (forward) {
-        constexpr int NT = rows_shape<T, N, NY, C::EF, C::GF>::NT;
-        const T* pi = static_cast<const T*>(in);
-        cx<T>* po = static_cast<cx<T>*>(out);
+    } else {
+        using C = rows_cfg<T, N, NY>;
+        auto go = [&](auto kernel, int64_t g, int nt, auto pin, auto pout) {
+            const int64_t blocks = (tiles + g - 1) / g;
+            if (!grid_fits(blocks, nt)) return hipErrorInvalidValue;
+            hipLaunchKernelGGL(kernel, dim3(blocks), dim3(nt), 0, s, pin, pout, t, tiles, map, T(me),
+                               T(mi));
+            return hipGetLastError();
+        };
+        if (forward) {
+            constexpr int NT = rows_shape<T, N, NY, C::EF, C::GF>::NT;
+            const T* pi = static_cast<const T*>(in);
+            cx<T>* po = static_cast<cx<T>*>(out);
+            if constexpr (NY == 1) {
+                if (map.pencil)
+                    return go(k_rows_r2c<T, N, 1, C::EF, C::GF, C::WF, true>, C::GF, NT, pi, po);
+            }
+            return go(k_rows_r2c<T, N, NY, C::EF, C::GF, C::WF, false>, C::GF, NT, pi, po);
+        }
+        constexpr int NT = rows_shape<T, N, NY, C::EI, C::GI>::NT;
+        const cx<T>* pi = static_cast<const cx<T>*>(in);
+        T* po = static_cast<T*>(out);
         if constexpr (NY == 1) {
             if (map.pencil)
-                return go(k_rows_r2c<T, N, 1, C::EF, C::GF, C::WF, true>, C::GF, NT, pi, po);
+                return go(k_rows_c2r<T, N, 1, C::EI, C::GI, C::WI, true>, C::GI, NT, pi, po);
         }
-        return go(k_rows_r2c<T, N, NY, C::EF, C::GF, C::WF, false>, C::GF, NT, pi, po);
+        return go(k_rows_c2r<T, N, NY, C::EI, C::GI, C::WI, false>, C::GI, NT, pi, po);
     }
-    constexpr int NT = rows_shape<T, N, NY, C::EI, C::GI>::NT;
-    const cx<T>* pi = static_cast<const cx<T>*>(in);
-    T* po = static_cast<T*>(out);
-    if constexpr (NY == 1) {
-        if (map.pencil)
-            return go(k_rows_c2r<T, N, 1, C::EI, C::GI, C::WI, true>, C::GI, NT, pi, po);
-    }
-    return go(k_rows_c2r<T, N, NY, C::EI, C::GI, C::WI, false>, C::GI, NT, pi, po);
-}
-
-int rows_step(int n) { return n >= 2048 ? n / 1024 : 1; }
-
-template <typename T>
-static hipError_t rows_t(bool forward, int n, int ny, const void* in, void* out, const void* tw,
-                         int64_t rows, row_map map, double me, double mi, hipStream_t s) {
-    if (n == 2048 && ny == 1)
-        return rows_n<T, 2048, 1>(forward, in, out, tw, rows, map, me, mi, s);
-    if (n == 2048 && ny == 2)
-        return rows_n<T, 2048, 2>(forward, in, out, tw, rows, map, me, mi, s);
-    if (n == 4096 && ny == 1)
-        return rows_n<T, 4096, 1>(forward, in, out, tw, rows, map, me, mi, s);
-    if (n == 4096 && ny == 4)
-        return rows_n<T, 4096, 4>(forward, in, out, tw, rows, map, me, mi, s);
-    return hipErrorInvalidValue;
 }
 
 hipError_t launch_rows(bool f64, bool forward, int n, int ny, const void* in, void* out,
                        const void* tw, int64_t rows, row_map map, double me, double mi,
                        hipStream_t s) {
-    return f64 ? rows_t<double>(forward, n, ny, in, out, tw, rows, map, me, mi, s)
-               : rows_t<float>(forward, n, ny, in, out, tw, rows, map, me, mi, s);
+#define GFFT_ROWS(T, N, NY) \
+    if (n == N && ny == NY) return rows_n<T, N, NY>(forward, in, out, tw, rows, map, me, mi, s);
+    if (f64) {
+        GFFT_ROWS(double, 1024, 8)
+        GFFT_ROWS(double, 2048, 1)
+        GFFT_ROWS(double, 2048, 4)
+        GFFT_ROWS(double, 4096, 1)
+        GFFT_ROWS(double, 4096, 4)
+    } else {
+        GFFT_ROWS(float, 512, 16)
+        GFFT_ROWS(float, 1024, 16)
+        GFFT_ROWS(float, 2048, 1)
+        GFFT_ROWS(float, 2048, 8)
+        GFFT_ROWS(float, 4096, 1)
+        GFFT_ROWS(float, 4096, 4)
+    }
+#undef GFFT_ROWS
+    return hipErrorInvalidValue;
 }
 
 template <typename T, int N>

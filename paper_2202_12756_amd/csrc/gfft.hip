@@ -285,12 +285,13 @@ gfft_status run_split_x(const gfft_plan* p, int sign, const void* src, void* dat
 }
 
 // Step 1 of long rows with the first step of y in the z pass, so that the
-// strided y pass runs on 1024-point lines, whose tiles leave a CU room for
-// others (a 4096-point FP64 tile of 4 columns fills one).  Needs the step's
-// rows contiguous: not in the paper's chunk order, nor with fewer rows of a
-// plane per chunk.  Not in place: a tile writes rows others have still to read.
+// strided y pass runs on shorter lines, whose tiles are wider and leave a CU
+// room for others (a 4096-point FP64 tile of 4 columns fills one).  Needs the
+// step's rows contiguous: not in the paper's chunk order, nor with fewer rows
+// of a plane per chunk.  Not in place: a tile writes rows others have still to
+// read.
 int y_step(const gfft_plan* p) {
-    const int ny = gfft::rows_step(int(p->n));
+    const int ny = gfft::rows_step(f64(p), int(p->n));
     if (ny == 1 || p->pencil || mfma_terms(p) != 0 || (p->flags & GFFT_INPLACE)) return 1;
     if ((p->flags & GFFT_FUSE_PACK) && (paper(p) || p->y < ny)) return 1;
     return ny;
@@ -303,13 +304,13 @@ gfft_status run_rows(const gfft_plan* p, bool fwd, const void* in, void* out, do
                                         p->batch * p->zrows, zmap(p), me, mi, s));
 }
 
-gfft_status run_y_1024(const gfft_plan* p, const void* src, void* data, int sign, hipStream_t s) {
+gfft_status run_y_lines(const gfft_plan* p, const void* src, void* data, int sign, hipStream_t s) {
     const int ny = y_step(p);
     gfft::line_map lm = ymap(p);
     lm.s_lo *= ny;
     lm.lg_y -= ilog2(ny);
-    return hip_status(gfft::launch_strided_1024(f64(p), int(p->n), sign, src, data, p->tw,
-                                                ny * p->k, p->batch * p->x, lm, s));
+    return hip_status(gfft::launch_strided_lines(f64(p), int(p->n), ny, sign, src, data,
+                                                 p->tw, ny * p->k, p->batch * p->x, lm, s));
 }
 
 // One pass for the whole transform of small full grids.
@@ -342,7 +343,7 @@ gfft_status forward(const gfft_plan* p, const void* in, void* out, double scale,
         if ((st = run_plane(p, true, in, out, scale, weighted, s)) != GFFT_OK) return st;
     } else if (y_step(p) > 1) {
         if ((st = run_rows(p, true, in, out, scale, weighted, s)) != GFFT_OK) return st;
-        if ((st = run_y_1024(p, out, out, -1, s)) != GFFT_OK) return st;
+        if ((st = run_y_lines(p, out, out, -1, s)) != GFFT_OK) return st;
     } else {
         if ((st = run_z_r2c(p, in, out, scale, weighted, s)) != GFFT_OK) return st;
         if ((st = run_y(p, out, out, -1, s)) != GFFT_OK) return st;
@@ -368,7 +369,7 @@ gfft_status run_inverse(const gfft_plan* p, const void* in, void* work, void* ou
     }
     if (plane_pass(p)) return run_plane(p, false, in, out, scale, weighted, s);
     if (y_step(p) > 1) {
-        if ((st = run_y_1024(p, in, work, +1, s)) != GFFT_OK) return st;
+        if ((st = run_y_lines(p, in, work, +1, s)) != GFFT_OK) return st;
         return run_rows(p, false, work, out, scale, weighted, s);
     }
     if ((st = run_y(p, in, work, +1, s)) != GFFT_OK) return st;

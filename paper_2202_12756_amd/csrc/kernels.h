@@ -55,21 +55,22 @@ hipError_t launch_z_c2r(bool f64, int n, const void* in, void* out, const void* 
 hipError_t launch_strided(bool f64, int n, int axis, int mfma_terms, int sign, const void* src,
                           void* data, const void* tw, int64_t m_cols, int64_t n_b, line_map lm,
                           hipStream_t s);
-// Rows of N = 2048 or 4096 in `rows` z rows (a multiple of N for ny > 1).
-// ny = 1: the z pass, also in place and for pencils (launch_z_* use it).
-// ny = rows_step(n) = N / 1024: z R2C of the rows y0 + (N/ny) j of a plane,
-// the ny-point y step over j and its twiddles, bin k1 to row y0 ny + k1
-// (forward; out of place), or the reverse; launch_strided_1024 is the rest of
-// the y transform: 1024-point lines over y0 (rows y0 ny + k1), in place or
-// from src.  Rows of the half spectrum follow `map`, ny consecutive ones
-// contiguous.
-int rows_step(int n);
+// z passes with a first y step over `rows` z rows (a multiple of N for
+// ny > 1).  ny = rows_step(): z R2C of the rows y0 + (N/ny) j of a plane, the
+// ny-point y step over j and its twiddles, bin k1 to row y0 ny + k1 (forward;
+// out of place), or the reverse; launch_strided_lines is the rest of the y
+// transform: lines of N/ny points over y0 (rows y0 ny + k1), in place or from
+// src.  Rows of the half spectrum follow `map`, ny consecutive ones contiguous.
+// rows_step is 1 where plain z and y passes are faster.
+// ny = 1, N = 2048 and 4096 only: the plain z pass, also in place and for
+// pencils (launch_z_* use it).
+int rows_step(bool f64, int n);
 hipError_t launch_rows(bool f64, bool forward, int n, int ny, const void* in, void* out,
                        const void* tw, int64_t rows, row_map map, double mul_edge, double mul_int,
                        hipStream_t s);
-hipError_t launch_strided_1024(bool f64, int n, int sign, const void* src, void* data,
-                               const void* tw, int64_t m_cols, int64_t n_b, line_map lm,
-                               hipStream_t s);
+hipError_t launch_strided_lines(bool f64, int n, int ny, int sign, const void* src, void* data,
+                                const void* tw, int64_t m_cols, int64_t n_b, line_map lm,
+                                hipStream_t s);
 
 // Copy `chunks` runs of `len` complex values: run c = (bb, j, xl) goes from
 // natural offset bb*X*N*K + (xl*N + j*Y)*K to send offset

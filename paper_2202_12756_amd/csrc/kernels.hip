@@ -738,23 +738,29 @@ hipError_t launch_strided(bool f64, int n, int axis, int mfma_terms, int sign, c
     GFFT_DISPATCH_N(strided_n, float, axis, mfma_terms, sign, src, data, tw, m_cols, n_b, lm, s)
 }
 
-template <typename T>
-static hipError_t strided_1024(int n, int sign, const void* src, void* data, const void* tw,
-                               int64_t m_cols, int64_t n_b, line_map lm, hipStream_t s) {
-    if (n == 2048)
-        return strided_run<T, 1024, 0, 0, false, kContig, 2>(sign, src, data, tw, m_cols, n_b, lm, s);
-    // FP32 4.71 TB/s in groups of 16, 4.39 contiguous; FP64 4.58, 4.68
-    constexpr int ORD = sizeof(T) == 4 ? kGrouped : kContig;
-    if (n == 4096)
-        return strided_run<T, 1024, 0, 0, false, ORD, 4>(sign, src, data, tw, m_cols, n_b, lm, s);
+// The y lines a z pass with a first y step leaves (rows_step), in the y tile
+// shape of their length and, in TB/s, the faster of the two orders: FP64 128
+// of 1024 5.49 grouped, 5.41 contiguous, 1024 of 4096 4.58, 4.68; FP32 32 of
+// 512 5.58, 5.78, 64 of 1024 5.55, 5.25, 256 of 2048 5.27, 4.89, 1024 of 4096
+// 4.71, 4.39.
+hipError_t launch_strided_lines(bool f64, int n, int ny, int sign, const void* src, void* data,
+                                const void* tw, int64_t m_cols, int64_t n_b, line_map lm,
+                                hipStream_t s) {
+#define GFFT_LINES(T, N, NY, ORD)                                                               \
+    if (n == N && ny == NY)                                                                     \
+        return strided_run<T, N / NY, 0, 0, false, ORD, NY>(sign, src, data, tw, m_cols, n_b, lm, s);
+    if (f64) {
+        GFFT_LINES(double, 1024, 8, kGrouped)
+        GFFT_LINES(double, 2048, 4, kContig)
+        GFFT_LINES(double, 4096, 4, kContig)
+    } else {
+        GFFT_LINES(float, 512, 16, kContig)
+        GFFT_LINES(float, 1024, 16, kGrouped)
+        GFFT_LINES(float, 2048, 8, kGrouped)
+        GFFT_LINES(float, 4096, 4, kGrouped)
+    }
+#undef GFFT_LINES
     return hipErrorInvalidValue;
-}
-
-hipError_t launch_strided_1024(bool f64, int n, int sign, const void* src, void* data,
-                               const void* tw, int64_t m_cols, int64_t n_b, line_map lm,
-                               hipStream_t s) {
-    return f64 ? strided_1024<double>(n, sign, src, data, tw, m_cols, n_b, lm, s)
-               : strided_1024<float>(n, sign, src, data, tw, m_cols, n_b, lm, s);
 }
 
 template <typename V>

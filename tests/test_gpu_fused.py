@@ -140,11 +140,14 @@ def test_small_grids(n, batch, inplace, dtype):
 
 @DTYPES
 @pytest.mark.parametrize("n,x,batch,order", [
-    (2048, 1, 2, "natural"), (2048, 2, 1, "send"), (2048, 1, 1, "send"), (2048, 2, 1, "paper"),
+    (512, 2, 3, "natural"), (512, 16, 1, "send"), (512, 8, 1, "send"), (512, 2, 1, "inplace"),
+    (1024, 1, 2, "natural"), (1024, 16, 1, "send"), (1024, 8, 1, "send"), (1024, 4, 1, "send"),
+    (1024, 2, 1, "paper"), (2048, 1, 2, "natural"), (2048, 8, 1, "send"), (2048, 2, 1, "send"), (2048, 1, 1, "send"), (2048, 2, 1, "paper"),
     (2048, 1, 1, "inplace"), (4096, 1, 1, "natural"), (4096, 4, 1, "send"), (4096, 2, 1, "send")])
 def test_long_rows_step1(n, x, batch, order, dtype):
-    """Step 1 at N = 2048 and 4096 with y split between the z and y passes,
-    and the layouts that keep the whole y pass, against the separate passes
+    """Step 1 of long rows with y split between the z and y passes, and the
+    layouts that keep the whole y pass (fewer rows of a plane per chunk than
+    the step, the paper's order, in place), against the separate passes
     (and one plane of them against the oracle), weighted and not."""
     p = Plan(n, dtype, slab_x=x, batch=batch, fuse_pack=order in ("send", "paper"),
              paper_order=order == "paper", inplace=order == "inplace")
