@@ -67,11 +67,13 @@ template <typename T, bool FWD, int N>
 struct zcfg {
     static constexpr bool F64 = sizeof(T) == 8;
     static constexpr bool MID32 = !F64 && (N == 256 || N == 512);
-    static constexpr int EMAX =
-        F64 ? (FWD ? (N >= 1024 ? 16 : 8) : 16) : (MID32 ? 16 : 32);
+    static constexpr int EMAX = N <= 16 ? 4
+                                : N <= 128 ? 8
+                                : F64 ? (FWD ? (N >= 1024 ? 16 : 8) : 16) : (MID32 ? 16 : 32);
     static constexpr int THREADS =
-        F64 ? (FWD ? (N >= 1024 ? 128 : 256) : 64)
-            : MID32 ? (FWD || N == 256 ? 256 : 128) : (FWD && N >= 1024 ? 256 : 64);
+        N <= 128 ? 256
+        : F64 ? (FWD ? (N >= 1024 ? 128 : 256) : 64)
+              : MID32 ? (FWD || N == 256 ? 256 : 128) : (FWD && N >= 1024 ? 256 : 64);
     static constexpr bool NTS = !FWD;
 };
 
@@ -113,9 +115,11 @@ __device__ __forceinline__ void z_r2c_body(
     for (int m = 0; m < E; ++m) lds[ix.at(xgeom<M, E, 1, 1>::template in_pad<PS>(t, m))] = a[m];
     __syncthreads();
     if (!valid) return;
-    // With ALIAS, all bins are formed in registers before the first store:
-    // stores through a pointer that may alias `in` would otherwise keep the
-    // twiddle loads from being issued early.
+    // FIRST: all bins are formed in registers before the first store, as a
+    // twiddle load behind a store waits for it (FP32 N = 64 374 -> 261 us over
+    // 537 MB, 256 224 -> 212; from 512 up the loads are hoisted anyway and
+    // FP32 loses 2-3%).  With ALIAS nothing can be hoisted.
+    constexpr bool FIRST = ALIAS || N <= 256;
     const cx<T> x_m{(a[0].x - a[0].y) * mul_edge, T(0)};
     cx<T>* dst = out + (PENCIL ? 0 : map_row(row, map) * K);
     auto put = [&](int k, cx<T> v) {
@@ -138,10 +142,10 @@ __device__ __forceinline__ void z_r2c_body(
         const cx<T> wb = cmul(tw[k], B);
         const T f = k == 0 ? mul_edge : mul_int;
         const cx<T> v{(A.x + wb.y) * f, (A.y - wb.x) * f};
-        if constexpr (ALIAS) a[m] = v;
+        if constexpr (FIRST) a[m] = v;
         else put(k, v);
     }
-    if constexpr (ALIAS) {
+    if constexpr (FIRST) {
 #pragma unroll
         for (int m = 0; m < E; ++m) put(t + m * TPT, a[m]);
     }
