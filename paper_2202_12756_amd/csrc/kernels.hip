@@ -483,14 +483,15 @@ __global__ __launch_bounds__(TC * N / E) void k_strided(
 
 // ---------------------------------------------------------------- pack
 // One run per chunk c = (bb, j, xl), elements of 16 bytes where the runs
-// allow it (V: an FP64 value or two FP32 ones).  A thread moves one element
-// per round, and there are as many threads as elements up to the dispatch
-// limit: like the streaming copy, the pass lives on many short workgroups
-// (1024^3/8: FP32 180 us, FP64 362, 5.95 TB/s; with 8-byte FP32 elements and
-// four rounds per thread 200 and 400).  A workgroup takes `per` whole runs
+// allow it (V: an FP64 value or two FP32 ones).  A thread moves U elements
+// (launch_pack), and there are as many threads as that takes up to the
+// dispatch limit: like the streaming copy, the pass lives on many short
+// workgroups (1024^3/8, U = 1: FP32 179 us, FP64 360, 6.0 TB/s; 2, 4, 8: 192,
+// 198, 204 and 390, 406, 401; 8-byte FP32 elements, four rounds per thread 197
+// and 389).  A workgroup takes `per` whole runs
 // where they are short, a part of one otherwise; all extents are in elements
 // of V, inv = 1 / len.
-template <typename V>
+template <typename V, int U>
 __global__ __launch_bounds__(kThreads) void k_pack(
     const V* __restrict__ src, V* __restrict__ dst, int64_t len, int64_t chunks,
     int64_t blocks_per_chunk, int per, float inv, int lg_x, int lg_p, int64_t x_step,
@@ -524,7 +525,15 @@ __global__ __launch_bounds__(kThreads) void k_pack(
     const V* s = src + (to_send ? nat : snd);
     V* d = dst + (to_send ? snd : nat);
     const int64_t step = blocks_per_chunk * kThreads;
-    for (int64_t e = part * kThreads + threadIdx.x; e < len; e += step) d[e] = s[e];
+    int64_t e = part * kThreads + threadIdx.x;
+    for (; e + (U - 1) * step < len; e += U * step) {
+        V v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = s[e + u * step];
+#pragma unroll
+        for (int u = 0; u < U; ++u) d[e + u * step] = v[u];
+    }
+    for (; e < len; e += step) d[e] = s[e];
 }
 
 // Row permutation copy: workgroup copies kRows rows, k values each.
@@ -648,16 +657,18 @@ static hipError_t strided_run(int sign, const void* src, void* data, const void*
 // 4.44 against a full grid's 3.73 / 4.31, launch order / contiguous without
 // the hint).  Below 4 KB few columns remain (FP32 128 at 2 KB 4.3 / 5.2), and
 // FP64 2048 (one 512-thread workgroup per CU) is 5% slower with the hint:
-// these, lines shared between tiles and the y passes take plain accesses, in
-// contiguous order (FP64 y 1024 4.88 against 4.76 in groups of 16, 512 5.23
-// against 4.65) except FP32 4096, whose 64-byte runs need their neighbours in
-// time (y 3.34 against 2.84, pencil x 3.00 against 2.60 in groups of 16).
+// these, lines shared between tiles and the y passes take plain accesses.
 // Where tiles share lines the hint makes them travel twice (15-50% slower).
+// Plain accesses go in groups of 16 (FP32 4096 y 3.34 TB/s, 2.84 contiguous,
+// pencil x 3.00 and 2.60; whole chains: FP64 512^3/4 in the paper's order 320
+// us against 337, FP64 1024 4 x 4 pencil 626 against 642, FP32 2048 1 x 256
+// 209 against 235), but contiguously in FP64 for y lines in natural order (512
+// 5.23 against 4.65, 1024 4.88 against 4.76), from N = 2048 (4096 16 x 32
+// pencil 1539 us against 1632) and for x lines of 256 (4.46 against 3.7).
 template <typename T, int N>
 struct line_order {
     static constexpr bool F64 = sizeof(T) == 8;
     static constexpr int NT = N <= 128 ? 2 : N == 512 ? 1 : (!F64 && N == 1024) || (F64 && N == 256) ? 4 : 6;
-    static constexpr int PLAIN = !F64 && N == 4096 ? kGrouped : kContig;
 };
 
 template <typename T, int N, int AX, int MF>
@@ -678,7 +689,13 @@ static hipError_t strided_ax(int sign, const void* src, void* data, const void* 
                 return strided_run<T, N, AX, MF, true, O::NT>(sign, src, data, tw, m_cols, n_b, lm, s);
         }
     }
-    return strided_run<T, N, AX, MF, false, O::PLAIN>(sign, src, data, tw, m_cols, n_b, lm, s);
+    if constexpr (F64 && (N >= 2048 || (AX == 1 && N == 256)))
+        return strided_run<T, N, AX, MF, false, kContig>(sign, src, data, tw, m_cols, n_b, lm, s);
+    if constexpr (F64 && AX == 0) {
+        if (lm.lg_y >= ilog2_c(N) && lm.s_lo == m_cols)
+            return strided_run<T, N, AX, MF, false, kContig>(sign, src, data, tw, m_cols, n_b, lm, s);
+    }
+    return strided_run<T, N, AX, MF, false, kGrouped>(sign, src, data, tw, m_cols, n_b, lm, s);
 }
 
 template <typename T, int N>
@@ -767,15 +784,15 @@ hipError_t launch_strided_lines(bool f64, int n, int ny, int sign, const void* s
     return hipErrorInvalidValue;
 }
 
-template <typename V>
-static hipError_t pack_v(const void* src, void* dst, int64_t chunks, int lg_x, int lg_p,
+template <typename V, int U>
+static hipError_t pack_u(const void* src, void* dst, int64_t chunks, int lg_x, int lg_p,
                          int64_t x_step, int64_t len, bool to_send, hipStream_t s) {
     if (chunks == 0 || len == 0) return hipSuccess;
     // runs of up to two rounds of a workgroup: several to a workgroup, so that
     // few of its lanes idle in the last round (TB/s, FP32 64^3/16 5.85 against
     // 3.75, 512^3/512 5.54 against 2.40; runs of three rounds 5.5 against 6.3)
     const int per = len <= 2 * kThreads ? int((4 * kThreads + len - 1) / len) : 1;
-    int64_t bpc = (len + kThreads - 1) / kThreads;
+    int64_t bpc = (len + U * kThreads - 1) / (U * kThreads);
     // k_pack strides over its chunk, so fewer blocks per chunk keep very
     // large grids within the dispatch's 32-bit work-item count
     const int64_t cap = int64_t(0xffffffff) / (chunks * kThreads);
@@ -783,10 +800,23 @@ static hipError_t pack_v(const void* src, void* dst, int64_t chunks, int lg_x, i
     if (bpc < 1) bpc = 1;
     const int64_t blocks = per > 1 ? (chunks + per - 1) / per : chunks * bpc;
     if (!grid_fits(blocks, kThreads)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_pack<V>), dim3(blocks), dim3(kThreads), 0, s,
+    hipLaunchKernelGGL((k_pack<V, U>), dim3(blocks), dim3(kThreads), 0, s,
                        static_cast<const V*>(src), static_cast<V*>(dst), len, chunks, bpc, per,
                        1.0f / float(len), lg_x, lg_p, x_step, to_send);
     return hipGetLastError();
+}
+
+// One element per thread, but eight at an eighth of the run apart where runs
+// are a power of two of 256 KB or more (pencils): reads and writes then stay a
+// fixed power of two apart for a whole run, and the spread avoids that (4096
+// 64 x 4 pencil, FP32 398 us against 518, FP64 798 against 1101; at 128 KB
+// 2048 32 x 4 97 against 91).
+template <typename V>
+static hipError_t pack_v(const void* src, void* dst, int64_t chunks, int lg_x, int lg_p,
+                         int64_t x_step, int64_t len, bool to_send, hipStream_t s) {
+    if (len * int64_t(sizeof(V)) >= int64_t(256) << 10 && (len & (len - 1)) == 0)
+        return pack_u<V, 8>(src, dst, chunks, lg_x, lg_p, x_step, len, to_send, s);
+    return pack_u<V, 1>(src, dst, chunks, lg_x, lg_p, x_step, len, to_send, s);
 }
 
 hipError_t launch_pack(bool f64, const void* src, void* dst, int64_t chunks, int lg_x,

@@ -7,7 +7,7 @@ import torch
 
 import oracle
 from helpers import TOL, cplx_input, host, real_input, rel_l2
-from paper_2202_12756_amd import Plan
+from paper_2202_12756_amd import PencilPlan, Plan
 
 pytestmark = pytest.mark.gpu
 
@@ -195,3 +195,17 @@ def test_pack_run_lengths(n, x, batch, dtype):
     torch.cuda.synchronize()
     assert (host(send) == oracle.pack_slab(ref, n // x)).all()
     assert torch.equal(back, s)
+
+
+@pytest.mark.parametrize("dtype,n,pr,pc", [(F32, 1024, 4, 2), (F64, 512, 2, 1), (F32, 64, 8, 2)])
+def test_pencil_pack_runs(dtype, n, pr, pc):
+    """The second exchange's pack with runs of a power of two: long (spread
+    over the run), and short, and the Nyquist column's odd ones."""
+    for col in {0, pc - 1}:
+        p = PencilPlan(n, dtype, (pr, pc), col)
+        a, _ = cplx_input(p.ypencil_shape, 28000 + n + col, dtype)
+        b = p.pack2(a)
+        want = a.view(p.batch, p.pc, p.x, p.h, n // pr, p.w).permute(0, 1, 3, 2, 4, 5)
+        torch.cuda.synchronize()
+        assert torch.equal(b, want.reshape(p.send2_shape))
+        assert torch.equal(p.unpack2(b), a)
