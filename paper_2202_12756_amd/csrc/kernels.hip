@@ -319,11 +319,13 @@ struct sshape {
 // -1 no transform (each element replaced by its conjugate): the same loads
 // and stores as the pass, a yardstick for its memory-access ceiling.
 // ORD: tile order (xcd_tile).
+// FLAT: sets of fewer columns than a tile; tiles take TC columns of all sets
+// numbered through (tiles_m: the number of all columns).
 // TWS: tw is the table of a transform TWS times as long.
 // src may be data itself (in place) or a distinct buffer of the same layout:
 // every load of a tile precedes its stores, and tiles own their elements.
 template <typename T, int N, int TC, int XP, int S, int E = 16, int MF = 0, bool NT = false,
-          int ORD = kContig, int TWS = 1>
+          int ORD = kContig, int TWS = 1, bool FLAT = false>
 __global__ __launch_bounds__(TC * N / E) void k_strided(
     const cx<T>* src, cx<T>* data, const cx<T>* __restrict__ tw, int64_t m_cols,
     int64_t tiles_m, line_map lm) {
@@ -339,10 +341,21 @@ __global__ __launch_bounds__(TC * N / E) void k_strided(
     const int c = threadIdx.x % TC;
     const int t = threadIdx.x / TC;
     const int64_t tile = xcd_tile<ORD>(blockIdx.x, gridDim.x);
-    const int64_t b = tile / tiles_m;
-    const int64_t m0 = (tile - b * tiles_m) * TC;
-    const int64_t m = m0 + c;
-    const bool valid = m < m_cols;
+    int64_t b, m0, m;
+    bool valid;
+    if constexpr (FLAT) {
+        int64_t g = tile * TC + c;
+        valid = g < tiles_m;
+        if (!valid) g = tiles_m - 1;
+        b = g / m_cols;
+        m = g - b * m_cols;
+        m0 = 0;
+    } else {
+        b = tile / tiles_m;
+        m0 = (tile - b * tiles_m) * TC;
+        m = m0 + c;
+        valid = m < m_cols;
+    }
     const int64_t ymask = (int64_t(1) << lm.lg_y) - 1;
     const int64_t set = (b >> lm.lg_bx) * lm.b_hi + (b & ((int64_t(1) << lm.lg_bx) - 1)) * lm.b_lo;
     const cx<T>* from = src + set;
@@ -366,7 +379,7 @@ __global__ __launch_bounds__(TC * N / E) void k_strided(
     auto uoff = [](int i, int d, int64_t H, int64_t Lo) {
         return int64_t(i >> d) * H + int64_t(i & ((1 << d) - 1)) * Lo;
     };
-    int64_t lane_off = (valid ? m : m_cols - 1) + off(t);
+    int64_t lane_off = (FLAT || valid ? m : m_cols - 1) + off(t);
     const cx<T>* lane = from + lane_off;
 
     cx<T> a[E];
@@ -641,6 +654,27 @@ static hipError_t strided_run(int sign, const void* src, void* data, const void*
     return hipGetLastError();
 }
 
+// y lines of pencils with narrow kz chunks: FP32 2048 1 x 1024 ranks (one bin)
+// z, y and x 171 -> 124 us, FP64 1024 1 x 256 96 -> 52, 4096 8 x 2048 81 -> 65.
+template <typename T, int N>
+static hipError_t strided_flat(int sign, const void* src, void* data, const void* tw,
+                               int64_t m_cols, int64_t n_b, line_map lm, hipStream_t s) {
+    using SH = sshape<T, N, 0>;
+    constexpr int TC = SH::TC;
+    const int64_t cols = m_cols * n_b, blocks = (cols + TC - 1) / TC;
+    if (!grid_fits(blocks, TC * SH::TPT)) return hipErrorInvalidValue;
+    const dim3 threads(TC * SH::TPT);
+    if (sign < 0)
+        hipLaunchKernelGGL((k_strided<T, N, TC, SH::XP, -1, SH::E, 0, false, kGrouped, 1, true>),
+                           dim3(blocks), threads, 0, s, static_cast<const cx<T>*>(src),
+                           static_cast<cx<T>*>(data), static_cast<const cx<T>*>(tw), m_cols, cols, lm);
+    else
+        hipLaunchKernelGGL((k_strided<T, N, TC, SH::XP, +1, SH::E, 0, false, kGrouped, 1, true>),
+                           dim3(blocks), threads, 0, s, static_cast<const cx<T>*>(src),
+                           static_cast<cx<T>*>(data), static_cast<const cx<T>*>(tw), m_cols, cols, lm);
+    return hipGetLastError();
+}
+
 // Tile order and hints of the strided passes.  x passes whose tiles own whole
 // 128-byte lines stream through non-temporally: neighbouring tiles share
 // nothing, and the eight XCDs are kept on one run of columns by dealing small
@@ -655,15 +689,17 @@ static hipError_t strided_run(int sign, const void* src, void* data, const void*
 //        3.93 / 3.91 / 3.68
 // FP64 256 gains from it up to 512 KB between a line's elements (p = 2 4.67 /
 // 4.44 against a full grid's 3.73 / 4.31, launch order / contiguous without
-// the hint).  Below 4 KB few columns remain (FP32 128 at 2 KB 4.3 / 5.2), and
+// the hint).  Below 4 KB few columns remain: contiguous order, from N = 512
+// (FP32 256) with the hint (FP32 512 at 1 KB 14.4 us against 17.2 grouped and
+// plain), below without (FP32 128 at 2 KB 5.2 against 4.3); and
 // FP64 2048 (one 512-thread workgroup per CU) is 5% slower with the hint:
 // these, lines shared between tiles and the y passes take plain accesses.
 // Where tiles share lines the hint makes them travel twice (15-50% slower).
 // Plain accesses go in groups of 16 (FP32 4096 y 3.34 TB/s, 2.84 contiguous,
 // pencil x 3.00 and 2.60; whole chains: FP64 512^3/4 in the paper's order 320
 // us against 337, FP64 1024 4 x 4 pencil 626 against 642, FP32 2048 1 x 256
-// 209 against 235), but contiguously in FP64 for y lines in natural order (512
-// 5.23 against 4.65, 1024 4.88 against 4.76), from N = 2048 (4096 16 x 32
+// 209 against 235), but contiguously for y lines of 512 (FP64 5.23 against
+// 4.65) and in FP64 for those of natural order (1024 4.88 against 4.76), from N = 2048 (4096 16 x 32
 // pencil 1539 us against 1632) and for x lines of 256 (4.46 against 3.7).
 template <typename T, int N>
 struct line_order {
@@ -687,12 +723,27 @@ static hipError_t strided_ax(int sign, const void* src, void* data, const void* 
             constexpr int64_t FAR = F64 && N == 256 ? int64_t(512) << 10 : int64_t(1) << 62;
             if (step >= 4096 && step < FAR)
                 return strided_run<T, N, AX, MF, true, O::NT>(sign, src, data, tw, m_cols, n_b, lm, s);
+            if constexpr (N >= 512 || (!F64 && N == 256)) {
+                if (step < 4096)
+                    return strided_run<T, N, AX, MF, true, kContig>(sign, src, data, tw, m_cols, n_b, lm,
+                                                                    s);
+            }
         }
+    }
+    if constexpr (AX == 0 && MF == 0 && N >= 64) {
+        // sets that would leave half (from N = 1024) or three quarters of a
+        // tile's lanes idle
+        if ((N >= 1024 ? 2 : 4) * m_cols <= SH::TC && m_cols > 0 && n_b > 1)
+            return strided_flat<T, N>(sign, src, data, tw, m_cols, n_b, lm, s);
+    }
+    if constexpr (AX == 1 && N <= 256) {
+        if (lm.s_lo * ES < 4096)
+            return strided_run<T, N, AX, MF, false, kContig>(sign, src, data, tw, m_cols, n_b, lm, s);
     }
     if constexpr (F64 && (N >= 2048 || (AX == 1 && N == 256)))
         return strided_run<T, N, AX, MF, false, kContig>(sign, src, data, tw, m_cols, n_b, lm, s);
-    if constexpr (F64 && AX == 0) {
-        if (lm.lg_y >= ilog2_c(N) && lm.s_lo == m_cols)
+    if constexpr ((F64 || N == 512) && AX == 0) {
+        if ((lm.lg_y >= ilog2_c(N) || N == 512) && lm.s_lo == m_cols)
             return strided_run<T, N, AX, MF, false, kContig>(sign, src, data, tw, m_cols, n_b, lm, s);
     }
     return strided_run<T, N, AX, MF, false, kGrouped>(sign, src, data, tw, m_cols, n_b, lm, s);

@@ -209,3 +209,19 @@ def test_pencil_pack_runs(dtype, n, pr, pc):
         torch.cuda.synchronize()
         assert torch.equal(b, want.reshape(p.send2_shape))
         assert torch.equal(p.unpack2(b), a)
+
+
+@DTYPES
+@pytest.mark.parametrize("n,pr,pc", [(64, 2, 8), (128, 4, 32), (512, 64, 64), (1024, 128, 128),
+                                     (2048, 512, 512)])
+def test_narrow_pencils(n, pr, pc, dtype):
+    """y lines of kz chunks narrower than a tile, several planes to a tile,
+    the last column's odd width and a ragged last tile included."""
+    for col in (0, pc - 1):
+        p = PencilPlan(n, dtype, (pr, pc), col, batch=3)
+        a, ref = cplx_input(p.ypencil_shape, 29000 + n + col, dtype)
+        # y = c' Y + y_l runs over (block, y_l)
+        ref = ref.transpose(0, 1, 3, 2, 4).reshape(3, n, p.x, p.w)
+        for sign in (-1, +1):
+            got = host(p.y_c2c(a.clone(), sign)).transpose(0, 1, 3, 2, 4).reshape(3, n, p.x, p.w)
+            assert rel_l2(got, oracle.c2c_axis(ref, 1, sign)) <= TOL[dtype]
