@@ -58,8 +58,10 @@ __device__ __forceinline__ int64_t xcd_tile(int64_t g, int64_t G) {
     } else {
         constexpr int64_t span = int64_t(kXcd) << ORD;
         const int64_t base = g & ~(span - 1), o = g - base;
-        if (base + span > G) return g;  // the tiles left over, in launch order
-        return base + ((o % kXcd) << ORD) + o / kXcd;
+        if (base + span <= G) return base + ((o % kXcd) << ORD) + o / kXcd;
+        // the tiles left over (all of a small grid): contiguous eighths
+        const int64_t per = (G - base) / kXcd;
+        return o >= per * kXcd ? g : base + (o % kXcd) * per + o / kXcd;
     }
 }
 
