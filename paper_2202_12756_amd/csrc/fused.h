@@ -887,6 +887,15 @@ struct plane_cfg {
 template <typename T, int N>
 static hipError_t plane_n(bool forward, const void* in, void* out, const void* tw, int64_t planes,
                           row_map map, double me, double mi, hipStream_t s) {
+    if (N <= 128 && planes * N > kSliceRows)
+        return in_slices(planes * N, [&](int64_t r0, int64_t nr) {
+            const int64_t ro = r0 * map.rs, co = r0 * (N / 2 + 1);
+            const void* src = forward ? static_cast<const void*>(static_cast<const T*>(in) + ro)
+                                      : static_cast<const cx<T>*>(in) + co;
+            void* dst = forward ? static_cast<void*>(static_cast<cx<T>*>(out) + co)
+                                : static_cast<T*>(out) + ro;
+            return plane_n<T, N>(forward, src, dst, tw, nr / N, map, me, mi, s);
+        });
     using C = plane_cfg<T, N>;
     constexpr int NT = plane_shape<T, N, 1, C::E>::NT;
     if (planes == 0) return hipSuccess;
@@ -903,8 +912,8 @@ static hipError_t plane_n(bool forward, const void* in, void* out, const void* t
 }
 
 // Where a plane fills at least a wave and fits on a CU with room for a second
-// one (FP64 up to N = 128: 131 KB) or at least once (FP32 N = 256: 262 KB); an FP64 256 x 256
-// plane (524 KB) would take the whole register file.
+// one (FP64 up to N = 128: 131 KB) or at least once (FP32 N = 256: 262 KB); an
+// FP64 256 x 256 plane (524 KB) would take the whole register file.
 bool plane_supported(bool f64, int n) {
     return n == 32 || n == 64 || n == 128 || (!f64 && n == 256);
 }

@@ -14,8 +14,10 @@
 // Pencil plans (section 2, pencil decomposition) reuse the same passes: the
 // z pass scatters each row's bins to the first exchange's chunks, and the
 // y/x passes address the received pencils through their line maps.
-// Memory bound: each pass reads and writes its array once.
-// fused.h holds the kernels that take several axes in one pass.
+// Memory bound: each pass reads and writes its array once.  fused.h holds the
+// kernels that take several axes, or part of one beside another, in a pass:
+// full transforms and step 1 run those where they apply, the passes here run
+// the rest, the single-pass entry points and the lines the others leave.
 #include "cx.h"
 #include "engine.h"
 #include "fused.h"
@@ -579,6 +581,14 @@ __global__ __launch_bounds__(kThreads) void k_copy16(const uint4* __restrict__ s
 template <typename T, int N>
 static hipError_t z_r2c_n(const void* in, void* out, const void* tw, int64_t rows,
                           row_map map, double me, double mi, hipStream_t s) {
+    if constexpr (N <= 128) {
+        if (rows > kSliceRows)
+            return in_slices(rows, [&](int64_t r0, int64_t nr) {
+                return z_r2c_n<T, N>(static_cast<const T*>(in) + r0 * map.rs,
+                                     static_cast<cx<T>*>(out) + r0 * (N / 2 + 1), tw, nr, map, me,
+                                     mi, s);
+            });
+    }
     using C = zcfg<T, true, N>;
     using Z = zshape<N / 2, C::EMAX, C::THREADS>;
     const int64_t blocks = (rows + Z::RPB - 1) / Z::RPB;
@@ -603,6 +613,13 @@ static hipError_t z_r2c_n(const void* in, void* out, const void* tw, int64_t row
 template <typename T, int N>
 static hipError_t z_c2r_n(const void* in, void* out, const void* tw, int64_t rows,
                           row_map map, double me, double mi, hipStream_t s) {
+    if constexpr (N <= 128) {
+        if (rows > kSliceRows)
+            return in_slices(rows, [&](int64_t r0, int64_t nr) {
+                return z_c2r_n<T, N>(static_cast<const cx<T>*>(in) + r0 * (N / 2 + 1),
+                                     static_cast<T*>(out) + r0 * map.rs, tw, nr, map, me, mi, s);
+            });
+    }
     using C = zcfg<T, false, N>;
     using Z = zshape<N / 2, C::EMAX, C::THREADS>;
     const int64_t blocks = (rows + Z::RPB - 1) / Z::RPB;
@@ -699,8 +716,9 @@ static hipError_t strided_flat(int sign, const void* src, void* data, const void
 // pencil x 3.00 and 2.60; whole chains: FP64 512^3/4 in the paper's order 320
 // us against 337, FP64 1024 4 x 4 pencil 626 against 642, FP32 2048 1 x 256
 // 209 against 235), but contiguously for y lines of 512 (FP64 5.23 against
-// 4.65) and in FP64 for those of natural order (1024 4.88 against 4.76), from N = 2048 (4096 16 x 32
-// pencil 1539 us against 1632) and for x lines of 256 (4.46 against 3.7).
+// 4.65) and in FP64 for those of natural order (1024 4.88 against 4.76), from
+// N = 2048 (4096 16 x 32 pencil 1539 us against 1632) and for x lines of 256
+// (4.46 against 3.7).
 template <typename T, int N>
 struct line_order {
     static constexpr bool F64 = sizeof(T) == 8;

@@ -71,4 +71,19 @@ inline bool grid_fits(int64_t blocks, int64_t threads) {
     return blocks <= 0x7fffffff && blocks * threads <= int64_t(0xffffffff);
 }
 
+// Rows of up to 128 reals take 2 to 8 threads each, so the most rows that fit
+// in memory (2^31 of 16 reals in 154 GB, in place) need more than one grid:
+// such passes run in slices of 2^28 rows, whole entries of the batch (an entry
+// has a power of two of at most N^2 rows), each at the same offset in rows of
+// both arrays.  launch(r0, rows of the slice).
+constexpr int64_t kSliceRows = int64_t(1) << 28;
+template <typename F>
+inline hipError_t in_slices(int64_t rows, F launch) {
+    for (int64_t r0 = 0; r0 < rows; r0 += kSliceRows) {
+        const hipError_t e = launch(r0, rows - r0 < kSliceRows ? rows - r0 : kSliceRows);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 }  // namespace gfft

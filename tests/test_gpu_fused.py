@@ -7,7 +7,7 @@ import torch
 
 import oracle
 from helpers import TOL, cplx_input, host, real_input, rel_l2
-from paper_2202_12756_amd import PencilPlan, Plan
+from paper_2202_12756_amd import PencilPlan, Plan, _lib
 
 pytestmark = pytest.mark.gpu
 
@@ -225,3 +225,46 @@ def test_narrow_pencils(n, pr, pc, dtype):
         for sign in (-1, +1):
             got = host(p.y_c2c(a.clone(), sign)).transpose(0, 1, 3, 2, 4).reshape(3, n, p.x, p.w)
             assert rel_l2(got, oracle.c2c_axis(ref, 1, sign)) <= TOL[dtype]
+
+
+@pytest.mark.parametrize("n", [16, 32])
+def test_rows_past_one_grid(n):
+    """More rows than one launch of the z passes (n = 16) or plane passes
+    (n = 32) takes, in place: the entries at both ends and around the end of
+    the first slice equal those of a small plan, bit for bit."""
+    slice_ = (1 << 28) // n
+    p = Plan(n, F32, slab_x=1, batch=slice_ + 3, inplace=True)
+    q = Plan(n, F32, slab_x=1, batch=2, inplace=True)
+    buf, small = p.empty_inplace(), q.empty_inplace()
+    buf.zero_()
+
+    def fwd(plan, b):
+        if n == 32:
+            return plan.r2c_(b)
+        a = plan._inplace_ptr(b)
+        plan._exec(_lib.gfft_exec_z_r2c, a, a, 1.0, 0)
+        return b
+
+    def inv(plan, b, scale):
+        if n == 32:
+            return plan.c2r_(b, scale=scale)
+        a = plan._inplace_ptr(b)
+        plan._exec(_lib.gfft_exec_z_c2r, a, a, scale, 0)
+        return plan.real_view(b)
+
+    at = [0, slice_ - 1, slice_ + 1]
+    want, ref = [], []
+    for i, b in enumerate(at):
+        xin, xref = real_input(q.real_shape, 29000 + n + i, F32)
+        p.real_view(buf)[b:b + 2].copy_(xin)
+        q.real_view(small).copy_(xin)
+        ref.append(xref)
+        want.append(fwd(q, small).clone())
+    fwd(p, buf)
+    torch.cuda.synchronize()
+    for b, f in zip(at, want):
+        assert torch.equal(buf[b:b + 2], f)
+    out = inv(p, buf, 1.0 / (n if n == 16 else n * n))
+    torch.cuda.synchronize()
+    for b, xref in zip(at, ref):
+        assert rel_l2(host(out[b:b + 2]), xref) <= TOL[F32]
