@@ -763,8 +763,9 @@ def main():
     rel = math.sqrt(num / den)
 
     # Instrumented repeat: the same K steps through the single-pass entry
-    # points (the same kernels in the same order), with HIP events between
-    # the passes on the launch stream: each kernel's live average duration.
+    # points, with HIP events between the passes on the launch stream: each
+    # kernel's live average duration.  The x passes are the step's own
+    # kernels; its z passes may also take the first step of y.
     passes = ["z_r2c", "y_fwd", "x_fwd", "x_inv", "y_inv", "z_c2r"]
 
     def step(ev):
