@@ -182,6 +182,41 @@ __device__ __forceinline__ void dft32(cx<T>* a) {
     }
 }
 
+// Radix 64 as 2 x 32 (decimation in time), as dft32: w64^k = cos(pi k/32) +
+// S i sin(pi k/32).
+template <int S, typename T>
+__device__ __forceinline__ void dft64(cx<T>* a) {
+    constexpr double C[17] = {  // cos(pi k / 32)
+        1.0, 0.99518472667219692873, 0.98078528040323043058, 0.95694033573220882438,
+        0.92387953251128673848, 0.88192126434835504956, 0.83146961230254523567, 0.77301045336273699338,
+        0.70710678118654757274, 0.63439328416364548779, 0.55557023301960217765, 0.47139673682599764204,
+        0.38268343236508978178, 0.29028467725446238656, 0.19509032201612827584, 0.09801714032956060363,
+        0.0,
+    };
+    cx<T> e[32], o[32];
+#pragma unroll
+    for (int i = 0; i < 32; ++i) {
+        e[i] = a[2 * i];
+        o[i] = a[2 * i + 1];
+    }
+    dft32<S>(e);
+    dft32<S>(o);
+#pragma unroll
+    for (int k = 0; k < 32; ++k) {
+        if (k == 8) o[k] = mul_w8_1<S>(o[k]);
+        else if (k == 16) o[k] = mul_si<S>(o[k]);
+        else if (k == 24) o[k] = mul_w8_3<S>(o[k]);
+        else if (k > 0)
+            o[k] = mul_cs<S>(o[k], T(k <= 16 ? C[k <= 16 ? k : 0] : -C[k > 16 ? 32 - k : 0]),
+                             T(k <= 16 ? C[k <= 16 ? 16 - k : 0] : C[k > 16 ? k - 16 : 0]));
+    }
+#pragma unroll
+    for (int k = 0; k < 32; ++k) {
+        a[k] = e[k] + o[k];
+        a[k + 32] = e[k] - o[k];
+    }
+}
+
 template <int R, int S, typename T>
 __device__ __forceinline__ void dft(cx<T>* a) {
     if constexpr (R == 2) {
@@ -194,8 +229,10 @@ __device__ __forceinline__ void dft(cx<T>* a) {
         dft16<S>(a);
     } else if constexpr (R == 32) {
         dft32<S>(a);
+    } else if constexpr (R == 64) {
+        dft64<S>(a);
     } else {
-        static_assert(R == 1, "radix must be 1, 2, 4, 8, 16 or 32");
+        static_assert(R == 1, "radix must be 1, 2, 4, 8, 16, 32 or 64");
     }
 }
 

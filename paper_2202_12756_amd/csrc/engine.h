@@ -22,8 +22,8 @@
 namespace gfft {
 
 // Radix of the stage that starts at span L: min(E, RM) while the remaining
-// length allows, then whatever is left (N, E, RM powers of two; RM = 16 or
-// 32).  With E > RM a thread runs E/RM butterflies per stage.
+// length allows, then whatever is left (N, E, RM powers of two; RM = 16, 32
+// or 64).  With E > RM a thread runs E/RM butterflies per stage.
 template <int N, int E, int L, int RM = 16>
 struct stage_radix {
     static constexpr int RMAX = E < RM ? E : RM;
@@ -66,7 +66,7 @@ template <int E, int RM = 16>
 struct first_radix_shift {
     static constexpr int R0 = E < RM ? E : RM;
     static constexpr int value =
-        R0 >= 32 ? 5 : R0 >= 16 ? 4 : R0 >= 8 ? 3 : R0 >= 4 ? 2 : R0 >= 2 ? 1 : 0;
+        R0 >= 64 ? 6 : R0 >= 32 ? 5 : R0 >= 16 ? 4 : R0 >= 8 ? 3 : R0 >= 4 ? 2 : R0 >= 2 ? 1 : 0;
 };
 
 // Exchange after a stage: every output slot q + r*NB goes to position

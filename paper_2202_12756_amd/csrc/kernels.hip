@@ -292,7 +292,15 @@ struct sshape {
     // runs), 4% faster than 16 (at N = 256 the x tile with 32 elements per
     // thread, the y tile with 16)
     static constexpr bool C32 = !F64 && !MFMA && (N == 256 || (N == 512 && AX == 1));
-    static constexpr int E = MFMA ? 16 : (N >= 512 || (C32 && AX == 1)) ? 32 : 16;
+    // FP32 lines of 2048 and x lines of 4096: 64 elements per thread, two
+    // stages and one exchange (64 x 32, 64 x 64) instead of three and two; a
+    // tile of 128 KiB fills the LDS, so its FFT phase overlaps nothing.  TB/s
+    // against 32 per thread: 2048 x 4.29 / 3.82 (slab of 64 planes), 3.78 / 2.97
+    // (8 x 8 pencil), y 3.55 / 3.40 and 4.56 / 4.38; 4096 x 3.16 / 3.00.  y lines
+    // of 4096 gain in some layouts and lose in others (natural 3.10 / 3.22, 8 x
+    // 16 pencil 3.74 / 3.49), and FP64 (256 registers of data) loses 2-35%.
+    static constexpr bool E64 = !F64 && !MFMA && (N == 2048 || (N == 4096 && AX == 1));
+    static constexpr int E = MFMA ? 16 : E64 ? 64 : (N >= 512 || (C32 && AX == 1)) ? 32 : 16;
     static constexpr int TPT = N / E;
     // FP32 y lines of N = 2048: two 8-column tiles per CU (9% faster than
     // one 16-column tile); FP64 y lines of N = 512: two 16-column tiles with
@@ -334,7 +342,7 @@ __global__ __launch_bounds__(TC * N / E) void k_strided(
     constexpr int TPT = N / E;
     constexpr bool SPLIT = XP == 2;
     static_assert(XP == 1 || XP == 2, "XP: whole values (1) or real/imaginary halves (2)");
-    constexpr int RM = radix_cap<T, MF>();
+    constexpr int RM = radix_cap<T, MF, E>();
     constexpr int PS = first_radix_shift<E, RM>::value;
     constexpr int NP = padded_len<N, PS>::value;
     __shared__ cx<T> lds[(NP * TC + XP - 1) / XP];

@@ -10,9 +10,10 @@ constexpr int ilog2_c(int v) { return v <= 1 ? 0 : 1 + ilog2_c(v / 2); }
 
 // Largest radix per FFT stage.  The FP32 vector kernels take radix-32
 // stages, one LDS exchange fewer for 512- and 1024-point transforms (FP32 is
-// bound by instruction issue); FP64 and the matrix-core stage keep radix 16.
-template <typename T, int MF = 0>
-constexpr int radix_cap() { return sizeof(T) == 4 && MF == 0 ? 32 : 16; }
+// bound by instruction issue), and radix 64 where a thread holds 64 elements;
+// FP64 and the matrix-core stage keep radix 16.
+template <typename T, int MF = 0, int E = 0>
+constexpr int radix_cap() { return sizeof(T) == 4 && MF == 0 ? (E >= 64 ? 64 : 32) : 16; }
 
 __device__ __forceinline__ int64_t map_row(int64_t r, row_map m) {
     const int64_t bx = r >> m.lg_n;

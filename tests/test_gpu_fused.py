@@ -109,6 +109,21 @@ def test_x_pass_orders(n, ranks, batch, dtype):
             assert rel_l2(host(got), want) <= TOL[dtype]
 
 
+@pytest.mark.parametrize("n,x,batch", [(2048, 1, 3), (2048, 8, 1), (4096, 1, 1), (4096, 4, 1)])
+def test_lines_of_64_elements_per_thread(n, x, batch):
+    """FP32 x and y lines of 2048 and 4096, both signs, on buffers on and off
+    the 128-byte line grid."""
+    p = Plan(n, F32, slab_x=x, batch=batch)
+    for shape, axis, run in ((p.pencil_shape, 1, p.x_c2c), (p.spectrum_shape, 2, p.y_c2c)):
+        data, ref = cplx_input(shape, 27000 + n + x, F32)
+        for sign in (-1, +1):
+            want = oracle.c2c_axis(ref, axis, sign)
+            for buf in (torch.empty_like(data), _offset(shape, p.cdtype)):
+                got = run(buf.copy_(data), sign)
+                torch.cuda.synchronize()
+                assert rel_l2(host(got), want) <= TOL[F32]
+
+
 @DTYPES
 @pytest.mark.parametrize("inplace", [False, True], ids=["out_of_place", "inplace"])
 @pytest.mark.parametrize("n,batch", [(16, 1), (16, 7), (32, 1), (32, 63), (32, 65)])
