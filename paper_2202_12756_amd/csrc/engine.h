@@ -152,16 +152,15 @@ struct xch_split {
     }
 };
 
-// Run the stages from span L to the end.  `tw` is a table of
-// W_Ntab^m (m = 0..Ntab-1) with Ntab = N * tws; entry idx*tws is W_N^idx.
-template <typename T, int N, int E, int S, int L, int RM = 16, class X>
-__device__ __forceinline__ void fft_from(cx<T> (&a)[E], int t,
-                                         const cx<T>* __restrict__ tw, int tws,
-                                         const X& xch) {
+// The butterflies of the stage from span L, outputs left in their slots.  `tw`
+// is a table of W_Ntab^m (m = 0..Ntab-1) with Ntab = N * tws; entry idx*tws is
+// W_N^idx.
+template <typename T, int N, int E, int S, int L, int RM>
+__device__ __forceinline__ void fft_stage(cx<T> (&a)[E], int t, const cx<T>* __restrict__ tw,
+                                          int tws) {
     constexpr int R = stage_radix<N, E, L, RM>::value;
     constexpr int NB = E / R;       // butterflies per thread
     constexpr int TPT = N / E;      // threads per transform
-    constexpr bool LAST = (L * R == N);
     static_assert(E % R == 0 && N % (L * R) == 0, "bad stage shape");
 
 #pragma unroll
@@ -182,7 +181,16 @@ __device__ __forceinline__ void fft_from(cx<T> (&a)[E], int t,
 #pragma unroll
         for (int r = 0; r < R; ++r) a[q + r * NB] = b[r];
     }
-    if constexpr (!LAST) {
+}
+
+// Run the stages from span L to the end.
+template <typename T, int N, int E, int S, int L, int RM = 16, class X>
+__device__ __forceinline__ void fft_from(cx<T> (&a)[E], int t,
+                                         const cx<T>* __restrict__ tw, int tws,
+                                         const X& xch) {
+    constexpr int R = stage_radix<N, E, L, RM>::value;
+    fft_stage<T, N, E, S, L, RM>(a, t, tw, tws);
+    if constexpr (L * R < N) {
         xch.template run<N, E, L, R>(a, t);
         fft_from<T, N, E, S, L * R, RM>(a, t, tw, tws, xch);
     }

@@ -23,9 +23,15 @@ __device__ __forceinline__ C* at_bytes(C* p, uint32_t off) {
 // FFT stages of R transforms side by side per thread (a[y], y < R), sharing
 // their twiddles and barriers; exchanges through LDS as real, then imaginary
 // parts.  Column c of TC; transform y occupies its own padded N x TC block.
-template <typename T, int N, int E, int R, int S, int L, int RM, int TC, int PS>
+// gap0, gap1: other work for the first exchange, beside the reads of the real
+// and of the imaginary parts.
+struct no_gap {
+    __device__ void operator()() const {}
+};
+template <typename T, int N, int E, int R, int S, int L, int RM, int TC, int PS, class G0 = no_gap,
+          class G1 = no_gap>
 __device__ __forceinline__ void fft_multi(cx<T> (&a)[R][E], int t, int c, const cx<T>* __restrict__ tw,
-                                          int tws, T* lds) {
+                                          int tws, T* lds, G0 gap0 = {}, G1 gap1 = {}) {
     constexpr int RX = stage_radix<N, E, L, RM>::value;
     constexpr int NB = E / RX, TPT = N / E;
     constexpr int NP = padded_len<N, PS>::value;
@@ -64,6 +70,8 @@ __device__ __forceinline__ void fft_multi(cx<T> (&a)[R][E], int t, int c, const 
                 for (int s = 0; s < E; ++s)
                     lds[y * NP * TC + ix.at(G::template out_pad<PS>(t, s))] = part ? a[y][s].y : a[y][s].x;
             __syncthreads();
+            if (part == 0) gap0();
+            else gap1();
 #pragma unroll
             for (int y = 0; y < R; ++y)
 #pragma unroll
@@ -77,6 +85,59 @@ __device__ __forceinline__ void fft_multi(cx<T> (&a)[R][E], int t, int c, const 
         fft_multi<T, N, E, R, S, L * RX, RM, TC, PS>(a, t, c, tw, tws, lds);
     }
 }
+
+// The real column kz = M of a tile's N rows beside the tile's own work: stage I
+// of its forward transform, run by threads t < N/4 between two of the tile's
+// barriers.  keep() takes Re Z[0] of every row from the column exchange, stage 0
+// X[M] = Re Z[0] - Im Z[0], stage I buf[I % 2]; each writes the other buffer, the
+// last in natural order.  Four values a thread, as these come on top of the
+// tile's own (8 or 16 would cost FP64 a wave per SIMD, or spill).
+template <typename T, int N>
+struct side_column {
+    static constexpr int E = 4, THREADS = N / E;
+    static constexpr int PS = first_radix_shift<E>::value, NP = padded_len<N, PS>::value;
+    static constexpr int STAGES = (ilog2_c(N) + 1) / 2;
+
+    cx<T> (*buf)[NP];
+    // re, im: row 0's part in the exchange buffer, rows LD apart
+    template <int LD>
+    __device__ __forceinline__ void keep(int t, const T* re) const {
+        if (t >= THREADS) return;
+#pragma unroll
+        for (int m = 0; m < E; ++m) buf[0][lds_pad<PS>(t + m * THREADS)].x = re[(t + m * THREADS) * LD];
+    }
+    template <int LD>
+    __device__ __forceinline__ void first(int t, const T* im, T mul) const {
+        if (t >= THREADS) return;
+        cx<T> e[E];
+#pragma unroll
+        for (int m = 0; m < E; ++m) {
+            const int n = t + m * THREADS;
+            e[m] = cx<T>{(buf[0][lds_pad<PS>(n)].x - im[n * LD]) * mul, T(0)};
+        }
+        run<0>(e, t, nullptr, 0);
+    }
+    template <int I>
+    __device__ __forceinline__ void stage(int t, const cx<T>* __restrict__ tw, int tws) const {
+        if constexpr (I < STAGES) {
+            if (t >= THREADS) return;
+            cx<T> e[E];
+#pragma unroll
+            for (int m = 0; m < E; ++m) e[m] = buf[I % 2][lds_pad<PS>(t + m * THREADS)];
+            run<I>(e, t, tw, tws);
+        }
+    }
+    template <int I>
+    __device__ __forceinline__ void run(cx<T> (&e)[E], int t, const cx<T>* __restrict__ tw,
+                                        int tws) const {
+        constexpr int L = 1 << (2 * I);
+        using G = xgeom<N, E, L, stage_radix<N, E, L>::value>;
+        fft_stage<T, N, E, -1, L, 16>(e, t, tw, tws);
+#pragma unroll
+        for (int m = 0; m < E; ++m) buf[(I + 1) % 2][G::template out_pad<PS>(t, m)] = e[m];
+    }
+    __device__ __forceinline__ cx<T> get(int k) const { return buf[STAGES % 2][lds_pad<PS>(k)]; }
+};
 
 // ---------------------------------------------------------------- plane 2D R2C / C2R
 // z R2C and y C2C of one x-plane (section 3, step 1; R = 1), or of every R-th
@@ -96,15 +157,16 @@ __device__ __forceinline__ void fft_multi(cx<T> (&a)[R][E], int t, int c, const 
 // parts.  The column pair makes the real split (bin k from Z[k] and Z[M-k];
 // the inverse's pre-process likewise) a register operation with one twiddle
 // per thread.  Columns 0 and M/2, their own partners, share thread p = 0.
-// The z half spectrum has M + 1 columns; kz = 0 and kz = M are real
-// for a real row, so they travel together as one complex column
-// P = X[.][0] + i X[.][M] (two real transforms for one complex one) and are
-// separated after the y FFT: X0 = (P + conj P(-k1)) / 2, XM = (P - conj
-// P(-k1)) / 2i.  The inverse packs the Hermitian parts of the kz = 0 and
-// kz = M columns the same way (the C2R keeps only the real part of those
-// columns after the y inverse, which is the inverse of their Hermitian
-// parts; both hold for the rows of one y0 by themselves, which are real
-// sequences in j).  Every load of a tile precedes the first barrier and
+// The z half spectrum has M + 1 columns.  Forward, column M is a side_column
+// of the first TY threads, in the gaps of the column exchange: as the
+// imaginary part of column 0 (both are real for a real row) it would take on
+// rounding errors of column 0's size, 1.4 to 2.4 times its own in FP32 on
+// fields that vary slowly along z.  The inverse does pack the two, P = G0 + i GM
+// of their Hermitian parts (the C2R keeps only the real part of those columns
+// after the y inverse, which is the inverse of their Hermitian parts; this
+// holds for the rows of one y0 by themselves, which are real sequences in j):
+// there they are summed into the same real row right after.  Every load of a
+// tile precedes the first barrier and
 // every store follows the last, so with R = 1 a plane may be transformed in
 // place.
 // TWD: the tile applies the twiddles W_N^(y0 k1) itself, which leaves an
@@ -130,7 +192,10 @@ struct plane_shape {
                          D = 6 * NY;
     static constexpr int AB = A > B ? A : B, CD = C > D ? C : D;
     static constexpr int LDS = AB > CD ? AB : CD;  // values of type T
+    using nyquist = side_column<T, NY>;
     static_assert(M % E == 0 && NY % EY == 0 && NY * TZ == H * TY, "plane shape");
+    static_assert(nyquist::THREADS <= NT && nyquist::STAGES <= (TY > 1 ? 4 : 2),
+                  "a barrier follows every stage of the side column");
 };
 
 template <typename T, int N, int R, int E, int W, int ORD = kGrouped, bool TWD = false>
@@ -156,12 +221,15 @@ __global__ __launch_bounds__((plane_shape<T, N, R, E>::NT), W) void k_plane_r2c(
     using IR = idx_rows<P::PS>;
     fft_regs<T, M, E, -1, RM>(a, t, tw, 2, xch_split<T, IR>{lds, IR{r * P::MP}});
 
-    // rows -> columns
+    // rows -> columns, and the side column's stages after the barriers
+    __shared__ cx<T> nyq[2][P::nyquist::NP];
+    const typename P::nyquist col_m{nyq};
     const cx<T> w = tw[p];
     cx<T> b[2][EY];
 #pragma unroll
     for (int m = 0; m < E; ++m) lds[r * P::LD + t + TZ * m] = a[m].x;
     __syncthreads();
+    col_m.template keep<P::LD>(tid, lds);
 #pragma unroll
     for (int m = 0; m < EY; ++m) {
         b[0][m].x = lds[(s + TY * m) * P::LD + p];
@@ -176,42 +244,45 @@ __global__ __launch_bounds__((plane_shape<T, N, R, E>::NT), W) void k_plane_r2c(
         b[0][m].y = lds[(s + TY * m) * P::LD + p];
         b[1][m].y = lds[(s + TY * m) * P::LD + c1];
     }
+    col_m.template first<P::LD>(tid, lds, mul_edge);
     __syncthreads();
+    col_m.template stage<1>(tid, tw, R);
     // real split, bin multipliers applied: with A = (Z[p] + conj Z[M-p])/2,
     // B = (Z[p] - conj Z[M-p])/2 and w = W_N^p,
     //   X[p] = A - i w B,  X[M-p] = conj(A + i w B);
-    // p = 0: column 0 becomes (X[0], X[M]) = (Re Z[0] + Im Z[0], Re - Im),
-    // column M/2 its conjugate.
+    // p = 0: X[0] = Re Z[0] + Im Z[0], and column M/2 is its own conjugate.
     const bool edge = p == 0;
 #pragma unroll
     for (int m = 0; m < EY; ++m) {
         const cx<T> z = b[0][m], v = b[1][m];
         const cx<T> A = scal(z + conjg(v), T(0.5)), B = cmul(w, scal(z - conjg(v), T(0.5)));
         b[0][m].x = edge ? (z.x + z.y) * mul_edge : (A.x + B.y) * mul_int;
-        b[0][m].y = edge ? (z.x - z.y) * mul_edge : (A.y - B.x) * mul_int;
+        b[0][m].y = edge ? T(0) : (A.y - B.x) * mul_int;
         b[1][m].x = edge ? v.x * mul_int : (A.x - B.y) * mul_int;
         b[1][m].y = edge ? -v.y * mul_int : (-A.y - B.x) * mul_int;
     }
 
     // y phase: NY-point FFTs of columns p and c1
-    fft_multi<T, NY, EY, 2, -1, 1, RM, H, P::PY>(b, s, p, tw, R, lds);
+    fft_multi<T, NY, EY, 2, -1, 1, RM, H, P::PY>(
+        b, s, p, tw, R, lds, [&] { col_m.template stage<2>(tid, tw, R); },
+        [&] { col_m.template stage<3>(tid, tw, R); });
+    if constexpr (TY == 1) __syncthreads();  // the side column's last stage
 
-    // the packed column goes through LDS; one thread per row separates it
-    cx<T>* col0 = reinterpret_cast<cx<T>*>(lds);
-    if (p == 0) {
+    // All of b before the first store: otherwise the last stage is spread over
+    // the stores and FP32 N = 256 (E = 32) spills 24 registers.
 #pragma unroll
-        for (int m = 0; m < EY; ++m) col0[s + TY * m] = b[0][m];
-    }
-    __syncthreads();
+    for (int m = 0; m < EY; ++m)
+        asm volatile("" : "+v"(b[0][m].x), "+v"(b[0][m].y), "+v"(b[1][m].x), "+v"(b[1][m].y));
     // store rows of the half spectrum: wave lanes are consecutive columns
     auto row_of = [&](int k1) {
         const int64_t row = plane * N + y0 * NY + k1;
         return out + (R > 1 && !TWD ? row : map_row(row, map)) * K;
     };
     // twiddles first: a load behind the stores would wait for them
-    cx<T> wt{T(1), T(0)};
+    cx<T> xm{};
+    if (tid < NY) xm = col_m.get(tid);
     if constexpr (TWD) {
-        if (tid < NY) wt = tw[y0 * tid];
+        if (tid < NY) xm = cmul(xm, tw[y0 * tid]);
 #pragma unroll
         for (int m = 0; m < EY; ++m) {
             const cx<T> wm = tw[y0 * (s + TY * m)];
@@ -222,21 +293,10 @@ __global__ __launch_bounds__((plane_shape<T, N, R, E>::NT), W) void k_plane_r2c(
 #pragma unroll
     for (int m = 0; m < EY; ++m) {
         cx<T>* dst = row_of(s + TY * m);
-        if (p != 0) dst[p] = b[0][m];
+        dst[p] = b[0][m];
         dst[c1] = b[1][m];
     }
-    if (tid < NY) {
-        const cx<T> v = col0[tid], pc = conjg(col0[(NY - tid) & (NY - 1)]);
-        const cx<T> sum = v + pc, dif = v - pc;
-        cx<T> x0{T(0.5) * sum.x, T(0.5) * sum.y}, xm{T(0.5) * dif.y, T(-0.5) * dif.x};
-        if constexpr (TWD) {
-            x0 = cmul(x0, wt);
-            xm = cmul(xm, wt);
-        }
-        cx<T>* dst = row_of(tid);
-        dst[0] = x0;  // X[k1][0]
-        dst[M] = xm;  // X[k1][M] = dif / 2i
-    }
+    if (tid < NY) row_of(tid)[M] = xm;
 }
 
 template <typename T, int N, int R, int E, int W, int ORD = kGrouped, bool TWD = false>
@@ -881,7 +941,7 @@ template <typename T, int N>
 struct plane_cfg {
     static constexpr bool F64 = sizeof(T) == 8;
     static constexpr int E = N <= 64 ? 8 : N == 128 ? 16 : 32;
-    static constexpr int W = F64 && N == 128 ? 2 : 4;
+    static constexpr int W = N == 128 ? (F64 ? 2 : 8) : 4;
 };
 
 template <typename T, int N>
@@ -946,7 +1006,7 @@ hipError_t launch_plane(bool f64, bool forward, int n, const void* in, void* out
 //        N = 256, R = 4: 207 / 209 + 229 (397 / 414 + 242)
 //   FP32 N = 128, R = 2: 208 / 215 + 182 (228 / 220 + 218)
 //        N = 256, R = 4: 212 / 206 + 217 (327 / 333 + 233)
-//        N = 512, R = 8: 226 / 237 + 311 (448 / 445 + 214)
+//        N = 512, R = 8: 236 / 237 + 311 (448 / 445 + 214)
 // and over 1.07 GB FP64 N = 512, R = 8: 446 / 492 + 598 (815 / 803 + 415).
 // N = 64 planes have room as they are.  Tiles in groups (ORD) of 64 run the x
 // pass at 4.73 TB/s for FP64 256 (contiguous 4.41), 4.93 for FP32 256 (4.43),
@@ -958,7 +1018,9 @@ struct split_cfg {
     static constexpr bool F64 = sizeof(T) == 8;
     static constexpr int R = N / 64;
     static constexpr int E = !F64 && N == 128 ? 8 : 16;
-    static constexpr int W = F64 && (N == 128 || N == 512) ? 2 : 4;
+    // FP32 512: two tiles of 16 waves on a CU need 64 registers or fewer (pair
+    // 1084 us, 1125 with 74)
+    static constexpr int W = F64 ? (N == 256 ? 4 : 2) : N == 512 ? 8 : 4;
     static constexpr int TC = N == 128 ? 32 : N == 256 ? (F64 ? 8 : 16) : (F64 ? 4 : 8);
     static constexpr int EX = F64 && N == 512 ? 4 : 8;
     static constexpr int WX = R * EX * int(sizeof(cx<T>)) > 256 ? 2 : 4;
