@@ -410,7 +410,8 @@ __global__ __launch_bounds__((plane_shape<T, N, R, E>::NT), W) void k_plane_c2r(
 // k_strided of shorter lines.  NY = 1 is a plain z pass.  As in k_plane_*,
 // thread (r, t) transforms row r, thread p then holds the columns p and M - p
 // (p = lt + NT1 q, q < Q) of all NY rows, so the real split and the y step
-// need no further exchange, and kz = 0 and kz = M travel as one column.
+// need no further exchange.  Thread 0 takes column M besides 0 and M/2; the
+// inverse packs the Hermitian parts of 0 and M into one, as in k_plane_c2r.
 // Exchanges are split into real and imaginary parts: whole values would
 // leave 4 waves on a CU at N = 4096.  Out of place for NY > 1.
 template <typename T, int N, int NY, int E, int G>
@@ -501,35 +502,32 @@ __global__ __launch_bounds__((rows_shape<T, N, NY, E, G>::NT), W) void k_rows_r2
         const int p = lt + NT1 * q, c1 = p == 0 ? H : M - p;
         const cx<T> w = WQ ? wq[q] : tw[p];
         const bool edge = p == 0;
+        if (q == 0 && edge) {
+            // X[M] = Re Z[0] - Im Z[0], a real column; before the others, as FP64
+            // with a y step has no registers to spare
+            cx<T> xm[NY];
+#pragma unroll
+            for (int j = 0; j < NY; ++j)
+                xm[j] = cx<T>{(b[0][0][j].x - b[0][0][j].y) * mul_edge, T(0)};
+            dft<NY, -1>(xm);
+#pragma unroll
+            for (int k1 = 0; k1 < NY; ++k1) put(k1, M, k1 > 0 ? cmul(xm[k1], wy[k1]) : xm[k1]);
+        }
         cx<T> u[NY], v[NY];
 #pragma unroll
         for (int j = 0; j < NY; ++j) {
             const cx<T> z = b[q][0][j], y = b[q][1][j];
             const cx<T> A = scal(z + conjg(y), T(0.5)), B = cmul(w, scal(z - conjg(y), T(0.5)));
             u[j].x = edge ? (z.x + z.y) * mul_edge : (A.x + B.y) * mul_int;
-            u[j].y = edge ? (z.x - z.y) * mul_edge : (A.y - B.x) * mul_int;
+            u[j].y = edge ? T(0) : (A.y - B.x) * mul_int;
             v[j].x = edge ? y.x * mul_int : (A.x - B.y) * mul_int;
             v[j].y = edge ? -y.y * mul_int : (-A.y - B.x) * mul_int;
         }
         dft<NY, -1>(u);
         dft<NY, -1>(v);
-        if (edge) {
-            // X0 = (P + conj P(-k1)) / 2, XM = (P - conj P(-k1)) / 2i
-#pragma unroll
-            for (int k1 = 0; k1 < NY; ++k1) {
-                const cx<T> pc = conjg(u[(NY - k1) % NY]), s = u[k1] + pc, d = u[k1] - pc;
-                cx<T> x0{T(0.5) * s.x, T(0.5) * s.y}, xm{T(0.5) * d.y, T(-0.5) * d.x};
-                if (k1 > 0) {
-                    x0 = cmul(x0, wy[k1]);
-                    xm = cmul(xm, wy[k1]);
-                }
-                put(k1, 0, x0);
-                put(k1, M, xm);
-            }
-        }
 #pragma unroll
         for (int k1 = 0; k1 < NY; ++k1) {
-            if (!edge) put(k1, p, k1 > 0 ? cmul(u[k1], wy[k1]) : u[k1]);
+            put(k1, p, k1 > 0 ? cmul(u[k1], wy[k1]) : u[k1]);
             put(k1, c1, k1 > 0 ? cmul(v[k1], wy[k1]) : v[k1]);
         }
     }

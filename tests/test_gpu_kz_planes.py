@@ -21,6 +21,7 @@ DTYPES = pytest.mark.parametrize("dtype", [F64, F32], ids=["f64", "f32"])
 # (n, x, batch): step 1 of slabs (x < n) and whole grids
 PLANE_TILES = [(32, 4, 2), (32, 32, 2), (64, 8, 2), (64, 64, 1), (128, 8, 1), (128, 128, 1),
                (256, 2, 1), (256, 256, 1), (512, 2, 1), (512, 512, 1), (1024, 2, 1)]
+ROW_TILES = [(2048, 1, 2), (4096, 1, 1)]
 
 
 def _spectrum(p, inplace, f):
@@ -33,7 +34,7 @@ def _spectrum(p, inplace, f):
 
 @DTYPES
 @pytest.mark.parametrize("inplace", [False, True], ids=["out_of_place", "inplace"])
-@pytest.mark.parametrize("n,x,batch", PLANE_TILES)
+@pytest.mark.parametrize("n,x,batch", PLANE_TILES + ROW_TILES)
 def test_empty_planes_stay_empty(n, x, batch, inplace, dtype):
     p = Plan(n, dtype, slab_x=x, batch=batch, inplace=inplace)
     g = synth.uniform((batch, x, n, 1), 31000 + n + x, dtype, "cpu").cuda().expand(p.real_shape)
@@ -45,3 +46,17 @@ def test_empty_planes_stay_empty(n, x, batch, inplace, dtype):
     F = _spectrum(p, inplace, g * sign)
     assert torch.count_nonzero(F[..., 0]) == 0
     assert torch.count_nonzero(F[..., n // 2]) > 0
+
+
+@DTYPES
+@pytest.mark.parametrize("n", [16, 1024, 2048, 4096])
+def test_z_pass_near_the_largest_value(n, dtype):
+    """Rows whose kz = 0 bin is 0.9 of the type's largest value keep it, and
+    the other bins are 0 (a constant row)."""
+    p = Plan(n, dtype, slab_x=1)
+    top = 0.9 * torch.finfo(dtype).max
+    F = p.z_r2c(torch.full(p.real_shape, top / n, dtype=dtype, device="cuda"))
+    assert torch.isfinite(torch.view_as_real(F)).all()
+    # log2 N rounded additions, one unit each
+    assert ((F[..., 0].real / top - 1).abs() <= (n.bit_length() + 2) * torch.finfo(dtype).eps).all()
+    assert torch.count_nonzero(F[..., 0].imag) == 0 and torch.count_nonzero(F[..., n // 2]) == 0
