@@ -653,13 +653,21 @@ __global__ __launch_bounds__((rows_shape<T, N, NY, E, G>::NT), W) void k_rows_c2
 //   thread tid = (y, z) = y M + z    holds the x line of (y, z),
 //          tid = (x, z) = x M + z    the y line,
 //          l = x N + y, l = tid and tid + NT, the two z lines.
-// The real split acts on the 3D transform Z of the packed grid: with
-// C = conj Z(-kx, -ky, -kz), X = (Z + C)/2 - (i/2) W_N^kz (Z - C), and
-// X(kz = M) = (Z + C)/2 + (i/2)(Z - C) at kz = 0; the inverse forms
-// Z' = (G + P) + i conj(W_N^kz) (G - P), P = conj G(-kx, -ky, M - kz), with
-// the Hermitian parts of kz = 0 and kz = M at kz = 0 (their anti-Hermitian
-// parts do not reach the real field).  Exchanges go real parts first, then
-// imaginary parts.  Row stride M + 1 and plane stride N (M + 1) + M keep the
+// Forward, z comes first and its real split follows in the registers of the two
+// lines, so that y and x act on every kz by itself, with rounding errors of its
+// own size (y first, on the packed grid, spreads those of a strong kz = 0 over
+// all kz: 500 times the error at kz = 1 in FP32 where kz = 0 is 1000 times
+// larger).  kz = 0 and kz = M are real N x N images; each takes half of the
+// slots of one column, pairs of its rows as real and imaginary parts:
+// T(x', y) = X(2x', y) + i X(2x' + 1, y), kz = 0 in slots 2x', kz = M in
+// 2x' + 1.  y runs on these as on any column, x as two N/2-point transforms, and
+// with C = conj T(-kx, -ky), E = (T + C)/2, O = (T - C)/2i the image's transform
+// is E + W_N^kx O at kx and E - W_N^kx O at kx + N/2.
+// The inverse forms Z' = (G + P) + i conj(W_N^kz) (G - P), P = conj G(-kx, -ky,
+// M - kz), with the Hermitian parts of kz = 0 and kz = M at kz = 0 (their
+// anti-Hermitian parts do not reach the real field), and runs the 3D transform
+// of the packed grid.  Exchanges go real parts first, then imaginary parts.
+// Row stride M + 1 and plane stride N (M + 1) + M keep the
 // lanes of all three line orders on different LDS banks (and leave room for
 // the M + 1 columns of a half spectrum).  All loads precede the first
 // barrier and all stores follow the last: grids may be transformed in place.
@@ -691,6 +699,33 @@ __device__ __forceinline__ void box_exchange(T* lds, cx<T> (&a)[N], F&& from, G&
     }
 }
 
+// N-point DFT as the two N/2-point DFTs of the even and odd inputs, joined, or
+// left as they are in the halves of a.
+template <int N, int S, typename T>
+__device__ __forceinline__ void dft_halves(cx<T>* a, const cx<T>* __restrict__ tw, bool join) {
+    cx<T> e[N / 2], o[N / 2];
+#pragma unroll
+    for (int i = 0; i < N / 2; ++i) {
+        e[i] = a[2 * i];
+        o[i] = a[2 * i + 1];
+    }
+    dft<N / 2, S>(e);
+    dft<N / 2, S>(o);
+    if (join) {
+#pragma unroll
+        for (int k = 0; k < N / 2; ++k) {
+            const cx<T> u = e[k], v = k > 0 ? twiddle<S>(o[k], tw[k]) : o[0];
+            e[k] = u + v;
+            o[k] = u - v;
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < N / 2; ++k) {
+        a[k] = e[k];
+        a[k + N / 2] = o[k];
+    }
+}
+
 template <typename T, int N>
 __global__ __launch_bounds__((box_shape<T, N>::NT), (box_shape<T, N>::W)) void k_box_r2c(
     const T* in, cx<T>* out, const cx<T>* __restrict__ tw, int64_t rs, T mul_edge, T mul_int) {
@@ -709,39 +744,82 @@ __global__ __launch_bounds__((box_shape<T, N>::NT), (box_shape<T, N>::W)) void k
     cx<T> a[N];
 #pragma unroll
     for (int m = 0; m < N; ++m) a[m] = src[(hi * N + m) * half + z];
-    dft<N, -1>(a);
     box_exchange<N>(lds, a, yline, zline);
-    dft<M, -1>(a);
-    dft<M, -1>(a + M);
-    box_exchange<N>(lds, a, zline, xline);
-    dft<N, -1>(a);
 
-    // real split: thread (ky, kz) reads the mirrored values of its x line
-    const int ym = (N - hi) & (N - 1), zm = (M - z) & (M - 1);
-    const cx<T> w = tw[z];
-    T s[N];  // sums of the real parts; a[m].x becomes their difference
+    // z and its real split (as in k_plane_r2c); X[0] and X[M] in slot 0
 #pragma unroll
-    for (int m = 0; m < N; ++m) lds[xline(m)] = a[m].x;
-    __syncthreads();
+    for (int h = 0; h < 2; ++h) {
+        cx<T>* b = a + h * M;
+        dft<M, -1>(b);
+        b[0] = cx<T>{(b[0].x + b[0].y) * mul_edge, (b[0].x - b[0].y) * mul_edge};
 #pragma unroll
-    for (int m = 0; m < N; ++m) {
-        const T c = lds[((N - m) & (N - 1)) * SX + ym * SY + zm];
-        s[m] = T(0.5) * (a[m].x + c);
-        a[m].x = T(0.5) * (a[m].x - c);
+        for (int k = 1; k < M / 2; ++k) {
+            const cx<T> u = b[k], v = conjg(b[M - k]);
+            const cx<T> A = scal(u + v, T(0.5)), B = cmul(tw[k], scal(u - v, T(0.5)));
+            b[k] = cx<T>{(A.x + B.y) * mul_int, (A.y - B.x) * mul_int};
+            b[M - k] = cx<T>{(A.x - B.y) * mul_int, (-A.y - B.x) * mul_int};
+        }
+        b[M / 2] = cx<T>{b[M / 2].x * mul_int, -b[M / 2].y * mul_int};
+    }
+
+    // z lines -> y lines; a line of even x fills the real parts of its pair's
+    // two slots 0, one of odd x the imaginary parts: X[0] in the even slot,
+    // X[M] in the odd one
+    const T x0[2] = {a[0].x, a[M].x};
+#pragma unroll
+    for (int part = 0; part < 2; ++part) {
+#pragma unroll
+        for (int m = 0; m < N; ++m) {
+            if (m % M != 0) {
+                lds[zline(m)] = part ? a[m].y : a[m].x;
+            } else if (((tid + (m / M) * NT) / N) % 2 == part) {
+                lds[zline(m) - part * SX] = x0[m / M];
+                lds[zline(m) - part * SX + SX] = a[m].y;
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int m = 0; m < N; ++m) {
+            const T v = lds[yline(m)];
+            if (part) a[m].y = v;
+            else a[m].x = v;
+        }
+        __syncthreads();
+    }
+    dft<N, -1>(a);
+    box_exchange<N>(lds, a, yline, xline);
+    dft_halves<N, -1>(a, tw, z != 0);
+
+    // the two images apart: (kx, ky) and (kx + N/2, ky) of both per thread
+    cx<T>* mir = reinterpret_cast<cx<T>*>(lds);
+    if (z == 0) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) mir[i * N + hi] = a[i];
     }
     __syncthreads();
+    const int q = tid / N, ky = tid % N, qm = (N / 2 - q) & (N / 2 - 1), ym = (N - ky) & (N - 1);
+    const cx<T> w = tw[q];
 #pragma unroll
-    for (int m = 0; m < N; ++m) lds[xline(m)] = a[m].y;
+    for (int im = 0; im < 2; ++im) {  // kz = 0, kz = M
+        const cx<T> u = mir[(q + im * (N / 2)) * N + ky], c = conjg(mir[(qm + im * (N / 2)) * N + ym]);
+        const cx<T> E = scal(u + c, T(0.5)), D = scal(u - c, T(0.5));
+        const cx<T> O = cmul(w, cx<T>{D.y, -D.x});
+        mir[(im + 1) * N * N + q * N + ky] = E + O;
+        mir[(im + 1) * N * N + (q + N / 2) * N + ky] = E - O;
+    }
     __syncthreads();
+    // both back to the column's threads: rows of K bins are complete within two
+    // stores (kz = 0 and M stored by the threads that form them reach memory in
+    // pieces: FP64 N = 32, 1000 grids 173 us against 152)
     cx<T>* dst = out + int64_t(blockIdx.x) * N * N * K + hi * K + z;
-    const T f = z == 0 ? mul_edge : mul_int;
+    if (z == 0) {
+#pragma unroll
+        for (int m = 0; m < N; ++m) a[m] = mir[N * N + m * N + hi];
+    }
 #pragma unroll
     for (int m = 0; m < N; ++m) {
-        const T c = lds[((N - m) & (N - 1)) * SX + ym * SY + zm];
-        const cx<T> A{s[m], T(0.5) * (a[m].y - c)}, D{a[m].x, T(0.5) * (a[m].y + c)};
-        const cx<T> B = cmul(w, D);
-        dst[m * N * K] = cx<T>{(A.x + B.y) * f, (A.y - B.x) * f};
-        if (z == 0) dst[m * N * K + M] = cx<T>{(A.x - B.y) * f, (A.y + B.x) * f};
+        dst[m * N * K] = a[m];
+        if (z == 0) dst[m * N * K + M] = mir[2 * N * N + m * N + hi];
     }
 }
 
@@ -1254,12 +1332,15 @@ static hipError_t box_n(bool forward, const void* in, void* out, const void* tw,
 }
 
 // One workgroup per grid pays where a grid is tiny or where there are enough
-// of them for the chip.  GPU time of a forward, box kernel against plane and
-// x passes (three passes at N = 16), us: FP64 N = 16 5.4 / 9.4 for one grid,
-// 15.8 / 53 for 1000; N = 32 17 / 8 for one, 18.2 / 14.2 for 32, 19.3 / 23.2
-// for 64, 137 / 195 for 1000; FP32 N = 16 4.7 / 7.9 and 10.0 / 44, N = 32
-// 12.6 / 7.3, 13.4 / 10.3, 14.1 / 15.4 and 62 / 97.
-bool box_supported(int n, int64_t grids) { return n == 16 || (n == 32 && grids >= 64); }
+// of them for the chip.  Box kernel against plane and x passes (three passes at
+// N = 16), us, forward / inverse: FP64 N = 16, GPU time of a forward, 5.4 / 9.4
+// for one grid, 18 / 53 for 1000; calls of N = 32 FP64 25 / 24 (23 / 24) for 64
+// grids, 26.5 / 25.8 (27.2 / 25.0) for 96, 30 / 28 (33 / 32) for 128, 150 / 157
+// (207 / 208) for 1000; FP32 17.7 / 15.8 (19.1 / 17.7) for 64, 61 / 62 (99 / 101)
+// for 1000.
+bool box_supported(bool f64, int n, int64_t grids) {
+    return n == 16 || (n == 32 && grids >= (f64 ? 96 : 64));
+}
 
 hipError_t launch_box(bool f64, bool forward, int n, const void* in, void* out, const void* tw,
                       int64_t grids, int64_t rs, double me, double mi, hipStream_t s) {

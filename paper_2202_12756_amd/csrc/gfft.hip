@@ -316,7 +316,7 @@ gfft_status run_y_lines(const gfft_plan* p, const void* src, void* data, int sig
 // One pass for the whole transform of small full grids.
 bool box_pass(const gfft_plan* p) {
     return !p->pencil && p->p == 1 && mfma_terms(p) == 0 &&
-           gfft::box_supported(int(p->n), p->batch);
+           gfft::box_supported(f64(p), int(p->n), p->batch);
 }
 
 gfft_status run_box(const gfft_plan* p, bool fwd, const void* in, void* out, double scale,

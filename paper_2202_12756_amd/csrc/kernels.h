@@ -113,7 +113,7 @@ hipError_t launch_split_x(bool f64, int n, int sign, const void* src, void* dst,
 // workgroup in one pass (box_supported: also says whether `grids` of them are
 // better off so).  rs: reals between real rows (N, or N + 2 in place); `in`
 // and `out` may be the same buffer.
-bool box_supported(int n, int64_t grids);
+bool box_supported(bool f64, int n, int64_t grids);
 hipError_t launch_box(bool f64, bool forward, int n, const void* in, void* out, const void* tw,
                       int64_t grids, int64_t rs, double mul_edge, double mul_int, hipStream_t s);
 

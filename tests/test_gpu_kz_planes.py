@@ -10,7 +10,9 @@ zeros.  With alternating signs along z the same holds for kz = 0.
 import pytest
 import torch
 
+import oracle
 import synth
+from helpers import TOL, host, rel_l2
 from paper_2202_12756_amd import Plan
 
 pytestmark = pytest.mark.gpu
@@ -22,6 +24,7 @@ DTYPES = pytest.mark.parametrize("dtype", [F64, F32], ids=["f64", "f32"])
 PLANE_TILES = [(32, 4, 2), (32, 32, 2), (64, 8, 2), (64, 64, 1), (128, 8, 1), (128, 128, 1),
                (256, 2, 1), (256, 256, 1), (512, 2, 1), (512, 512, 1), (1024, 2, 1)]
 ROW_TILES = [(2048, 1, 2), (4096, 1, 1)]
+BOXES = [(16, 16, 3), (32, 32, 97)]
 
 
 def _spectrum(p, inplace, f):
@@ -34,7 +37,7 @@ def _spectrum(p, inplace, f):
 
 @DTYPES
 @pytest.mark.parametrize("inplace", [False, True], ids=["out_of_place", "inplace"])
-@pytest.mark.parametrize("n,x,batch", PLANE_TILES + ROW_TILES)
+@pytest.mark.parametrize("n,x,batch", BOXES + PLANE_TILES + ROW_TILES)
 def test_empty_planes_stay_empty(n, x, batch, inplace, dtype):
     p = Plan(n, dtype, slab_x=x, batch=batch, inplace=inplace)
     g = synth.uniform((batch, x, n, 1), 31000 + n + x, dtype, "cpu").cuda().expand(p.real_shape)
@@ -46,6 +49,24 @@ def test_empty_planes_stay_empty(n, x, batch, inplace, dtype):
     F = _spectrum(p, inplace, g * sign)
     assert torch.count_nonzero(F[..., 0]) == 0
     assert torch.count_nonzero(F[..., n // 2]) > 0
+
+
+@DTYPES
+@pytest.mark.parametrize("n,x,batch", BOXES + [(32, 4, 2), (64, 64, 1), (128, 128, 1), (256, 2, 1),
+                                               (512, 2, 1), (1024, 1, 1), (2048, 1, 1)])
+def test_odd_planes_beside_a_strong_kz_0(n, x, batch, dtype):
+    """g(x, y) + 1e-4 noise: the odd kz see only the differences f[n] -
+    f[n + N/2] of z's first butterflies, which are exact (1 <= g < 2), so each
+    odd plane is as accurate as on the noise alone.  Its reference is the
+    transform of f - g (exact too), as g has no odd kz."""
+    p = Plan(n, dtype, slab_x=x, batch=batch)
+    g = 1.5 + 0.5 * synth.uniform((batch, x, n, 1), 32000 + n, dtype, "cpu")
+    f = g + 1e-4 * synth.uniform(p.real_shape, 32500 + n, dtype, "cpu")
+    rest = (f.double() - g.double()).numpy()
+    want = oracle.r2c3d(rest) if x == n else oracle.r2c2d_planes(rest)
+    got = host(p.r2c(f.cuda()))
+    for k in (1, 3, n // 4 + 1, n // 2 - 1):
+        assert rel_l2(got[..., k], want[..., k]) <= TOL[dtype], k
 
 
 @DTYPES
