@@ -20,6 +20,14 @@ __device__ __forceinline__ C* at_bytes(C* p, uint32_t off) {
     return reinterpret_cast<C*>(reinterpret_cast<char*>(p) + off);
 }
 
+// Hermitian part of a pair of bins, v at k and u at -k.  A bin that is its own
+// partner keeps its real part, whatever its imaginary part holds (infinities and
+// NaN too): the transform of a real field has none there.
+template <typename T>
+__device__ __forceinline__ cx<T> hermitian(cx<T> v, cx<T> u, bool own) {
+    return {T(0.5) * (v.x + u.x), own ? T(0) : T(0.5) * (v.y - u.y)};
+}
+
 // FFT stages of R transforms side by side per thread (a[y], y < R), sharing
 // their twiddles and barriers; exchanges through LDS as real, then imaginary
 // parts.  Column c of TC; transform y occupies its own padded N x TC block.
@@ -321,7 +329,9 @@ __global__ __launch_bounds__((plane_shape<T, N, R, E>::NT), W) void k_plane_c2r(
         const int64_t row = plane * N + y0 * NY + k1;
         return in + (R > 1 && !TWD ? row : map_row(row, map)) * K;
     };
-    auto turn = [&](cx<T> v, int k1) { return TWD ? cmulc(v, tw[y0 * k1]) : v; };
+    // k1 = 0 is left as it is: a product with 1 - 0i makes NaN of an infinite
+    // imaginary part
+    auto turn = [&](cx<T> v, int k1) { return TWD && k1 != 0 ? cmulc(v, tw[y0 * k1]) : v; };
     cx<T> b[2][EY];
     cx<T>* col0 = reinterpret_cast<cx<T>*>(lds);
 #pragma unroll
@@ -345,8 +355,8 @@ __global__ __launch_bounds__((plane_shape<T, N, R, E>::NT), W) void k_plane_c2r(
     __syncthreads();
     if (tid < NY) {
         const int kn = (NY - tid) & (NY - 1);
-        const cx<T> h0 = scal(col0[tid] + conjg(col0[kn]), T(0.5));
-        const cx<T> hm = scal(col0[NY + tid] + conjg(col0[NY + kn]), T(0.5));
+        const cx<T> h0 = hermitian(col0[tid], col0[kn], tid == kn);
+        const cx<T> hm = hermitian(col0[NY + tid], col0[NY + kn], tid == kn);
         col0[2 * NY + tid] = cx<T>{h0.x - hm.y, h0.y + hm.x};  // h0 + i hm
     }
     __syncthreads();
@@ -592,8 +602,9 @@ __global__ __launch_bounds__((rows_shape<T, N, NY, E, G>::NT), W) void k_rows_c2
             }
 #pragma unroll
             for (int k1 = 0; k1 < NY; ++k1) {
-                const cx<T> h0 = scal(b[0][0][k1] + conjg(b[0][0][(NY - k1) % NY]), T(0.5));
-                const cx<T> hm = scal(h[k1] + conjg(h[(NY - k1) % NY]), T(0.5));
+                constexpr auto kn = [](int k) { return (NY - k) % NY; };
+                const cx<T> h0 = hermitian(b[0][0][k1], b[0][0][kn(k1)], k1 == kn(k1));
+                const cx<T> hm = hermitian(h[k1], h[kn(k1)], k1 == kn(k1));
                 g[k1] = cx<T>{h0.x - hm.y, h0.y + hm.x};
             }
 #pragma unroll
@@ -857,8 +868,8 @@ __global__ __launch_bounds__((box_shape<T, N>::NT), (box_shape<T, N>::W)) void k
     for (int i = 0; i < 2; ++i) {
         const int l = tid + i * NT;
         const int lm = ((N - l / N) & (N - 1)) * N + ((N - l % N) & (N - 1));
-        const cx<T> h0 = scal(g0[i] + conjg(col[lm]), T(0.5) * mul_edge);
-        const cx<T> hm = scal(gm[i] + conjg(col[N * N + lm]), T(0.5) * mul_edge);
+        const cx<T> h0 = scal(hermitian(g0[i], col[lm], l == lm), mul_edge);
+        const cx<T> hm = scal(hermitian(gm[i], col[N * N + lm], l == lm), mul_edge);
         const cx<T> s = h0 + hm, d = h0 - hm;
         col[2 * N * N + l] = cx<T>{s.x - d.y, s.y + d.x};
     }
@@ -978,8 +989,11 @@ __global__ __launch_bounds__((xr_shape<T, N, R, TC, EX>::NT), W) void k_strided_
         }
         dft<R, S>(v);
         if constexpr (S > 0) {
+            // k1 = 0 as it is: see `turn` in k_plane_c2r
+            if (k1 != 0) {
 #pragma unroll
-            for (int y = 1; y < R; ++y) v[y] = twiddle<S>(v[y], w[y]);
+                for (int y = 1; y < R; ++y) v[y] = twiddle<S>(v[y], w[y]);
+            }
         }
 #pragma unroll
         for (int y = 0; y < R; ++y) a[y][i] = v[y];

@@ -81,3 +81,54 @@ def test_z_pass_near_the_largest_value(n, dtype):
     # log2 N rounded additions, one unit each
     assert ((F[..., 0].real / top - 1).abs() <= (n.bit_length() + 2) * torch.finfo(dtype).eps).all()
     assert torch.count_nonzero(F[..., 0].imag) == 0 and torch.count_nonzero(F[..., n // 2]) == 0
+
+
+@DTYPES
+@pytest.mark.parametrize("order", ["natural", "inplace", "send"])
+@pytest.mark.parametrize("n,x,batch", BOXES + [(32, 32, 2), (32, 4, 2), (64, 64, 1), (64, 2, 1),
+                                               (128, 128, 1), (128, 2, 1), (256, 256, 1), (256, 2, 1),
+                                               (512, 512, 1), (512, 16, 1), (1024, 16, 1), (2048, 8, 1),
+                                               (4096, 4, 1)])
+def test_imaginary_parts_that_do_not_count(n, x, batch, order, dtype):
+    """A bin that is its own Hermitian partner counts by its real part alone
+    (w Re(G) in the inverse's definition): infinities and NaN there leave the
+    result as zeros do, bit for bit, and the rest of the spectrum is the same."""
+    if order == "send" and x == n:
+        pytest.skip("a full grid has no send order")
+    p = Plan(n, dtype, slab_x=x, batch=batch, inplace=order == "inplace", fuse_pack=order == "send")
+    own = [0, n // 2]
+    torch.manual_seed(33000 + n)
+    g = torch.randn((batch, x, n, n // 2 + 1, 2), dtype=dtype, device="cuda")
+
+    def inverse(value):
+        v = g.clone()
+        for ky in own:
+            for kz in own:
+                v[:, own if x == n else slice(None), ky, kz, 1] = value
+        c = torch.view_as_complex(v)
+        if order == "inplace":
+            return p.c2r_(c, scale=0.5).clone()
+        return p.c2r(p.pack(c) if order == "send" else c, scale=0.5)
+
+    want = inverse(0.0)
+    assert torch.isfinite(want).all()
+    for value in (float("inf"), float("nan")):
+        assert torch.equal(inverse(value), want)
+
+
+@DTYPES
+@pytest.mark.parametrize("n", [16, 64, 1024, 2048, 4096])
+def test_z_pass_discards_edge_imaginary_parts(n, dtype):
+    """gfft_exec_z_c2r: the imaginary parts of kz = 0 and kz = N/2 are
+    discarded, whatever they hold."""
+    p = Plan(n, dtype, slab_x=1)
+    torch.manual_seed(34000 + n)
+    g = torch.randn(p.spectrum_shape + (2,), dtype=dtype, device="cuda")
+    out = []
+    for value in (0.0, float("inf"), float("nan")):
+        v = g.clone()
+        v[..., 0, 1] = value
+        v[..., n // 2, 1] = value
+        out.append(p.z_c2r(torch.view_as_complex(v)))
+    assert torch.isfinite(out[0]).all()
+    assert torch.equal(out[1], out[0]) and torch.equal(out[2], out[0])
