@@ -836,7 +836,7 @@ __global__ __launch_bounds__((box_shape<T, N>::NT), (box_shape<T, N>::W)) void k
 
 template <typename T, int N>
 __global__ __launch_bounds__((box_shape<T, N>::NT), (box_shape<T, N>::W)) void k_box_c2r(
-    const cx<T>* in, T* out, const cx<T>* __restrict__ tw, int64_t rs, T mul_edge, T mul_int) {
+    const cx<T>* in, T* out, const cx<T>* __restrict__ tw, int64_t rs, T scale, T weight) {
     using P = box_shape<T, N>;
     constexpr int M = P::M, K = P::K, NT = P::NT, SY = P::SY, SX = P::SX;
     __shared__ T lds[P::LDS];
@@ -868,8 +868,8 @@ __global__ __launch_bounds__((box_shape<T, N>::NT), (box_shape<T, N>::W)) void k
     for (int i = 0; i < 2; ++i) {
         const int l = tid + i * NT;
         const int lm = ((N - l / N) & (N - 1)) * N + ((N - l % N) & (N - 1));
-        const cx<T> h0 = scal(hermitian(g0[i], col[lm], l == lm), mul_edge);
-        const cx<T> hm = scal(hermitian(gm[i], col[N * N + lm], l == lm), mul_edge);
+        const cx<T> h0 = hermitian(g0[i], col[lm], l == lm);
+        const cx<T> hm = hermitian(gm[i], col[N * N + lm], l == lm);
         const cx<T> s = h0 + hm, d = h0 - hm;
         col[2 * N * N + l] = cx<T>{s.x - d.y, s.y + d.x};
     }
@@ -901,7 +901,7 @@ __global__ __launch_bounds__((box_shape<T, N>::NT), (box_shape<T, N>::W)) void k
     for (int m = 0; m < N; ++m) {
         const T c = lds[((N - m) & (N - 1)) * SX + ym * SY + zm];
         const cx<T> D = cmulc(cx<T>{d[m], a[m].y + c}, w);
-        const cx<T> v{(a[m].x - D.y) * mul_int, (a[m].y - c + D.x) * mul_int};
+        const cx<T> v{(a[m].x - D.y) * weight, (a[m].y - c + D.x) * weight};
         a[m].x = z == 0 ? a[m].x : v.x;
         a[m].y = z == 0 ? a[m].y : v.y;
     }
@@ -911,6 +911,10 @@ __global__ __launch_bounds__((box_shape<T, N>::NT), (box_shape<T, N>::W)) void k
     box_exchange<N>(lds, a, xline, zline);
     dft<M, +1>(a);
     dft<M, +1>(a + M);
+    // the scale between the sums, as in the separate passes: neither the
+    // largest nor the smallest spectra leave the type's range on the way
+#pragma unroll
+    for (int m = 0; m < N; ++m) a[m] = scal(a[m], scale);
     box_exchange<N>(lds, a, zline, yline);
     dft<N, +1>(a);
     const int half = int(rs / 2);
@@ -1330,18 +1334,19 @@ hipError_t launch_rows(bool f64, bool forward, int n, int ny, const void* in, vo
 
 template <typename T, int N>
 static hipError_t box_n(bool forward, const void* in, void* out, const void* tw, int64_t grids,
-                        int64_t rs, double me, double mi, hipStream_t s) {
+                        int64_t rs, double scale, bool weighted, hipStream_t s) {
     constexpr int NT = box_shape<T, N>::NT;
     if (grids == 0) return hipSuccess;
     if (!grid_fits(grids, NT)) return hipErrorInvalidValue;
     if (forward)
         hipLaunchKernelGGL((k_box_r2c<T, N>), dim3(grids), dim3(NT), 0, s,
                            static_cast<const T*>(in), static_cast<cx<T>*>(out),
-                           static_cast<const cx<T>*>(tw), rs, T(me), T(mi));
+                           static_cast<const cx<T>*>(tw), rs, T(scale),
+                           T(weighted ? 2.0 * scale : scale));
     else
         hipLaunchKernelGGL((k_box_c2r<T, N>), dim3(grids), dim3(NT), 0, s,
                            static_cast<const cx<T>*>(in), static_cast<T*>(out),
-                           static_cast<const cx<T>*>(tw), rs, T(me), T(mi));
+                           static_cast<const cx<T>*>(tw), rs, T(scale), T(weighted ? 0.5 : 1.0));
     return hipGetLastError();
 }
 
@@ -1357,13 +1362,13 @@ bool box_supported(bool f64, int n, int64_t grids) {
 }
 
 hipError_t launch_box(bool f64, bool forward, int n, const void* in, void* out, const void* tw,
-                      int64_t grids, int64_t rs, double me, double mi, hipStream_t s) {
+                      int64_t grids, int64_t rs, double scale, bool weighted, hipStream_t s) {
     if (n != 16 && n != 32) return hipErrorInvalidValue;
     if (f64)
-        return n == 16 ? box_n<double, 16>(forward, in, out, tw, grids, rs, me, mi, s)
-                       : box_n<double, 32>(forward, in, out, tw, grids, rs, me, mi, s);
-    return n == 16 ? box_n<float, 16>(forward, in, out, tw, grids, rs, me, mi, s)
-                   : box_n<float, 32>(forward, in, out, tw, grids, rs, me, mi, s);
+        return n == 16 ? box_n<double, 16>(forward, in, out, tw, grids, rs, scale, weighted, s)
+                       : box_n<double, 32>(forward, in, out, tw, grids, rs, scale, weighted, s);
+    return n == 16 ? box_n<float, 16>(forward, in, out, tw, grids, rs, scale, weighted, s)
+                   : box_n<float, 32>(forward, in, out, tw, grids, rs, scale, weighted, s);
 }
 
 }  // namespace gfft

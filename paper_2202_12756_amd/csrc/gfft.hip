@@ -321,9 +321,8 @@ bool box_pass(const gfft_plan* p) {
 
 gfft_status run_box(const gfft_plan* p, bool fwd, const void* in, void* out, double scale,
                     bool weighted, hipStream_t s) {
-    const double me = scale, mi = weighted ? (fwd ? 2.0 : 0.5) * scale : scale;
-    return hip_status(gfft::launch_box(f64(p), fwd, int(p->n), in, out, p->tw, p->batch, p->rs, me,
-                                       mi, s));
+    return hip_status(gfft::launch_box(f64(p), fwd, int(p->n), in, out, p->tw, p->batch, p->rs,
+                                       scale, weighted, s));
 }
 
 gfft_status forward(const gfft_plan* p, const void* in, void* out, double scale,

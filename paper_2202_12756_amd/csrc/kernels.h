@@ -112,10 +112,11 @@ hipError_t launch_split_x(bool f64, int n, int sign, const void* src, void* dst,
 // The whole 3D transform of natural-order grids of N = 16 or 32, one grid per
 // workgroup in one pass (box_supported: also says whether `grids` of them are
 // better off so).  rs: reals between real rows (N, or N + 2 in place); `in`
-// and `out` may be the same buffer.
+// and `out` may be the same buffer.  weighted: bins 0 < kz < N/2 doubled
+// (forward) or halved (inverse), as in the adjoints.
 bool box_supported(bool f64, int n, int64_t grids);
 hipError_t launch_box(bool f64, bool forward, int n, const void* in, void* out, const void* tw,
-                      int64_t grids, int64_t rs, double mul_edge, double mul_int, hipStream_t s);
+                      int64_t grids, int64_t rs, double scale, bool weighted, hipStream_t s);
 
 // Copy n16 16-byte elements from src to dst (one per work-item).
 hipError_t launch_copy16(const void* src, void* dst, int64_t n16, hipStream_t s);

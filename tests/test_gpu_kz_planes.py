@@ -132,3 +132,27 @@ def test_z_pass_discards_edge_imaginary_parts(n, dtype):
         out.append(p.z_c2r(torch.view_as_complex(v)))
     assert torch.isfinite(out[0]).all()
     assert torch.equal(out[1], out[0]) and torch.equal(out[2], out[0])
+
+
+@DTYPES
+@pytest.mark.parametrize("n,batch", [(16, 2), (32, 97), (32, 2), (64, 1)])
+def test_scales_at_the_ends_of_the_range(n, batch, dtype):
+    """The scale is applied between the sums: before z in the inverse, after z
+    in the adjoint.  A spectrum of g in every bin is N^3 g at the origin, N^2 g
+    after x and y and g / N once scaled by N^-3; a constant field N g likewise.
+    So both come out as g and N g to rounding (sums of equal values and powers
+    of two are exact; 32 eps is ample) from g / N just above the smallest normal
+    value to N^2 g at a quarter of the largest."""
+    p = Plan(n, dtype, batch=batch)
+    fi = torch.finfo(dtype)
+    for g in (0.25 * fi.max / n ** 2, 1.1 * fi.tiny * n):
+        G = torch.zeros(p.spectrum_shape, dtype=p.cdtype, device="cuda")
+        torch.view_as_real(G)[..., 0] = g
+        f = p.c2r(G, scale=1.0 / n ** 3)
+        assert torch.isfinite(f).all()
+        at = f[:, 0, 0, 0] / g
+        assert ((at - 1).abs() <= 32 * fi.eps).all()
+        h = torch.full(p.real_shape, g * n, dtype=dtype, device="cuda")
+        A = p.c2r_adjoint(h, scale=1.0 / n ** 3)
+        assert torch.isfinite(torch.view_as_real(A)).all()
+        assert ((A[:, 0, 0, 0].real / (g * n) - 1).abs() <= 32 * fi.eps).all()
