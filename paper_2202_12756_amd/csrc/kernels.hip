@@ -658,25 +658,37 @@ static bool whole_lines(const void* data, int64_t m_cols, const line_map& lm, in
            lm.b_hi % la == 0 && lm.b_lo % la == 0 && lm.s_hi % la == 0 && lm.s_lo % la == 0;
 }
 
+// More line sets than one grid takes go in several launches, each of whole
+// b_hi groups of sets (sets of one group share b_lo offsets): the most short
+// lines that fit in memory need it, as a tile's lanes past the last column count
+// (N = 16 in place: 9 of 256, so 2^24 planes, 20 GB of FP32).
 template <typename T, int N, int AX, int MF, bool NT, int ORD, int TWS = 1>
 static hipError_t strided_run(int sign, const void* src, void* data, const void* tw, int64_t m_cols,
                               int64_t n_b, line_map lm, hipStream_t s) {
     using SH = sshape<T, N, AX, (MF > 0)>;
     constexpr int TC = SH::TC;
     const int64_t tiles_m = (m_cols + TC - 1) / TC;
-    const int64_t blocks = tiles_m * n_b;
-    if (blocks == 0) return hipSuccess;
-    if (!grid_fits(blocks, TC * SH::TPT)) return hipErrorInvalidValue;
     const dim3 threads(TC * SH::TPT);
-    if (MF < 0 || sign < 0)
-        hipLaunchKernelGGL((k_strided<T, N, TC, SH::XP, -1, SH::E, MF, NT, ORD, TWS>), dim3(blocks),
-                           threads, 0, s, static_cast<const cx<T>*>(src),
-                           static_cast<cx<T>*>(data), static_cast<const cx<T>*>(tw), m_cols, tiles_m, lm);
-    else if constexpr (MF >= 0)
-        hipLaunchKernelGGL((k_strided<T, N, TC, SH::XP, +1, SH::E, MF, NT, ORD, TWS>), dim3(blocks),
-                           threads, 0, s, static_cast<const cx<T>*>(src),
-                           static_cast<cx<T>*>(data), static_cast<const cx<T>*>(tw), m_cols, tiles_m, lm);
-    return hipGetLastError();
+    if (tiles_m * n_b == 0) return hipSuccess;
+    const int64_t groups = (int64_t(1) << 31) / ((tiles_m * threads.x) << lm.lg_bx);
+    const int64_t most = groups > 0 ? groups << lm.lg_bx : n_b;
+    for (int64_t b0 = 0; b0 < n_b; b0 += most) {
+        const int64_t blocks = tiles_m * (n_b - b0 < most ? n_b - b0 : most);
+        if (!grid_fits(blocks, threads.x)) return hipErrorInvalidValue;
+        const int64_t off = (b0 >> lm.lg_bx) * lm.b_hi;
+        const cx<T>* from = static_cast<const cx<T>*>(src) + off;
+        cx<T>* to = static_cast<cx<T>*>(data) + off;
+        const cx<T>* t = static_cast<const cx<T>*>(tw);
+        if (MF < 0 || sign < 0)
+            hipLaunchKernelGGL((k_strided<T, N, TC, SH::XP, -1, SH::E, MF, NT, ORD, TWS>),
+                               dim3(blocks), threads, 0, s, from, to, t, m_cols, tiles_m, lm);
+        else if constexpr (MF >= 0)
+            hipLaunchKernelGGL((k_strided<T, N, TC, SH::XP, +1, SH::E, MF, NT, ORD, TWS>),
+                               dim3(blocks), threads, 0, s, from, to, t, m_cols, tiles_m, lm);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 // y lines of pencils with narrow kz chunks: FP32 2048 1 x 1024 ranks (one bin)
