@@ -511,9 +511,8 @@ __global__ __launch_bounds__(TC * N / E) void k_strided(
 // dispatch limit: like the streaming copy, the pass lives on many short
 // workgroups (1024^3/8, U = 1: FP32 179 us, FP64 360, 6.0 TB/s; 2, 4, 8: 192,
 // 198, 204 and 390, 406, 401; 8-byte FP32 elements, four rounds per thread 197
-// and 389).  A workgroup takes `per` whole runs
-// where they are short, a part of one otherwise; all extents are in elements
-// of V, inv = 1 / len.
+// and 389).  A workgroup takes `per` whole runs where they are short (per > 0),
+// a part of one otherwise; all extents are in elements of V, inv = 1 / len.
 template <typename V, int U>
 __global__ __launch_bounds__(kThreads) void k_pack(
     const V* __restrict__ src, V* __restrict__ dst, int64_t len, int64_t chunks,
@@ -529,13 +528,13 @@ __global__ __launch_bounds__(kThreads) void k_pack(
         snd = plane + ((j << lg_x) + xl) * len;
     };
     int64_t nat, snd;
-    if (per > 1) {
+    if (per > 0) {
         const int64_t first = int64_t(blockIdx.x) * per;
         const int runs = int(chunks - first < per ? chunks - first : per), l = int(len);
         for (int e = threadIdx.x; e < runs * l; e += kThreads) {
-            // exact: e < 2^11, so e + 1/2 is at least 2^-10 of a run away from
-            // a run's end
-            const int c = int((float(e) + 0.5f) * inv);
+            // exact where per > 1 (l < 2^10): e < 2^11, so e + 1/2 is at least
+            // 2^-11 of a run away from a run's end
+            const int c = per == 1 ? 0 : int((float(e) + 0.5f) * inv);
             run(first + c, nat, snd);
             const int o = e - c * l;
             dst[(to_send ? snd : nat) + o] = src[(to_send ? nat : snd) + o];
@@ -877,17 +876,28 @@ template <typename V, int U>
 static hipError_t pack_u(const void* src, void* dst, int64_t chunks, int lg_x, int lg_p,
                          int64_t x_step, int64_t len, bool to_send, hipStream_t s) {
     if (chunks == 0 || len == 0) return hipSuccess;
-    // runs of up to two rounds of a workgroup: several to a workgroup, so that
-    // few of its lanes idle in the last round (TB/s, FP32 64^3/16 5.85 against
-    // 3.75, 512^3/512 5.54 against 2.40; runs of three rounds 5.5 against 6.3)
-    const int per = len <= 2 * kThreads ? int((4 * kThreads + len - 1) / len) : 1;
+    // Whole runs, as many as fill a round of the workgroup, where a run cut into
+    // rounds would leave most of its last one idle: up to two rounds (512 MB of
+    // FP64 64 16 x 4 pencil runs of 128 elements 171 us, four rounds' worth of
+    // runs to a workgroup 193; slab 64/8, 264 elements, 180 and 197), four in
+    // arrays of up to 64 MB (FP64 1024/1024, 513 elements, 9.8 us, parts 11.6, but
+    // 183 and 176 over 512 MB).  8-byte elements (runs of an odd length, at most
+    // N/2 + 1): always, short ones four rounds' worth (FP32 128/128, 65 elements,
+    // 185 us, one round's 244; 1024/1024 186, parts 307; 4096/4096 190, 253).
+    constexpr bool PAIR = sizeof(V) == 16;
+    const int64_t whole = !PAIR ? 8 * kThreads + 1
+                          : chunks * len * int64_t(sizeof(V)) <= int64_t(64) << 20 ? 4 * kThreads + 76
+                                                                                    : 2 * kThreads;
+    const int64_t fill = PAIR || len > 2 * kThreads ? kThreads : 4 * kThreads;
+    const bool even = PAIR && len > kThreads && len % kThreads == 0;  // no idle lanes in parts
+    const int per = len <= whole && !even ? int((fill + len - 1) / len) : 0;
     int64_t bpc = (len + U * kThreads - 1) / (U * kThreads);
     // k_pack strides over its chunk, so fewer blocks per chunk keep very
     // large grids within the dispatch's 32-bit work-item count
     const int64_t cap = int64_t(0xffffffff) / (chunks * kThreads);
     if (bpc > cap) bpc = cap;
     if (bpc < 1) bpc = 1;
-    const int64_t blocks = per > 1 ? (chunks + per - 1) / per : chunks * bpc;
+    const int64_t blocks = per > 0 ? (chunks + per - 1) / per : chunks * bpc;
     if (!grid_fits(blocks, kThreads)) return hipErrorInvalidValue;
     hipLaunchKernelGGL((k_pack<V, U>), dim3(blocks), dim3(kThreads), 0, s,
                        static_cast<const V*>(src), static_cast<V*>(dst), len, chunks, bpc, per,
@@ -895,15 +905,16 @@ static hipError_t pack_u(const void* src, void* dst, int64_t chunks, int lg_x, i
     return hipGetLastError();
 }
 
-// One element per thread, but eight at an eighth of the run apart where runs
-// are a power of two of 256 KB or more (pencils): reads and writes then stay a
-// fixed power of two apart for a whole run, and the spread avoids that (4096
-// 64 x 4 pencil, FP32 398 us against 518, FP64 798 against 1101; at 128 KB
-// 2048 32 x 4 97 against 91).
+// One element per thread, but eight at an eighth of the run apart for runs of a
+// power of two (pencils) whose planes are 4 MB or more apart: reads and writes
+// then stay a large power of two apart for a whole run, and the spread avoids
+// that (4096 64 x 4, planes 4 and 8 MB apart, FP32 396 us against 515, FP64 794
+// against 1090; with planes 2 MB or less apart it loses 2-30%: FP64 2048 32 x 4
+// 232 against 173).
 template <typename V>
 static hipError_t pack_v(const void* src, void* dst, int64_t chunks, int lg_x, int lg_p,
                          int64_t x_step, int64_t len, bool to_send, hipStream_t s) {
-    if (len * int64_t(sizeof(V)) >= int64_t(256) << 10 && (len & (len - 1)) == 0)
+    if (x_step * int64_t(sizeof(V)) >= int64_t(4) << 20 && len >= 32 * kThreads && (len & (len - 1)) == 0)
         return pack_u<V, 8>(src, dst, chunks, lg_x, lg_p, x_step, len, to_send, s);
     return pack_u<V, 1>(src, dst, chunks, lg_x, lg_p, x_step, len, to_send, s);
 }
