@@ -206,14 +206,14 @@ struct plane_shape {
                   "a barrier follows every stage of the side column");
 };
 
-template <typename T, int N, int R, int E, int W, int ORD = kGrouped, bool TWD = false>
+template <typename T, int N, int R, int E, int W, bool TWD = false>
 __global__ __launch_bounds__((plane_shape<T, N, R, E>::NT), W) void k_plane_r2c(
-    const T* in, cx<T>* out, const cx<T>* __restrict__ tw, row_map map, T mul_edge, T mul_int) {
+    const T* in, cx<T>* out, const cx<T>* __restrict__ tw, row_map map, T mul_edge, T mul_int, int ord) {
     using P = plane_shape<T, N, R, E>;
     constexpr int M = P::M, K = P::K, H = P::H, NY = P::NY, TZ = P::TZ, TY = P::TY, EY = P::EY,
                   RM = P::RM;
     __shared__ T lds[P::LDS];
-    const int64_t tile = xcd_tile<ORD>(blockIdx.x, gridDim.x);
+    const int64_t tile = xcd_tile(ord, blockIdx.x, gridDim.x);
     const int64_t plane = tile / R;
     const int y0 = int(tile % R);
     const int tid = threadIdx.x;
@@ -307,14 +307,14 @@ __global__ __launch_bounds__((plane_shape<T, N, R, E>::NT), W) void k_plane_r2c(
     if (tid < NY) row_of(tid)[M] = xm;
 }
 
-template <typename T, int N, int R, int E, int W, int ORD = kGrouped, bool TWD = false>
+template <typename T, int N, int R, int E, int W, bool TWD = false>
 __global__ __launch_bounds__((plane_shape<T, N, R, E>::NT), W) void k_plane_c2r(
-    const cx<T>* in, T* out, const cx<T>* __restrict__ tw, row_map map, T mul_edge, T mul_int) {
+    const cx<T>* in, T* out, const cx<T>* __restrict__ tw, row_map map, T mul_edge, T mul_int, int ord) {
     using P = plane_shape<T, N, R, E>;
     constexpr int M = P::M, K = P::K, H = P::H, NY = P::NY, TZ = P::TZ, TY = P::TY, EY = P::EY,
                   RM = P::RM;
     __shared__ T lds[P::LDS];
-    const int64_t tile = xcd_tile<ORD>(blockIdx.x, gridDim.x);
+    const int64_t tile = xcd_tile(ord, blockIdx.x, gridDim.x);
     const int64_t plane = tile / R;
     const int y0 = int(tile % R);
     const int tid = threadIdx.x;
@@ -439,7 +439,7 @@ struct rows_shape {
 template <typename T, int N, int NY, int E, int G, int W, bool PENCIL>
 __global__ __launch_bounds__((rows_shape<T, N, NY, E, G>::NT), W) void k_rows_r2c(
     const T* in, cx<T>* out, const cx<T>* __restrict__ tw, int64_t tiles, row_map map, T mul_edge,
-    T mul_int) {
+    T mul_int, int ord) {
     using P = rows_shape<T, N, NY, E, G>;
     constexpr int M = P::M, K = P::K, H = P::H, R = P::R, TZ = P::TZ, NT1 = P::NT1, Q = P::Q,
                   RM = P::RM, LD = P::LD;
@@ -450,7 +450,7 @@ __global__ __launch_bounds__((rows_shape<T, N, NY, E, G>::NT), W) void k_rows_r2
     const int lt = threadIdx.x % NT1;
     T* lds = lds_all + grp * P::SZ;
     const int r = lt / TZ, t = lt % TZ;
-    const int64_t blk = xcd_tile<kGrouped>(blockIdx.x, gridDim.x);
+    const int64_t blk = xcd_tile(ord, blockIdx.x, gridDim.x);
     const int64_t tile = blk * G + grp;
     const bool valid = tile < tiles;
     // tiles past the end (last workgroup) load the last tile and drop it
@@ -546,7 +546,7 @@ __global__ __launch_bounds__((rows_shape<T, N, NY, E, G>::NT), W) void k_rows_r2
 template <typename T, int N, int NY, int E, int G, int W, bool PENCIL>
 __global__ __launch_bounds__((rows_shape<T, N, NY, E, G>::NT), W) void k_rows_c2r(
     const cx<T>* in, T* out, const cx<T>* __restrict__ tw, int64_t tiles, row_map map, T mul_edge,
-    T mul_int) {
+    T mul_int, int ord) {
     using P = rows_shape<T, N, NY, E, G>;
     constexpr int M = P::M, K = P::K, H = P::H, R = P::R, TZ = P::TZ, NT1 = P::NT1, Q = P::Q,
                   RM = P::RM, LD = P::LD;
@@ -557,7 +557,7 @@ __global__ __launch_bounds__((rows_shape<T, N, NY, E, G>::NT), W) void k_rows_c2
     const int lt = threadIdx.x % NT1;
     T* lds = lds_all + grp * P::SZ;
     const int r = lt / TZ, t = lt % TZ;
-    const int64_t blk = xcd_tile<kGrouped>(blockIdx.x, gridDim.x);
+    const int64_t blk = xcd_tile(ord, blockIdx.x, gridDim.x);
     const int64_t tile = blk * G + grp;
     const bool valid = tile < tiles;
     const int64_t tl = valid ? tile : tiles - 1;
@@ -931,7 +931,7 @@ __global__ __launch_bounds__((box_shape<T, N>::NT), (box_shape<T, N>::W)) void k
 // needs no exchange.  src and dst may be the same buffer.
 //   NT: non-temporal loads and stores (no reuse), where every 128-byte line
 //       belongs to one tile;
-//   ORD: tile order (xcd_tile).
+//   ord: tile order (xcd_tile).
 template <typename T, int N, int R, int TC, int EX>
 struct xr_shape {
     static constexpr int K = N / 2 + 1, NY = N / R, TPT = N / EX, NT = TC * TPT;
@@ -943,14 +943,14 @@ struct xr_shape {
     static constexpr int TILES = (COLS + TC - 1) / TC;  // per grid
 };
 
-template <typename T, int N, int R, int TC, int EX, int S, bool NT, int W, int ORD>
+template <typename T, int N, int R, int TC, int EX, int S, bool NT, int W>
 __global__ __launch_bounds__((xr_shape<T, N, R, TC, EX>::NT), W) void k_strided_r(
-    const cx<T>* src, cx<T>* dst, const cx<T>* __restrict__ tw) {
+    const cx<T>* src, cx<T>* dst, const cx<T>* __restrict__ tw, int ord) {
     using P = xr_shape<T, N, R, TC, EX>;
     constexpr int K = P::K, NY = P::NY, TPT = P::TPT;
     __shared__ T lds[P::LDS];
     const int c = threadIdx.x % TC, t = threadIdx.x / TC;
-    const int64_t tile = xcd_tile<ORD>(blockIdx.x, gridDim.x);
+    const int64_t tile = xcd_tile(ord, blockIdx.x, gridDim.x);
     const int64_t b = tile / P::TILES;
     const int m = int(tile - b * P::TILES) * TC + c;
     const bool valid = m < P::COLS;
@@ -1051,16 +1051,17 @@ static hipError_t plane_n(bool forward, const void* in, void* out, const void* t
         });
     using C = plane_cfg<T, N>;
     constexpr int NT = plane_shape<T, N, 1, C::E>::NT;
+    const int ord = tile_order(planes * N * (N / 2 + 1) * int64_t(sizeof(cx<T>)), kGrouped);
     if (planes == 0) return hipSuccess;
     if (!grid_fits(planes, NT)) return hipErrorInvalidValue;
     if (forward)
         hipLaunchKernelGGL((k_plane_r2c<T, N, 1, C::E, C::W>), dim3(planes), dim3(NT), 0, s,
                            static_cast<const T*>(in), static_cast<cx<T>*>(out),
-                           static_cast<const cx<T>*>(tw), map, T(me), T(mi));
+                           static_cast<const cx<T>*>(tw), map, T(me), T(mi), ord);
     else
         hipLaunchKernelGGL((k_plane_c2r<T, N, 1, C::E, C::W>), dim3(planes), dim3(NT), 0, s,
                            static_cast<const cx<T>*>(in), static_cast<T*>(out),
-                           static_cast<const cx<T>*>(tw), map, T(me), T(mi));
+                           static_cast<const cx<T>*>(tw), map, T(me), T(mi), ord);
     return hipGetLastError();
 }
 
@@ -1129,17 +1130,18 @@ static hipError_t split_rows_n(bool forward, const void* in, void* out, const vo
                                int64_t planes, row_map map, double me, double mi, hipStream_t s) {
     using C = split_cfg<T, N>;
     constexpr int NT = plane_shape<T, N, C::R, C::E>::NT;
+    const int ord = tile_order(planes * N * (N / 2 + 1) * int64_t(sizeof(cx<T>)), C::ROWS_ORD);
     const int64_t blocks = planes * C::R;
     if (blocks == 0) return hipSuccess;
     if (!grid_fits(blocks, NT)) return hipErrorInvalidValue;
     if (forward)
-        hipLaunchKernelGGL((k_plane_r2c<T, N, C::R, C::E, C::W, C::ROWS_ORD>), dim3(blocks), dim3(NT), 0, s,
+        hipLaunchKernelGGL((k_plane_r2c<T, N, C::R, C::E, C::W>), dim3(blocks), dim3(NT), 0, s,
                            static_cast<const T*>(in), static_cast<cx<T>*>(out),
-                           static_cast<const cx<T>*>(tw), map, T(me), T(mi));
+                           static_cast<const cx<T>*>(tw), map, T(me), T(mi), ord);
     else
-        hipLaunchKernelGGL((k_plane_c2r<T, N, C::R, C::E, C::W, C::ROWS_ORD>), dim3(blocks), dim3(NT), 0, s,
+        hipLaunchKernelGGL((k_plane_c2r<T, N, C::R, C::E, C::W>), dim3(blocks), dim3(NT), 0, s,
                            static_cast<const cx<T>*>(in), static_cast<T*>(out),
-                           static_cast<const cx<T>*>(tw), map, T(me), T(mi));
+                           static_cast<const cx<T>*>(tw), map, T(me), T(mi), ord);
     return hipGetLastError();
 }
 
@@ -1148,13 +1150,16 @@ static hipError_t split_x_run(const void* src, void* dst, const void* tw, int64_
                               hipStream_t s) {
     using C = split_cfg<T, N>;
     using P = xr_shape<T, N, C::R, C::TC, C::EX>;
-    constexpr int ORD = NT == C::NT ? C::ORD : kGrouped;
+    // N = 128 in launch order at every size (16 MB of FP64 forward 16 us, contiguous 18)
+    const int large = NT == C::NT ? C::ORD : kGrouped;
+    const int ord = N == 128 ? large
+                             : tile_order(batch * N * N * (N / 2 + 1) * int64_t(sizeof(cx<T>)), large);
     const int64_t blocks = batch * P::TILES;
     if (blocks == 0) return hipSuccess;
     if (!grid_fits(blocks, P::NT)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_strided_r<T, N, C::R, C::TC, C::EX, S, NT, C::WX, ORD>), dim3(blocks),
+    hipLaunchKernelGGL((k_strided_r<T, N, C::R, C::TC, C::EX, S, NT, C::WX>), dim3(blocks),
                        dim3(P::NT), 0, s, static_cast<const cx<T>*>(src),
-                       static_cast<cx<T>*>(dst), static_cast<const cx<T>*>(tw));
+                       static_cast<cx<T>*>(dst), static_cast<const cx<T>*>(tw), ord);
     return hipGetLastError();
 }
 
@@ -1264,19 +1269,23 @@ static hipError_t rows_n(bool forward, const void* in, void* out, const void* tw
     const int64_t tiles = rows / NY;
     if (tiles == 0) return hipSuccess;
     const cx<T>* t = static_cast<const cx<T>*>(tw);
+    // FP32 2048: groups at every size, as for its y lines (strided_run)
+    const int ord = sizeof(T) == 4 && N == 2048
+                        ? kGrouped
+                        : tile_order(rows * (N / 2 + 1) * int64_t(sizeof(cx<T>)), kGrouped);
     if constexpr (N <= 1024) {
         // k_plane_*: 2 NY elements per thread, two NY-point columns of it
         constexpr int E = 2 * NY, R = N / NY, W = 2;
         constexpr int NT = plane_shape<T, N, R, E>::NT;
         if (!grid_fits(tiles, NT)) return hipErrorInvalidValue;
         if (forward)
-            hipLaunchKernelGGL((k_plane_r2c<T, N, R, E, W, kGrouped, true>), dim3(tiles), dim3(NT),
+            hipLaunchKernelGGL((k_plane_r2c<T, N, R, E, W, true>), dim3(tiles), dim3(NT),
                                0, s, static_cast<const T*>(in), static_cast<cx<T>*>(out), t, map,
-                               T(me), T(mi));
+                               T(me), T(mi), ord);
         else
-            hipLaunchKernelGGL((k_plane_c2r<T, N, R, E, W, kGrouped, true>), dim3(tiles), dim3(NT),
+            hipLaunchKernelGGL((k_plane_c2r<T, N, R, E, W, true>), dim3(tiles), dim3(NT),
                                0, s, static_cast<const cx<T>*>(in), static_cast<T*>(out), t, map,
-                               T(me), T(mi));
+                               T(me), T(mi), ord);
         return hipGetLastError();
     } else {
         using C = rows_cfg<T, N, NY>;
@@ -1284,7 +1293,7 @@ static hipError_t rows_n(bool forward, const void* in, void* out, const void* tw
             const int64_t blocks = (tiles + g - 1) / g;
             if (!grid_fits(blocks, nt)) return hipErrorInvalidValue;
             hipLaunchKernelGGL(kernel, dim3(blocks), dim3(nt), 0, s, pin, pout, t, tiles, map, T(me),
-                               T(mi));
+                               T(mi), ord);
             return hipGetLastError();
         };
         if (forward) {

@@ -87,7 +87,7 @@ template <typename T, int N, int EMAX, int THREADS, bool NTS, bool ALIAS,
           bool PENCIL = false>
 __device__ __forceinline__ void z_r2c_body(
     const T* in, cx<T>* out, const cx<T>* __restrict__ tw,
-    int64_t rows, row_map map, T mul_edge, T mul_int) {
+    int64_t rows, row_map map, T mul_edge, T mul_int, int ord) {
     constexpr int M = N / 2, K = M + 1;
     using Z = zshape<M, EMAX, THREADS>;
     constexpr int E = Z::E, TPT = Z::TPT, RPB = Z::RPB;
@@ -97,7 +97,7 @@ __device__ __forceinline__ void z_r2c_body(
 
     const int rl = threadIdx.x / TPT;
     const int t = threadIdx.x % TPT;
-    const int64_t blk = xcd_tile<kGrouped>(blockIdx.x, gridDim.x);
+    const int64_t blk = xcd_tile(ord, blockIdx.x, gridDim.x);
     const int64_t row = blk * RPB + rl;
     const bool valid = row < rows;
 
@@ -157,31 +157,30 @@ __device__ __forceinline__ void z_r2c_body(
 template <typename T, int N, int EMAX, int THREADS, bool NTS>
 __global__ __launch_bounds__((zshape<N / 2, EMAX, THREADS>::NT)) void k_z_r2c(
     const T* __restrict__ in, cx<T>* __restrict__ out, const cx<T>* __restrict__ tw,
-    int64_t rows, row_map map, T mul_edge, T mul_int) {
-    z_r2c_body<T, N, EMAX, THREADS, NTS, false>(in, out, tw, rows, map, mul_edge, mul_int);
+    int64_t rows, row_map map, T mul_edge, T mul_int, int ord) {
+    z_r2c_body<T, N, EMAX, THREADS, NTS, false>(in, out, tw, rows, map, mul_edge, mul_int, ord);
 }
 
 template <typename T, int N, int EMAX, int THREADS, bool NTS>
 __global__ __launch_bounds__((zshape<N / 2, EMAX, THREADS>::NT)) void k_z_r2c_inplace(
     const T* in, cx<T>* out, const cx<T>* __restrict__ tw,
-    int64_t rows, row_map map, T mul_edge, T mul_int) {
-    z_r2c_body<T, N, EMAX, THREADS, NTS, true>(in, out, tw, rows, map, mul_edge, mul_int);
+    int64_t rows, row_map map, T mul_edge, T mul_int, int ord) {
+    z_r2c_body<T, N, EMAX, THREADS, NTS, true>(in, out, tw, rows, map, mul_edge, mul_int, ord);
 }
 
 // Pencil plans: bins scattered to the first exchange's chunks.
 template <typename T, int N, int EMAX, int THREADS>
 __global__ __launch_bounds__((zshape<N / 2, EMAX, THREADS>::NT)) void k_z_r2c_pencil(
     const T* __restrict__ in, cx<T>* __restrict__ out, const cx<T>* __restrict__ tw,
-    int64_t rows, row_map map, T mul_edge, T mul_int) {
-    z_r2c_body<T, N, EMAX, THREADS, false, false, true>(in, out, tw, rows, map, mul_edge,
-                                                               mul_int);
+    int64_t rows, row_map map, T mul_edge, T mul_int, int ord) {
+    z_r2c_body<T, N, EMAX, THREADS, false, false, true>(in, out, tw, rows, map, mul_edge, mul_int, ord);
 }
 
 // ---------------------------------------------------------------- z C2R
 template <typename T, int N, int EMAX, int THREADS, bool NTS, bool PENCIL = false>
 __device__ __forceinline__ void z_c2r_body(
     const cx<T>* in, T* out, const cx<T>* __restrict__ tw,
-    int64_t rows, row_map map, T mul_edge, T mul_int) {
+    int64_t rows, row_map map, T mul_edge, T mul_int, int ord) {
     constexpr int M = N / 2, K = M + 1;
     using Z = zshape<M, EMAX, THREADS>;
     constexpr int E = Z::E, TPT = Z::TPT, RPB = Z::RPB;
@@ -191,7 +190,7 @@ __device__ __forceinline__ void z_c2r_body(
 
     const int rl = threadIdx.x / TPT;
     const int t = threadIdx.x % TPT;
-    const int64_t blk = xcd_tile<kGrouped>(blockIdx.x, gridDim.x);
+    const int64_t blk = xcd_tile(ord, blockIdx.x, gridDim.x);
     const int64_t row = blk * RPB + rl;
     const bool valid = row < rows;
     const idx_rows<PS> ix{rl * MP};
@@ -252,8 +251,8 @@ __device__ __forceinline__ void z_c2r_body(
 template <typename T, int N, int EMAX, int THREADS, bool NTS>
 __global__ __launch_bounds__((zshape<N / 2, EMAX, THREADS>::NT)) void k_z_c2r(
     const cx<T>* __restrict__ in, T* __restrict__ out, const cx<T>* __restrict__ tw,
-    int64_t rows, row_map map, T mul_edge, T mul_int) {
-    z_c2r_body<T, N, EMAX, THREADS, NTS>(in, out, tw, rows, map, mul_edge, mul_int);
+    int64_t rows, row_map map, T mul_edge, T mul_int, int ord) {
+    z_c2r_body<T, N, EMAX, THREADS, NTS>(in, out, tw, rows, map, mul_edge, mul_int, ord);
 }
 
 // In place: every load of a row precedes the barrier after the LDS fill, and
@@ -261,16 +260,16 @@ __global__ __launch_bounds__((zshape<N / 2, EMAX, THREADS>::NT)) void k_z_c2r(
 template <typename T, int N, int EMAX, int THREADS, bool NTS>
 __global__ __launch_bounds__((zshape<N / 2, EMAX, THREADS>::NT)) void k_z_c2r_inplace(
     const cx<T>* in, T* out, const cx<T>* __restrict__ tw,
-    int64_t rows, row_map map, T mul_edge, T mul_int) {
-    z_c2r_body<T, N, EMAX, THREADS, NTS>(in, out, tw, rows, map, mul_edge, mul_int);
+    int64_t rows, row_map map, T mul_edge, T mul_int, int ord) {
+    z_c2r_body<T, N, EMAX, THREADS, NTS>(in, out, tw, rows, map, mul_edge, mul_int, ord);
 }
 
 // Pencil plans: bins gathered from the first exchange's chunks.
 template <typename T, int N, int EMAX, int THREADS, bool NTS>
 __global__ __launch_bounds__((zshape<N / 2, EMAX, THREADS>::NT)) void k_z_c2r_pencil(
     const cx<T>* __restrict__ in, T* __restrict__ out, const cx<T>* __restrict__ tw,
-    int64_t rows, row_map map, T mul_edge, T mul_int) {
-    z_c2r_body<T, N, EMAX, THREADS, NTS, true>(in, out, tw, rows, map, mul_edge, mul_int);
+    int64_t rows, row_map map, T mul_edge, T mul_int, int ord) {
+    z_c2r_body<T, N, EMAX, THREADS, NTS, true>(in, out, tw, rows, map, mul_edge, mul_int, ord);
 }
 
 // ---------------------------------------------------------------- y / x C2C
@@ -328,17 +327,18 @@ struct sshape {
 // MF: 0 vector stages; 2 or 3 the first radix-16 stage on the matrix cores;
 // -1 no transform (each element replaced by its conjugate): the same loads
 // and stores as the pass, a yardstick for its memory-access ceiling.
-// ORD: tile order (xcd_tile).
+// ord: tile order (xcd_tile).
 // FLAT: sets of fewer columns than a tile; tiles take TC columns of all sets
-// numbered through (tiles_m: the number of all columns).
+// numbered through (tiles_m: the number of all columns).  Otherwise tiles_m is
+// below 2^31, as the grid is.
 // TWS: tw is the table of a transform TWS times as long.
 // src may be data itself (in place) or a distinct buffer of the same layout:
 // every load of a tile precedes its stores, and tiles own their elements.
 template <typename T, int N, int TC, int XP, int S, int E = 16, int MF = 0, bool NT = false,
-          int ORD = kContig, int TWS = 1, bool FLAT = false>
+          int TWS = 1, bool FLAT = false>
 __global__ __launch_bounds__(TC * N / E) void k_strided(
     const cx<T>* src, cx<T>* data, const cx<T>* __restrict__ tw, int64_t m_cols,
-    int64_t tiles_m, line_map lm) {
+    int64_t tiles_m, line_map lm, int ord) {
     constexpr int TPT = N / E;
     constexpr bool SPLIT = XP == 2;
     static_assert(XP == 1 || XP == 2, "XP: whole values (1) or real/imaginary halves (2)");
@@ -350,18 +350,20 @@ __global__ __launch_bounds__(TC * N / E) void k_strided(
 
     const int c = threadIdx.x % TC;
     const int t = threadIdx.x / TC;
-    const int64_t tile = xcd_tile<ORD>(blockIdx.x, gridDim.x);
+    const int64_t tile = xcd_tile(ord, blockIdx.x, gridDim.x);
     int64_t b, m0, m;
     bool valid;
     if constexpr (FLAT) {
-        int64_t g = tile * TC + c;
-        valid = g < tiles_m;
-        if (!valid) g = tiles_m - 1;
-        b = g / m_cols;
-        m = g - b * m_cols;
+        // the tile's first column by a scalar division, the lane's by a short one
+        const int64_t g0 = tile * TC, b0 = g0 / m_cols;
+        valid = g0 + c < tiles_m;
+        const uint32_t r = uint32_t(g0 - b0 * m_cols) + (valid ? c : uint32_t(tiles_m - 1 - g0));
+        const uint32_t q = r / uint32_t(m_cols);
+        b = b0 + q;
+        m = r - q * uint32_t(m_cols);
         m0 = 0;
     } else {
-        b = tile / tiles_m;
+        b = uint32_t(tile) / uint32_t(tiles_m);
         m0 = (tile - b * tiles_m) * TC;
         m = m0 + c;
         valid = m < m_cols;
@@ -599,21 +601,22 @@ static hipError_t z_r2c_n(const void* in, void* out, const void* tw, int64_t row
     using C = zcfg<T, true, N>;
     using Z = zshape<N / 2, C::EMAX, C::THREADS>;
     const int64_t blocks = (rows + Z::RPB - 1) / Z::RPB;
+    const int ord = tile_order(rows * (N / 2 + 1) * int64_t(sizeof(cx<T>)), kGrouped);
     if (blocks == 0) return hipSuccess;
     if (!grid_fits(blocks, Z::NT)) return hipErrorInvalidValue;
     if (map.pencil)
         hipLaunchKernelGGL((k_z_r2c_pencil<T, N, C::EMAX, C::THREADS>), dim3(blocks),
                            dim3(Z::NT), 0, s, static_cast<const T*>(in), static_cast<cx<T>*>(out),
-                           static_cast<const cx<T>*>(tw), rows, map, T(me), T(mi));
+                           static_cast<const cx<T>*>(tw), rows, map, T(me), T(mi), ord);
     else if (in == out)
         hipLaunchKernelGGL((k_z_r2c_inplace<T, N, C::EMAX, C::THREADS, C::NTS>),
                            dim3(blocks), dim3(Z::NT), 0, s, static_cast<const T*>(in),
                            static_cast<cx<T>*>(out), static_cast<const cx<T>*>(tw), rows, map,
-                           T(me), T(mi));
+                           T(me), T(mi), ord);
     else
         hipLaunchKernelGGL((k_z_r2c<T, N, C::EMAX, C::THREADS, C::NTS>), dim3(blocks),
                            dim3(Z::NT), 0, s, static_cast<const T*>(in), static_cast<cx<T>*>(out),
-                           static_cast<const cx<T>*>(tw), rows, map, T(me), T(mi));
+                           static_cast<const cx<T>*>(tw), rows, map, T(me), T(mi), ord);
     return hipGetLastError();
 }
 
@@ -630,22 +633,23 @@ static hipError_t z_c2r_n(const void* in, void* out, const void* tw, int64_t row
     using C = zcfg<T, false, N>;
     using Z = zshape<N / 2, C::EMAX, C::THREADS>;
     const int64_t blocks = (rows + Z::RPB - 1) / Z::RPB;
+    const int ord = tile_order(rows * (N / 2 + 1) * int64_t(sizeof(cx<T>)), kGrouped);
     if (blocks == 0) return hipSuccess;
     if (!grid_fits(blocks, Z::NT)) return hipErrorInvalidValue;
     if (map.pencil)
         hipLaunchKernelGGL((k_z_c2r_pencil<T, N, C::EMAX, C::THREADS, C::NTS>),
                            dim3(blocks), dim3(Z::NT), 0, s, static_cast<const cx<T>*>(in),
                            static_cast<T*>(out), static_cast<const cx<T>*>(tw), rows, map,
-                           T(me), T(mi));
+                           T(me), T(mi), ord);
     else if (in == out)
         hipLaunchKernelGGL((k_z_c2r_inplace<T, N, C::EMAX, C::THREADS, C::NTS>),
                            dim3(blocks), dim3(Z::NT), 0, s, static_cast<const cx<T>*>(in),
                            static_cast<T*>(out), static_cast<const cx<T>*>(tw), rows, map,
-                           T(me), T(mi));
+                           T(me), T(mi), ord);
     else
         hipLaunchKernelGGL((k_z_c2r<T, N, C::EMAX, C::THREADS, C::NTS>), dim3(blocks),
                            dim3(Z::NT), 0, s, static_cast<const cx<T>*>(in), static_cast<T*>(out),
-                           static_cast<const cx<T>*>(tw), rows, map, T(me), T(mi));
+                           static_cast<const cx<T>*>(tw), rows, map, T(me), T(mi), ord);
     return hipGetLastError();
 }
 
@@ -661,14 +665,20 @@ static bool whole_lines(const void* data, int64_t m_cols, const line_map& lm, in
 // b_hi groups of sets (sets of one group share b_lo offsets): the most short
 // lines that fit in memory need it, as a tile's lanes past the last column count
 // (N = 16 in place: 9 of 256, so 2^24 planes, 20 GB of FP32).
-template <typename T, int N, int AX, int MF, bool NT, int ORD, int TWS = 1>
-static hipError_t strided_run(int sign, const void* src, void* data, const void* tw, int64_t m_cols,
-                              int64_t n_b, line_map lm, hipStream_t s) {
+template <typename T, int N, int AX, int MF, bool NT, int TWS = 1>
+static hipError_t strided_run(int large, int sign, const void* src, void* data, const void* tw,
+                              int64_t m_cols, int64_t n_b, line_map lm, hipStream_t s) {
     using SH = sshape<T, N, AX, (MF > 0)>;
     constexpr int TC = SH::TC;
     const int64_t tiles_m = (m_cols + TC - 1) / TC;
     const dim3 threads(TC * SH::TPT);
     if (tiles_m * n_b == 0) return hipSuccess;
+    // FP32 lines of 2048 and what a first y step leaves of them share so much at
+    // their tiles' edges that groups win at every size (one plane in place 31 us
+    // an inverse, contiguous 35)
+    const int ord = sizeof(T) == 4 && N * TWS == 2048
+                        ? large
+                        : tile_order(m_cols * n_b * N * int64_t(sizeof(cx<T>)), large);
     const int64_t groups = (int64_t(1) << 31) / ((tiles_m * threads.x) << lm.lg_bx);
     const int64_t most = groups > 0 ? groups << lm.lg_bx : n_b;
     for (int64_t b0 = 0; b0 < n_b; b0 += most) {
@@ -679,11 +689,11 @@ static hipError_t strided_run(int sign, const void* src, void* data, const void*
         cx<T>* to = static_cast<cx<T>*>(data) + off;
         const cx<T>* t = static_cast<const cx<T>*>(tw);
         if (MF < 0 || sign < 0)
-            hipLaunchKernelGGL((k_strided<T, N, TC, SH::XP, -1, SH::E, MF, NT, ORD, TWS>),
-                               dim3(blocks), threads, 0, s, from, to, t, m_cols, tiles_m, lm);
+            hipLaunchKernelGGL((k_strided<T, N, TC, SH::XP, -1, SH::E, MF, NT, TWS>),
+                               dim3(blocks), threads, 0, s, from, to, t, m_cols, tiles_m, lm, ord);
         else if constexpr (MF >= 0)
-            hipLaunchKernelGGL((k_strided<T, N, TC, SH::XP, +1, SH::E, MF, NT, ORD, TWS>),
-                               dim3(blocks), threads, 0, s, from, to, t, m_cols, tiles_m, lm);
+            hipLaunchKernelGGL((k_strided<T, N, TC, SH::XP, +1, SH::E, MF, NT, TWS>),
+                               dim3(blocks), threads, 0, s, from, to, t, m_cols, tiles_m, lm, ord);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -698,16 +708,17 @@ static hipError_t strided_flat(int sign, const void* src, void* data, const void
     using SH = sshape<T, N, 0>;
     constexpr int TC = SH::TC;
     const int64_t cols = m_cols * n_b, blocks = (cols + TC - 1) / TC;
+    const int ord = tile_order(cols * N * int64_t(sizeof(cx<T>)), kGrouped);
     if (!grid_fits(blocks, TC * SH::TPT)) return hipErrorInvalidValue;
     const dim3 threads(TC * SH::TPT);
     if (sign < 0)
-        hipLaunchKernelGGL((k_strided<T, N, TC, SH::XP, -1, SH::E, 0, false, kGrouped, 1, true>),
+        hipLaunchKernelGGL((k_strided<T, N, TC, SH::XP, -1, SH::E, 0, false, 1, true>),
                            dim3(blocks), threads, 0, s, static_cast<const cx<T>*>(src),
-                           static_cast<cx<T>*>(data), static_cast<const cx<T>*>(tw), m_cols, cols, lm);
+                           static_cast<cx<T>*>(data), static_cast<const cx<T>*>(tw), m_cols, cols, lm, ord);
     else
-        hipLaunchKernelGGL((k_strided<T, N, TC, SH::XP, +1, SH::E, 0, false, kGrouped, 1, true>),
+        hipLaunchKernelGGL((k_strided<T, N, TC, SH::XP, +1, SH::E, 0, false, 1, true>),
                            dim3(blocks), threads, 0, s, static_cast<const cx<T>*>(src),
-                           static_cast<cx<T>*>(data), static_cast<const cx<T>*>(tw), m_cols, cols, lm);
+                           static_cast<cx<T>*>(data), static_cast<const cx<T>*>(tw), m_cols, cols, lm, ord);
     return hipGetLastError();
 }
 
@@ -759,10 +770,10 @@ static hipError_t strided_ax(int sign, const void* src, void* data, const void* 
                                   (HALF & ((int64_t(1) << lm.lg_y) - 1)) * lm.s_lo) / HALF * ES;
             constexpr int64_t FAR = F64 && N == 256 ? int64_t(512) << 10 : int64_t(1) << 62;
             if (step >= 4096 && step < FAR)
-                return strided_run<T, N, AX, MF, true, O::NT>(sign, src, data, tw, m_cols, n_b, lm, s);
+                return strided_run<T, N, AX, MF, true>(O::NT, sign, src, data, tw, m_cols, n_b, lm, s);
             if constexpr (N >= 512 || (!F64 && N == 256)) {
                 if (step < 4096)
-                    return strided_run<T, N, AX, MF, true, kContig>(sign, src, data, tw, m_cols, n_b, lm,
+                    return strided_run<T, N, AX, MF, true>(kContig, sign, src, data, tw, m_cols, n_b, lm,
                                                                     s);
             }
         }
@@ -775,15 +786,15 @@ static hipError_t strided_ax(int sign, const void* src, void* data, const void* 
     }
     if constexpr (AX == 1 && N <= 256) {
         if (lm.s_lo * ES < 4096)
-            return strided_run<T, N, AX, MF, false, kContig>(sign, src, data, tw, m_cols, n_b, lm, s);
+            return strided_run<T, N, AX, MF, false>(kContig, sign, src, data, tw, m_cols, n_b, lm, s);
     }
     if constexpr (F64 && (N >= 2048 || (AX == 1 && N == 256)))
-        return strided_run<T, N, AX, MF, false, kContig>(sign, src, data, tw, m_cols, n_b, lm, s);
+        return strided_run<T, N, AX, MF, false>(kContig, sign, src, data, tw, m_cols, n_b, lm, s);
     if constexpr ((F64 || N == 512) && AX == 0) {
         if ((lm.lg_y >= ilog2_c(N) || N == 512) && lm.s_lo == m_cols)
-            return strided_run<T, N, AX, MF, false, kContig>(sign, src, data, tw, m_cols, n_b, lm, s);
+            return strided_run<T, N, AX, MF, false>(kContig, sign, src, data, tw, m_cols, n_b, lm, s);
     }
-    return strided_run<T, N, AX, MF, false, kGrouped>(sign, src, data, tw, m_cols, n_b, lm, s);
+    return strided_run<T, N, AX, MF, false>(kGrouped, sign, src, data, tw, m_cols, n_b, lm, s);
 }
 
 template <typename T, int N>
@@ -857,7 +868,7 @@ hipError_t launch_strided_lines(bool f64, int n, int ny, int sign, const void* s
                                 hipStream_t s) {
 #define GFFT_LINES(T, N, NY, ORD)                                                               \
     if (n == N && ny == NY)                                                                     \
-        return strided_run<T, N / NY, 0, 0, false, ORD, NY>(sign, src, data, tw, m_cols, n_b, lm, s);
+        return strided_run<T, N / NY, 0, 0, false, NY>(ORD, sign, src, data, tw, m_cols, n_b, lm, s);
     if (f64) {
         GFFT_LINES(double, 1024, 8, kGrouped)
         GFFT_LINES(double, 2048, 4, kContig)

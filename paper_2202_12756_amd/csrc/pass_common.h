@@ -39,31 +39,37 @@ __device__ __forceinline__ int64_t pencil_bin(int64_t r, int k, int K, const row
 // Tile order.  Consecutive workgroup ids are dealt round-robin to the 8 XCDs,
 // each with its own L2.  Neighbouring tiles share cache lines at their edges
 // and should meet in one L2; the XCDs together should work on one region of
-// memory.  ORD >= 0 deals groups of 2^ORD neighbouring tiles to the XCDs in
+// memory.  ord >= 0 deals groups of 2^ord neighbouring tiles to the XCDs in
 // turn (0: launch order); kContig gives every XCD one contiguous eighth of the
 // tiles.  Groups of 16 (kGrouped) are within 2% of the best order for almost
-// every pass: FP64 1024-point z rows R2C 5.89 TB/s (contiguous 5.56), C2R 5.95
-// (5.63); N = 2048 z 5.66 (5.30).  The long y lines of FP64 and the x lines
-// measured below keep orders of their own.
+// every pass over a large array: FP64 1024-point z rows R2C 5.89 TB/s (contiguous
+// 5.56), C2R 5.95 (5.63); N = 2048 z 5.66 (5.30).  The long y lines of FP64 and
+// the x lines measured below keep orders of their own.
 constexpr int kContig = -1;
 constexpr int kGrouped = 4;
-template <int ORD>
-__device__ __forceinline__ int64_t xcd_tile(int64_t g, int64_t G) {
-    constexpr int kXcd = 8;
-    if constexpr (ORD == 0) {
-        return g;
-    } else if constexpr (ORD < 0) {
-        const int64_t per = G / kXcd;
-        if (g >= per * kXcd) return g;
-        return (g % kXcd) * per + g / kXcd;
-    } else {
-        constexpr int64_t span = int64_t(kXcd) << ORD;
-        const int64_t base = g & ~(span - 1), o = g - base;
-        if (base + span <= G) return base + ((o % kXcd) << ORD) + o / kXcd;
+__device__ __forceinline__ int64_t xcd_tile(int ord, uint32_t g, uint32_t G) {
+    constexpr uint32_t kXcd = 8;
+    if (ord == 0) return g;
+    uint32_t base = 0, o = g;
+    if (ord > 0) {
+        const uint32_t span = kXcd << ord;
+        base = g & ~(span - 1);
+        o = g - base;
+        if (G - base >= span) return base + ((o % kXcd) << ord) + o / kXcd;
         // the tiles left over (all of a small grid): contiguous eighths
-        const int64_t per = (G - base) / kXcd;
-        return o >= per * kXcd ? g : base + (o % kXcd) * per + o / kXcd;
     }
+    const uint32_t per = (G - base) / kXcd;
+    return o >= per * kXcd ? g : base + (o % kXcd) * per + o / kXcd;
+}
+
+// The order of a pass over a complex array of `bytes`: `large`, but contiguous
+// eighths where the array is of the size of the eight L2s (32 MB) or less.  There
+// a pass finds what the one before it left in its own XCD's L2 only if both deal
+// the array out alike: pairs of 16 MB of reals in place, FP64 256 slabs 32 us
+// against 47 with groups, 512 37 against 55; over all N and layouts 9% less at
+// 8 MB, 10% at 16, 2% at 32, nothing at 64.
+inline int tile_order(int64_t bytes, int large) {
+    return bytes <= int64_t(40) << 20 ? kContig : large;
 }
 
 // Grids are one-dimensional, and a dispatch carries its size in work-items
