@@ -700,12 +700,14 @@ static hipError_t strided_run(int large, int sign, const void* src, void* data, 
     return hipSuccess;
 }
 
-// y lines of pencils with narrow kz chunks: FP32 2048 1 x 1024 ranks (one bin)
-// z, y and x 171 -> 124 us, FP64 1024 1 x 256 96 -> 52, 4096 8 x 2048 81 -> 65.
-template <typename T, int N>
+// Lines of sets narrower than a tile, the columns of all sets numbered through:
+// y lines of pencils with narrow kz chunks (FP32 2048 1 x 1024 ranks, one bin, z, y
+// and x 171 -> 124 us, FP64 1024 1 x 256 96 -> 52, 4096 8 x 2048 81 -> 65) and the
+// 9 or 17 columns of N = 16 and 32.
+template <typename T, int N, int AX>
 static hipError_t strided_flat(int sign, const void* src, void* data, const void* tw,
                                int64_t m_cols, int64_t n_b, line_map lm, hipStream_t s) {
-    using SH = sshape<T, N, 0>;
+    using SH = sshape<T, N, AX>;
     constexpr int TC = SH::TC;
     const int64_t cols = m_cols * n_b, blocks = (cols + TC - 1) / TC;
     const int ord = tile_order(cols * N * int64_t(sizeof(cx<T>)), kGrouped);
@@ -778,11 +780,13 @@ static hipError_t strided_ax(int sign, const void* src, void* data, const void* 
             }
         }
     }
-    if constexpr (AX == 0 && MF == 0 && N >= 64) {
-        // sets that would leave half (from N = 1024) or three quarters of a
-        // tile's lanes idle
-        if ((N >= 1024 ? 2 : 4) * m_cols <= SH::TC && m_cols > 0 && n_b > 1)
-            return strided_flat<T, N>(sign, src, data, tw, m_cols, n_b, lm, s);
+    if constexpr (MF == 0 && (AX == 0 || N <= 32)) {
+        // sets that would leave half (from N = 1024), three quarters or (N = 16)
+        // 15 of 16 of a tile's lanes idle: 512 MB of N = 16 slabs 9 columns FP64 232
+        // us, a tile per set 348, but 18 columns 228 and 209; N = 32 17 columns 210
+        // and 500
+        if ((N >= 1024 ? 2 : N == 16 ? 16 : 4) * m_cols <= SH::TC && m_cols > 0 && n_b > 1)
+            return strided_flat<T, N, AX>(sign, src, data, tw, m_cols, n_b, lm, s);
     }
     if constexpr (AX == 1 && N <= 256) {
         if (lm.s_lo * ES < 4096)
