@@ -1067,26 +1067,35 @@ static hipError_t plane_n(bool forward, const void* in, void* out, const void* t
 
 // Where a plane fills at least a wave and fits on a CU with room for a second
 // one (FP64 up to N = 128: 131 KB) or at least once (FP32 N = 256: 262 KB); an
-// FP64 256 x 256 plane (524 KB) would take the whole register file.
-bool plane_supported(bool f64, int n) {
-    return n == 32 || n == 64 || n == 128 || (!f64 && n == 256);
+// FP64 256 x 256 plane (524 KB) would take the whole register file.  From N =
+// 128 up a plane is long for one workgroup, and few of them leave CUs idle: there
+// z and y passes are faster.  Step 1 forward / inverse in us, in brackets those:
+// FP64 128 16 planes 12.0 / 12.4 (9.1 / 9.0), 96 13.5 / 13.6 (13.7 / 12.8), 192
+// 16.8 / 16.6 (23.1 / 17.6); FP32 128 64 9.4 / 9.6 (8.6 / 8.3), 96 9.6 / 10.0
+// (10.8 / 10.7); FP32 256 32 24.5 / 28.4 (12.8 / 12.1), 128 28 / 32 (31 / 28), 192
+// 30 / 35 (41 / 38).  N = 32 and 64: 5.2-6.2 (7.8-8.8) from one plane on.
+bool plane_supported(bool f64, int n, int64_t planes, bool forward) {
+    if (n == 128) return planes >= (f64 && !forward ? 160 : 96);
+    if (!f64 && n == 256) return planes >= (forward ? 128 : 192);
+    return n == 32 || n == 64;
 }
 
 hipError_t launch_plane(bool f64, bool forward, int n, const void* in, void* out, const void* tw,
                         int64_t planes, row_map map, double me, double mi, hipStream_t s) {
-    if (!plane_supported(f64, n)) return hipErrorInvalidValue;
     if (f64) {
         switch (n) {
             case 32: return plane_n<double, 32>(forward, in, out, tw, planes, map, me, mi, s);
             case 64: return plane_n<double, 64>(forward, in, out, tw, planes, map, me, mi, s);
-            default: return plane_n<double, 128>(forward, in, out, tw, planes, map, me, mi, s);
+            case 128: return plane_n<double, 128>(forward, in, out, tw, planes, map, me, mi, s);
+            default: return hipErrorInvalidValue;
         }
     }
     switch (n) {
         case 32: return plane_n<float, 32>(forward, in, out, tw, planes, map, me, mi, s);
         case 64: return plane_n<float, 64>(forward, in, out, tw, planes, map, me, mi, s);
         case 128: return plane_n<float, 128>(forward, in, out, tw, planes, map, me, mi, s);
-        default: return plane_n<float, 256>(forward, in, out, tw, planes, map, me, mi, s);
+        case 256: return plane_n<float, 256>(forward, in, out, tw, planes, map, me, mi, s);
+        default: return hipErrorInvalidValue;
     }
 }
 

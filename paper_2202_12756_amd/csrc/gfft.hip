@@ -255,8 +255,9 @@ gfft_status check_r2c_args(const gfft_plan* p, const void* real, const void* cpl
 // Step 1 or its inverse as one pass per plane where a plane fits on a CU
 // (not for pencil plans, whose z output is cut into kz chunks, nor with the
 // matrix-core stage, which belongs to the y pass).
-bool plane_pass(const gfft_plan* p) {
-    return !p->pencil && mfma_terms(p) == 0 && gfft::plane_supported(f64(p), int(p->n));
+bool plane_pass(const gfft_plan* p, bool fwd) {
+    return !p->pencil && mfma_terms(p) == 0 &&
+           gfft::plane_supported(f64(p), int(p->n), p->batch * p->x, fwd);
 }
 
 gfft_status run_plane(const gfft_plan* p, bool fwd, const void* in, void* out, double scale,
@@ -338,7 +339,7 @@ gfft_status forward(const gfft_plan* p, const void* in, void* out, double scale,
         if ((st = run_split_rows(p, true, in, out, scale, weighted, s)) != GFFT_OK) return st;
         return run_split_x(p, -1, out, out, s);
     }
-    if (plane_pass(p)) {
+    if (plane_pass(p, true)) {
         if ((st = run_plane(p, true, in, out, scale, weighted, s)) != GFFT_OK) return st;
     } else if (y_step(p) > 1) {
         if ((st = run_rows(p, true, in, out, scale, weighted, s)) != GFFT_OK) return st;
@@ -366,7 +367,7 @@ gfft_status run_inverse(const gfft_plan* p, const void* in, void* work, void* ou
         if ((st = run_x(p, in, work, +1, s)) != GFFT_OK) return st;
         in = work;
     }
-    if (plane_pass(p)) return run_plane(p, false, in, out, scale, weighted, s);
+    if (plane_pass(p, false)) return run_plane(p, false, in, out, scale, weighted, s);
     if (y_step(p) > 1) {
         if ((st = run_y_lines(p, in, work, +1, s)) != GFFT_OK) return st;
         return run_rows(p, false, work, out, scale, weighted, s);
@@ -389,7 +390,7 @@ gfft_status inverse(const gfft_plan* p, void* in, void* out, double scale, bool 
 // the spectrum, or nothing where one kernel reads the input and writes the
 // field (small grids; slabs with step 1 in one pass).
 int64_t keep_work_bytes(const gfft_plan* p) {
-    return box_pass(p) || (p->p > 1 && plane_pass(p)) ? 0 : cplx_bytes(p);
+    return box_pass(p) || (p->p > 1 && plane_pass(p, false)) ? 0 : cplx_bytes(p);
 }
 
 // Second-exchange pack of a pencil plan with pr > pc: every y-pencil block

@@ -86,11 +86,12 @@ hipError_t launch_pack_rows(bool f64, const void* src, void* dst, int64_t rows, 
 
 // Step 1 (z R2C and y C2C of every x-plane) in one pass, or its inverse
 // (y C2C, then z C2R), one plane per workgroup, where a plane fits on a CU
-// (plane_supported: N = 32 to 128, FP32 also N = 256).  Rows of the half
-// spectrum follow `map` as in the z passes; the bin multipliers are those of
-// the z passes.  `in` and `out` may be the same buffer (in-place plans): each
-// plane is read whole before any of it is written.
-bool plane_supported(bool f64, int n);
+// (N = 32 to 128, FP32 also N = 256); plane_supported also says whether `planes` of
+// them are better off so.  Rows of the half spectrum follow `map` as in the z
+// passes; the bin multipliers are those of the z passes.  `in` and `out` may be
+// the same buffer (in-place plans): each plane is read whole before any of it is
+// written.
+bool plane_supported(bool f64, int n, int64_t planes, bool forward);
 hipError_t launch_plane(bool f64, bool forward, int n, const void* in, void* out, const void* tw,
                         int64_t planes, row_map map, double mul_edge, double mul_int,
                         hipStream_t s);

@@ -21,7 +21,8 @@ F64, F32 = torch.float64, torch.float32
 DTYPES = pytest.mark.parametrize("dtype", [F64, F32], ids=["f64", "f32"])
 
 # (n, x, batch): step 1 of slabs (x < n) and whole grids
-PLANE_TILES = [(32, 4, 2), (32, 32, 2), (64, 8, 2), (64, 64, 1), (128, 8, 1), (128, 128, 1),
+PLANE_TILES = [(32, 4, 2), (32, 32, 2), (64, 8, 2), (64, 64, 1), (128, 8, 1), (128, 8, 24),
+               (128, 128, 1), (256, 8, 24),
                (256, 2, 1), (256, 256, 1), (512, 2, 1), (512, 512, 1), (1024, 2, 1)]
 ROW_TILES = [(2048, 1, 2), (4096, 1, 1)]
 BOXES = [(16, 16, 3), (32, 32, 97)]
@@ -52,7 +53,7 @@ def test_empty_planes_stay_empty(n, x, batch, inplace, dtype):
 
 
 @DTYPES
-@pytest.mark.parametrize("n,x,batch", BOXES + [(32, 4, 2), (64, 64, 1), (128, 128, 1), (256, 2, 1),
+@pytest.mark.parametrize("n,x,batch", BOXES + [(32, 4, 2), (64, 64, 1), (128, 8, 24), (128, 128, 1), (256, 2, 1),
                                                (512, 2, 1), (1024, 1, 1), (2048, 1, 1)])
 def test_odd_planes_beside_a_strong_kz_0(n, x, batch, dtype):
     """g(x, y) + 1e-4 noise: the odd kz see only the differences f[n] -
@@ -86,7 +87,8 @@ def test_z_pass_near_the_largest_value(n, dtype):
 @DTYPES
 @pytest.mark.parametrize("order", ["natural", "inplace", "send"])
 @pytest.mark.parametrize("n,x,batch", BOXES + [(32, 32, 2), (32, 4, 2), (64, 64, 1), (64, 2, 1),
-                                               (128, 128, 1), (128, 2, 1), (256, 256, 1), (256, 2, 1),
+                                               (128, 128, 1), (128, 2, 1), (128, 8, 24), (256, 8, 24),
+                                               (256, 256, 1), (256, 2, 1),
                                                (512, 512, 1), (512, 16, 1), (1024, 16, 1), (2048, 8, 1),
                                                (4096, 4, 1)])
 def test_imaginary_parts_that_do_not_count(n, x, batch, order, dtype):
