@@ -748,9 +748,12 @@ static hipError_t strided_flat(int sign, const void* src, void* data, const void
 // pencil x 3.00 and 2.60; whole chains: FP64 512^3/4 in the paper's order 320
 // us against 337, FP64 1024 4 x 4 pencil 626 against 642, FP32 2048 1 x 256
 // 209 against 235), but contiguously for y lines of 512 (FP64 5.23 against
-// 4.65) and in FP64 for those of natural order (1024 4.88 against 4.76), from
-// N = 2048 (4096 16 x 32 pencil 1539 us against 1632) and for x lines of 256
-// (4.46 against 3.7).
+// 4.65), for those of natural order in FP64 (1024 4.88 against 4.76) and of FP32
+// 1024 (128 planes 234 us against 243, with the matrix-core stage 330 and 340; its
+// lines of 64 327 and 336), for FP32 4096 pencils whose tiles own their lines (16 x
+// 32 315 and 352), and in FP64 from N = 2048 (4096 16 x 32 pencil 1539 us against
+// 1632) and for x lines of 256 (4.46 against 3.7) and 512 (the paper's order, p = 8,
+// 223 us against 243).
 template <typename T, int N>
 struct line_order {
     static constexpr bool F64 = sizeof(T) == 8;
@@ -792,10 +795,14 @@ static hipError_t strided_ax(int sign, const void* src, void* data, const void* 
         if (lm.s_lo * ES < 4096)
             return strided_run<T, N, AX, MF, false>(kContig, sign, src, data, tw, m_cols, n_b, lm, s);
     }
-    if constexpr (F64 && (N >= 2048 || (AX == 1 && N == 256)))
+    if constexpr (F64 && (N >= 2048 || (AX == 1 && (N == 256 || N == 512))))
         return strided_run<T, N, AX, MF, false>(kContig, sign, src, data, tw, m_cols, n_b, lm, s);
-    if constexpr ((F64 || N == 512) && AX == 0) {
+    if constexpr (AX == 0 && (F64 || N == 512 || N == 1024 || (MF > 0 && N == 64))) {
         if ((lm.lg_y >= ilog2_c(N) || N == 512) && lm.s_lo == m_cols)
+            return strided_run<T, N, AX, MF, false>(kContig, sign, src, data, tw, m_cols, n_b, lm, s);
+    }
+    if constexpr (AX == 0 && !F64 && N == 4096) {
+        if (whole_lines(data, m_cols, lm, 128 / ES))
             return strided_run<T, N, AX, MF, false>(kContig, sign, src, data, tw, m_cols, n_b, lm, s);
     }
     return strided_run<T, N, AX, MF, false>(kGrouped, sign, src, data, tw, m_cols, n_b, lm, s);
