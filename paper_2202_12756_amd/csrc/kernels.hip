@@ -791,6 +791,12 @@ static hipError_t strided_ax(int sign, const void* src, void* data, const void* 
         if ((N >= 1024 ? 2 : N == 16 ? 16 : 4) * m_cols <= SH::TC && m_cols > 0 && n_b > 1)
             return strided_flat<T, N, AX>(sign, src, data, tw, m_cols, n_b, lm, s);
     }
+    // FP64 x lines of 64 in tiles of 32 columns: the 33 of the paper's order would
+    // take two (512 MB 240 us, numbered through 208, one tile of 64 204)
+    if constexpr (MF == 0 && AX == 1 && F64 && N == 64) {
+        if (m_cols > SH::TC && m_cols < 2 * SH::TC && n_b > 1)
+            return strided_flat<T, N, AX>(sign, src, data, tw, m_cols, n_b, lm, s);
+    }
     if constexpr (AX == 1 && N <= 256) {
         if (lm.s_lo * ES < 4096)
             return strided_run<T, N, AX, MF, false>(kContig, sign, src, data, tw, m_cols, n_b, lm, s);

@@ -43,9 +43,9 @@ def test_planes_past_one_grid_of_y(x):
 
 @pytest.mark.parametrize("dtype", [torch.float64, torch.float32], ids=["f64", "f32"])
 @pytest.mark.parametrize("order", ["natural", "send", "paper"])
-@pytest.mark.parametrize("n,x,batch", [(16, 1, 2), (16, 4, 33), (32, 2, 9)])
+@pytest.mark.parametrize("n,x,batch", [(16, 1, 2), (16, 4, 33), (32, 2, 9), (64, 4, 3)])
 def test_lines_of_narrow_sets(n, x, batch, order, dtype):
-    """y and x lines of 9 and 17 columns, the last tile ragged."""
+    """y and x lines of 9, 17 and 33 columns, the last tile ragged."""
     p = Plan(n, dtype, slab_x=x, batch=batch, fuse_pack=order in ("send", "paper"),
              paper_order=order == "paper")
     a, ref = cplx_input((batch, x, n, n // 2 + 1), 38000 + n, dtype)
