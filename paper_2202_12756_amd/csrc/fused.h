@@ -408,7 +408,17 @@ __global__ __launch_bounds__((plane_shape<T, N, R, E>::NT), W) void k_plane_c2r(
     fft_regs<T, M, E, +1, RM>(g, t, tw, 2, xch_split<T, IR>{lds, IR{r * P::MP}});
     cx<T>* dst = reinterpret_cast<cx<T>*>(out + (plane * N + y0 + R * r) * map.rs);
 #pragma unroll
-    for (int m = 0; m < E; ++m) dst[t + TZ * m] = g[m];
+    for (int m = 0; m < E; ++m) {
+        // real rows past a y step are long: not read again soon, they leave the
+        // memory cache to the half spectrum (256 MB of reals, FP64 1024 207 -> 151
+        // us an inverse, FP32 512 196 -> 152; pairs of 64 MB FP32 512 88 -> 91)
+        if constexpr (TWD) {
+            __builtin_nontemporal_store(g[m].x, &dst[t + TZ * m].x);
+            __builtin_nontemporal_store(g[m].y, &dst[t + TZ * m].y);
+        } else {
+            dst[t + TZ * m] = g[m];
+        }
+    }
 }
 
 // ---------------------------------------------------------------- long rows: z with a short y step
