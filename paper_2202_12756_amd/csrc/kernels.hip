@@ -863,6 +863,11 @@ hipError_t launch_z_r2c(bool f64, int n, const void* in, void* out, const void* 
 
 hipError_t launch_z_c2r(bool f64, int n, const void* in, void* out, const void* tw,
                         int64_t rows, row_map map, double me, double mi, hipStream_t s) {
+    // FP64 2048 rows in an array of the L2s' size: a row to a 64-thread workgroup
+    // and whole-value exchanges (one plane 12.5 us, k_rows_c2r 16.3; 16 planes 227
+    // and 196)
+    if (f64 && n == 2048 && tile_order(rows * 1025 * 16, kGrouped) == kContig)
+        return z_c2r_n<double, 2048>(in, out, tw, rows, map, me, mi, s);
     if (n >= 2048) return launch_rows(f64, false, n, 1, in, out, tw, rows, map, me, mi, s);
     if (f64) { GFFT_DISPATCH_TO_1024(z_c2r_n, double, in, out, tw, rows, map, me, mi, s) }
     GFFT_DISPATCH_TO_1024(z_c2r_n, float, in, out, tw, rows, map, me, mi, s)
