@@ -605,6 +605,20 @@ static hipError_t z_r2c_n(const void* in, void* out, const void* tw, int64_t row
     // best in launch order (512 MB 198 us, groups 208; 64 and 128 lose 10-20% by it)
     const bool spread = sizeof(T) == 8 && N == 256 && map.paper;
     const int ord = tile_order(rows * (N / 2 + 1) * int64_t(sizeof(cx<T>)), spread ? 0 : kGrouped);
+    if constexpr (sizeof(T) == 4 && N <= 128) {
+        // chunks of one bin, a block of rows each: as many rows as can be at a time
+        // (512 MB, one plane's columns to a rank: N = 64 203 us, the 8-values shape
+        // 261, 128 242 and 272)
+        if (map.pencil && map.lg_w == 0 && map.lg_rows >= 6) {
+            using ZW = zshape<N / 2, 32, 64>;
+            const int64_t wide = (rows + ZW::RPB - 1) / ZW::RPB;
+            if (!grid_fits(wide, ZW::NT)) return hipErrorInvalidValue;
+            hipLaunchKernelGGL((k_z_r2c_pencil<T, N, 32, 64>), dim3(wide), dim3(ZW::NT), 0, s,
+                               static_cast<const T*>(in), static_cast<cx<T>*>(out),
+                               static_cast<const cx<T>*>(tw), rows, map, T(me), T(mi), ord);
+            return hipGetLastError();
+        }
+    }
     if (blocks == 0) return hipSuccess;
     if (!grid_fits(blocks, Z::NT)) return hipErrorInvalidValue;
     if (map.pencil)

@@ -89,3 +89,16 @@ def test_short_pencil_lines(n, pr, pc, dtype):
         for sign in (-1, +1):
             assert rel_l2(lines(host(p.x_c2c(g.clone(), sign))),
                           oracle.c2c_axis(lines(gref), 1, sign)) <= TOL[dtype]
+
+
+@pytest.mark.parametrize("n,pr,pc", [(16, 1, 8), (32, 1, 16), (64, 1, 32), (128, 1, 64), (128, 4, 64)])
+def test_rows_into_chunks_of_one_bin(n, pr, pc):
+    """FP32 z rows written one bin to a chunk, 64 rows of a grid and more (a row or
+    two to a thread) and fewer."""
+    p = PencilPlan(n, torch.float32, (pr, pc), 0, batch=3)
+    f, ref = real_input(p.real_shape, 39800 + n, torch.float32)
+    want = oracle.r2c_last(ref)
+    got = p.z_r2c(f)
+    for c in range(pc):
+        k0, k1 = p.kz_range(c)
+        assert rel_l2(host(p.chunk(got, c)), want[..., k0:k1]) <= TOL[torch.float32]
