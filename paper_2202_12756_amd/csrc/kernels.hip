@@ -721,7 +721,8 @@ static hipError_t strided_run(int large, int sign, const void* src, void* data, 
 // y lines of pencils with narrow kz chunks (FP32 2048 1 x 1024 ranks, one bin, z, y
 // and x 171 -> 124 us, FP64 1024 1 x 256 96 -> 52, 4096 8 x 2048 81 -> 65) and the
 // 9 or 17 columns of N = 16 and 32.
-template <typename T, int N, int AX>
+// MF: 0 or -1 (k_strided).
+template <typename T, int N, int AX, int MF>
 static hipError_t strided_flat(int sign, const void* src, void* data, const void* tw,
                                int64_t m_cols, int64_t n_b, line_map lm, hipStream_t s) {
     using SH = sshape<T, N, AX>;
@@ -730,12 +731,12 @@ static hipError_t strided_flat(int sign, const void* src, void* data, const void
     const int ord = tile_order(cols * N * int64_t(sizeof(cx<T>)), kGrouped);
     if (!grid_fits(blocks, TC * SH::TPT)) return hipErrorInvalidValue;
     const dim3 threads(TC * SH::TPT);
-    if (sign < 0)
-        hipLaunchKernelGGL((k_strided<T, N, TC, SH::XP, -1, SH::E, 0, false, 1, true>),
+    if (MF < 0 || sign < 0)
+        hipLaunchKernelGGL((k_strided<T, N, TC, SH::XP, -1, SH::E, MF, false, 1, true>),
                            dim3(blocks), threads, 0, s, static_cast<const cx<T>*>(src),
                            static_cast<cx<T>*>(data), static_cast<const cx<T>*>(tw), m_cols, cols, lm, ord);
-    else
-        hipLaunchKernelGGL((k_strided<T, N, TC, SH::XP, +1, SH::E, 0, false, 1, true>),
+    else if constexpr (MF >= 0)
+        hipLaunchKernelGGL((k_strided<T, N, TC, SH::XP, +1, SH::E, MF, false, 1, true>),
                            dim3(blocks), threads, 0, s, static_cast<const cx<T>*>(src),
                            static_cast<cx<T>*>(data), static_cast<const cx<T>*>(tw), m_cols, cols, lm, ord);
     return hipGetLastError();
@@ -800,19 +801,19 @@ static hipError_t strided_ax(int sign, const void* src, void* data, const void* 
             }
         }
     }
-    if constexpr (MF == 0 && (AX == 0 || N <= 32)) {
+    if constexpr (MF <= 0 && (AX == 0 || N <= 32)) {
         // sets that would leave half (from N = 1024), three quarters or (N = 16)
         // 15 of 16 of a tile's lanes idle: 512 MB of N = 16 slabs 9 columns FP64 232
         // us, a tile per set 348, but 18 columns 228 and 209; N = 32 17 columns 210
         // and 500
         if ((N >= 1024 ? 2 : N == 16 ? 16 : 4) * m_cols <= SH::TC && m_cols > 0 && n_b > 1)
-            return strided_flat<T, N, AX>(sign, src, data, tw, m_cols, n_b, lm, s);
+            return strided_flat<T, N, AX, MF>(sign, src, data, tw, m_cols, n_b, lm, s);
     }
     // FP64 x lines of 64 in tiles of 32 columns: the 33 of the paper's order would
     // take two (512 MB 240 us, numbered through 208, one tile of 64 204)
-    if constexpr (MF == 0 && AX == 1 && F64 && N == 64) {
+    if constexpr (MF <= 0 && AX == 1 && F64 && N == 64) {
         if (m_cols > SH::TC && m_cols < 2 * SH::TC && n_b > 1)
-            return strided_flat<T, N, AX>(sign, src, data, tw, m_cols, n_b, lm, s);
+            return strided_flat<T, N, AX, MF>(sign, src, data, tw, m_cols, n_b, lm, s);
     }
     if constexpr (AX == 1 && N <= 256) {
         if (lm.s_lo * ES < 4096)
