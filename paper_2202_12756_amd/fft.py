@@ -14,7 +14,11 @@ _REAL = {torch.float64: _lib.GFFT_F64, torch.float32: _lib.GFFT_F32}
 _CPLX = {torch.float64: torch.complex128, torch.float32: torch.complex64}
 
 
-_raw_stream = torch._C._cuda_getCurrentRawStream
+try:
+    from torch._C import _cuda_getCurrentRawStream as _raw_stream
+except ImportError:  # a torch built without a GPU runtime: the package still imports
+    def _raw_stream(index: int) -> int:
+        return torch.cuda.current_stream(index).cuda_stream
 
 
 def _stream(device) -> int:
