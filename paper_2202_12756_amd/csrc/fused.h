@@ -950,7 +950,8 @@ struct xr_shape {
     static constexpr int NP = padded_len<N, PS>::value;
     static constexpr int LDS = R * NP * TC;  // values of type T
     static constexpr int COLS = NY * K;
-    static constexpr int TILES = (COLS + TC - 1) / TC;  // per grid
+    static constexpr int TILES = COLS / TC;  // per grid
+    static_assert(COLS % TC == 0, "tiles own whole columns");
 };
 
 template <typename T, int N, int R, int TC, int EX, int S, bool NT, int W>
@@ -963,15 +964,13 @@ __global__ __launch_bounds__((xr_shape<T, N, R, TC, EX>::NT), W) void k_strided_
     const int64_t tile = xcd_tile(ord, blockIdx.x, gridDim.x);
     const int64_t b = tile / P::TILES;
     const int m = int(tile - b * P::TILES) * TC + c;
-    const bool valid = m < P::COLS;
-    const int ml = valid ? m : P::COLS - 1;
-    const int k1 = ml / K;
+    const int k1 = m / K;
     // Element (x, y0) of this lane: a workgroup-uniform base plus the lane's
     // byte offset, which fits 32 bits (checked below), so that one vector
     // register addresses all of them.
     constexpr int64_t XS = int64_t(N) * K, YS = int64_t(NY) * K;
     static_assert((TPT * XS + NY * K) * int64_t(sizeof(cx<T>)) < (int64_t(1) << 32), "lane offset");
-    const uint32_t lane = uint32_t((t * XS + ml) * int64_t(sizeof(cx<T>)));
+    const uint32_t lane = uint32_t((t * XS + m) * int64_t(sizeof(cx<T>)));
     src += b * N * XS;
     dst += b * N * XS;
 
@@ -1012,7 +1011,6 @@ __global__ __launch_bounds__((xr_shape<T, N, R, TC, EX>::NT), W) void k_strided_
         for (int y = 0; y < R; ++y) a[y][i] = v[y];
     }
     fft_multi<T, N, EX, R, S, 1, P::RM, TC, P::PS>(a, t, c, tw, 1, lds);
-    if (!valid) return;
 #pragma unroll
     for (int i = 0; i < EX; ++i)
 #pragma unroll
