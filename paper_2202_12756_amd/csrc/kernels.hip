@@ -62,9 +62,11 @@ struct zshape {
 // Workgroups are dealt to the XCDs in groups of 16: TB/s against contiguous
 // eighths, R2C / C2R, FP64 N = 1024 5.89 / 5.95 (5.56 / 5.63), 512 5.76 / 6.09
 // (5.39 / 5.75), FP32 1024 5.32 / 5.35 (4.96 / 5.07), 512 5.19 / 5.25 (4.93 /
-// 5.08).  The C2R also stores its line-aligned real rows
-// non-temporally (they are not read again soon); the R2C's complex rows are
-// not line-aligned and gain nothing from it.
+// 5.08).  The C2R also stores its line-aligned real rows non-temporally (they are
+// not read again soon); the R2C's complex rows are not line-aligned and gain
+// nothing from it.  Up to N = 128: 8 values per thread (N = 16: 4) in 256-thread
+// workgroups, both types and directions (FP32 64 C2R 3.7 times, R2C 1.7 times as
+// fast as the 64-thread shape; FP64 4-15% C2R, 3-8% R2C).
 template <typename T, bool FWD, int N>
 struct zcfg {
     static constexpr bool F64 = sizeof(T) == 8;
@@ -76,15 +78,13 @@ struct zcfg {
         N <= 128 ? 256
         : F64 ? (FWD ? (N >= 1024 ? 128 : 256) : 64)
               : MID32 ? (FWD || N == 256 ? 256 : 128) : (FWD && N >= 1024 ? 256 : 64);
-    static constexpr bool NTS = !FWD;
 };
 
 // ---------------------------------------------------------------- z R2C
 // ALIAS: `in` and `out` are the same buffer (in-place plans).  Each row is
 // read completely before the first barrier and written after the last one,
 // so a row is never overwritten before all of it has been loaded.
-template <typename T, int N, int EMAX, int THREADS, bool NTS, bool ALIAS,
-          bool PENCIL = false>
+template <typename T, int N, int EMAX, int THREADS, bool ALIAS, bool PENCIL = false>
 __device__ __forceinline__ void z_r2c_body(
     const T* in, cx<T>* out, const cx<T>* __restrict__ tw,
     int64_t rows, row_map map, T mul_edge, T mul_int, int ord) {
@@ -125,14 +125,8 @@ __device__ __forceinline__ void z_r2c_body(
     const cx<T> x_m{(a[0].x - a[0].y) * mul_edge, T(0)};
     cx<T>* dst = out + (PENCIL ? 0 : map_row(row, map) * K);
     auto put = [&](int k, cx<T> v) {
-        if constexpr (PENCIL) {
-            out[pencil_bin(row, k, K, map)] = v;
-        } else if constexpr (NTS) {
-            __builtin_nontemporal_store(v.x, &dst[k].x);
-            __builtin_nontemporal_store(v.y, &dst[k].y);
-        } else {
-            dst[k] = v;
-        }
+        if constexpr (PENCIL) out[pencil_bin(row, k, K, map)] = v;
+        else dst[k] = v;
     };
 #pragma unroll
     for (int m = 0; m < E; ++m) {
@@ -154,18 +148,18 @@ __device__ __forceinline__ void z_r2c_body(
     if (t == 0) put(M, x_m);
 }
 
-template <typename T, int N, int EMAX, int THREADS, bool NTS>
+template <typename T, int N, int EMAX, int THREADS>
 __global__ __launch_bounds__((zshape<N / 2, EMAX, THREADS>::NT)) void k_z_r2c(
     const T* __restrict__ in, cx<T>* __restrict__ out, const cx<T>* __restrict__ tw,
     int64_t rows, row_map map, T mul_edge, T mul_int, int ord) {
-    z_r2c_body<T, N, EMAX, THREADS, NTS, false>(in, out, tw, rows, map, mul_edge, mul_int, ord);
+    z_r2c_body<T, N, EMAX, THREADS, false>(in, out, tw, rows, map, mul_edge, mul_int, ord);
 }
 
-template <typename T, int N, int EMAX, int THREADS, bool NTS>
+template <typename T, int N, int EMAX, int THREADS>
 __global__ __launch_bounds__((zshape<N / 2, EMAX, THREADS>::NT)) void k_z_r2c_inplace(
     const T* in, cx<T>* out, const cx<T>* __restrict__ tw,
     int64_t rows, row_map map, T mul_edge, T mul_int, int ord) {
-    z_r2c_body<T, N, EMAX, THREADS, NTS, true>(in, out, tw, rows, map, mul_edge, mul_int, ord);
+    z_r2c_body<T, N, EMAX, THREADS, true>(in, out, tw, rows, map, mul_edge, mul_int, ord);
 }
 
 // Pencil plans: bins scattered to the first exchange's chunks.
@@ -173,11 +167,11 @@ template <typename T, int N, int EMAX, int THREADS>
 __global__ __launch_bounds__((zshape<N / 2, EMAX, THREADS>::NT)) void k_z_r2c_pencil(
     const T* __restrict__ in, cx<T>* __restrict__ out, const cx<T>* __restrict__ tw,
     int64_t rows, row_map map, T mul_edge, T mul_int, int ord) {
-    z_r2c_body<T, N, EMAX, THREADS, false, false, true>(in, out, tw, rows, map, mul_edge, mul_int, ord);
+    z_r2c_body<T, N, EMAX, THREADS, false, true>(in, out, tw, rows, map, mul_edge, mul_int, ord);
 }
 
 // ---------------------------------------------------------------- z C2R
-template <typename T, int N, int EMAX, int THREADS, bool NTS, bool PENCIL = false>
+template <typename T, int N, int EMAX, int THREADS, bool PENCIL = false>
 __device__ __forceinline__ void z_c2r_body(
     const cx<T>* in, T* out, const cx<T>* __restrict__ tw,
     int64_t rows, row_map map, T mul_edge, T mul_int, int ord) {
@@ -239,37 +233,33 @@ __device__ __forceinline__ void z_c2r_body(
     cx<T>* dst = reinterpret_cast<cx<T>*>(out + row * map.rs);
 #pragma unroll
     for (int m = 0; m < E; ++m) {
-        if constexpr (NTS) {
-            __builtin_nontemporal_store(a[m].x, &dst[t + m * TPT].x);
-            __builtin_nontemporal_store(a[m].y, &dst[t + m * TPT].y);
-        } else {
-            dst[t + m * TPT] = a[m];
-        }
+        __builtin_nontemporal_store(a[m].x, &dst[t + m * TPT].x);
+        __builtin_nontemporal_store(a[m].y, &dst[t + m * TPT].y);
     }
 }
 
-template <typename T, int N, int EMAX, int THREADS, bool NTS>
+template <typename T, int N, int EMAX, int THREADS>
 __global__ __launch_bounds__((zshape<N / 2, EMAX, THREADS>::NT)) void k_z_c2r(
     const cx<T>* __restrict__ in, T* __restrict__ out, const cx<T>* __restrict__ tw,
     int64_t rows, row_map map, T mul_edge, T mul_int, int ord) {
-    z_c2r_body<T, N, EMAX, THREADS, NTS>(in, out, tw, rows, map, mul_edge, mul_int, ord);
+    z_c2r_body<T, N, EMAX, THREADS>(in, out, tw, rows, map, mul_edge, mul_int, ord);
 }
 
 // In place: every load of a row precedes the barrier after the LDS fill, and
 // every store follows the last barrier of the FFT.
-template <typename T, int N, int EMAX, int THREADS, bool NTS>
+template <typename T, int N, int EMAX, int THREADS>
 __global__ __launch_bounds__((zshape<N / 2, EMAX, THREADS>::NT)) void k_z_c2r_inplace(
     const cx<T>* in, T* out, const cx<T>* __restrict__ tw,
     int64_t rows, row_map map, T mul_edge, T mul_int, int ord) {
-    z_c2r_body<T, N, EMAX, THREADS, NTS>(in, out, tw, rows, map, mul_edge, mul_int, ord);
+    z_c2r_body<T, N, EMAX, THREADS>(in, out, tw, rows, map, mul_edge, mul_int, ord);
 }
 
 // Pencil plans: bins gathered from the first exchange's chunks.
-template <typename T, int N, int EMAX, int THREADS, bool NTS>
+template <typename T, int N, int EMAX, int THREADS>
 __global__ __launch_bounds__((zshape<N / 2, EMAX, THREADS>::NT)) void k_z_c2r_pencil(
     const cx<T>* __restrict__ in, T* __restrict__ out, const cx<T>* __restrict__ tw,
     int64_t rows, row_map map, T mul_edge, T mul_int, int ord) {
-    z_c2r_body<T, N, EMAX, THREADS, NTS, true>(in, out, tw, rows, map, mul_edge, mul_int, ord);
+    z_c2r_body<T, N, EMAX, THREADS, true>(in, out, tw, rows, map, mul_edge, mul_int, ord);
 }
 
 // ---------------------------------------------------------------- y / x C2C
@@ -626,12 +616,12 @@ static hipError_t z_r2c_n(const void* in, void* out, const void* tw, int64_t row
                            dim3(Z::NT), 0, s, static_cast<const T*>(in), static_cast<cx<T>*>(out),
                            static_cast<const cx<T>*>(tw), rows, map, T(me), T(mi), ord);
     else if (in == out)
-        hipLaunchKernelGGL((k_z_r2c_inplace<T, N, C::EMAX, C::THREADS, C::NTS>),
+        hipLaunchKernelGGL((k_z_r2c_inplace<T, N, C::EMAX, C::THREADS>),
                            dim3(blocks), dim3(Z::NT), 0, s, static_cast<const T*>(in),
                            static_cast<cx<T>*>(out), static_cast<const cx<T>*>(tw), rows, map,
                            T(me), T(mi), ord);
     else
-        hipLaunchKernelGGL((k_z_r2c<T, N, C::EMAX, C::THREADS, C::NTS>), dim3(blocks),
+        hipLaunchKernelGGL((k_z_r2c<T, N, C::EMAX, C::THREADS>), dim3(blocks),
                            dim3(Z::NT), 0, s, static_cast<const T*>(in), static_cast<cx<T>*>(out),
                            static_cast<const cx<T>*>(tw), rows, map, T(me), T(mi), ord);
     return hipGetLastError();
@@ -654,17 +644,17 @@ static hipError_t z_c2r_n(const void* in, void* out, const void* tw, int64_t row
     if (blocks == 0) return hipSuccess;
     if (!grid_fits(blocks, Z::NT)) return hipErrorInvalidValue;
     if (map.pencil)
-        hipLaunchKernelGGL((k_z_c2r_pencil<T, N, C::EMAX, C::THREADS, C::NTS>),
+        hipLaunchKernelGGL((k_z_c2r_pencil<T, N, C::EMAX, C::THREADS>),
                            dim3(blocks), dim3(Z::NT), 0, s, static_cast<const cx<T>*>(in),
                            static_cast<T*>(out), static_cast<const cx<T>*>(tw), rows, map,
                            T(me), T(mi), ord);
     else if (in == out)
-        hipLaunchKernelGGL((k_z_c2r_inplace<T, N, C::EMAX, C::THREADS, C::NTS>),
+        hipLaunchKernelGGL((k_z_c2r_inplace<T, N, C::EMAX, C::THREADS>),
                            dim3(blocks), dim3(Z::NT), 0, s, static_cast<const cx<T>*>(in),
                            static_cast<T*>(out), static_cast<const cx<T>*>(tw), rows, map,
                            T(me), T(mi), ord);
     else
-        hipLaunchKernelGGL((k_z_c2r<T, N, C::EMAX, C::THREADS, C::NTS>), dim3(blocks),
+        hipLaunchKernelGGL((k_z_c2r<T, N, C::EMAX, C::THREADS>), dim3(blocks),
                            dim3(Z::NT), 0, s, static_cast<const cx<T>*>(in), static_cast<T*>(out),
                            static_cast<const cx<T>*>(tw), rows, map, T(me), T(mi), ord);
     return hipGetLastError();
