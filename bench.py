@@ -1,15 +1,16 @@
 """Benchmark: 3D R2C + C2R round trip of a 1024^3 FP64 grid on one MI355X.
 
 One step = the whole hot path once through the public calls: gfft_exec_r2c
-(z pass, y pass, x pass) and gfft_exec_c2r (x, y, z passes with the 1/N^3
-normalization fused), on a synthetic seeded uniform[-1,1) field already
-resident in HBM.  `value` is the wall-clock rate of those K steps; HIP events
-around each step give its median and minimum.  An instrumented repeat of the
-same K steps through the single-pass entry points, with HIP events between
-the passes on the launch stream, gives each kernel's live duration (the
-roofline figure).  Two yardsticks sit beside it: the library's streaming
-copy (contiguous traffic) and the y and x passes' loads and stores without
-their transform (the ceiling of their access pattern).
+and gfft_exec_c2r (with the 1/N^3 normalization fused), on a synthetic seeded
+uniform[-1,1) field already resident in HBM.  `value` is the wall-clock rate of
+those K steps; HIP events around each step give its median and minimum.  Two
+repeats follow: the same step under torch's kernel trace gives the duration of
+each kernel that it launches (`step_kernels`; the slowest is the roofline
+figure), and K steps through the single-pass entry points, with HIP events
+between them, give theirs (`per_pass_*`: the whole z, y and x passes, which the
+step itself runs only in part).  Two yardsticks sit beside them: the library's
+streaming copy (contiguous traffic) and the y and x passes' loads and stores
+without their transform (the ceiling of their access pattern).
 
 Prints ONE JSON line (rank 0).  Run ``python bench.py --help`` for options.
 """
@@ -71,8 +72,9 @@ def kernel_source_hash() -> str:
 
 
 def recorded_traffic(path: str, pass_name: str):
-    """Calibrated HBM bytes per launch of `pass_name` from the PMC summary,
-    or None when the summary is missing or the kernels changed since."""
+    """Calibrated HBM bytes per launch of `pass_name` (a pass or a kernel) from
+    the PMC summary, or None when the summary is missing or the kernels changed
+    since."""
     if not os.path.exists(path):
         return None
     sha, rows, col = None, {}, None
@@ -85,10 +87,56 @@ def recorded_traffic(path: str, pass_name: str):
                 col = cells.index("HBM bytes (scaled)") if "HBM bytes (scaled)" in cells else None
             elif line.startswith("| ") and col is not None and len(cells) > col \
                     and cells[col].isdigit():
-                rows[cells[0]] = int(cells[col])
+                rows[cells[0]] = rows[short_kernel(cells[1].strip("`"))] = int(cells[col])
     if sha != kernel_source_hash():
         return None
     return rows.get(pass_name)
+
+
+def short_kernel(name: str) -> str:
+    """A kernel's name and template arguments: the library's namespace, the
+    return type and the parameter list off."""
+    return name.split("(")[0].replace("void ", "").replace("gfft::", "").strip()
+
+
+def kernel_bytes(name: str, R: int, C: int) -> int:
+    """Bytes one launch of a full transform's kernel reads and writes: lines of
+    the half spectrum (C) in place, or the field (R) and the half spectrum."""
+    return 2 * C if short_kernel(name).startswith("k_strided") else R + C
+
+
+def step_kernels(run, steps: int = 5) -> dict:
+    """Mean device ms of each library kernel that run() launches, by torch's
+    kernel trace ({} where it cannot trace, as under another profiler)."""
+    if "ROCP_TOOL_LIBRARIES" in os.environ:
+        return {}
+    try:
+        from torch.profiler import ProfilerActivity, profile
+
+        with profile(activities=[ProfilerActivity.CUDA]) as prof:
+            for _ in range(steps + 1):  # the first launches may miss the trace
+                run()
+            torch.cuda.synchronize()
+    except (ImportError, RuntimeError) as e:
+        print(f"[bench] no kernel trace: {e}", file=sys.stderr, flush=True)
+        return {}
+    times: dict = {}
+    for e in sorted(prof.events(), key=lambda e: e.time_range.start):
+        if "gfft::" in e.name:
+            times.setdefault(short_kernel(e.name), []).append(e.device_time / 1e3)
+    return {k: sum(v[-steps:]) / len(v[-steps:]) for k, v in times.items()}
+
+
+def roofline(kernels: dict, R: int, C: int, traffic) -> dict:
+    """The roofline entry of the slowest of the step's kernels; traffic(name)
+    gives its recorded HBM bytes."""
+    dom = max(kernels, key=kernels.get)
+    nbytes = kernel_bytes(dom, R, C)
+    gbs = nbytes / (kernels[dom] * 1e-3) / 1e9
+    return {"bound": "hbm", "kernel": dom, "achieved": round(gbs, 1), "peak": PEAK_HBM_GBS,
+            "unit": "GB/s", "frac": round(gbs / PEAK_HBM_GBS, 4), "traffic": traffic(dom),
+            "algorithmic_bytes_per_launch": nbytes, "avg_launch_ms": round(kernels[dom], 4),
+            "source": "kernel trace of a repeat of the timed step"}
 
 
 def gflop_pair(n: int) -> float:
@@ -762,10 +810,12 @@ def main():
         del dlt
     rel = math.sqrt(num / den)
 
-    # Instrumented repeat: the same K steps through the single-pass entry
-    # points, with HIP events between the passes on the launch stream: each
-    # kernel's live average duration.  The x passes are the step's own
-    # kernels; its z passes may also take the first step of y.
+    # The step's own kernels
+    kernels = step_kernels(lambda: (plan.r2c(x, F), plan.c2r(F, y, scale)))
+
+    # The single-pass entry points: whole z, y and x passes with HIP events
+    # between them on the launch stream.  The step runs these kernels only in
+    # part: its z passes may take the first step of y, its x passes the last.
     passes = ["z_r2c", "y_fwd", "x_fwd", "x_inv", "y_inv", "z_c2r"]
 
     def step(ev):
@@ -800,13 +850,12 @@ def main():
     C = n * n * k * 2 * b
     bytes_pass = {"z_r2c": R + C, "y_fwd": 2 * C, "x_fwd": 2 * C,
                   "x_inv": 2 * C, "y_inv": 2 * C, "z_c2r": C + R}
-    kernel_name = {"z_r2c": "k_z_r2c", "y_fwd": "k_strided", "x_fwd": "k_strided",
-                   "x_inv": "k_strided", "y_inv": "k_strided", "z_c2r": "k_z_c2r"}
     gbs = {p: bytes_pass[p] / (per_pass[p] * 1e-3) / 1e9 for p in passes}
-    dom = max(passes, key=lambda p: per_pass[p])
-    traffic = None
-    if n == 1024 and dtype == torch.float64:
-        traffic = recorded_traffic(args.traffic or TRAFFIC_FILE, dom)
+
+    def traffic(name):
+        if n == 1024 and dtype == torch.float64:
+            return recorded_traffic(args.traffic or TRAFFIC_FILE, name)
+        return None
 
     gflop = gflop_pair(n)
     model_bytes = 2 * (R + 5 * C)
@@ -828,21 +877,15 @@ def main():
                                 f"{args.seed}); forward R2C + inverse C2R with 1/N^3 "
                                 f"through gfft_exec_r2c / gfft_exec_c2r"),
                    "n": n, "slab_x": n, "batch": 1},
-        "roofline": {"bound": "hbm",
-                     "kernel": f"{kernel_name[dom]} ({dom})",
-                     "achieved": round(gbs[dom], 1),
-                     "peak": PEAK_HBM_GBS, "unit": "GB/s",
-                     "frac": round(gbs[dom] / PEAK_HBM_GBS, 4),
-                     "traffic": traffic,
-                     "algorithmic_bytes_per_launch": bytes_pass[dom],
-                     "avg_launch_ms": round(per_pass[dom], 4),
-                     "source": ("HIP events between the passes of an instrumented repeat "
-                                "of the K steps through the single-pass entry points")},
+        "roofline": roofline(kernels, R, C, traffic) if kernels else None,
+        "step_kernels_ms": {k: round(v, 4) for k, v in kernels.items()},
         "step_ms": {"mean_wall": round(ms_step, 4),
                     "mean_events": round(sum(step_ms) / len(step_ms), 4),
                     "median": round(step_ms[len(step_ms) // 2], 4),
                     "min": round(step_ms[0], 4), "max": round(step_ms[-1], 4)},
         "exec_ms": {"r2c": round(r2c_ms, 4), "c2r": round(c2r_ms, 4)},
+        "per_pass_source": ("single-pass entry points (whole passes, not the step's kernels), "
+                            "HIP events between them"),
         "per_pass_ms": {p: round(v, 4) for p, v in per_pass.items()},
         "per_pass_GBps": {p: round(v, 1) for p, v in gbs.items()},
         "instrumented_ms_per_step": round(ms_instrumented, 4),
@@ -863,16 +906,20 @@ def main():
     ms_tcopy = time_pairs(lambda: y.copy_(x), 5, 1)
     line["copy_GBps"] = round(2 * R / (ms_copy * 1e-3) / 1e9, 1)
     line["torch_copy_GBps"] = round(2 * R / (ms_tcopy * 1e-3) / 1e9, 1)
-    line["roofline"]["frac_of_copy"] = round(gbs[dom] / line["copy_GBps"], 4)
+    if kernels:
+        line["roofline"]["frac_of_copy"] = round(line["roofline"]["achieved"] / line["copy_GBps"], 4)
     line["pair_frac_of_copy"] = round(model_bytes / (ms_step * 1e-3) / 1e9
                                       / line["copy_GBps"], 4)
     # the strided passes' own access-pattern ceilings: their loads and stores
     # without the transform (gfft_exec_pass_copy), on the same spectrum
     line["pattern_copy_GBps"] = pattern_copies(plan, F, F, 2 * C)
-    if dom[0] in "yx":
-        ceil = line["pattern_copy_GBps"][dom[0]]
+    # whole lines in a full grid's step are its x pass, which is the entry
+    # point's kernel
+    if kernels and line["roofline"]["kernel"].startswith(
+            f"k_strided<{'double' if dtype == torch.float64 else 'float'}, {n},"):
+        ceil = line["pattern_copy_GBps"]["x"]
         line["roofline"]["pattern_copy_GBps"] = ceil
-        line["roofline"]["frac_of_pattern_copy"] = round(gbs[dom] / ceil, 4)
+        line["roofline"]["frac_of_pattern_copy"] = round(line["roofline"]["achieved"] / ceil, 4)
     if not args.no_variants:
         del F, y
         torch.cuda.empty_cache()
