@@ -1028,14 +1028,15 @@ __global__ __launch_bounds__((xr_shape<T, N, R, TC, EX>::NT), W) void k_strided_
 // Shape of the one-plane kernels: elements per thread and the minimum of
 // waves per SIMD the register allocation keeps.  Measured over 537 MB of
 // reals (forward / inverse step 1, us; in brackets the separate z and y
-// passes, or for FP32 forward the earlier plane kernel): FP64 N = 64 8 per
-// thread 199 / 200 (417 / 490), 16 per thread 201 / 231; N = 128 16 per
-// thread at 2 waves 215 / 209 (405 / 433), at 4 waves 238 / 212, 8 per thread
-// 227 / 308; FP32 N = 64 8 per thread 219 / 222 (252 / 455), 16 per thread
-// 252 / 255; N = 128 16 per thread 228 / 220 (272 / 491), 8 per thread
-// 247 / 261; N = 256 32 per thread 327 / 333 (379 / 451): there one plane
-// fills half a CU's registers and its phases do not overlap another's.  The
-// streaming copy of the same bytes takes 173.  N = 32 (8 per thread, one wave a
+// passes): FP64 N = 64 197 / 179 (363 / 462), N = 128 224 / 210 (365 / 408);
+// FP32 N = 64 209 / 214 (468 / 479), N = 128 208 / 215 (432 / 450), N = 256
+// 309 / 331 (416 / 443): there one plane fills half a CU's registers and its
+// phases do not overlap another's.  Chosen over (forward / inverse, against
+// the form of its time): FP64 N = 64 16 per thread 201 / 231 against 199 /
+// 200; N = 128 at 4 waves 238 / 212 and 8 per thread 227 / 308 against 215 /
+// 209; FP32 N = 64 16 per thread 252 / 255 against 219 / 222; N = 128 8 per
+// thread 247 / 261 against 228 / 220.  The streaming copy of the same bytes
+// takes 173.  N = 32 (8 per thread, one wave a
 // plane; 4 per thread the same within 5%): a whole transform of 333 grids with
 // its x pass 59 (126) in FP64, 37 (81) in FP32.
 template <typename T, int N>
@@ -1113,12 +1114,12 @@ hipError_t launch_plane(bool f64, bool forward, int n, const void* in, void* out
 // and keep the x tile's runs at 64 bytes or more.  Measured over 537 MB of
 // reals, row tiles forward / inverse and x pass, us (in brackets the step 1
 // and x passes they replace):
-//   FP64 N = 128, R = 2: 198 / 198 + 194 (215 / 209 + 217)
-//        N = 256, R = 4: 207 / 209 + 229 (397 / 414 + 242)
-//   FP32 N = 128, R = 2: 208 / 215 + 182 (228 / 220 + 218)
-//        N = 256, R = 4: 212 / 206 + 217 (327 / 333 + 233)
-//        N = 512, R = 8: 236 / 237 + 311 (448 / 445 + 214)
-// and over 1.07 GB FP64 N = 512, R = 8: 446 / 492 + 598 (815 / 803 + 415).
+//   FP64 N = 128, R = 2: 197 / 177 + 195 (224 / 210 + 217)
+//        N = 256, R = 4: 206 / 215 + 200 to 228 (358 / 412 + 242)
+//   FP32 N = 128, R = 2: 203 / 199 + 182 (208 / 215 + 218)
+//        N = 256, R = 4: 200 / 218 + 207 to 222 (309 / 331 + 233)
+//        N = 512, R = 8: 236 / 242 + 293 to 319 (419 / 445 + 214)
+// and over 1.07 GB FP64 N = 512, R = 8: 446 / 481 + 568 to 614 (762 / 844 + 415).
 // N = 64 planes have room as they are.  Tiles in groups (ORD) of 64 run the x
 // pass at 4.73 TB/s for FP64 256 (contiguous 4.41), 4.93 for FP32 256 (4.43),
 // and 3.46 / 3.60 for FP32 / FP64 512 (3.27 / 3.08), whose 64-byte runs share
@@ -1238,14 +1239,15 @@ hipError_t launch_split_x(bool f64, int n, int sign, const void* src, void* dst,
 
 // First y step of the z pass (rows_step): NY rows a tile, leaving y lines of
 // L = N / NY for launch_strided_lines.  TB/s of the z passes with the step,
-// forward / inverse, and of the lines; in brackets the plain z and y passes:
-//   FP64 N = 1024, NY = 8   5.53 / 5.58 and 5.49 (5.70 / 5.80 and 4.86)
-//        2048, 4            5.19 / 5.53 and 5.1  (5.66 / 5.95 and 4.24)
-//        4096, 4            4.81 / 5.47 and 4.69 (5.27 / 5.76 and 3.52)
-//   FP32 N = 512, NY = 16   5.61 / 5.37 and 5.78 (4.93 / 5.08 and 4.77)
-//        1024, 16           5.55 / 5.60 and 5.55 (4.65 / 5.0 and 4.55)
-//        2048, 8            4.78 / 5.04 and 5.27 (4.96 / 5.41 and 3.76)
-//        4096, 4            4.51 / 5.03 and 4.71 (4.80 / 5.13 and 2.84)
+// forward / inverse, and of the lines, over 2.1 GB of FP64 and 1.07 GB of FP32
+// reals (N = 4096 twice that); in brackets the plain z and y passes:
+//   FP64 N = 1024, NY = 8   5.76 / 5.28 and 5.59 / 5.43 (6.05 / 5.68 and 4.92 / 4.87)
+//        2048, 4            5.31 / 5.24 and 4.61 / 4.52 (5.62 / 5.77 and 4.05 / 4.06)
+//        4096, 4            4.87 / 5.35 and 4.64 / 4.62 (5.26 / 5.71 and 3.49 / 3.48)
+//   FP32 N = 512, NY = 16   5.82 / 5.10 and 5.85 / 5.72 (5.43 / 5.01 and 4.85 / 4.76)
+//        1024, 16           5.79 / 5.16 and 5.75 / 5.56 (5.49 / 5.12 and 4.66 / 4.56)
+//        2048, 8            5.16 / 4.66 and 5.20 / 5.01 (5.15 / 5.05 and 3.98 / 3.84)
+//        4096, 4            4.63 / 4.91 and 4.71 / 4.65 (4.64 / 5.06 and 3.36 / 3.33)
 // Shorter lines run faster, longer first steps slower (FP32 1024 with 32 rows
 // 4.9, 4096 with 8 3.1 / 4.5; FP64 1024 with 16 5.2): NY is where the two
 // together are fastest.  FP64 512 gains nothing (16 rows 5.42 / 5.48 and 5.70
@@ -1266,8 +1268,8 @@ int rows_step(bool f64, int n) {
 // inverse (I).  TB/s over 2.1 / 4.3 GB of FP64 and half as much FP32 reals
 // (N = 2048 / 4096, 64 / 32 planes) at NY = 1, the plain z passes, forward /
 // inverse, in brackets passes with whole-value exchanges in contiguous order:
-//   FP64 2048 5.66 / 5.95 (4.65 / 4.93), 4096 5.27 / 5.76 (4.84 / 4.98)
-//   FP32 2048 4.96 / 5.41 (4.67 / 4.57), 4096 4.80 / 5.13 (4.25 / 4.13)
+//   FP64 2048 5.62 / 5.77 (4.65 / 4.93), 4096 5.26 / 5.71 (4.84 / 4.98)
+//   FP32 2048 5.15 / 5.05 (4.67 / 4.57), 4096 4.64 / 5.06 (4.25 / 4.13)
 // One tile a workgroup at N = 4096, NY = 1 runs at 4.2: rows share a line at
 // their ends, so tiles of neighbouring rows go together.
 template <typename T, int N, int NY>

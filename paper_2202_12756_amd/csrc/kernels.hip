@@ -282,8 +282,10 @@ struct sshape {
     // thread, the y tile with 16)
     static constexpr bool C32 = !F64 && !MFMA && (N == 256 || (N == 512 && AX == 1));
     // FP32 lines of 2048 and x lines of 4096: 64 elements per thread, two
-    // stages and one exchange (64 x 32, 64 x 64) instead of three and two; a
-    // tile of 128 KiB fills the LDS, so its FFT phase overlaps nothing.  TB/s
+    // stages and one exchange (64 x 32, 64 x 64) instead of three and two; an x
+    // tile of 128 KiB fills the LDS, so its FFT phase overlaps nothing (a y tile
+    // of 2048 takes half, two per CU).  The 4096 tile needs all 256 VGPRs and
+    // spills 19 to 25 of them; it is the faster one all the same.  TB/s
     // against 32 per thread: 2048 x 4.29 / 3.82 (slab of 64 planes), 3.78 / 2.97
     // (8 x 8 pencil), y 3.55 / 3.40 and 4.56 / 4.38; 4096 x 3.16 / 3.00.  y lines
     // of 4096 gain in some layouts and lose in others (natural 3.10 / 3.22, 8 x
